@@ -328,18 +328,23 @@ tc_status tc_batch_autotune(const tc_graph* const* graphs, int32_t num_graphs, v
  * thresholds, a flat JSON object of integers:
  *   "heavy_min"   (0 .. 2^24, default 32768): rows b with fewer probes than
  *                 this, and tables of at most 2^10 slots, are packed several
- *                 to a work-group; the others get work-groups of their own;
+ *                 to a work-group; the others get work-groups of their own
+ *                 (short rows, see below: from 2048 probes on, if heavy_min
+ *                 is not lower);
  *   "pack_target" (1024 .. 2^24, default 65536): probes per pack (plus one
  *                 row's);
  *   "pack_slots"  (1024 .. 16384, default 4096): LDS table slots per pack
- *                 (plus one row's table);
+ *                 (plus one row's table; a short row's slots count half);
  *   "wave_chunk"  (1024 .. 32767, default 32767): probes per wave item of a
  *                 row with work-groups of its own, at most;
  *   "min_groups"  (0 .. 2^22, default 16384): a class of such rows whose
  *                 probes would fill fewer work-groups than this gets smaller
  *                 wave items (down to 1024 probes) so that it fills the GPU;
  *                 a class too small to fill them even then keeps wave_chunk
- *                 (few large units suit a batch of many small graphs).
+ *                 (few large units suit a batch of many small graphs). Short
+ *                 rows are shared out by weight instead.
+ * Short rows are the last 65534 ranks: all their columns lie in those ranks,
+ * and their probes are read from a 16-bit form of them.
  * They change how the work is scheduled, never a count. Graphs take theirs
  * from the tuning table when tc_preprocess builds them (the defaults when the
  * table has no entry for their size).

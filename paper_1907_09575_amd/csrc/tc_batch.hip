@@ -87,6 +87,10 @@ Tuning parse_tuning(const char* js) {
 
 constexpr int kItemClasses = NUM_CLASSES - CLS_WG_SMALL;  // wg_small .. global
 
+// Probes of a unit of short rows' groups: a small graph's bundles are sized to
+// spread that one graph over the GPU, and merged up to this for a batch.
+constexpr uint64_t kUnitProbes = 65536;
+
 // Per graph entry of the plan: where its units come from (device copy).
 struct BatchSrc {
   const PackRow* pack_recs[2];
@@ -97,9 +101,15 @@ struct BatchSrc {
   const uint64_t* tprefix;
   const int64_t* row_ptr;
   uint32_t n_packs[2];
-  uint32_t pack_slots[2];
-  uint32_t n_groups[kItemClasses];
-  int32_t kind[kItemClasses];  // BatchKind of each item class under the plan's LDS cap
+  uint32_t pack_slots[2], pack_slots16[2];
+  uint32_t n_packs32[2];                // packs of 32-bit rows come first (the others: short rows)
+  uint32_t n_groups32[kItemClasses];   // groups of 32-bit rows (they come first)
+  int32_t kind[kItemClasses], kind16[kItemClasses];  // BatchKind of each item class under the plan's LDS cap
+  uint32_t max_keys[kItemClasses];                   // hit counters of its short rows (FULL support)
+  // short rows: a unit is `merge` consecutive bundles of their groups
+  const uint32_t* bundle[kItemClasses];
+  uint32_t n_bundles[kItemClasses], n_units16[kItemClasses];
+  uint32_t merge;
   uint64_t unit_off;
 };
 
@@ -111,7 +121,7 @@ __global__ __launch_bounds__(256) void k_batch_units(const BatchSrc* __restrict_
   const BatchSrc& s = src[blockIdx.x];
   const uint32_t np0 = s.n_packs[0], np1 = s.n_packs[1];
   uint32_t total = np0 + np1;
-  for (int c = 0; c < kItemClasses; ++c) total += s.n_groups[c];
+  for (int c = 0; c < kItemClasses; ++c) total += s.n_groups32[c] + s.n_units16[c];
   for (uint32_t j = threadIdx.x; j < total; j += blockDim.x) {
     BatchUnit u;
     uint64_t wgt = 0;
@@ -120,25 +130,43 @@ __global__ __launch_bounds__(256) void k_batch_units(const BatchSrc* __restrict_
       const int c = j < np0 ? 0 : 1;
       const uint32_t p = j < np0 ? j : j - np0;
       const PackInfo& pi = s.pack_info[c][p];
-      wgt = pi.q1 - pi.q0 + 64ull * (pi.r1 - pi.r0);
+      const bool s16 = p >= s.n_packs32[c];
+      wgt = (pi.q1 - pi.q0) * (s16 ? 2 : 1) + 64ull * (pi.r1 - pi.r0);
       u.p0 = s.pack_recs[c];
       u.p1 = s.pack_info[c];
       u.index = p;
-      u.slots = s.pack_slots[c];
-      u.kind = BK_PACK;
+      u.slots = s16 ? s.pack_slots16[c] : s.pack_slots[c];
+      u.kind = s16 ? BK_PACK16 : BK_PACK;
     } else {
       uint32_t r = j - np0 - np1;
       int c = 0;
-      while (r >= s.n_groups[c]) r -= s.n_groups[c++];
-      const CountItem* g = s.items[c] + (uint64_t)r * kWaves;
-      for (int w = 0; w < kWaves; ++w) wgt += g[w].len;
-      const int32_t b = g[0].b;
-      wgt += (uint64_t)(s.row_ptr[b + 1] - s.row_ptr[b]);
-      u.p0 = g;
-      u.p1 = nullptr;
-      u.index = r;
-      u.slots = 0;
-      u.kind = s.kind[c];
+      while (r >= s.n_groups32[c] + s.n_units16[c]) {
+        r -= s.n_groups32[c] + s.n_units16[c];
+        ++c;
+      }
+      if (r < s.n_groups32[c]) {
+        const CountItem* g = s.items[c] + (uint64_t)r * kWaves;
+        for (int w = 0; w < kWaves; ++w) wgt += g[w].len;
+        wgt += g[0].d;
+        u.p0 = g;
+        u.p1 = nullptr;
+        u.index = r;
+        u.slots = 0;
+        u.kind = s.kind[c];
+      } else {
+        r -= s.n_groups32[c];
+        const CountItem* items = s.items[c] + (uint64_t)s.n_groups32[c] * kWaves;
+        const uint32_t b1 = (r + 1) * s.merge;
+        u.p0 = items;
+        u.index = s.bundle[c][r * s.merge];
+        u.end = s.bundle[c][b1 < s.n_bundles[c] ? b1 : s.n_bundles[c]];
+        u.slots = s.max_keys[c];
+        u.kind = s.kind16[c];
+        if (u.end > u.index) {
+          const CountItem& last = items[u.end * kWaves - 1];
+          wgt = 2 * (last.q0 + last.len - items[(uint64_t)u.index * kWaves].q0) + 64 * (u.end - u.index);
+        }
+      }
     }
     const uint64_t o = s.unit_off + j;
     units[o] = u;
@@ -166,6 +194,7 @@ struct BatchPlan {
   uint32_t chunk = 1;  // units per queue atomic
   unsigned grid = 0;
   size_t lds = 0;
+  bool only16 = false;
   int cus = 0;
   Tuning tun;
   Owned own;
@@ -208,6 +237,7 @@ struct PlanHost {
   size_t lds = 0;
   uint64_t units = 0;
   int64_t hbm_units = 0;
+  bool only16 = true;  // all units are short rows' with their tables in LDS
 };
 
 void plan_host(PlanHost& H, const PlanEntry* entries, int64_t num, CountMode mode, const Tuning& t,
@@ -236,6 +266,8 @@ void plan_host(PlanHost& H, const PlanEntry* entries, int64_t num, CountMode mod
     A.tend = w.tend;
     A.T = w.n_tasks;
     A.m = (uint32_t)g.m;
+    A.col16 = g.col16;
+    A.n = (int32_t)g.n;
     A.q = 1;
     if (mode != MODE_COUNT) {
       TC_REQUIRE(entries[i].support != nullptr || g.m == 0, TC_EINVAL, "batch plan: null support array");
@@ -255,20 +287,45 @@ void plan_host(PlanHost& H, const PlanEntry* entries, int64_t num, CountMode mod
       s.pack_info[c] = w.pack_info[c];
       s.n_packs[c] = (uint32_t)w.n_packs[c];
       if (w.n_packs[c] == 0) continue;
+      s.n_packs32[c] = (uint32_t)w.n_packs32[c];
       s.pack_slots[c] = w.wp.pack_slots + (1u << w.pack_log2S[c]);
-      lds = std::max(lds, pack_lds_bytes(s.pack_slots[c], mode));
+      s.pack_slots16[c] = pack16_slots(w.wp.pack_slots, w.pack_log2S[c]);
+      if (w.n_packs32[c] > 0) {
+        lds = std::max(lds, pack_lds_bytes(s.pack_slots[c], mode));
+        H.only16 = false;
+      }
+      if (w.n_packs32[c] < w.n_packs[c]) lds = std::max(lds, pack16_lds_bytes(s.pack_slots16[c], mode, kWaves));
       off += (uint64_t)w.n_packs[c];
     }
     for (int c = 0; c < kItemClasses; ++c) {
       const int cls = CLS_WG_SMALL + c;
       s.items[c] = w.items[cls];
-      s.n_groups[c] = (uint32_t)(w.n_items[cls] / kWaves);
-      if (s.n_groups[c] == 0) continue;
-      const bool hbm = cls == CLS_GLOBAL || w.cls_log2S[cls] > t.lds_cap_log2;
-      s.kind[c] = hbm ? BK_ITEMS_HBM : BK_ITEMS;
-      lds = std::max(lds, items_lds_bytes(hbm ? -1 : w.cls_log2S[cls], mode));
-      if (hbm) hbm_units += s.n_groups[c];
-      off += s.n_groups[c];
+      if (w.n_items[cls] == 0) continue;
+      s.n_groups32[c] = (uint32_t)(w.n_items32[cls] / kWaves);
+      if (s.n_groups32[c] > 0) {
+        const bool hbm = cls == CLS_GLOBAL || w.cls_log2S[cls] > t.lds_cap_log2;
+        s.kind[c] = hbm ? BK_ITEMS_HBM : BK_ITEMS;
+        lds = std::max(lds, items_lds_bytes(hbm ? -1 : w.cls_log2S[cls], mode));
+        if (hbm) hbm_units += s.n_groups32[c];
+        H.only16 = false;
+      }
+      if (w.n_bundles[cls] > 0) {
+        // (a bitmap serves any row; the cap still names the rows by the
+        // slots their 32-bit table would take)
+        const bool hbm = std::min(w.cls_log2S[cls], kMaxLog2S) > t.lds_cap_log2;
+        s.kind16[c] = hbm ? BK_BITS_HBM : BK_BITS;
+        s.max_keys[c] = bits_max_keys(w.cls_log2S[cls], mode);
+        s.bundle[c] = w.bundle[cls];
+        s.n_bundles[c] = (uint32_t)w.n_bundles[cls];
+        s.merge = (uint32_t)std::max<uint64_t>(1, kUnitProbes / w.bundle_w);
+        s.n_units16[c] = (uint32_t)div_up(s.n_bundles[c], s.merge);
+        lds = std::max(lds, hbm ? items_lds_bytes(-1, mode) : bits_lds_bytes(g.n, w.cls_log2S[cls], mode));
+        if (hbm) {
+          hbm_units += s.n_units16[c];
+          H.only16 = false;
+        }
+      }
+      off += s.n_groups32[c] + s.n_units16[c];
     }
   }
   H.lds = std::max(lds, items_lds_bytes(-1, mode));
@@ -334,8 +391,9 @@ BatchPlan* make_plan(const PlanEntry* entries, int64_t num, CountMode mode, cons
   P->n_units = (int64_t)off;
   P->hbm_units = H.hbm_units;
   P->lds = H.lds;
+  P->only16 = H.only16;
   plan_grid(t, P->lds, P->n_units, P->cus, P->bpc, P->grid, P->chunk);
-  batch_kernel_lds(mode, P->lds);
+  batch_kernel_lds(mode, P->lds, P->only16);
 
   P->d_args = P->own.alloc<CountArgs>(std::max<int64_t>(num, 1));
   P->d_units = P->own.alloc<BatchUnit>(std::max<int64_t>(P->n_units, 1));
@@ -374,8 +432,8 @@ namespace {
 
 void plan_launch(BatchPlan& P, int64_t* d_counts, hipStream_t st, bool timed) {
   for (const auto& z : P.support) zero_i32(z.first, z.second, st, timed);
-  launch_batch(P.mode, P.d_args, P.d_units, P.n_units, P.chunk, P.n_graphs, P.d_queue, d_counts, P.grid, P.lds, st,
-               timed);
+  launch_batch(P.mode, P.d_args, P.d_units, P.n_units, P.chunk, P.n_graphs, P.d_queue, d_counts, P.grid, P.lds,
+               P.only16, st, timed);
 }
 
 }  // namespace
@@ -539,7 +597,7 @@ void count_batched_noalloc(const PlanEntry* entries, int64_t num, int64_t* d_cou
   unsigned grid = 0;
   uint32_t chunk = 1;
   plan_grid(t, H.lds, (int64_t)H.units, cus, bpc, grid, chunk);
-  batch_kernel_lds(MODE_COUNT, H.lds);
+  batch_kernel_lds(MODE_COUNT, H.lds, H.only16);
   auto* d_queue = reinterpret_cast<unsigned int*>(base);
   auto* d_args = reinterpret_cast<CountArgs*>(base + L.args);
   auto* d_srcs = reinterpret_cast<BatchSrc*>(base + L.srcs);
@@ -552,7 +610,8 @@ void count_batched_noalloc(const PlanEntry* entries, int64_t num, int64_t* d_cou
     TC_HIP(hipGetLastError());
   }
   // clears the counts and the queue counter (a kernel), then the persistent launch
-  launch_batch(MODE_COUNT, d_args, d_units, (int64_t)H.units, chunk, num, d_queue, d_counts, grid, H.lds, st, true);
+  launch_batch(MODE_COUNT, d_args, d_units, (int64_t)H.units, chunk, num, d_queue, d_counts, grid, H.lds,
+               H.only16, st, true);
   // the host copies above read H's vectors: they must be done before H goes
   TC_HIP(hipStreamSynchronize(st));
 }

@@ -42,6 +42,17 @@
 //            compiled for the occupancy its LDS allows.
 //   global - a row whose table would not fit LDS (|U_b| > 8192): lookups are
 //            binary searches in the sorted U_b in HBM.
+// Short rows (b >= b16, see kShortSpan) of the same classes are launched apart:
+// their probes are read from the 16-bit columns, two per load, and looked up
+//   - in a bitmap over the column distances n - k (item classes, global
+//     included): one 4-byte LDS read and a bit extract per probe, no
+//     collisions, at most 8 KiB for a row of any length;
+//   - in buckets of four 16-bit slots (packs): one 8-byte LDS read.
+// The 32-bit kernels are bound by HBM at 4 bytes per probe; these move half
+// of that and are bound by vector issue (about 8 instructions per probe and
+// lane of which half is the lookup). tc_count, RMAT: scale 20 1215 -> 660 us,
+// scale 22 5422 -> 3440 us (of which 690 us are its 32-bit packs), scale 14
+// (n = 16384, all rows short) 170 -> 57 us.
 // Reductions: per-lane 32-bit hit counters, wave reduction by xor shuffles,
 // one 64-bit atomic per work-group into the caller's counter (order-free and
 // exact).
@@ -55,8 +66,12 @@ using Args = CountArgs;
 
 constexpr int kU = 8;                   // 64-probe batches per super-batch
 constexpr int kBmWords = 2 * kU;        // per-wave task-end bitmap (64 * kU bits)
-constexpr int kMarkInts = kWaves * kBmWords;          // packs
-constexpr int kItemMarkInts = kWavesBig * kBmWords;   // item work-groups (up to 8 waves)
+
+// LDS words of one wave: its task-end bitmap and, in the support modes, the
+// running hit count at the end of each of its window's tasks.
+__host__ __device__ constexpr int wave_words(int mode) {
+  return kBmWords + (mode == MODE_SUPPORT_FULL || mode == MODE_SUPPORT_ORIENTED ? 64 : 0);
+}
 
 constexpr int32_t kEmpty = -1;
 // FULL support, single-row LDS tables: a slot's value word is the key's index
@@ -189,9 +204,15 @@ struct TableRef {
   const uint32_t* row_desc;
   int nrows;
   int lds_hits;  // packs, FULL: the (b, k) credits are counted in LDS
+  // bitmaps, FULL: keys of smaller distance than each word's (pfx), hits per
+  // key in order of distance (cnt; null: credited to U directly)
+  const uint16_t* pfx;
+  uint32_t* cnt;
 };
 
-enum TableKind : int { TK_SINGLE = 0, TK_MULTI = 1, TK_GLOBAL = 2 };
+// Short rows: TK_MULTI16 (packs), TK_BITS (bitmap), TK_GLOBAL16 (HBM).
+enum TableKind : int { TK_SINGLE = 0, TK_MULTI = 1, TK_GLOBAL = 2, TK_MULTI16 = 3, TK_BITS = 4, TK_GLOBAL16 = 5 };
+constexpr uint32_t kEmpty16 = 0xFFFFu;  // empty 16-bit slot: above every distance (kShortSpan)
 
 // A hit: k = col[pos] was found in U_b at `where` (an LDS slot, or for the HBM
 // fallback its position in col); ts is the first probe position of the task,
@@ -230,20 +251,53 @@ __device__ __forceinline__ void credit(const Args& A, const TableRef& t, int whe
   }
 }
 
-// Support modes credit every hit to its task's own edge (a, b) through the
-// task window: lane j owns window task j and keeps its hits in a register.
-// The lanes of one task are a contiguous run of each 64-probe batch, so after
-// a batch's lookups lane j adds the hits of its run - the batch's hit ballot
-// masked to the lanes [lo, hi) its task covers; when the window moves on (or
-// the wave's range ends) it adds them to the task's edge with one global
-// atomic. A task cut between waves gets one atomic from each.
-__device__ __forceinline__ uint64_t lane_range_mask(int lo, int hi) {
-  lo = lo < 0 ? 0 : (lo > 64 ? 64 : lo);
-  hi = hi < 0 ? 0 : (hi > 64 ? 64 : hi);
-  if (hi <= lo) return 0;
-  const uint64_t below_hi = hi >= 64 ? ~0ull : ((1ull << hi) - 1ull);
-  return below_hi & ~((1ull << lo) - 1ull);
+// The (a, k) credits of a batch of units (FULL): lanes of hm hit with the
+// first entry of their unit, lanes of hm1 with the second. A wave's units are
+// runs of consecutive entries, so the credits are dealt to the lanes in entry
+// order, 64 entries at a time: an atomic instruction then covers half the
+// cache lines it would with every other entry per lane (RMAT scale 20, FULL:
+// 6.19 ms with an atomic per half word, 4.48 ms so).
+__device__ __forceinline__ void credit_probed(const Args& A, uint32_t pos, uint64_t hm, uint64_t hm1) {
+  const int lane = lane_id();
+  const uint64_t mine = (lane & 1) ? hm1 : hm;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int j = 32 * h + (lane >> 1);
+    const uint32_t p = 2 * (uint32_t)__builtin_amdgcn_ds_bpermute(j << 2, (int)pos) + (uint32_t)(lane & 1);
+    if (((mine >> j) & 1ull) && p < A.m) atomicAdd(&A.support[p], 1);
+  }
 }
+
+// A short row's hit (FULL) with a key of distance v of U_b: its (b, k) credit.
+// `where` is the key's slot (packs), its bitmap word's contents (bitmaps) or
+// its position in U (HBM).
+template <int KIND>
+__device__ __forceinline__ void credit16(const Args& A, const TableRef& t, uint32_t where, uint32_t v) {
+  if (KIND == TK_BITS) {
+    // keys of smaller distance come after k in U_b
+    const uint32_t r = (uint32_t)t.pfx[v >> 5] + (uint32_t)__builtin_popcount(where & ((1u << (v & 31)) - 1u));
+    if (t.cnt) {
+      atomicAdd(&t.cnt[r], 1u);
+    } else {
+      const uint64_t p = (uint64_t)(t.rs + t.d - 1) - r;
+      if (p < A.m) atomicAdd(&A.support[p], 1);
+    }
+  } else if (KIND == TK_MULTI16 && t.lds_hits) {
+    atomicAdd(reinterpret_cast<unsigned int*>(&t.val[where]), 1u << kPackValBits);
+  } else {
+    const uint32_t other = KIND == TK_GLOBAL16 ? where : (uint32_t)t.val[where];
+    if (other < A.m) atomicAdd(&A.support[other], 1);
+  }
+}
+
+// Support modes credit every hit to its task's own edge (a, b) through the
+// task window. Along a window the wave keeps the number of its hits so far;
+// the lane that holds a task's last probe (the end marks name it) notes the
+// count there, inclusive, in the task's LDS word, and when the window is done
+// lane j adds the difference of its task's word and the one before to the
+// task's edge with one global atomic. A batch without a task end costs only
+// its ballot and a scalar add. A task cut between waves gets one atomic from
+// each.
 
 // Count mode needs only whether the bucket holds k: an OR of four compares
 // (no slot index, no branch).
@@ -253,6 +307,102 @@ __device__ __forceinline__ bool bucket_has(const int4& v, int32_t k) {
 
 __device__ __forceinline__ int match_slot(const int4& v, int32_t k) {
   return v.x == k ? 0 : v.y == k ? 1 : v.z == k ? 2 : v.w == k ? 3 : -1;
+}
+
+// The same for a bucket of four 16-bit slots. Each half of x ^ vv is 0 where
+// the slot holds v; the packed minimum with 1 leaves 0 there and 1 elsewhere.
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pk_ne(uint32_t x, uint32_t vv) {
+  const u16x2 one = {1, 1};
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, x ^ vv), one));
+}
+__device__ __forceinline__ bool bucket16_has(const uint2& b, uint32_t vv) {
+  const uint32_t e = pk_ne(b.x, vv) & pk_ne(b.y, vv);
+  return (e & (e >> 16) & 1u) == 0;
+}
+__device__ __forceinline__ int match_slot16(const uint2& b, uint32_t v) {
+  return (b.x & 0xFFFFu) == v ? 0 : (b.x >> 16) == v ? 1 : (b.y & 0xFFFFu) == v ? 2 : (b.y >> 16) == v ? 3 : -1;
+}
+
+// Lookups of a super-batch of units (short rows): w[u] holds this lane's two
+// column distances of batch u; 0 is no key. Hits of
+// the first and the second probe of batch u set bit u of f0 and f1 (support
+// modes).
+template <int MODE, int KIND>
+__device__ __forceinline__ void probe_units(const Args& A, const TableRef& tr, const int32_t (&w)[kU],
+                                            const uint32_t (&bbase)[kU], const uint32_t (&bmask)[kU],
+                                            uint32_t& hits, uint32_t& f0, uint32_t& f1) {
+  constexpr bool kMask = MODE == MODE_SUPPORT_FULL || MODE == MODE_SUPPORT_ORIENTED;
+  constexpr bool FULL = MODE == MODE_SUPPORT_FULL;
+  if constexpr (KIND == TK_BITS) {
+    const uint32_t* bits = reinterpret_cast<const uint32_t*>(tr.tab);
+    uint32_t x0[kU], x1[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      x0[u] = bits[((uint32_t)w[u] >> 5) & 0x7FFu];
+      x1[u] = bits[(uint32_t)w[u] >> 21];
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const uint32_t b0 = __builtin_amdgcn_ubfe(x0[u], (uint32_t)w[u] & 31u, 1);
+      const uint32_t b1 = __builtin_amdgcn_ubfe(x1[u], ((uint32_t)w[u] >> 16) & 31u, 1);
+      hits += b0 + b1;
+      if (kMask) {
+        f0 |= b0 << u;
+        f1 |= b1 << u;
+      }
+      if (FULL) {
+        if (b0) credit16<KIND>(A, tr, x0[u], (uint32_t)w[u] & 0xFFFFu);
+        if (b1) credit16<KIND>(A, tr, x1[u], (uint32_t)w[u] >> 16);
+      }
+    }
+  } else if constexpr (KIND == TK_MULTI16) {
+    const uint2* tab2 = reinterpret_cast<const uint2*>(tr.tab);
+    constexpr int kG = 4;  // batches whose buckets are read together
+#pragma unroll
+    for (int g0 = 0; g0 < kU; g0 += kG) {
+      uint2 x[2 * kG];
+#pragma unroll
+      for (int u = g0; u < g0 + kG; ++u) {
+        x[2 * (u - g0)] = tab2[bbase[u] + ((uint32_t)w[u] & bmask[u])];  // (a pack's tables: bmask < 2^16)
+        x[2 * (u - g0) + 1] = tab2[bbase[u] + (((uint32_t)w[u] >> 16) & bmask[u])];
+      }
+#pragma unroll
+      for (int u = g0; u < g0 + kG; ++u) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const uint32_t v = h ? (uint32_t)w[u] >> 16 : (uint32_t)w[u] & 0xFFFFu;
+          const uint32_t vv = v | (v << 16);
+          uint2 b = x[2 * (u - g0) + h];
+          bool found = bucket16_has(b, vv);
+          uint32_t bk = v & bmask[u];
+          // full first bucket: continue into the next ones (bounded by D)
+          for (int i = 0; !found && (b.y >> 16) != kEmpty16 && i < tr.D; ++i) {
+            bk = (bk + 1) & bmask[u];
+            b = tab2[bbase[u] + bk];
+            found = bucket16_has(b, vv);
+          }
+          hits += found ? 1u : 0u;
+          if (kMask) (h ? f1 : f0) |= (found ? 1u : 0u) << u;
+          if (FULL && found)
+            credit16<KIND>(A, tr, (bbase[u] + bk) * kBucket + (uint32_t)match_slot16(b, v), v);
+        }
+      }
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t v = h ? (uint32_t)w[u] >> 16 : (uint32_t)w[u] & 0xFFFFu;
+        const int64_t where = v ? hbm_find(A.hcol, tr.rs, tr.d, A.n - (int32_t)v) : -1;
+        if (where < 0) continue;
+        ++hits;
+        if (kMask) (h ? f1 : f0) |= 1u << u;
+        if (FULL) credit16<KIND>(A, tr, (uint32_t)where, v);
+      }
+    }
+  }
 }
 
 // The first window of a wave's probe range [q, q + len) (task t holds probe
@@ -280,6 +430,7 @@ __device__ __forceinline__ Window window_first(const Args& A, uint32_t t, uint64
 template <int MODE, int KIND, int VAR>
 __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64_t q, uint32_t len,
                            uint32_t* bm, uint32_t& hits, const Window& w0) {
+  uint32_t* const tend = bm + kBmWords;  // support modes: hits up to each window task's end
   // the range is the wave's own (uniform across its lanes): scalar registers
   // (readfirstlane returns int: widen through uint32_t, never sign-extend)
   t = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
@@ -287,13 +438,15 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
   q = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(q >> 32)) << 32) |
       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)q);
   constexpr bool GLOBAL = KIND == TK_GLOBAL;
-  constexpr bool MULTI = KIND == TK_MULTI;
-  constexpr bool MH = VAR == VAR_MUL, WIDE = VAR == VAR_WIDE;
+  constexpr bool SHORT = KIND == TK_MULTI16 || KIND == TK_BITS || KIND == TK_GLOBAL16;  // probes are units
+  constexpr bool MULTI = KIND == TK_MULTI || KIND == TK_MULTI16;
+  constexpr bool MH = VAR == VAR_MUL, WIDE = VAR == VAR_WIDE && !SHORT;
   constexpr bool kTaskHits = MODE == MODE_SUPPORT_FULL || MODE == MODE_SUPPORT_ORIENTED;
   constexpr uint32_t SB = 64u * kU;
   const int lane = lane_id();
   const int64_t T = A.T;
-  const __amdgpu_buffer_rsrc_t rsrc = col_rsrc(A.col, A.m);
+  const __amdgpu_buffer_rsrc_t rsrc =
+      SHORT ? col_rsrc(reinterpret_cast<const int32_t*>(A.col16), (A.m + 1) / 2) : col_rsrc(A.col, A.m);
   const int4* tab4 = reinterpret_cast<const int4*>(tr.tab);
 
   // window of tasks t .. t + 63, one per lane: end prefix and col start (the
@@ -312,17 +465,16 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
   uint32_t P0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)w0.P0);  // start of the window's first task
 
   uint32_t done = 0;
-  uint32_t tcnt = 0;  // support modes: hits of this lane's window task
   while (done < len) {
     const uint32_t rem = len - done;
     // end of the lane's task relative to the current position, within the range
     const uint32_t e = Pe - done;
     // start of the lane's task relative to the current position (wraps below
     // it for lane 0 when the range begins inside its task), so cbase = col
-    // index of relative probe 0
+    // index (short rows: unit) of relative probe 0
     const uint32_t e_prev = (uint32_t)__shfl_up((int)e, 1, 64);
     const uint32_t s_rel = lane == 0 ? P0 - done : e_prev;
-    const uint32_t cbase = tsj - s_rel;
+    const uint32_t cbase = (SHORT ? tsj >> 1 : tsj) - s_rel;
     // probes of this window (wave-uniform: kept in a scalar register)
     const uint32_t lim = (uint32_t)__builtin_amdgcn_readfirstlane(__shfl((int)e, 63, 64));
     if (lim == 0) break;  // unreachable when every task has a probe; guards progress
@@ -343,13 +495,18 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
     uint32_t ntsj = 0;
     if (more) fetch((int64_t)t + 64 + lane, nPe, ntsj);  // next window, in flight meanwhile
 
+    uint32_t run = 0;  // support modes: the window's hits so far (uniform)
     for (uint32_t sb = 0; sb < lim; sb += SB) {
       const uint32_t c0 = (uint32_t)__popcll(__ballot(e <= sb));
       const bool inner = e > sb && e <= sb + SB;
       uint32_t jl[kU];
+      uint64_t ends[kU];  // support modes: lanes of batch u that hold a task's last probe
       if (__ballot(inner) == 0) {
 #pragma unroll
-        for (int u = 0; u < kU; ++u) jl[u] = c0;
+        for (int u = 0; u < kU; ++u) {
+          jl[u] = c0;
+          if (kTaskHits) ends[u] = 0;
+        }
       } else {
         // bit p set <=> some task ends right after probe sb + p
         if (inner) atomicOr(&bm[(e - sb - 1) >> 5], 1u << ((e - sb - 1) & 31));
@@ -361,6 +518,7 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
           const uint32_t hi = __builtin_amdgcn_readfirstlane(bm[2 * u + 1]);
           jl[u] = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, pre));
           pre += (uint32_t)__builtin_popcount(lo) + (uint32_t)__builtin_popcount(hi);
+          if (kTaskHits) ends[u] = ((uint64_t)hi << 32) | lo;
         }
         wave_sync_lds();
         if (lane < (int)(SB / 32)) bm[lane] = 0;
@@ -370,6 +528,7 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
       int32_t k[kU];
       bool ok[kU];
       uint32_t fmask = 0;  // support modes: bit u = this lane's probe of batch u hit
+      uint32_t fmask1 = 0;  // short rows: its second probe (bits of fmask: the first)
 #pragma unroll
       for (int u = 0; u < kU; ++u) {
         // ds_bpermute uses lane index bits only, so lanes past the window
@@ -392,7 +551,9 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
         else k[u] = col_load(rsrc, ok[u] ? pos[u] * 4u : kOffNone);
       }
 
-      if constexpr (!GLOBAL) {
+      if constexpr (SHORT) {
+        probe_units<MODE, KIND>(A, tr, k, bbase, bmask, hits, fmask, fmask1);
+      } else if constexpr (!GLOBAL) {
         // buckets are read in groups of kG so that the 16-byte results of one
         // group fit the register budget of 8 waves per SIMD
         constexpr int kG = 2;
@@ -457,22 +618,37 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
         }
       }
       if constexpr (kTaskHits) {
-        // this lane's task covers the relative probes [s_rel, e) (s_rel may
-        // be below 0 for lane 0); add the hits of batch u that fall there
-        const int ts0 = (int)s_rel, te0 = (int)e;
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
           const uint64_t hm = __ballot((fmask >> u) & 1u);
-          if (hm) {
-            const int base = (int)(sb + 64u * (uint32_t)u);
-            tcnt += (uint32_t)__popcll(hm & lane_range_mask(ts0 - base, te0 - base));
+          const uint64_t hm1 = SHORT ? __ballot((fmask1 >> u) & 1u) : 0;
+          if (MODE == MODE_SUPPORT_FULL && SHORT && (hm | hm1)) credit_probed(A, pos[u], hm, hm1);
+          if (ends[u]) {
+            // hits of this lane's probes and the ones before it
+            uint32_t c = __builtin_amdgcn_mbcnt_hi((uint32_t)(hm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hm, run));
+            c += (fmask >> u) & 1u;
+            if (SHORT) {
+              c = __builtin_amdgcn_mbcnt_hi((uint32_t)(hm1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hm1, c));
+              c += (fmask1 >> u) & 1u;
+            }
+            if ((ends[u] >> lane) & 1ull) tend[jl[u]] = c;
           }
+          run += (uint32_t)__popcll(hm) + (SHORT ? (uint32_t)__popcll(hm1) : 0u);
         }
       }
     }
-    if (kTaskHits && tcnt) {  // the window task's own edge
-      if (tsj - 1u < A.m) atomicAdd(&A.support[tsj - 1u], (int)tcnt);
-      tcnt = 0;
+    if constexpr (kTaskHits) {
+      wave_sync_lds();
+      if (run) {
+        // (a task without probes here ends where the one before it does, and
+        // its word was not written)
+        const uint32_t ce = tend[lane];
+        const uint32_t cp = (uint32_t)__shfl_up((int)ce, 1, 64);
+        const uint32_t c = ce - (lane == 0 ? 0u : cp);
+        const bool any = lane == 0 ? e > 0 : e != e_prev;
+        if (any && c && tsj - 1u < A.m) atomicAdd(&A.support[tsj - 1u], (int)c);
+        wave_sync_lds();
+      }
     }
     if (more) {
       t += 64;  // a window that is not the last covers exactly its 64 tasks
@@ -487,9 +663,9 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
 // Work-group total of the hits (returned to thread 0, which also adds it to
 // A.count when that is set).
 template <int MODE>
-__device__ __forceinline__ unsigned long long block_flush(uint32_t hits, const Args& A) {
-  __shared__ unsigned long long s_sum[kWavesBig];
-  unsigned long long h = wave_sum((unsigned long long)hits);
+__device__ __forceinline__ unsigned long long block_flush(unsigned long long hits, const Args& A) {
+  __shared__ unsigned long long s_sum[kPackWavesMax];
+  unsigned long long h = wave_sum(hits);
   if (lane_id() == 0) s_sum[threadIdx.x >> 6] = h;
   __syncthreads();
   unsigned long long tot = 0;
@@ -512,6 +688,24 @@ __device__ __forceinline__ void block_init() {
   if (MODE == MODE_BLOCK && threadIdx.x < 64) shift_counters()[threadIdx.x] = 0;
 }
 
+// Puts distance v into the first free 16-bit slot of bucket bk (two words of
+// two slots); the slot's index, or -1 if the bucket is full.
+__device__ __forceinline__ int insert16(uint32_t* tab, uint32_t bk, uint32_t v) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    uint32_t* w = &tab[bk * 2 + i];
+    uint32_t old = *w;
+    while ((old >> 16) == kEmpty16) {  // a slot of this word is free
+      const bool low = (old & 0xFFFFu) == kEmpty16;
+      const uint32_t want = low ? (old & 0xFFFF0000u) | v : (old & 0xFFFFu) | (v << 16);
+      const uint32_t was = atomicCAS(w, old, want);
+      if (was == old) return (int)(bk * kBucket + 2 * i + (low ? 0 : 1));
+      old = was;
+    }
+  }
+  return -1;
+}
+
 // Packs of light rows (one work-group each): up to kPackRows rows, one per
 // thread for its metadata; all their tables are built together in LDS (keys
 // flattened over the work-group), then the pack's probe range - the tasks of
@@ -519,34 +713,63 @@ __device__ __forceinline__ void block_init() {
 // each task looking up its own row's table.
 constexpr int kPackMetaWords = 3 * kPackRows + 1;  // row_t0, row_desc, key prefix (+ end)
 
-template <int MODE, int VAR>
+// LDS words before a pack's tables (a multiple of four: buckets are read as
+// 16 bytes).
+__host__ __device__ constexpr int pack_head_words(int mode, int waves) {
+  return (waves * wave_words(mode) + kPackMetaWords + 3) & ~3;
+}
+
+// Exclusive scan over the first kPackRows threads of a work-group (the others
+// bring 0) and the total; two barriers.
+__device__ __forceinline__ uint32_t pack_scan(uint32_t v, uint32_t* s_w, uint32_t& total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t inc = wave_incl_scan(v);
+  if (lane == 63 && wave < kPackRows / 64) s_w[wave] = inc;
+  __syncthreads();
+  uint32_t before = 0, tot = 0;
+#pragma unroll
+  for (int w = 0; w < kPackRows / 64; ++w) {
+    if (w < wave) before += s_w[w];
+    tot += s_w[w];
+  }
+  __syncthreads();
+  total = tot;
+  return before + inc - v;
+}
+
+// WAVES: waves of the work-group, which share the pack's probes (4, or more
+// where a class has too few packs to fill the GPU: see launch_short).
+template <int MODE, int VAR, bool SHORT, int WAVES>
 __device__ __forceinline__ unsigned long long pack_body(const Args& A, const PackRow* __restrict__ recs,
                                           const PackInfo* __restrict__ info, uint32_t pack,
                                           uint32_t pack_slots, int32_t* smem) {
   __shared__ int s_D;
   __shared__ uint32_t s_w[4], s_w2[4];
   constexpr bool VALS = MODE == MODE_SUPPORT_FULL;
+  constexpr int NT = 64 * WAVES;
+  static_assert(kPackWavesMax % WAVES == 0 && NT >= kPackRows, "pack work-group shape");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  uint32_t* bm = reinterpret_cast<uint32_t*>(smem) + wave * kBmWords;
-  uint32_t* row_t0 = reinterpret_cast<uint32_t*>(smem) + kMarkInts;
+  uint32_t* bm = reinterpret_cast<uint32_t*>(smem) + wave * wave_words(MODE);
+  uint32_t* row_t0 = reinterpret_cast<uint32_t*>(smem) + WAVES * wave_words(MODE);
   uint32_t* row_desc = row_t0 + kPackRows;
   uint32_t* row_k0 = row_desc + kPackRows;  // kPackRows + 1 entries
-  int32_t* tab = smem + kMarkInts + kPackMetaWords + 3;  // + 3 keeps 16-byte alignment
-  int32_t* val = tab + pack_slots;
+  int32_t* tab = smem + pack_head_words(MODE, WAVES);
+  int32_t* val = tab + (SHORT ? pack_slots / 2 : pack_slots);  // (short rows: 16-bit slots)
   if (lane < kBmWords) bm[lane] = 0;
   block_init<MODE>();
 
   const PackInfo& pi = info[pack];
   const uint32_t r0 = pi.r0, r1 = pi.r1;
   const int nr = (int)(r1 - r0);  // 1 .. kPackRows
-  // this wave's quarter of the pack's probes, its first task, and its first
+  // this wave's share of the pack's probes, its first task, and its first
   // window (in flight while the tables are built)
   const uint64_t q0 = pi.q0, W = pi.q1 - pi.q0;
-  const uint64_t wq0 = q0 + W * (uint64_t)wave / kWaves, wq1 = q0 + W * (uint64_t)(wave + 1) / kWaves;
-  const uint32_t wt = (uint32_t)__builtin_amdgcn_readfirstlane((int)pi.wt[wave]);
+  const uint64_t wq0 = q0 + pack_share(W, wave * (kPackWavesMax / WAVES));
+  const uint64_t wq1 = q0 + pack_share(W, (wave + 1) * (kPackWavesMax / WAVES));
+  const uint32_t wt = (uint32_t)__builtin_amdgcn_readfirstlane((int)pi.wt[wave * (kPackWavesMax / WAVES)]);
   const uint32_t wlen = (uint32_t)(wq1 - wq0);
   const Window w0 = window_first(A, wt, wq0, wlen);
-  const bool lds_hits = VALS && W < kPackLdsHitsMax;  // (uniform: the pack's probes)
+  const bool lds_hits = VALS && (SHORT ? 2 * W : W) < kPackLdsHitsMax;  // (uniform: the pack's probes)
   uint32_t d = 0, S = 0, rs = 0;
   if (tid < nr) {
     const PackRow pr = recs[r0 + tid];
@@ -558,8 +781,8 @@ __device__ __forceinline__ unsigned long long pack_body(const Args& A, const Pac
     row_t0[tid] = pr.tb;
   }
   uint32_t S_tot, K_tot;
-  const uint32_t off = block_excl_scan(S, s_w, S_tot);
-  const uint32_t k0 = block_excl_scan(d, s_w2, K_tot);
+  const uint32_t off = pack_scan(S, s_w, S_tot);
+  const uint32_t k0 = pack_scan(d, s_w2, K_tot);
   if (tid < nr) {
     row_desc[tid] = (off / kBucket) | ((S / kBucket - 1) << 16);
     row_k0[tid] = k0;
@@ -568,7 +791,7 @@ __device__ __forceinline__ unsigned long long pack_body(const Args& A, const Pac
     row_k0[nr] = K_tot;
     s_D = 0;
   }
-  for (uint32_t i = tid; i < S_tot; i += 256) tab[i] = kEmpty;
+  for (uint32_t i = tid; i < (SHORT ? S_tot / 2 : S_tot); i += NT) tab[i] = kEmpty;
   __syncthreads();
 
   // build: key x of the pack belongs to the last row i with row_k0[i] <= x;
@@ -577,7 +800,7 @@ __device__ __forceinline__ unsigned long long pack_body(const Args& A, const Pac
   if (tid < nr) s_rs[tid] = rs;
   __syncthreads();
   int md = 0;
-  for (uint32_t x = tid; x < K_tot; x += 256) {
+  for (uint32_t x = tid; x < K_tot; x += NT) {
     int lo = 0, hi = nr;
     while (hi - lo > 1) {
       const int mid = (lo + hi) >> 1;
@@ -588,9 +811,13 @@ __device__ __forceinline__ unsigned long long pack_body(const Args& A, const Pac
     const int32_t key = A.hcol[p];
     const uint32_t dsc = row_desc[lo];
     const uint32_t base = dsc & 0xFFFFu, bmask = dsc >> 16;
-    uint32_t bk = bucket_of<VAR == VAR_MUL>(key, bmask);
+    const uint32_t v = (uint32_t)(A.n - key);  // (short rows)
+    uint32_t bk = SHORT ? v & bmask : bucket_of<VAR == VAR_MUL>(key, bmask);
     int disp = 0, slot = -1;
     while (true) {
+      if constexpr (SHORT) {
+        slot = insert16(reinterpret_cast<uint32_t*>(tab), base + bk, v);
+      } else
 #pragma unroll
       for (int s2 = 0; s2 < kBucket; ++s2) {
         if (slot < 0 && atomicCAS(&tab[(base + bk) * kBucket + s2], kEmpty, key) == kEmpty)
@@ -608,16 +835,16 @@ __device__ __forceinline__ unsigned long long pack_body(const Args& A, const Pac
   if (md) atomicMax(&s_D, md);
   __syncthreads();
 
-  TableRef tr{tab, val, 0, s_D, 0, 0, row_t0, row_desc, nr, lds_hits ? 1 : 0};
+  TableRef tr{tab, val, 0, s_D, 0, 0, row_t0, row_desc, nr, lds_hits ? 1 : 0, nullptr, nullptr};
   uint32_t hits = 0;
-  if (wlen > 0) wave_probe<MODE, TK_MULTI, VAR>(A, tr, wt, wq0, wlen, bm, hits, w0);
+  if (wlen > 0) wave_probe<MODE, SHORT ? TK_MULTI16 : TK_MULTI, VAR>(A, tr, wt, wq0, wlen, bm, hits, w0);
   if constexpr (VALS) {
     if (lds_hits) {
       // the (b, k) credits of the pack: one atomic per slot that was hit, at
       // the U position of its key (row found from the key index)
       __syncthreads();
-      for (uint32_t i = tid; i < S_tot; i += 256) {
-        if (tab[i] == kEmpty) continue;
+      for (uint32_t i = tid; i < S_tot; i += NT) {
+        if (SHORT ? reinterpret_cast<const uint16_t*>(tab)[i] == kEmpty16 : tab[i] == kEmpty) continue;
         const uint32_t w = (uint32_t)val[i];
         const uint32_t c = w >> kPackValBits;
         if (c == 0) continue;
@@ -639,7 +866,7 @@ __device__ __forceinline__ unsigned long long pack_body(const Args& A, const Pac
 // Register budgets (waves per SIMD) of the pack kernel and of the persistent
 // batch kernel in count mode (their LDS use would allow about 6 work-groups per
 // CU; 5 with spill-free registers runs faster).
-constexpr int kOccPacks = 5, kOccBatch = 5;
+constexpr int kOccPacks = 5, kOccBatch = 5, kOccBatch16 = 6;
 
 template <int MODE, int VAR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
@@ -647,7 +874,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
 void k_count_packs(Args A, const PackRow* __restrict__ recs, const PackInfo* __restrict__ info,
                    uint32_t pack_slots) {
   extern __shared__ int4 smem4[];  // 16-byte aligned: tables are read as int4 buckets
-  pack_body<MODE, VAR>(A, recs, info, blockIdx.x, pack_slots, reinterpret_cast<int32_t*>(smem4));
+  pack_body<MODE, VAR, false, kWaves>(A, recs, info, blockIdx.x, pack_slots, reinterpret_cast<int32_t*>(smem4));
+}
+
+// The short rows' packs of both pack classes in one launch: the first n0
+// work-groups take those of the first list.
+template <int MODE, int OCC, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(OCC)))
+void k_count_packs16(Args A, const PackRow* __restrict__ recs0, const PackInfo* __restrict__ info0, uint32_t n0,
+                     const PackRow* __restrict__ recs1, const PackInfo* __restrict__ info1, uint32_t pack_slots) {
+  extern __shared__ int4 smem4[];
+  const bool first = blockIdx.x < n0;
+  pack_body<MODE, VAR_BASE, true, WAVES>(A, first ? recs0 : recs1, first ? info0 : info1,
+                                         first ? blockIdx.x : blockIdx.x - n0, pack_slots,
+                                         reinterpret_cast<int32_t*>(smem4));
 }
 
 // Heavy rows: work-group = kWaves consecutive items of the same row b.
@@ -657,21 +897,20 @@ __device__ __forceinline__ unsigned long long items_body(const Args& A, const Co
   __shared__ int s_D;
   constexpr bool VALS = MODE == MODE_SUPPORT_FULL;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  uint32_t* bm = reinterpret_cast<uint32_t*>(smem) + wave * kBmWords;
-  const int32_t b = grp[0].b;
-  const int64_t rs = A.row_ptr[b], d = A.row_ptr[b + 1] - rs;
+  uint32_t* bm = reinterpret_cast<uint32_t*>(smem) + wave * wave_words(MODE);
+  const int64_t rs = grp[0].rs, d = grp[0].d;
   // this wave's item and its first window (in flight while the table is built)
   const CountItem it = grp[wave];
   const Window w0 = window_first(A, it.t0, it.q0, it.len);
   if (lane < kBmWords) bm[lane] = 0;
   block_init<MODE>();
   uint32_t hits = 0;
-  TableRef tr{nullptr, nullptr, 0, 0, rs, d, nullptr, nullptr, 0};
+  TableRef tr{nullptr, nullptr, 0, 0, rs, d, nullptr, nullptr, 0, 0, nullptr, nullptr};
   if (GLOBAL) {
     __syncthreads();  // shift counters cleared before any credit
   } else {
     const uint32_t S = 1u << grp[0].log2S;
-    int32_t* tab = smem + kItemMarkInts;
+    int32_t* tab = smem + kWavesBig * wave_words(MODE);
     int32_t* val = tab + S;
     for (uint32_t i = tid; i < S; i += blockDim.x) tab[i] = kEmpty;
     if (tid == 0) s_D = 0;
@@ -702,6 +941,172 @@ __device__ __forceinline__ unsigned long long items_body(const Args& A, const Co
   return block_flush<MODE>(hits, A);
 }
 
+// A group of kWaves items of one short row: its keys in a bitmap over the
+// distances [0, n - b]. FULL support also holds, for every bitmap word with
+// keys, the number of keys of smaller distance, and a hit counter per key, if
+// the row's keys fit the max_keys counters of the launch.
+struct BitsLds {
+  uint32_t* bm;    // this wave's words
+  uint32_t* bits;
+  uint32_t* cnt;
+  uint16_t* pfx;
+};
+template <int MODE>
+__device__ __forceinline__ BitsLds bits_lds(const Args& A, uint32_t max_keys, int32_t* smem) {
+  BitsLds L;
+  L.bm = reinterpret_cast<uint32_t*>(smem) + (threadIdx.x >> 6) * wave_words(MODE);
+  L.bits = reinterpret_cast<uint32_t*>(smem) + kWaves * wave_words(MODE);
+  L.cnt = L.bits + bitmap_words(A.n);
+  L.pfx = reinterpret_cast<uint16_t*>(L.cnt + max_keys);
+  return L;
+}
+
+// Keys of the row a thread holds in registers (loaded ahead).
+constexpr int kKeyRegs = 4;
+__device__ __forceinline__ void bits_keys(const Args& A, const CountItem& it, int32_t (&key)[kKeyRegs]) {
+#pragma unroll
+  for (int j = 0; j < kKeyRegs; ++j) {
+    const uint32_t i = threadIdx.x + (uint32_t)j * (64 * kWaves);
+    key[j] = i < it.d ? A.hcol[(uint64_t)it.rs + i] : 0;
+  }
+}
+
+// Clears and fills the bitmap of `it`'s row; ends with a barrier. The caller
+// has passed a barrier since the bitmap was last read.
+template <int MODE>
+__device__ __forceinline__ void bits_build(const Args& A, const BitsLds& L, const CountItem& it, uint32_t max_keys,
+                                           const int32_t (&key)[kKeyRegs]) {
+  constexpr bool FULL = MODE == MODE_SUPPORT_FULL;
+  constexpr uint32_t NT = 64 * kWaves;
+  const uint32_t words = ((uint32_t)(A.n - it.b) >> 5) + 1;
+  for (uint32_t i = threadIdx.x; i < words; i += NT) L.bits[i] = 0;
+  if (FULL && it.d <= max_keys)
+    for (uint32_t i = threadIdx.x; i < it.d; i += NT) L.cnt[i] = 0;
+  __syncthreads();
+  auto put = [&](uint32_t i, int32_t k) {
+    const uint32_t v = (uint32_t)(A.n - k);
+    atomicOr(&L.bits[v >> 5], 1u << (v & 31));
+    // (ascending columns: distances fall along the row, and the last key of
+    // a word is the word's smallest distance)
+    if (FULL && (i + 1 == it.d || (uint32_t)(A.n - A.hcol[(uint64_t)it.rs + i + 1]) >> 5 != v >> 5))
+      L.pfx[v >> 5] = (uint16_t)(it.d - 1 - i);
+  };
+#pragma unroll
+  for (int j = 0; j < kKeyRegs; ++j) {
+    const uint32_t i = threadIdx.x + (uint32_t)j * NT;
+    if (i < it.d) put(i, key[j]);
+  }
+  for (uint32_t i = threadIdx.x + kKeyRegs * NT; i < it.d; i += NT) put(i, A.hcol[(uint64_t)it.rs + i]);
+  __syncthreads();
+}
+
+template <int MODE>
+__device__ __forceinline__ void bits_probe(const Args& A, const BitsLds& L, const CountItem& it, uint32_t max_keys,
+                                           const Window& w0, uint32_t& hits) {
+  constexpr bool FULL = MODE == MODE_SUPPORT_FULL;
+  TableRef tr{reinterpret_cast<const int32_t*>(L.bits), nullptr, 0, 0, (int64_t)it.rs, (int64_t)it.d, nullptr,
+              nullptr, 0, 0, L.pfx, it.d <= max_keys ? L.cnt : nullptr};
+  if (it.len) wave_probe<MODE, TK_BITS, VAR_BASE>(A, tr, it.t0, it.q0, it.len, L.bm, hits, w0);
+  if constexpr (FULL) {
+    // the (b, k) credits of the work-group: one atomic per key that was hit
+    if (it.d <= max_keys) {
+      __syncthreads();
+      for (uint32_t i = threadIdx.x; i < it.d; i += 64 * kWaves) {
+        const uint32_t c = L.cnt[i];
+        const uint64_t p = (uint64_t)it.rs + it.d - 1 - i;
+        if (c && p < (uint64_t)A.m) atomicAdd(&A.support[p], (int)c);
+      }
+    }
+  }
+}
+
+// The groups [g, end) of one class's short rows (items: the first of them),
+// end > g. A group's chain of dependent loads (item, then the row's keys and
+// the wave's first window) costs more than the probes of most groups, so the
+// next group's keys and window and the item of the one after are loaded while
+// the present one is probed. Returns this thread's hits.
+template <int MODE>
+__device__ __forceinline__ unsigned long long bits_groups(const Args& A, const CountItem* __restrict__ items,
+                                                          uint32_t g, uint32_t end, uint32_t max_keys,
+                                                          int32_t* smem) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const BitsLds L = bits_lds<MODE>(A, max_keys, smem);
+  if (lane < kBmWords) L.bm[lane] = 0;
+  auto item = [&](uint32_t i) { return items[(uint64_t)(i < end ? i : end - 1) * kWaves + wave]; };
+  CountItem it = item(g), next = item(g + 1);
+  int32_t key[kKeyRegs];
+  bits_keys(A, it, key);
+  Window w = window_first(A, it.t0, it.q0, it.len);
+  unsigned long long sum = 0;
+  for (;;) {
+    bits_build<MODE>(A, L, it, max_keys, key);
+    const CountItem cur = it;
+    const Window w0 = w;
+    it = next;
+    bits_keys(A, it, key);
+    w = window_first(A, it.t0, it.q0, it.len);
+    next = item(g + 2);
+    uint32_t hits = 0;
+    bits_probe<MODE>(A, L, cur, max_keys, w0, hits);
+    sum += hits;
+    if (++g >= end) break;
+    __syncthreads();  // every wave is done with the bitmap
+  }
+  return sum;
+}
+
+// The same with the rows looked up in U_b in HBM (batch units under an LDS cap).
+template <int MODE>
+__device__ __forceinline__ unsigned long long bits_groups_hbm(const Args& A, const CountItem* __restrict__ items,
+                                                              uint32_t g, uint32_t end, int32_t* smem) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t* bm = reinterpret_cast<uint32_t*>(smem) + wave * wave_words(MODE);
+  if (lane < kBmWords) bm[lane] = 0;
+  wave_sync_lds();
+  unsigned long long sum = 0;
+  for (; g < end; ++g) {
+    const CountItem it = items[(uint64_t)g * kWaves + wave];
+    TableRef tr{nullptr, nullptr, 0, 0, (int64_t)it.rs, (int64_t)it.d, nullptr, nullptr, 0, 0, nullptr, nullptr};
+    uint32_t hits = 0;
+    if (it.len)
+      wave_probe<MODE, TK_GLOBAL16, VAR_BASE>(A, tr, it.t0, it.q0, it.len, bm, hits,
+                                              window_first(A, it.t0, it.q0, it.len));
+    sum += hits;
+  }
+  return sum;
+}
+
+// The short rows' items of all item classes in one launch: a work-group takes
+// one bundle of groups (kWaves items of one row each); the work-groups from
+// end[c - 1] to end[c] take those of list c.
+constexpr int kItemLists = NUM_CLASSES - CLS_WG_SMALL;
+struct ItemLists {
+  const CountItem* items[kItemLists];
+  const uint32_t* bundle[kItemLists];
+  uint32_t end[kItemLists];
+};
+
+template <int MODE, int OCC>
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(OCC)))
+void k_count_bits(Args A, ItemLists lists, uint32_t max_keys) {
+  extern __shared__ int4 smem4[];
+  const CountItem* items = lists.items[0];
+  const uint32_t* bundle = lists.bundle[0];
+  uint32_t base = 0;
+#pragma unroll
+  for (int c = 1; c < kItemLists; ++c) {
+    if (blockIdx.x >= lists.end[c - 1]) {
+      items = lists.items[c];
+      bundle = lists.bundle[c];
+      base = lists.end[c - 1];
+    }
+  }
+  const uint32_t g = bundle[blockIdx.x - base];
+  const uint32_t end = bundle[blockIdx.x - base + 1];
+  if (g >= end) return;  // (a group longer than a bundle leaves the next one empty)
+  block_flush<MODE>(bits_groups<MODE>(A, items, g, end, max_keys, reinterpret_cast<int32_t*>(smem4)), A);
+}
+
 // OCC: waves per SIMD the kernel's registers are budgeted for. A class whose
 // tables limit a CU to fewer work-groups gets the registers that would
 // otherwise go unused (fewer spills in the probe loop).
@@ -717,6 +1122,9 @@ void k_count_items(Args A, const CountItem* __restrict__ items) {
 // but 7 waves per SIMD with spill-free registers run faster; wg_huge tables
 // (32 KiB) allow 4-5 work-groups per CU and wg_giant tables (64 KiB) 2.
 // Support modes hold more state per probe and run at 4.
+constexpr int kOccBits = 7, kOccBitsOriented = 5, kOccBitsFull = 4;  // (bitmaps take at most 8 KiB: registers limit the waves)
+constexpr int kOccPacks16 = 7;
+constexpr uint32_t kPacks16Waves = 512;  // packs up to which 16 waves share one
 constexpr int kOccSmall = 7, kOccLarge = 7, kOccHuge = 5, kOccGiant = 4, kOccSupport = 5;
 
 template <int MODE, bool GLOBAL, int VAR>
@@ -761,15 +1169,66 @@ const char* const kLaunchNames[4][NUM_CLASSES] = {
     {"block:pack_small", "block:pack_large", "block:wg_small", "block:wg_large", "block:wg_huge",
      "block:wg_giant", "block:global"}};
 
+const char* const kBitsNames[3] = {"count:short_items", "support_full:short_items", "support_oriented:short_items"};
+const char* const kPacks16Names[3] = {"count:short_packs", "support_full:short_packs", "support_oriented:short_packs"};
+
 // Work-groups per launch of one class: a dispatch holds fewer than 2^32
 // work-items (a class of more groups, e.g. small wave items on a very large
 // graph, is launched in pieces; each group finds its data by its index).
 constexpr int64_t kClassLaunchMax = (int64_t)1 << 22;
 
+// The short rows' items.
+template <int MODE>
+void launch_bits(const WorkSet& w, const Args& A, hipStream_t st) {
+  ItemLists lists;
+  uint32_t bundles = 0;
+  int log2S = 6;
+  for (int i = 0; i < kItemLists; ++i) {
+    const int c = CLS_WG_SMALL + i;
+    lists.items[i] = w.items[c] + w.n_items32[c];
+    lists.bundle[i] = w.bundle[c];
+    if (w.n_items[c] > w.n_items32[c]) log2S = std::max(log2S, std::min(w.cls_log2S[c], kMaxLog2S));
+    bundles += (uint32_t)w.n_bundles[c];
+    lists.end[i] = bundles;
+  }
+  if (bundles == 0) return;
+  const size_t lds = bits_lds_bytes(A.n, log2S, MODE);
+  const uint32_t max_keys = bits_max_keys(log2S, MODE);
+  constexpr int OCC = MODE == MODE_SUPPORT_FULL ? kOccBitsFull : MODE == MODE_COUNT ? kOccBits : kOccBitsOriented;
+  TC_LAUNCH(kBitsNames[MODE], (k_count_bits<MODE, OCC>), dim3(bundles), dim3(64 * kWaves), lds, st, A, lists,
+            max_keys);
+}
+
+// The short rows' packs. With few of them (a small graph) more waves share
+// each pack: four would leave most of the GPU idle behind a few long chains
+// of windows.
+template <int MODE>
+void launch_packs16(const WorkSet& w, const Args& A, hipStream_t st) {
+  uint32_t n[2], slots = 0;
+  const PackInfo* info[2];
+  for (int c = 0; c < 2; ++c) {
+    n[c] = (uint32_t)(w.n_packs[c] - w.n_packs32[c]);
+    info[c] = w.pack_info[c] + w.n_packs32[c];
+    if (n[c]) slots = std::max(slots, pack16_slots(w.wp.pack_slots, w.pack_log2S[c]));
+  }
+  const uint32_t packs = n[0] + n[1];
+  if (packs == 0) return;
+  constexpr int OCC = MODE == MODE_SUPPORT_FULL ? 4 : kOccPacks16;
+  const int waves = packs <= kPacks16Waves ? 16 : packs <= 2 * kPacks16Waves ? 8 : kWaves;
+  const size_t lds = pack16_lds_bytes(slots, MODE, waves);
+  auto* f = waves == 16 ? k_count_packs16<MODE, 4, 16> : waves == 8 ? k_count_packs16<MODE, 4, 8>
+                                                                    : k_count_packs16<MODE, OCC, kWaves>;
+  if (lds > 65536)
+    TC_HIP(hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  // (at most one pack per short row: fewer than 2^16)
+  TC_LAUNCH(kPacks16Names[MODE], f, dim3(packs), dim3(64 * waves), lds, st, A, w.pack_recs[0], info[0], n[0],
+            w.pack_recs[1], info[1], slots);
+}
+
 template <int MODE, int VAR>
 void launch_items_class(const WorkSet& w, const Args& A, int c, size_t mark_bytes, hipStream_t st) {
-  if (w.n_items[c] == 0) return;
-  const int64_t groups = w.n_items[c] / class_waves(c);
+  if (w.n_items32[c] == 0) return;
+  const int64_t groups = w.n_items32[c] / class_waves(c);
   const bool global = c == CLS_GLOBAL;
   const void* f = global ? items_kernel<MODE, true, VAR>(c) : items_kernel<MODE, false, VAR>(c);
   const size_t lds = global ? mark_bytes : items_lds_bytes(w.cls_log2S[c], MODE);
@@ -838,21 +1297,26 @@ void launch_mode(const WorkSet& w, const Args& A, hipStream_t st) {
     TC_HIP(hipStreamWaitEvent(side->aux, side->fork, 0));
   }
   // heavy classes first (on st), then the light ones (on the side stream)
+  if constexpr (MODE == MODE_BLOCK)
+    TC_REQUIRE(w.b16 >= w.nrows, TC_EDEVICE, "launch_count: short rows in a rank's block");
+  else
+    launch_bits<MODE>(w, A, st);
   for (int c = CLS_WG_LARGE; c <= CLS_GLOBAL; ++c) launch_items_class<MODE, VAR>(w, A, c, mark_bytes, st);
   const hipStream_t ls = side ? side->aux : st;
-  for (int c = CLS_PACK_SMALL; c <= CLS_PACK_LARGE; ++c) {
-    if (w.n_packs[c] == 0) continue;
+  for (int c = CLS_PACK_LARGE; c >= CLS_PACK_SMALL; --c) {
+    if (w.n_packs32[c] == 0) continue;
     // a pack's tables take at most wp.pack_slots plus one row's table
     const uint32_t slots = w.wp.pack_slots + (1u << w.pack_log2S[c]);
     const size_t lds = pack_lds_bytes(slots, MODE);
     if (lds > 65536)
       TC_HIP(hipFuncSetAttribute((const void*)k_count_packs<MODE, VAR>,
                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    for (int64_t p0 = 0; p0 < w.n_packs[c]; p0 += kClassLaunchMax)  // (pieces: see kClassLaunchMax)
+    for (int64_t p0 = 0; p0 < w.n_packs32[c]; p0 += kClassLaunchMax)  // (pieces: see kClassLaunchMax)
       TC_LAUNCH(kLaunchNames[MODE][c], (k_count_packs<MODE, VAR>),
-                dim3((unsigned)std::min<int64_t>(kClassLaunchMax, w.n_packs[c] - p0)), dim3(256), lds, ls, A,
+                dim3((unsigned)std::min<int64_t>(kClassLaunchMax, w.n_packs32[c] - p0)), dim3(256), lds, ls, A,
                 w.pack_recs[c], w.pack_info[c] + p0, slots);
   }
+  if constexpr (MODE != MODE_BLOCK) launch_packs16<MODE>(w, A, ls);
   launch_items_class<MODE, VAR>(w, A, CLS_WG_SMALL, mark_bytes, ls);
   if (side) {
     TC_HIP(hipEventRecord(side->join, side->aux));
@@ -880,8 +1344,12 @@ __global__ void k_batch_clear(unsigned long long* counts, int64_t n, unsigned in
 // atomic takes `chunk` consecutive units (a tuning choice: fewer atomics on
 // the one counter against coarser balance). Each unit runs the same body as
 // its class's own kernel with its graph's arguments.
-template <int MODE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == MODE_COUNT ? kOccBatch : 4)))
+// ONLY16: every unit is one of short rows with its table in LDS (all graphs
+// of up to kShortSpan vertices): the other bodies, whose registers would
+// limit the waves, are left out.
+template <int MODE, bool ONLY16>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
+    MODE == MODE_SUPPORT_FULL ? 4 : ONLY16 ? kOccBatch16 : MODE == MODE_COUNT ? kOccBatch : 4)))
 void k_count_batch(const Args* __restrict__ gargs, const BatchUnit* __restrict__ units, uint32_t n_units,
                    uint32_t chunk, unsigned int* __restrict__ queue, unsigned long long* __restrict__ counts) {
   extern __shared__ int4 smem4[];
@@ -900,9 +1368,19 @@ void k_count_batch(const Args* __restrict__ gargs, const BatchUnit* __restrict__
       const BatchUnit bu = units[u];
       Args A = gargs[bu.graph];
       A.count = counts + bu.graph;
-      if (bu.kind == BK_PACK) {
-        pack_body<MODE, VAR_BASE>(A, static_cast<const PackRow*>(bu.p0), static_cast<const PackInfo*>(bu.p1),
-                                  bu.index, bu.slots, smem);
+      if (bu.kind == BK_PACK16) {
+        pack_body<MODE, VAR_BASE, true, kWaves>(A, static_cast<const PackRow*>(bu.p0), static_cast<const PackInfo*>(bu.p1),
+                                        bu.index, bu.slots, smem);
+      } else if (bu.kind == BK_PACK) {
+        pack_body<MODE, VAR_BASE, false, kWaves>(A, static_cast<const PackRow*>(bu.p0), static_cast<const PackInfo*>(bu.p1),
+                                         bu.index, bu.slots, smem);
+      } else if (ONLY16 || bu.kind == BK_BITS) {
+        if (bu.index < bu.end)
+          block_flush<MODE>(bits_groups<MODE>(A, static_cast<const CountItem*>(bu.p0), bu.index, (uint32_t)bu.end,
+                                              bu.slots, smem), A);
+      } else if (bu.kind == BK_BITS_HBM) {
+        block_flush<MODE>(bits_groups_hbm<MODE>(A, static_cast<const CountItem*>(bu.p0), bu.index, (uint32_t)bu.end,
+                                                smem), A);
       } else if (bu.kind == BK_ITEMS) {
         items_body<MODE, false, VAR_BASE>(A, static_cast<const CountItem*>(bu.p0), smem);
       } else {
@@ -915,14 +1393,15 @@ void k_count_batch(const Args* __restrict__ gargs, const BatchUnit* __restrict__
 template <int MODE>
 void launch_batch_mode(const Args* d_args, const BatchUnit* d_units, int64_t n_units, uint32_t chunk,
                        unsigned int* d_queue, unsigned long long* counts, unsigned grid, size_t lds,
-                       hipStream_t st, bool timed) {
+                       bool only16, hipStream_t st, bool timed) {
   static const char* const kNames[3] = {"count:batch", "support_full:batch", "support_oriented:batch"};
   if (n_units == 0) return;
+  auto* f = only16 ? k_count_batch<MODE, true> : k_count_batch<MODE, false>;
   if (timed)
-    TC_LAUNCH(kNames[MODE], k_count_batch<MODE>, dim3(grid), dim3(256), lds, st, d_args, d_units,
-              (uint32_t)n_units, chunk, d_queue, counts);
+    TC_LAUNCH(kNames[MODE], f, dim3(grid), dim3(256), lds, st, d_args, d_units, (uint32_t)n_units, chunk, d_queue,
+              counts);
   else
-    hipLaunchKernelGGL(k_count_batch<MODE>, dim3(grid), dim3(256), lds, st, d_args, d_units,
+    hipLaunchKernelGGL(f, dim3(grid), dim3(256), lds, st, d_args, d_units,
                        (uint32_t)n_units, chunk, d_queue, counts);
 }
 
@@ -930,17 +1409,34 @@ void launch_batch_mode(const Args* d_args, const BatchUnit* d_units, int64_t n_u
 
 size_t pack_lds_bytes(uint32_t slots, int mode) {
   const size_t vals = mode == MODE_SUPPORT_FULL ? 2 : 1;
-  return sizeof(int32_t) * ((size_t)kMarkInts + kPackMetaWords + 3 + (size_t)slots * vals);
+  return sizeof(int32_t) * ((size_t)pack_head_words(mode, kWaves) + (size_t)slots * vals);
 }
 
 size_t items_lds_bytes(int log2S, int mode) {
   const size_t vals = mode == MODE_SUPPORT_FULL ? 2 : 1;
-  return sizeof(int32_t) * ((size_t)kItemMarkInts + (log2S < 0 ? 0 : ((size_t)1 << log2S) * vals));
+  return sizeof(int32_t) * ((size_t)kWavesBig * wave_words(mode) + (log2S < 0 ? 0 : ((size_t)1 << log2S) * vals));
+}
+
+size_t pack16_lds_bytes(uint32_t slots, int mode, int waves) {
+  return sizeof(int32_t) * ((size_t)pack_head_words(mode, waves) + slots / 2 +
+                            (mode == MODE_SUPPORT_FULL ? (size_t)slots : 0));
+}
+
+// Hit counters of a bitmap work-group (FULL): one per key of the class's
+// longest row, as far as its 32-bit table would fit LDS.
+uint32_t bits_max_keys(int log2S, int mode) {
+  return mode == MODE_SUPPORT_FULL && log2S <= kMaxLog2S ? 1u << (log2S <= 12 ? log2S - 2 : log2S - 1) : 0u;
+}
+
+size_t bits_lds_bytes(int64_t n, int log2S, int mode) {
+  const size_t words = bitmap_words((int32_t)n);
+  return sizeof(int32_t) * ((size_t)kWaves * wave_words(mode) + words + bits_max_keys(log2S, mode)) +
+         (mode == MODE_SUPPORT_FULL ? sizeof(uint16_t) * ((words + 1) & ~(size_t)1) : 0);
 }
 
 void launch_batch(CountMode mode, const CountArgs* d_args, const BatchUnit* d_units, int64_t n_units,
                   uint32_t chunk, int64_t n_out, unsigned int* d_queue, int64_t* d_counts, unsigned grid,
-                  size_t lds, hipStream_t st, bool timed) {
+                  size_t lds, bool only16, hipStream_t st, bool timed) {
   TC_REQUIRE(chunk >= 1, TC_EINVAL, "launch_batch: chunk must be >= 1");
   TC_REQUIRE(mode == MODE_COUNT || mode == MODE_SUPPORT_FULL || mode == MODE_SUPPORT_ORIENTED, TC_EINVAL,
              "launch_batch: unsupported mode");
@@ -950,14 +1446,14 @@ void launch_batch(CountMode mode, const CountArgs* d_args, const BatchUnit* d_un
   else hipLaunchKernelGGL(k_batch_clear, dim3(cg), dim3(256), 0, st, counts, n_out, d_queue);
   switch (mode) {
     case MODE_COUNT:
-      launch_batch_mode<MODE_COUNT>(d_args, d_units, n_units, chunk, d_queue, counts, grid, lds, st, timed);
+      launch_batch_mode<MODE_COUNT>(d_args, d_units, n_units, chunk, d_queue, counts, grid, lds, only16, st, timed);
       break;
     case MODE_SUPPORT_FULL:
-      launch_batch_mode<MODE_SUPPORT_FULL>(d_args, d_units, n_units, chunk, d_queue, counts, grid, lds, st, timed);
+      launch_batch_mode<MODE_SUPPORT_FULL>(d_args, d_units, n_units, chunk, d_queue, counts, grid, lds, only16, st, timed);
       break;
     default:
-      launch_batch_mode<MODE_SUPPORT_ORIENTED>(d_args, d_units, n_units, chunk, d_queue, counts, grid, lds, st,
-                                               timed);
+      launch_batch_mode<MODE_SUPPORT_ORIENTED>(d_args, d_units, n_units, chunk, d_queue, counts, grid, lds, only16,
+                                               st, timed);
       break;
   }
   TC_HIP(hipGetLastError());
@@ -978,8 +1474,9 @@ void launch_count(const CountView& v, CountMode mode, int64_t* d_count, int32_t*
   TC_REQUIRE(v.pm < kMaxEdges, TC_EOVERFLOW, "launch_count: probe side of 2^32 - 256 entries or more");
   const bool wide = v.pm > kMaxBufferEdges;
   TC_REQUIRE(!wide || mode != MODE_BLOCK, TC_EOVERFLOW, "launch_count: a rank's probe side of 2^30 entries or more");
+  TC_REQUIRE(w.b16 >= w.nrows || v.pcol16 != nullptr, TC_EDEVICE, "launch_count: no short columns");
   Args A{v.hrow_ptr, v.hcol, v.pcol, w.tstart, w.tprefix, w.tbeg, w.tend, w.n_tasks, (uint32_t)v.pm,
-         reinterpret_cast<unsigned long long*>(d_count), d_support,
+         v.pcol16, (int32_t)w.nrows, reinterpret_cast<unsigned long long*>(d_count), d_support,
          reinterpret_cast<unsigned long long*>(d_per_shift), v.q, v.xy};
   TC_REQUIRE(v.hash == 0 || mode == MODE_COUNT, TC_EINVAL, "launch_count: multiplicative hashing counts only");
   TC_REQUIRE(!(wide && v.hash), TC_EOVERFLOW, "launch_count: multiplicative hashing below 2^30 edges only");
@@ -1001,12 +1498,17 @@ void launch_count(const CountView& v, CountMode mode, int64_t* d_count, int32_t*
   }
 }
 
-void batch_kernel_lds(CountMode mode, size_t lds) {
+template <bool ONLY16>
+static const void* batch_kernel(CountMode mode) {
+  return mode == MODE_COUNT          ? (const void*)k_count_batch<MODE_COUNT, ONLY16>
+         : mode == MODE_SUPPORT_FULL ? (const void*)k_count_batch<MODE_SUPPORT_FULL, ONLY16>
+                                     : (const void*)k_count_batch<MODE_SUPPORT_ORIENTED, ONLY16>;
+}
+
+void batch_kernel_lds(CountMode mode, size_t lds, bool only16) {
   if (lds <= 65536) return;
-  const void* f = mode == MODE_COUNT          ? (const void*)k_count_batch<MODE_COUNT>
-                  : mode == MODE_SUPPORT_FULL ? (const void*)k_count_batch<MODE_SUPPORT_FULL>
-                                              : (const void*)k_count_batch<MODE_SUPPORT_ORIENTED>;
-  TC_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  TC_HIP(hipFuncSetAttribute(only16 ? batch_kernel<true>(mode) : batch_kernel<false>(mode),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
 }
 
 void zero_i32(int32_t* p, int64_t n, hipStream_t st, bool timed) {

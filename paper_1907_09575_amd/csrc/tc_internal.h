@@ -65,10 +65,11 @@ struct alignas(8) CountItem {
   int32_t b;       // hashed row (rank)
   uint32_t t0;     // task containing q0
   uint64_t q0;     // first global probe index
-  uint32_t len;    // number of probes
+  uint32_t len;    // number of probes (short rows: units)
   uint32_t log2S;  // hash table size (slots) = 1 << log2S
+  uint32_t rs, d;  // the row itself: U_b = col[rs, rs + d)
 };
-static_assert(sizeof(CountItem) == 24, "CountItem layout");
+static_assert(sizeof(CountItem) == 32, "CountItem layout");
 
 // Launch classes of the count kernels (see tc_count.hip).
 enum ItemClass : int {
@@ -105,6 +106,33 @@ constexpr int kBucket = 4;              // slots per hash bucket (one 16-byte LD
 // up to 256 threads) must stay below 2^32 work-items: fewer than kMaxEdges.
 constexpr int64_t kMaxEdges = (1ll << 32) - 256;
 constexpr int64_t kMaxBufferEdges = (1ll << 30) - 64;  // below: probe reads by 32-bit byte offsets
+
+// Short columns. The last kShortSpan + 1 rows of U (ranks from n - kShortSpan
+// up) have all their entries k in the same ranks, so the distance n - k of
+// any entry that a task of such a row looks up fits 16 bits, exactly. U's
+// columns are kept a second time in that form (Graph::col16), and the rows
+// from Graph::b16 on ("short rows") are counted from it: half the bytes per
+// probe, and a bitmap or 16-bit table in LDS instead of 32-bit slots. RMAT
+// (edge factor 16): short rows hold 99% of all probes at scale 20, 94% at
+// scale 22.
+//   col16[i] = n - col[i] if that is at most kShortSpan, else 0; the first
+// entry of every row (never probed: probes start after their task's own
+// entry) and the entries past m are 0. No key of a short row's table is 0.
+// Probes are read two at a time: a short row's task (entries [i, end) of U_a)
+// covers the 32-bit words i / 2 .. (end - 1) / 2 of col16 ("units"). The half
+// word before i, if the first word holds it, is the task's own entry b, and
+// the one at end the first entry of the next row (0): neither is ever a key
+// of U_b, so no half needs a mask.
+constexpr int64_t kShortSpan = 65534;
+constexpr int64_t kMaxShortEdges = (1ll << 31) - 64;  // units by 32-bit byte offsets
+inline int64_t short_rows_begin(int64_t n, int64_t m) {
+  return m > kMaxShortEdges ? n : (n > kShortSpan ? n - kShortSpan : 0);
+}
+// Probes a task of a short row is charged for in the work decomposition (two
+// per unit), and its units.
+__host__ __device__ inline uint32_t short_units(uint32_t first, uint32_t end) {
+  return (uint32_t)(((uint64_t)end + 1) >> 1) - (first >> 1);
+}
 
 // Waves sharing one table in a work-group of item class c: the classes whose
 // tables allow only a few work-groups per CU get twice the waves per table.
@@ -178,15 +206,20 @@ struct alignas(16) PackRow {
   uint32_t tb, te;  // its tasks [tb, te) (class-major order)
 };
 // A pack: its rows [r0, r1) of the class, its probes [q0, q1) and, for each
-// of its kWaves equal shares of them, the task holding the share's first
+// of kPackWavesMax equal shares of them, the task holding the share's first
 // probe (computed once when the work is built, instead of searched for by
-// every launch).
+// every launch). A pack work-group has 4, 8 or 16 waves, each taking
+// consecutive shares.
+constexpr int kPackWavesMax = 16;
 struct alignas(16) PackInfo {
   uint64_t q0, q1;
   uint32_t r0, r1;
-  uint32_t wt[kWaves];
+  uint32_t wt[kPackWavesMax];
+  uint32_t pad[2];
 };
-static_assert(sizeof(PackRow) == 16 && sizeof(PackInfo) == 48, "pack record layout");
+static_assert(sizeof(PackRow) == 16 && sizeof(PackInfo) == 96, "pack record layout");
+// First probe of share i (of kPackWavesMax) of a pack of W probes.
+__host__ __device__ inline uint64_t pack_share(uint64_t W, int i) { return W * (uint64_t)i / kPackWavesMax; }
 
 // Row-bucket thresholds: which rows are packed and how the work is cut.
 struct WorkParams {
@@ -205,28 +238,38 @@ struct WorkParams {
 struct WorkSet {
   int64_t nrows = 0, n_tasks = 0, probes = 0;
   WorkParams wp;  // the thresholds this decomposition was built with
+  int64_t b16 = 0;  // short rows: hashed rows from b16 on (nrows: none)
   uint32_t* tbeg = nullptr;     // nrows, tasks of hashed row b: [tbeg[b], tend[b]) (class-major order)
   uint32_t* tend = nullptr;     // nrows
   uint32_t* tstart = nullptr;   // n_tasks, probe-side index of the task's first probe
-  uint64_t* tprefix = nullptr;  // n_tasks + 1, exclusive prefix of task lengths
+  uint64_t* tprefix = nullptr;  // n_tasks + 1, exclusive prefix of task lengths (probes; short rows: units)
 
   // pack classes: pack p covers pack_rows[c][pack_ptr[c][p] .. pack_ptr[c][p+1])
   int32_t* pack_rows[2] = {nullptr, nullptr};   // light rows b of the class, ascending
   uint32_t* pack_ptr[2] = {nullptr, nullptr};
   PackRow* pack_recs[2] = {nullptr, nullptr};   // the rows' records, same order
-  PackInfo* pack_info[2] = {nullptr, nullptr};  // one per pack, heaviest first (launch order)
+  PackInfo* pack_info[2] = {nullptr, nullptr};  // one per pack, heaviest first (launch order), short rows' last
   int64_t n_pack_rows[2] = {0, 0};
   int64_t n_packs[2] = {0, 0};
+  int64_t n_packs32[2] = {0, 0};                // packs of rows below b16 (they come first)
   int32_t pack_log2S[2] = {0, 0};               // largest row table of the class (log2 slots)
 
   // work-group classes: n_items[c] items (a multiple of kWaves)
   CountItem* items[NUM_CLASSES] = {};
   int64_t n_items[NUM_CLASSES] = {};
+  int64_t n_items32[NUM_CLASSES] = {};  // items of rows below b16 (they come first)
+  // short rows' groups of an item class (kWaves items each, counted from the
+  // class's first) in bundles of about equal weight, one per work-group:
+  // bundle i holds the groups [bundle[c][i], bundle[c][i + 1])
+  uint32_t* bundle[NUM_CLASSES] = {};
+  int64_t n_bundles[NUM_CLASSES] = {};
+  uint64_t bundle_w = 1;  // probes of a bundle
   int32_t cls_log2S[NUM_CLASSES] = {};
   uint32_t cls_chunk[NUM_CLASSES] = {};  // probes per wave item of each item class
 
   // per class: rows, table keys, tasks, probes (host copy)
   int64_t cls_stats[NUM_CLASSES][4] = {};
+  uint64_t cls_probes[NUM_CLASSES] = {};  // (read back by build_work; see finish_work)
 };
 
 // Streams that have used an object's device memory, each with an event
@@ -265,6 +308,7 @@ struct Graph {
   int64_t* row_ptr = nullptr;  // n + 1, U rows
   int32_t* col = nullptr;      // m, rows sorted ascending
   int32_t* perm = nullptr;     // n, perm[original id] = rank
+  uint16_t* col16 = nullptr;   // m (+ padding), short columns
   WorkSet w;
 };
 
@@ -310,6 +354,7 @@ struct CountView {
   const WorkSet* w;
   int32_t q = 1, xy = 0;  // MODE_BLOCK: grid size and (x + y) % q
   int hash = 0;           // 1: multiplicative hashing (MODE_COUNT only)
+  const uint16_t* pcol16 = nullptr;  // short columns of the probe side (w->b16 < w->nrows)
 };
 
 void launch_count(const CountView& v, CountMode mode, int64_t* d_count, int32_t* d_support,
@@ -327,6 +372,8 @@ struct CountArgs {
   const uint32_t* __restrict__ tend;
   int64_t T;
   uint32_t m;  // entries of col
+  const uint16_t* __restrict__ col16;  // short columns of the probe side
+  int32_t n;                           // vertices: col16 holds n - k
   unsigned long long* count;
   int32_t* support;
   unsigned long long* per_shift;  // MODE_BLOCK: q counters
@@ -336,14 +383,18 @@ struct CountArgs {
 // ---- batched persistent count (tc_count.hip kernel, tc_batch.cpp plan) -------
 // One unit of the persistent launch: a pack of light rows, a work-group of
 // kWaves items sharing an LDS table, or such a group whose row is looked up
-// in HBM.
-enum BatchKind : int32_t { BK_PACK = 0, BK_ITEMS = 1, BK_ITEMS_HBM = 2 };
+// in HBM; the same three of short rows.
+enum BatchKind : int32_t { BK_PACK = 0, BK_ITEMS = 1, BK_ITEMS_HBM = 2, BK_PACK16 = 3, BK_BITS = 4, BK_BITS_HBM = 5 };
 
 struct alignas(16) BatchUnit {
-  const void* p0;      // pack: PackRow records of the class; items: the group's first item
-  const void* p1;      // pack: PackInfo records of the class
+  const void* p0;      // pack: PackRow records of the class; items: the group's first item;
+                       // bits: first item of the class's short rows
+  union {
+    const void* p1;    // pack: PackInfo records of the class
+    uint64_t end;      // bits: groups [index, end)
+  };
   uint32_t index;      // pack: pack number
-  uint32_t slots;      // pack: table slots reserved for the pack
+  uint32_t slots;      // pack: table slots reserved for the pack; bits: hit counters (FULL)
   int32_t graph;       // entry of the plan's graph list (and of the output)
   int32_t kind;        // BatchKind
 };
@@ -356,10 +407,10 @@ static_assert(sizeof(BatchUnit) == 32, "BatchUnit layout");
 // capture).
 void launch_batch(CountMode mode, const CountArgs* d_args, const BatchUnit* d_units, int64_t n_units,
                   uint32_t chunk, int64_t n_out, unsigned int* d_queue, int64_t* d_counts, unsigned grid,
-                  size_t lds, hipStream_t st, bool timed);
+                  size_t lds, bool only16, hipStream_t st, bool timed);
 // Allow the persistent kernel of `mode` `lds` bytes of dynamic LDS (call
-// outside any capture).
-void batch_kernel_lds(CountMode mode, size_t lds);
+// outside any capture). only16: all units are BK_PACK16 or BK_BITS.
+void batch_kernel_lds(CountMode mode, size_t lds, bool only16);
 // Batch plans (tc_batch.hip): one persistent launch over many graphs in one
 // mode; support modes write each entry's own support array (cleared by every
 // launch of the plan). tuning_json as tc_batch_create's. Synchronises st.
@@ -387,9 +438,24 @@ void zero_i32(int32_t* p, int64_t n, hipStream_t st, bool timed);
 // lookups), in CountMode `mode` (full support tables also hold U positions).
 size_t pack_lds_bytes(uint32_t slots, int mode);
 size_t items_lds_bytes(int log2S, int mode);
+// The same of short rows of n: a pack with `slots` 16-bit slots; an item
+// work-group with a bitmap, of a class whose largest 32-bit table has 2^log2S
+// slots (bits_max_keys: its hit counters).
+size_t pack16_lds_bytes(uint32_t slots, int mode, int waves);
+size_t bits_lds_bytes(int64_t n, int log2S, int mode);
+uint32_t bits_max_keys(int log2S, int mode);
+// Slots per pack of short rows: two for each of the pack_slots threshold (they
+// are half as wide), as far as FULL support's value words leave room in LDS
+// (six bytes a slot); a pack's tables take one row's more.
+inline uint32_t short_pack_slots(uint32_t pack_slots) { return pack_slots < 10240 ? 2 * pack_slots : 20480; }
+inline uint32_t pack16_slots(uint32_t pack_slots, int log2S) { return short_pack_slots(pack_slots) + (1u << log2S); }
+// Words of the bitmap over a short row's column distances, [0, min(n, kShortSpan)].
+__host__ __device__ inline uint32_t bitmap_words(int32_t n) {
+  return (uint32_t)((n < kShortSpan ? n : kShortSpan) >> 5) + 1;
+}
 
 inline CountView graph_view(const Graph& g) {
-  return CountView{g.row_ptr, g.col, g.col, g.m, &g.w, 1, 0, g.hash};
+  return CountView{g.row_ptr, g.col, g.col, g.m, &g.w, 1, 0, g.hash, g.col16};
 }
 
 // Entry points that rely on the <j,i,k> task layout of a graph's own work
@@ -405,11 +471,16 @@ inline void require_plain(const Graph& g, const char* where) {
 // bounds, tb_val = first probe | end << 32 of each task, tb_prefix = the
 // exclusive prefix of their probe counts with the total at [T]): classes,
 // class-major order, packs and items. hrow_ptr gives |U_b| of every hashed row.
+// tb_prefix counts short rows' tasks (b >= b16) in units (short_units).
 // all_rows: every hashed row gets a work unit, also rows without tasks (the
 // ablation of the doubly sparse traversal; they go to pack_small).
 void build_work(WorkSet& w, Owned& own, int64_t nrows, const int64_t* hrow_ptr, int64_t T,
                 const uint32_t* tb_row, const int64_t* tb_ptr, const uint64_t* tb_val,
-                const uint64_t* tb_prefix, const WorkParams& wp, hipStream_t st, bool all_rows = false);
+                const uint64_t* tb_prefix, int64_t b16, const WorkParams& wp, hipStream_t st,
+                bool all_rows = false);
+// Probe totals of the classes and of the set, from what build_work reads
+// back; call once the stream it ran on is synchronised.
+void finish_work(WorkSet& w);
 
 // ---- tuning table (tc_tuning.cpp) ----------------------------------------------
 // Tuned settings by key "<arch>/<CUs>cu/<kind>_e<k>" (kind "graph" for one

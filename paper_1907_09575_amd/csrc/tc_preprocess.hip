@@ -432,18 +432,41 @@ __global__ __launch_bounds__(256) void k_orient_hi(uint64_t* __restrict__ pk, in
   dc.flush(hist);
 }
 
-// Column of a sorted orient key, written by the orient sort's last pass.
+// Column of a sorted orient key and its short form, written by the orient
+// sort's last pass (k_row_bounds clears the first entry of every row).
 struct ColEpi {
   int32_t* col;
+  uint16_t* col16;
+  int64_t n;
   int s;
   __device__ void operator()(uint64_t pos, uint64_t key) const {
-    col[pos] = (int32_t)(key & ((1ull << s) - 1));
+    const int32_t k = (int32_t)(key & ((1ull << s) - 1));
+    col[pos] = k;
+    const int64_t v = n - k;
+    col16[pos] = (uint16_t)(v <= kShortSpan ? v : 0);
   }
 };
 
 __global__ void k_col(const uint64_t* __restrict__ okey, int64_t m, int s, int32_t* __restrict__ col) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < m) col[i] = (int32_t)(okey[i] & ((1ull << s) - 1));
+}
+
+// U's row pointers from the sorted orient keys (k_bounds), and the zeros of
+// the short columns: the first entry of every row and the padding.
+__global__ void k_row_bounds(const uint64_t* __restrict__ keys, int64_t m, int s, int64_t n,
+                             int64_t* __restrict__ row_ptr, uint16_t* __restrict__ col16) {
+  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (r > n) return;
+  int64_t lo = 0, hi = m;
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) >> 1;
+    if ((int64_t)(keys[mid] >> s) < r) lo = mid + 1;
+    else hi = mid;
+  }
+  row_ptr[r] = lo;
+  col16[lo] = 0;  // (an empty row: the first entry of a later one, or the padding)
+  if (r == n) col16[m + 1] = 0;
 }
 
 // W+ = sum_a C(d+(a), 2) and max d+(a).
@@ -479,37 +502,41 @@ __global__ __launch_bounds__(256) void k_row_stats(const int64_t* __restrict__ r
   }
 }
 
-// Class of every hashed row b (-1 = no work) and the class's largest table
-// (maxima reduced per wave before one atomic per wave and class).
+// Class of every hashed row b (-1 = no work), each class's largest table and
+// weight, and the weight of its short rows (reduced per wave before one atomic
+// per wave and class).
+// Work of a hashed row is weighed in probes, a short row's units as two each.
+__device__ __forceinline__ uint64_t row_weight(uint64_t w, int64_t b, int64_t b16) { return b >= b16 ? 2 * w : w; }
+
 __global__ __launch_bounds__(256) void k_classify(const int64_t* __restrict__ tptr,
                                                   const uint64_t* __restrict__ tprefix,
                                                   const int64_t* __restrict__ row_ptr, int64_t n, bool all_rows,
-                                                  uint64_t heavy_min, int8_t* __restrict__ cls,
+                                                  uint64_t heavy_min, uint64_t heavy_min16, int64_t b16,
+                                                  int8_t* __restrict__ cls,
                                                   int* __restrict__ cls_log2S,
                                                   unsigned long long* __restrict__ cls_probes) {
   __shared__ int s_max[NUM_CLASSES];
-  __shared__ unsigned long long s_w[NUM_CLASSES];
-  if (threadIdx.x < NUM_CLASSES) {
-    s_max[threadIdx.x] = 0;
-    s_w[threadIdx.x] = 0;
-  }
+  __shared__ unsigned long long s_w[2 * NUM_CLASSES];  // all rows, short rows
+  if (threadIdx.x < NUM_CLASSES) s_max[threadIdx.x] = 0;
+  if (threadIdx.x < 2 * NUM_CLASSES) s_w[threadIdx.x] = 0;
   __syncthreads();
   int lmax[NUM_CLASSES];
-  unsigned long long lw[NUM_CLASSES];
+  unsigned long long lw[NUM_CLASSES], lw16[NUM_CLASSES];
 #pragma unroll
   for (int k = 0; k < NUM_CLASSES; ++k) {
     lmax[k] = 0;
     lw[k] = 0;
+    lw16[k] = 0;
   }
   for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < n; b += (int64_t)gridDim.x * blockDim.x) {
     int c = -1, l = 0;
-    const uint64_t W = tprefix[tptr[b + 1]] - tprefix[tptr[b]];
+    const uint64_t W = row_weight(tprefix[tptr[b + 1]] - tprefix[tptr[b]], b, b16);
     if (W > 0) {
       l = table_log2(row_ptr[b + 1] - row_ptr[b]);
       if (l > kMaxLog2S) c = CLS_GLOBAL;
       else if (l > 13) c = CLS_WG_GIANT;
       else if (l > 12) c = CLS_WG_HUGE;
-      else if (W < heavy_min && l <= 10) c = l <= 8 ? CLS_PACK_SMALL : CLS_PACK_LARGE;
+      else if (W < (b >= b16 ? heavy_min16 : heavy_min) && l <= 10) c = l <= 8 ? CLS_PACK_SMALL : CLS_PACK_LARGE;
       else c = l <= 10 ? CLS_WG_SMALL : CLS_WG_LARGE;
     } else if (all_rows) {
       // no doubly sparse traversal: a row without work is still visited (a
@@ -522,6 +549,7 @@ __global__ __launch_bounds__(256) void k_classify(const int64_t* __restrict__ tp
     for (int k = 0; k < NUM_CLASSES; ++k) {
       lmax[k] = c == k && l > lmax[k] ? l : lmax[k];
       lw[k] += c == k ? W : 0;
+      lw16[k] += c == k && b >= b16 ? W : 0;
     }
   }
 #pragma unroll
@@ -530,20 +558,22 @@ __global__ __launch_bounds__(256) void k_classify(const int64_t* __restrict__ tp
     const unsigned long long wk = wave_sum(lw[k]);
     if (lane_id() == 0 && mk > 0) atomicMax(&s_max[k], mk);
     if (lane_id() == 0 && wk > 0) atomicAdd(&s_w[k], wk);
+    const unsigned long long wk16 = wave_sum(lw16[k]);
+    if (lane_id() == 0 && wk16 > 0) atomicAdd(&s_w[NUM_CLASSES + k], wk16);
   }
   __syncthreads();
   if (threadIdx.x < NUM_CLASSES && s_max[threadIdx.x] > 0) atomicMax(&cls_log2S[threadIdx.x], s_max[threadIdx.x]);
-  if (threadIdx.x < NUM_CLASSES && s_w[threadIdx.x] > 0) atomicAdd(&cls_probes[threadIdx.x], s_w[threadIdx.x]);
+  if (threadIdx.x < 2 * NUM_CLASSES && s_w[threadIdx.x] > 0) atomicAdd(&cls_probes[threadIdx.x], s_w[threadIdx.x]);
 }
 
-// Per-class sums (rows, table keys, tasks, probes): LDS accumulation per
-// block, one partial row per block, then a column reduction.
+// Per-class sums (rows, table keys, tasks; the probes come from
+// k_task_permute): LDS accumulation per block, one partial row per block, then
+// a column reduction.
 constexpr int kStatCols = NUM_CLASSES * 4;
 
 __global__ __launch_bounds__(256) void k_class_stats(const int8_t* __restrict__ cls, int64_t n,
                                                      const uint32_t* __restrict__ tbeg,
                                                      const uint32_t* __restrict__ tend,
-                                                     const uint64_t* __restrict__ tprefix,
                                                      const int64_t* __restrict__ row_ptr,
                                                      unsigned long long* __restrict__ partial) {
   __shared__ unsigned long long acc[kStatCols];
@@ -555,7 +585,6 @@ __global__ __launch_bounds__(256) void k_class_stats(const int8_t* __restrict__ 
       atomicAdd(&acc[c * 4 + 0], 1ull);
       atomicAdd(&acc[c * 4 + 1], (unsigned long long)(row_ptr[b + 1] - row_ptr[b]));
       atomicAdd(&acc[c * 4 + 2], (unsigned long long)(tend[b] - tbeg[b]));
-      atomicAdd(&acc[c * 4 + 3], (unsigned long long)(tprefix[tend[b]] - tprefix[tbeg[b]]));
     }
   }
   __syncthreads();
@@ -626,12 +655,15 @@ struct CmItems {
   const int8_t* cls;
   const int64_t* tptr;
   const uint64_t* tprefix;
+  int64_t b16;
+  uint32_t chunk16;  // short rows
   uint32_t chunk[NUM_CLASSES];
   __device__ uint32_t operator()(int64_t i) const {
     const uint32_t b = crow[i];
     const int c = cls[b];
     if (c == CLS_PACK_SMALL || c == CLS_PACK_LARGE) return 0;
-    return wg_parts(tprefix[tptr[b + 1]] - tprefix[tptr[b]], class_waves(c), chunk[c]);
+    const uint64_t W = tprefix[tptr[b + 1]] - tprefix[tptr[b]];
+    return (int64_t)b >= b16 ? wg_parts(2 * W, kWaves, chunk16) : wg_parts(W, class_waves(c), chunk[c]);
   }
 };
 
@@ -650,35 +682,115 @@ __global__ void k_cm_place(const uint32_t* __restrict__ crow, int64_t R, const u
 
 // Task t (hashed-row order) to its class-major slot: first probe and the
 // class-major exclusive prefix (the row's base plus the prefix within the
-// row, which keeps its order).
-__global__ void k_task_permute(int64_t T, const uint32_t* __restrict__ tb_row,
-                               const int64_t* __restrict__ tb_ptr, const uint64_t* __restrict__ tb_val,
-                               const uint64_t* __restrict__ tb_prefix, const uint32_t* __restrict__ tbeg,
-                               const uint32_t* __restrict__ cm_pos, const uint64_t* __restrict__ wsc,
-                               uint32_t* __restrict__ tstart, uint64_t* __restrict__ tprefix) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= T) return;
-  const uint32_t b = tb_row[t];
-  const int64_t p0 = tb_ptr[b];
-  const int64_t nt = (int64_t)tbeg[b] + (t - p0);
-  tstart[nt] = (uint32_t)tb_val[t];
-  tprefix[nt] = wsc[cm_pos[b]] + (tb_prefix[t] - tb_prefix[p0]);
+// row, which keeps its order); and the probes of every class, kPermuteTasks
+// tasks per thread so that the global atomics stay few.
+constexpr int kPermuteTasks = 16;
+__global__ __launch_bounds__(256) void k_task_permute(int64_t T, const uint32_t* __restrict__ tb_row,
+                                                      const int64_t* __restrict__ tb_ptr,
+                                                      const uint64_t* __restrict__ tb_val,
+                                                      const uint64_t* __restrict__ tb_prefix,
+                                                      const int8_t* __restrict__ cls,
+                                                      const uint32_t* __restrict__ tbeg,
+                                                      const uint32_t* __restrict__ cm_pos,
+                                                      const uint64_t* __restrict__ wsc,
+                                                      uint32_t* __restrict__ tstart, uint64_t* __restrict__ tprefix,
+                                                      unsigned long long* __restrict__ cls_probes) {
+  __shared__ unsigned long long s_p[NUM_CLASSES];
+  if (threadIdx.x < NUM_CLASSES) s_p[threadIdx.x] = 0;
+  __syncthreads();
+  const int64_t base = (int64_t)blockIdx.x * (256 * kPermuteTasks) + threadIdx.x;
+  int c_run = -1;  // probes of a run of this thread's tasks in one class
+  unsigned long long p_run = 0;
+  constexpr int kB = 4;  // tasks whose loads are in flight together (positions clamped, no branch)
+  for (int j0 = 0; j0 < kPermuteTasks; j0 += kB) {
+    uint32_t b[kB];
+    uint64_t v[kB], pre[kB];
+#pragma unroll
+    for (int j = 0; j < kB; ++j) {
+      const int64_t t = base + (int64_t)(j0 + j) * 256, tc = t < T ? t : T - 1;
+      b[j] = tb_row[tc];
+      v[j] = tb_val[tc];
+      pre[j] = tb_prefix[tc];
+    }
+    int64_t p0[kB];
+    uint32_t tb[kB], cm[kB];
+    int c[kB];
+#pragma unroll
+    for (int j = 0; j < kB; ++j) {
+      p0[j] = tb_ptr[b[j]];
+      tb[j] = tbeg[b[j]];
+      cm[j] = cm_pos[b[j]];
+      c[j] = cls[b[j]];
+    }
+    uint64_t off[kB];
+#pragma unroll
+    for (int j = 0; j < kB; ++j) off[j] = wsc[cm[j]] - tb_prefix[p0[j]];
+#pragma unroll
+    for (int j = 0; j < kB; ++j) {
+      const int64_t t = base + (int64_t)(j0 + j) * 256;
+      if (t >= T) continue;
+      const int64_t nt = (int64_t)tb[j] + (t - p0[j]);
+      const uint32_t first = (uint32_t)v[j];
+      tstart[nt] = first;
+      tprefix[nt] = off[j] + pre[j];
+      if (c[j] != c_run) {
+        if (p_run) atomicAdd(&s_p[c_run], p_run);
+        c_run = c[j];
+        p_run = 0;
+      }
+      p_run += (uint32_t)(v[j] >> 32) - first;
+    }
+  }
+  if (p_run) atomicAdd(&s_p[c_run], p_run);
+  __syncthreads();
+  if (threadIdx.x < NUM_CLASSES && s_p[threadIdx.x]) atomicAdd(&cls_probes[threadIdx.x], s_p[threadIdx.x]);
 }
 
-// Values of a device array at NUM_CLASSES + 1 positions (class boundaries).
-template <class T>
-__global__ void k_gather_at(const T* __restrict__ a, const int64_t* __restrict__ at, int k, T* __restrict__ out) {
-  if ((int)threadIdx.x < k) out[threadIdx.x] = a[at[threadIdx.x]];
+// Where each class begins among the class-major rows (cptr), where its short
+// rows begin (a class's rows ascend), and the item offsets at both.
+struct ClassBounds {
+  int64_t row[NUM_CLASSES + 1], row16[NUM_CLASSES];
+  uint32_t item[NUM_CLASSES + 1], item16[NUM_CLASSES];
+  uint32_t tasks;  // of all rows (a check)
+  uint32_t packs[2], packs32[2];
+};
+__global__ void k_class_bounds(const uint32_t* __restrict__ crow, int64_t R, const int64_t* __restrict__ cptr,
+                               const uint32_t* __restrict__ usc, const uint32_t* __restrict__ tsc, int64_t b16,
+                               ClassBounds* __restrict__ out) {
+  const int c = threadIdx.x;
+  if (c > NUM_CLASSES) return;
+  out->row[c] = cptr[c];
+  out->item[c] = usc[cptr[c]];
+  if (c == NUM_CLASSES) {
+    out->tasks = tsc[R];
+    return;
+  }
+  int64_t lo = cptr[c], hi = cptr[c + 1];
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) >> 1;
+    if ((int64_t)crow[mid] < b16) lo = mid + 1;
+    else hi = mid;
+  }
+  out->row16[c] = lo;
+  out->item16[c] = usc[lo];
+}
+
+// Packs of a class of nr rows, and those of its rows below i16.
+__global__ void k_pack_totals(const uint32_t* __restrict__ flags, const uint32_t* __restrict__ pos, int64_t nr,
+                              int64_t i16, int c, ClassBounds* __restrict__ out) {
+  const uint32_t total = pos[nr - 1] + flags[nr - 1];
+  out->packs[c] = total;
+  out->packs32[c] = i16 < nr ? pos[i16] : total;
 }
 
 __global__ void k_rows_work(const int32_t* __restrict__ rows, int64_t nr,
                             const uint32_t* __restrict__ tbeg, const uint32_t* __restrict__ tend,
                             const uint64_t* __restrict__ tprefix, const int64_t* __restrict__ row_ptr,
-                            uint64_t* __restrict__ w, uint32_t* __restrict__ slots) {
+                            int64_t b16, uint64_t* __restrict__ w, uint32_t* __restrict__ slots) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= nr) return;
   int64_t b = rows[i];
-  w[i] = tprefix[tend[b]] - tprefix[tbeg[b]];
+  w[i] = row_weight(tprefix[tend[b]] - tprefix[tbeg[b]], b, b16);
   // a row without tasks (visited only without the doubly sparse traversal)
   // needs no table
   slots[i] = 1u << pack_table_log2(tend[b] > tbeg[b] ? row_ptr[b + 1] - row_ptr[b] : 0);
@@ -687,20 +799,23 @@ __global__ void k_rows_work(const int32_t* __restrict__ rows, int64_t nr,
 // A pack starts at row i when the running probe total, the running table
 // slots or the row index enters a new multiple of its budget; so a pack holds
 // at most kPackRows rows, at most `slots` slots plus one row's table, and at
-// most `target` probes plus one row's.
+// most `target` probes plus one row's. The short rows (from row i16 on) start
+// a pack of their own and hold `slots16`.
 __global__ void k_pack_flags(const uint64_t* __restrict__ pw, const uint32_t* __restrict__ ps,
-                             int64_t nr, uint64_t target, uint32_t slots, uint32_t* __restrict__ flags) {
+                             int64_t nr, int64_t i16, uint64_t target, uint32_t slots32,
+                             uint32_t slots16, uint32_t* __restrict__ flags) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= nr) return;
-  flags[i] = (i == 0 || pw[i] / target != pw[i - 1] / target || ps[i] / slots != ps[i - 1] / slots ||
+  const uint32_t slots = i >= i16 ? slots16 : slots32;
+  flags[i] = (i == 0 || i == i16 || pw[i] / target != pw[i - 1] / target || ps[i] / slots != ps[i - 1] / slots ||
               i / kPackRows != (i - 1) / kPackRows)
                  ? 1u
                  : 0u;
 }
 
 // Records of the pack rows (one thread per row) and of the packs (one thread
-// per pack: probe range and each wave share's first task, by binary search in
-// the pack's task prefixes).
+// per share of a pack: the share's first task, by binary search in the pack's
+// task prefixes; the first share's also the rows and the probe range).
 __global__ void k_pack_recs(const int32_t* __restrict__ rows, int64_t nr, const int64_t* __restrict__ row_ptr,
                             const uint32_t* __restrict__ tbeg, const uint32_t* __restrict__ tend,
                             PackRow* __restrict__ recs) {
@@ -717,28 +832,29 @@ __global__ void k_pack_recs(const int32_t* __restrict__ rows, int64_t nr, const 
 
 __global__ void k_pack_info(const uint32_t* __restrict__ pack_ptr, int64_t np, const PackRow* __restrict__ recs,
                             const uint64_t* __restrict__ tprefix, PackInfo* __restrict__ info) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t p = i / kPackWavesMax;
+  const int w = (int)(i % kPackWavesMax);
   if (p >= np) return;
-  PackInfo pi;
-  pi.r0 = pack_ptr[p];
-  pi.r1 = pack_ptr[p + 1];
-  const uint32_t t_lo = recs[pi.r0].tb, t_hi = recs[pi.r1 - 1].te;
-  pi.q0 = tprefix[t_lo];
-  pi.q1 = tprefix[t_hi];
-  const uint64_t W = pi.q1 - pi.q0;
-  for (int w = 0; w < kWaves; ++w) {
-    const uint64_t wq0 = pi.q0 + W * (uint64_t)w / kWaves;
-    // last task t in [t_lo, t_hi) with tprefix[t] <= wq0 (t_lo when the pack
-    // has no task: the share is then empty and never probed)
-    uint32_t lo = t_lo, hi = t_hi > t_lo ? t_hi : t_lo + 1;
-    while (hi - lo > 1) {
-      const uint32_t mid = lo + (hi - lo) / 2;
-      if (tprefix[mid] <= wq0) lo = mid;
-      else hi = mid;
-    }
-    pi.wt[w] = lo;
+  const uint32_t r0 = pack_ptr[p], r1 = pack_ptr[p + 1];
+  const uint32_t t_lo = recs[r0].tb, t_hi = recs[r1 - 1].te;
+  const uint64_t q0 = tprefix[t_lo], q1 = tprefix[t_hi];
+  const uint64_t wq0 = q0 + pack_share(q1 - q0, w);
+  // last task t in [t_lo, t_hi) with tprefix[t] <= wq0 (t_lo when the pack
+  // has no task: the share is then empty and never probed)
+  uint32_t lo = t_lo, hi = t_hi > t_lo ? t_hi : t_lo + 1;
+  while (hi - lo > 1) {
+    const uint32_t mid = lo + (hi - lo) / 2;
+    if (tprefix[mid] <= wq0) lo = mid;
+    else hi = mid;
   }
-  info[p] = pi;
+  info[p].wt[w] = lo;
+  if (w == 0) {
+    info[p].q0 = q0;
+    info[p].q1 = q1;
+    info[p].r0 = r0;
+    info[p].r1 = r1;
+  }
 }
 
 // Launch order of a class's packs: heaviest first (longest-processing-time
@@ -746,14 +862,45 @@ __global__ void k_pack_info(const uint32_t* __restrict__ pack_ptr, int64_t np, c
 // fewer than kPackLptMin packs keep pack order (their launch is short; the
 // sort would cost more than it saves, and batch plans order units themselves).
 // Key = the complement of the pack's weight (its probes plus 64 per row), so
-// that an ascending sort puts the heaviest first.
+// that an ascending sort puts the heaviest first; the packs of short rows
+// (from pack p16 on) carry the top bit, so that they stay last.
 constexpr int64_t kPackLptMin = 2048;
-__global__ void k_pack_keys(const PackInfo* __restrict__ info, int64_t np, uint32_t* __restrict__ key,
+
+// Short rows. Their bitmaps are cheap to set up, so a row gets work-groups of
+// its own from kShortHeavyMin probes on (if heavy_min is not lower).
+constexpr uint64_t kShortHeavyMin = 2048;
+// Probes of a bundle, one work-group's share of the short rows' items, W
+// probes in all: 1 / 16384 of them, but no less than 24K, under which a
+// work-group's set-up shows (RMAT scale 18, 205M probes: 225 us in 8192
+// bundles, 289 us in 16384), unless that would leave the 2048 work-groups
+// that the GPU holds at once without one each, and no more than 256K, above
+// which the last ones show (scale 22, 7.2G probes: 2662 us in 16384 bundles,
+// 2586 us in 32768).
+inline uint64_t bundle_weight(uint64_t W) {
+  const uint64_t least = std::max<uint64_t>(4096, std::min<uint64_t>(24 << 10, W / 2048));
+  return std::min<uint64_t>(256 << 10, std::max(least, W / 16384));
+}
+
+// Bundle boundaries of one class's short groups (items: the first of them;
+// q0 grows along the groups): bundle i starts at the first group whose first
+// probe lies i * per units after the first group's.
+__global__ void k_bundles(const CountItem* __restrict__ items, int64_t groups, uint64_t per, int64_t n_bundles,
+                          uint32_t* __restrict__ bundle) {
+  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (j >= groups) return;
+  const uint64_t q0 = items[0].q0;
+  const int64_t at = (int64_t)((items[j * kWaves].q0 - q0) / per);
+  const int64_t before = j ? (int64_t)((items[(j - 1) * kWaves].q0 - q0) / per) : -1;
+  for (int64_t i = before + 1; i <= at; ++i) bundle[i] = (uint32_t)j;
+  if (j == groups - 1)
+    for (int64_t i = at + 1; i <= n_bundles; ++i) bundle[i] = (uint32_t)groups;
+}
+__global__ void k_pack_keys(const PackInfo* __restrict__ info, int64_t np, int64_t p16, uint32_t* __restrict__ key,
                             uint32_t* __restrict__ idx) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= np) return;
   const uint64_t w = info[p].q1 - info[p].q0 + 64ull * (info[p].r1 - info[p].r0);
-  key[p] = 0xFFFFFFFFu - (uint32_t)(w < 0xFFFFFFFFull ? w : 0xFFFFFFFFull);
+  key[p] = (0x7FFFFFFFu - (uint32_t)(w < 0x7FFFFFFFull ? w : 0x7FFFFFFFull)) | (p >= p16 ? 0x80000000u : 0u);
   idx[p] = (uint32_t)p;
 }
 
@@ -811,7 +958,9 @@ __global__ void k_emit_items(const uint32_t* __restrict__ offs, const uint32_t* 
   it.t0 = (uint32_t)a;
   it.q0 = q0;
   it.len = (uint32_t)(q1 - q0);
-  it.log2S = (uint32_t)table_log2(row_ptr[b + 1] - row_ptr[b]);
+  it.rs = (uint32_t)row_ptr[b];
+  it.d = (uint32_t)(row_ptr[b + 1] - row_ptr[b]);
+  it.log2S = (uint32_t)table_log2(it.d);
   items[j] = it;
 }
 
@@ -987,6 +1136,8 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
   // ---- 4: orient, U in CSR -------------------------------------------------
   g->row_ptr = g->owned.alloc<int64_t>(n + 1);
   g->col = g->owned.alloc<int32_t>(m);
+  g->col16 = g->owned.alloc<uint16_t>(m + 2);
+  const int64_t b16 = short_rows_begin(n, m);
   const uint64_t* okey = obuf.as<uint64_t>();
   {
     if (m > 0) {
@@ -1005,11 +1156,11 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
       // S's buffer is the ping-pong partner (S is not read after the
       // partition); the last pass also writes each key's column: U's col
       bool alt = radix_sort<uint64_t, NoVal, ColEpi>(obuf.as<uint64_t>(), sbuf.as<uint64_t>(), nullptr, nullptr,
-                                                     m, 0, 2 * s, st, "orient", ColEpi{g->col, s},
+                                                     m, 0, 2 * s, st, "orient", ColEpi{g->col, g->col16, n, s},
                                                      ohist);
       if (alt) okey = sbuf.as<uint64_t>();
-      TC_LAUNCH("bounds", (k_bounds<uint64_t>), dim3(grid_for(n + 1)), dim3(kT), 0, st, okey, m, s, n,
-                         g->row_ptr);
+      TC_LAUNCH("row_bounds", k_row_bounds, dim3(grid_for(n + 1)), dim3(kT), 0, st, okey, m, s, n, g->row_ptr,
+                g->col16);
       if (m == 1)  // no sort pass ran
         TC_LAUNCH("col", k_col, dim3(grid_for(m)), dim3(kT), 0, st, okey, m, s, g->col);
     } else {
@@ -1066,7 +1217,7 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
         tl.val.swap(tv);
       }
     }
-    finish_tasks(tl, n, st);
+    finish_tasks(tl, n, b16, st);
     g->wedges_plus = (int64_t)h.wplus;
     g->max_dplus = (int64_t)h.maxd;
   }
@@ -1075,8 +1226,9 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
 
   // ---- 6: work classes ------------------------------------------------------
   build_work(g->w, g->owned, n, g->row_ptr, tl.T, tl.row.as<uint32_t>(), tl.ptr.as<int64_t>(),
-             tl.val.as<uint64_t>(), tl.prefix.as<uint64_t>(), default_work_params(m), st);
+             tl.val.as<uint64_t>(), tl.prefix.as<uint64_t>(), b16, default_work_params(m), st);
   check_sorts(st);
+  finish_work(g->w);
   g->arena_bytes = g->owned.bytes;
   note_use(*g, st);
   return g.release();
@@ -1139,11 +1291,15 @@ Graph* build_variant(const Graph& base, int flags, const WorkParams& wp, hipStre
   g->row_ptr = base.row_ptr;  // U is shared, not owned
   g->col = base.col;
   g->perm = base.perm;
+  g->col16 = base.col16;
   g->variant = flags;
   g->hash = (flags & TC_VARIANT_MUL_HASH) ? 1 : 0;
   g->base = &base;
   const bool ijk = (flags & TC_VARIANT_IJK) != 0, no_dcsr = (flags & TC_VARIANT_NO_DCSR) != 0;
   const int64_t n = g->n, m = g->m;
+  // (<i,j,k> looks up whole rows, first entries included, and the hashing
+  // ablation compares 32-bit tables: no short rows there)
+  const int64_t b16 = ijk || g->hash ? n : short_rows_begin(n, m);
   TaskLists tl;
   if (m > 0) {
     DevBuf erow(sizeof(uint32_t) * (size_t)m);
@@ -1157,28 +1313,33 @@ Graph* build_variant(const Graph& base, int flags, const WorkParams& wp, hipStre
       pr.tkey = tk.as<uint32_t>();
       pr.tval = tv.as<uint64_t>();
     }, st);
-    if (T > 0) sort_tasks(tl, tk, tv, T, n, g->sbits, st, "variant_tasks");
+    if (T > 0) sort_tasks(tl, tk, tv, T, n, g->sbits, b16, st, "variant_tasks");
   }
   build_work(g->w, g->owned, n, g->row_ptr, tl.T, tl.row.as<uint32_t>(), tl.ptr.as<int64_t>(),
-             tl.val.as<uint64_t>(), tl.prefix.as<uint64_t>(), wp, st, no_dcsr);
+             tl.val.as<uint64_t>(), tl.prefix.as<uint64_t>(), b16, wp, st, no_dcsr);
   check_sorts(st);
+  finish_work(g->w);
   g->arena_bytes = g->owned.bytes;
   note_use(*g, st);  // (and the base, whose U the build read)
   return g.release();
 }
 
-// Probes of a task from its (first probe | end << 32) value.
+// Length of a task from its (first probe | end << 32) value: its probes, or
+// its units if its row is a short one.
 struct TaskLenLoad {
   const uint64_t* val;
+  const uint32_t* row;
+  int64_t b16;
   __device__ uint64_t operator()(int64_t t) const {
     const uint64_t v = val[t];
-    return (uint64_t)((uint32_t)(v >> 32) - (uint32_t)v);
+    const uint32_t first = (uint32_t)v, end = (uint32_t)(v >> 32);
+    return (int64_t)row[t] >= b16 ? short_units(first, end) : end - first;
   }
 };
 
 // Probe prefixes and row pointers of the tasks in tl.row / tl.val (tl.T of
 // them, sorted by row; tl.ptr allocated with nrows + 1 entries).
-void finish_tasks(TaskLists& tl, int64_t nrows, hipStream_t st) {
+void finish_tasks(TaskLists& tl, int64_t nrows, int64_t b16, hipStream_t st) {
   const int64_t T = tl.T;
   if (T == 0) {
     TC_LAUNCH("fill_i64", k_fill_i64, dim3(grid_for(nrows + 1)), dim3(kT), 0, st, tl.ptr.as<int64_t>(),
@@ -1186,14 +1347,14 @@ void finish_tasks(TaskLists& tl, int64_t nrows, hipStream_t st) {
     return;
   }
   tl.prefix.alloc(sizeof(uint64_t) * (size_t)(T + 1));
-  device_excl_scan_f<uint64_t>(TaskLenLoad{tl.val.as<uint64_t>()}, tl.prefix.as<uint64_t>(), T,
-                               tl.prefix.as<uint64_t>() + T, st);
+  device_excl_scan_f<uint64_t>(TaskLenLoad{tl.val.as<uint64_t>(), tl.row.as<uint32_t>(), b16},
+                               tl.prefix.as<uint64_t>(), T, tl.prefix.as<uint64_t>() + T, st);
   TC_LAUNCH("bounds", (k_bounds<uint32_t>), dim3(grid_for(nrows + 1)), dim3(kT), 0, st,
             tl.row.as<uint32_t>(), T, 0, nrows, tl.ptr.as<int64_t>());
   TC_HIP(hipGetLastError());
 }
 
-void sort_tasks(TaskLists& tl, DevBuf& tk, DevBuf& tv, int64_t T, int64_t nrows, int key_bits,
+void sort_tasks(TaskLists& tl, DevBuf& tk, DevBuf& tv, int64_t T, int64_t nrows, int key_bits, int64_t b16,
                 hipStream_t st, const char* name) {
   tl.T = T;
   tl.ptr.alloc(sizeof(int64_t) * (size_t)(nrows + 1));
@@ -1208,14 +1369,15 @@ void sort_tasks(TaskLists& tl, DevBuf& tk, DevBuf& tv, int64_t T, int64_t nrows,
       tl.val.swap(tv);
     }
   }
-  finish_tasks(tl, nrows, st);
+  finish_tasks(tl, nrows, b16, st);
 }
 
 void build_work(WorkSet& w, Owned& own, int64_t n, const int64_t* hrow_ptr, int64_t T,
                 const uint32_t* tb_row, const int64_t* tb_ptr, const uint64_t* tb_val,
-                const uint64_t* tb_prefix, const WorkParams& wp, hipStream_t st, bool all_rows) {
+                const uint64_t* tb_prefix, int64_t b16, const WorkParams& wp, hipStream_t st, bool all_rows) {
   w.nrows = n;
   w.wp = wp;
+  w.b16 = b16;
   w.n_tasks = T;
   w.tbeg = own.alloc<uint32_t>(n);
   w.tend = own.alloc<uint32_t>(n);
@@ -1232,26 +1394,23 @@ void build_work(WorkSet& w, Owned& own, int64_t n, const int64_t* hrow_ptr, int6
     w.probes = 0;
     return;
   }
-  // the probe total is read back with the row count below (one host sync)
-  uint64_t h_probes = 0;
-  TC_HIP(hipMemcpyAsync(&h_probes, tb_prefix + T, sizeof(h_probes), hipMemcpyDeviceToHost, st));
   DevBuf cls(sizeof(int8_t) * (size_t)n);
-  // per class: probes (64-bit counters first: 8-byte aligned for their
-  // atomics), then the largest table (log2 slots)
-  DevBuf clsl(sizeof(unsigned long long) * NUM_CLASSES + sizeof(int) * NUM_CLASSES);
+  // per class: weight and probes (64-bit counters first: 8-byte aligned for
+  // their atomics), then the largest table (log2 slots)
+  DevBuf clsl(sizeof(unsigned long long) * 3 * NUM_CLASSES + sizeof(int) * NUM_CLASSES);
   TC_HIP(hipMemsetAsync(clsl.p, 0, clsl.bytes, st));
-  unsigned long long* d_cw = clsl.as<unsigned long long>();
-  int* d_cl = reinterpret_cast<int*>(clsl.as<char>() + sizeof(unsigned long long) * NUM_CLASSES);
+  unsigned long long* d_cp = clsl.as<unsigned long long>();  // probes (k_task_permute)
+  unsigned long long* d_cw = d_cp + NUM_CLASSES;
+  int* d_cl = reinterpret_cast<int*>(d_cw + 2 * NUM_CLASSES);
   TC_LAUNCH("classify", k_classify, dim3(grid_reduce(n)), dim3(kT), 0, st, tb_ptr, tb_prefix, hrow_ptr, n,
-            all_rows, wp.heavy_min, cls.as<int8_t>(), d_cl, d_cw);
+            all_rows, wp.heavy_min, std::min(wp.heavy_min, kShortHeavyMin), b16, cls.as<int8_t>(), d_cl, d_cw);
   TC_HIP(hipGetLastError());
   struct {
-    unsigned long long cw[NUM_CLASSES];
+    unsigned long long cw[NUM_CLASSES], cw16[NUM_CLASSES];
     int cl[NUM_CLASSES];
   } hc;
-  static_assert(sizeof(hc.cw) + sizeof(hc.cl) == sizeof(unsigned long long) * NUM_CLASSES + sizeof(int) * NUM_CLASSES,
-                "class scalars layout");
-  TC_HIP(hipMemcpyAsync(&hc, clsl.p, sizeof(hc.cw) + sizeof(hc.cl), hipMemcpyDeviceToHost, st));
+  TC_HIP(hipMemcpyAsync(&hc, d_cw, sizeof(unsigned long long) * 2 * NUM_CLASSES + sizeof(int) * NUM_CLASSES,
+                        hipMemcpyDeviceToHost, st));
   const unsigned long long* h_cw = hc.cw;
   const int* h_cl = hc.cl;
 
@@ -1266,7 +1425,6 @@ void build_work(WorkSet& w, Owned& own, int64_t n, const int64_t* hrow_ptr, int6
     p.key = ckey.as<uint32_t>();
     p.row = crow_in.as<uint32_t>();
   }, st);
-  w.probes = (int64_t)h_probes;
   TC_REQUIRE(R > 0, TC_EDEVICE, "build_work: tasks but no row with work");
   uint32_t* crow = reinterpret_cast<uint32_t*>(own.alloc<int32_t>(R));  // pack classes keep their rows
   {
@@ -1289,7 +1447,14 @@ void build_work(WorkSet& w, Owned& own, int64_t n, const int64_t* hrow_ptr, int6
     // provided it has the probes to fill them with items of kWaveChunkMin (a
     // class too small for that stays at wp.wave_chunk: few, large units suit
     // a batch of many small graphs). h_cw is valid: compact synchronised st.
-    CmItems cmi{crow, cls.as<int8_t>(), tb_ptr, tb_prefix, {}};
+    CmItems cmi{crow, cls.as<int8_t>(), tb_ptr, tb_prefix, b16, 0, {}};
+    // Short rows: bundles of groups of about equal weight (k_bundles), enough
+    // of them to fill the GPU several times, and items that cut a heavy row
+    // at that weight.
+    uint64_t cw16 = 0;
+    for (int c = CLS_WG_SMALL; c < NUM_CLASSES; ++c) cw16 += hc.cw16[c];
+    const uint64_t bundle_w = w.bundle_w = bundle_weight(cw16);
+    cmi.chunk16 = (uint32_t)std::min<uint64_t>(wp.wave_chunk, bundle_w / kWaves);
     for (int c = 0; c < NUM_CLASSES; ++c) {
       const uint64_t per_group = wp.min_groups ? h_cw[c] / ((uint64_t)wp.min_groups * class_waves(c)) : ~0ull;
       cmi.chunk[c] = per_group < kWaveChunkMin ? wp.wave_chunk
@@ -1301,27 +1466,26 @@ void build_work(WorkSet& w, Owned& own, int64_t n, const int64_t* hrow_ptr, int6
     DevBuf cm_pos(sizeof(uint32_t) * (size_t)n);
     TC_LAUNCH("cm_place", k_cm_place, dim3(grid_for(R)), dim3(kT), 0, st, crow, R, tsc.as<uint32_t>(), w.tbeg,
               w.tend, cm_pos.as<uint32_t>());
-    TC_LAUNCH("task_permute", k_task_permute, dim3(grid_for(T)), dim3(kT), 0, st, T, tb_row, tb_ptr, tb_val,
-              tb_prefix, w.tbeg, cm_pos.as<uint32_t>(), wsc.as<uint64_t>(), w.tstart, w.tprefix);
+    TC_LAUNCH("task_permute", k_task_permute, dim3((unsigned)div_up(T, kT * kPermuteTasks)), dim3(kT), 0, st, T,
+              tb_row, tb_ptr, tb_val, tb_prefix, cls.as<int8_t>(), w.tbeg, cm_pos.as<uint32_t>(),
+              wsc.as<uint64_t>(), w.tstart, w.tprefix, d_cp);
     TC_HIP(hipMemcpyAsync(w.tprefix + T, tb_prefix + T, sizeof(uint64_t), hipMemcpyDeviceToDevice, st));
-    // class boundaries and the item offsets there
-    DevBuf ub(sizeof(uint32_t) * (NUM_CLASSES + 1));
-    TC_LAUNCH("gather_at", (k_gather_at<uint32_t>), dim3(1), dim3(64), 0, st, usc.as<uint32_t>(),
-              cptr.as<int64_t>(), NUM_CLASSES + 1, ub.as<uint32_t>());
-    int64_t h_cp[NUM_CLASSES + 1];
-    uint32_t h_ub[NUM_CLASSES + 1], h_tt = 0;
-    TC_HIP(hipMemcpyAsync(h_cp, cptr.p, sizeof(h_cp), hipMemcpyDeviceToHost, st));
-    TC_HIP(hipMemcpyAsync(h_ub, ub.p, sizeof(h_ub), hipMemcpyDeviceToHost, st));
-    TC_HIP(hipMemcpyAsync(&h_tt, tsc.as<uint32_t>() + R, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    // class boundaries, where each class's short rows begin, and the item
+    // offsets there
+    DevBuf cb(sizeof(ClassBounds));
+    TC_LAUNCH("class_bounds", k_class_bounds, dim3(1), dim3(64), 0, st, crow, R, cptr.as<int64_t>(),
+              usc.as<uint32_t>(), tsc.as<uint32_t>(), b16, cb.as<ClassBounds>());
+    ClassBounds h;
+    TC_HIP(hipMemcpyAsync(&h, cb.p, offsetof(ClassBounds, packs), hipMemcpyDeviceToHost, st));
     TC_HIP(hipStreamSynchronize(st));
-    TC_REQUIRE((int64_t)h_tt == T && h_cp[NUM_CLASSES] == R, TC_EDEVICE,
+    const int64_t* h_cp = h.row;
+    TC_REQUIRE((int64_t)h.tasks == T && h_cp[NUM_CLASSES] == R, TC_EDEVICE,
                "build_work: class-major task order lost tasks");
     TC_HIP(hipGetLastError());
 
     // packs of the two pack classes: flags for both, one host sync for both
     // pack counts, then the pack pointers
     DevBuf pf[2], pp[2];
-    DevBuf ptot(sizeof(uint32_t) * 2);
     for (int c = CLS_PACK_SMALL; c <= CLS_PACK_LARGE; ++c) {
       const int64_t r0 = h_cp[c], total = h_cp[c + 1] - h_cp[c];
       if (total == 0) continue;
@@ -1329,19 +1493,21 @@ void build_work(WorkSet& w, Owned& own, int64_t n, const int64_t* hrow_ptr, int6
       DevBuf wk(sizeof(uint64_t) * (size_t)total), pw(sizeof(uint64_t) * (size_t)total);
       DevBuf sl(sizeof(uint32_t) * (size_t)total), psl(sizeof(uint32_t) * (size_t)total);
       TC_LAUNCH("rows_work", k_rows_work, dim3(grid_for(total)), dim3(kT), 0, st, rows, total, w.tbeg,
-                w.tend, w.tprefix, hrow_ptr, wk.as<uint64_t>(), sl.as<uint32_t>());
+                w.tend, w.tprefix, hrow_ptr, b16, wk.as<uint64_t>(), sl.as<uint32_t>());
       device_excl_scan<uint64_t, uint64_t>(wk.as<uint64_t>(), pw.as<uint64_t>(), total, d_tot64, st);
       device_excl_scan<uint32_t, uint32_t>(sl.as<uint32_t>(), psl.as<uint32_t>(), total, d_tot32, st);
       pf[c].alloc(sizeof(uint32_t) * (size_t)total);
       pp[c].alloc(sizeof(uint32_t) * (size_t)total);
       TC_LAUNCH("pack_flags", k_pack_flags, dim3(grid_for(total)), dim3(kT), 0, st, pw.as<uint64_t>(),
-                psl.as<uint32_t>(), total, wp.pack_target, wp.pack_slots, pf[c].as<uint32_t>());
-      device_excl_scan<uint32_t, uint32_t>(pf[c].as<uint32_t>(), pp[c].as<uint32_t>(), total,
-                                           ptot.as<uint32_t>() + c, st);
+                psl.as<uint32_t>(), total, h.row16[c] - r0, wp.pack_target, wp.pack_slots,
+                short_pack_slots(wp.pack_slots), pf[c].as<uint32_t>());
+      device_excl_scan<uint32_t, uint32_t>(pf[c].as<uint32_t>(), pp[c].as<uint32_t>(), total, nullptr, st);
+      TC_LAUNCH("pack_totals", k_pack_totals, dim3(1), dim3(1), 0, st, pf[c].as<uint32_t>(), pp[c].as<uint32_t>(),
+                total, h.row16[c] - r0, c, cb.as<ClassBounds>());
     }
-    uint32_t h_np[2] = {0, 0};
     if (h_cp[CLS_PACK_LARGE + 1] > h_cp[CLS_PACK_SMALL]) {
-      TC_HIP(hipMemcpyAsync(h_np, ptot.p, sizeof(h_np), hipMemcpyDeviceToHost, st));
+      TC_HIP(hipMemcpyAsync(h.packs, cb.as<ClassBounds>()->packs, sizeof(h.packs) + sizeof(h.packs32),
+                            hipMemcpyDeviceToHost, st));
       TC_HIP(hipStreamSynchronize(st));
     }
     for (int c = 0; c < NUM_CLASSES; ++c) {
@@ -1349,7 +1515,7 @@ void build_work(WorkSet& w, Owned& own, int64_t n, const int64_t* hrow_ptr, int6
       const int64_t r0 = h_cp[c], nr = h_cp[c + 1] - h_cp[c];
       if (nr == 0) continue;
       if (c == CLS_PACK_SMALL || c == CLS_PACK_LARGE) {
-        const int64_t np = h_np[c];
+        const int64_t np = h.packs[c], np32 = h.packs32[c];
         uint32_t* pack_ptr = own.alloc<uint32_t>(np + 1);
         TC_LAUNCH("pack_emit", k_pack_emit, dim3(grid_for(nr)), dim3(kT), 0, st, pf[c].as<uint32_t>(),
                   pp[c].as<uint32_t>(), nr, pack_ptr, np);
@@ -1362,16 +1528,16 @@ void build_work(WorkSet& w, Owned& own, int64_t n, const int64_t* hrow_ptr, int6
                   w.tbeg, w.tend, w.pack_recs[c]);
         if (np < kPackLptMin) {
           // few packs (a launch of one or two rounds): pack order
-          TC_LAUNCH("pack_info", k_pack_info, dim3(grid_for(np)), dim3(kT), 0, st, pack_ptr, np, w.pack_recs[c],
+          TC_LAUNCH("pack_info", k_pack_info, dim3(grid_for(np * kPackWavesMax)), dim3(kT), 0, st, pack_ptr, np, w.pack_recs[c],
                     w.tprefix, w.pack_info[c]);
         } else {
           // the class's packs in launch order: heaviest first
           DevBuf raw(sizeof(PackInfo) * (size_t)np);
           DevBuf key(sizeof(uint32_t) * (size_t)np), key2(sizeof(uint32_t) * (size_t)np);
           DevBuf idx(sizeof(uint32_t) * (size_t)np), idx2(sizeof(uint32_t) * (size_t)np);
-          TC_LAUNCH("pack_info", k_pack_info, dim3(grid_for(np)), dim3(kT), 0, st, pack_ptr, np, w.pack_recs[c],
+          TC_LAUNCH("pack_info", k_pack_info, dim3(grid_for(np * kPackWavesMax)), dim3(kT), 0, st, pack_ptr, np, w.pack_recs[c],
                     w.tprefix, raw.as<PackInfo>());
-          TC_LAUNCH("pack_keys", k_pack_keys, dim3(grid_for(np)), dim3(kT), 0, st, raw.as<PackInfo>(), np,
+          TC_LAUNCH("pack_keys", k_pack_keys, dim3(grid_for(np)), dim3(kT), 0, st, raw.as<PackInfo>(), np, np32,
                     key.as<uint32_t>(), idx.as<uint32_t>());
           const bool alt = radix_sort<uint32_t, uint32_t>(key.as<uint32_t>(), key2.as<uint32_t>(), idx.as<uint32_t>(),
                                                           idx2.as<uint32_t>(), np, 0, 32, st, "pack_lpt");
@@ -1381,9 +1547,10 @@ void build_work(WorkSet& w, Owned& own, int64_t n, const int64_t* hrow_ptr, int6
         TC_HIP(hipGetLastError());
         w.n_pack_rows[c] = nr;
         w.n_packs[c] = np;
+        w.n_packs32[c] = np32;
         w.pack_log2S[c] = h_cl[c];
       } else {
-        const int64_t total = (int64_t)h_ub[c + 1] - (int64_t)h_ub[c];
+        const int64_t total = (int64_t)h.item[c + 1] - (int64_t)h.item[c];
         if (total == 0) continue;
         CountItem* items = own.alloc<CountItem>(total);
         TC_LAUNCH("emit_items", k_emit_items, dim3(grid_for(total)), dim3(kT), 0, st, usc.as<uint32_t>() + r0,
@@ -1391,6 +1558,16 @@ void build_work(WorkSet& w, Owned& own, int64_t n, const int64_t* hrow_ptr, int6
         TC_HIP(hipGetLastError());
         w.items[c] = items;
         w.n_items[c] = total;
+        w.n_items32[c] = (int64_t)h.item16[c] - (int64_t)h.item[c];
+        const int64_t groups = (total - w.n_items32[c]) / kWaves;
+        if (groups > 0) {
+          const uint64_t per = bundle_w / 2;  // units
+          w.n_bundles[c] = div_up((int64_t)(hc.cw16[c] / 2), (int64_t)per);
+          w.bundle[c] = own.alloc<uint32_t>(w.n_bundles[c] + 1);
+          TC_LAUNCH("bundles", k_bundles, dim3(grid_for(groups)), dim3(kT), 0, st, items + w.n_items32[c], groups,
+                    per, w.n_bundles[c], w.bundle[c]);
+          TC_HIP(hipGetLastError());
+        }
       }
     }
   }
@@ -1399,12 +1576,21 @@ void build_work(WorkSet& w, Owned& own, int64_t n, const int64_t* hrow_ptr, int6
     DevBuf part(sizeof(unsigned long long) * (size_t)nb * kStatCols);
     DevBuf sums(sizeof(unsigned long long) * kStatCols);
     TC_LAUNCH("class_stats", k_class_stats, dim3((unsigned)nb), dim3(kT), 0, st, cls.as<int8_t>(), n,
-              w.tbeg, w.tend, w.tprefix, hrow_ptr, part.as<unsigned long long>());
+              w.tbeg, w.tend, hrow_ptr, part.as<unsigned long long>());
     TC_LAUNCH("reduce_cols", k_reduce_cols, dim3(kStatCols), dim3(kT), 0, st,
               part.as<unsigned long long>(), nb, kStatCols, sums.as<unsigned long long>());
     TC_HIP(hipGetLastError());
-    // (valid once st is synchronised: both callers check their sorts next)
+    // (valid once st is synchronised: every caller checks its sorts next)
     TC_HIP(hipMemcpyAsync(&w.cls_stats[0][0], sums.p, sizeof(w.cls_stats), hipMemcpyDeviceToHost, st));
+    TC_HIP(hipMemcpyAsync(w.cls_probes, d_cp, sizeof(w.cls_probes), hipMemcpyDeviceToHost, st));
+  }
+}
+
+void finish_work(WorkSet& w) {
+  w.probes = 0;
+  for (int c = 0; c < NUM_CLASSES; ++c) {
+    w.cls_stats[c][3] = (int64_t)w.cls_probes[c];
+    w.probes += w.cls_stats[c][3];
   }
 }
 

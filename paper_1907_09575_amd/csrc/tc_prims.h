@@ -918,19 +918,20 @@ struct TaskLists {
   int64_t T = 0;
   DevBuf row;     // uint32 [T]: hashed row of each task
   DevBuf val;     // uint64 [T]: first probe | (end of the probe range) << 32
-  DevBuf prefix;  // uint64 [T + 1]: exclusive prefix of the probe counts, total at [T]
+  DevBuf prefix;  // uint64 [T + 1]: exclusive prefix of the probe counts (short rows: units), total at [T]
   DevBuf ptr;     // int64 [nrows + 1]: tasks of row b are [ptr[b], ptr[b + 1])
 };
 
 // Sort T emitted tasks (tk = hashed row in [0, 2^key_bits), tv = first
 // probe | end << 32) stably by row and fill `tl`. tk / tv are consumed as
 // sort buffers (tl may take them over).
-void sort_tasks(TaskLists& tl, DevBuf& tk, DevBuf& tv, int64_t T, int64_t nrows, int key_bits,
+void sort_tasks(TaskLists& tl, DevBuf& tk, DevBuf& tv, int64_t T, int64_t nrows, int key_bits, int64_t b16,
                 hipStream_t st, const char* name);
 // Probe prefixes (tl.prefix) and row pointers (tl.ptr, allocated by the
 // caller with nrows + 1 entries) of the tl.T tasks in tl.row / tl.val,
-// sorted by row; the tail of sort_tasks.
-void finish_tasks(TaskLists& tl, int64_t nrows, hipStream_t st);
+// sorted by row; the tail of sort_tasks. Tasks of rows b16 and up (short
+// rows) are counted in units.
+void finish_tasks(TaskLists& tl, int64_t nrows, int64_t b16, hipStream_t st);
 // check_sorts for the task sorts of sort_tasks (synchronises st).
 void check_task_sorts(hipStream_t st);
 
