@@ -343,7 +343,8 @@ tc_status tc_batch_autotune(const tc_graph* const* graphs, int32_t num_graphs, v
  *                 a class too small to fill them even then keeps wave_chunk
  *                 (few large units suit a batch of many small graphs). Short
  *                 rows are shared out by weight instead.
- * Short rows are the last 65534 ranks: all their columns lie in those ranks,
+ * Short rows are the last 65534 ranks (in a graph of more ranks: if its degrees
+ * are uneven): all their columns lie in those ranks,
  * and their probes are read from a 16-bit form of them.
  * They change how the work is scheduled, never a count. Graphs take theirs
  * from the tuning table when tc_preprocess builds them (the defaults when the

@@ -212,6 +212,12 @@ struct TableRef {
 
 // Short rows: TK_MULTI16 (packs), TK_BITS (bitmap), TK_GLOBAL16 (HBM).
 enum TableKind : int { TK_SINGLE = 0, TK_MULTI = 1, TK_GLOBAL = 2, TK_MULTI16 = 3, TK_BITS = 4, TK_GLOBAL16 = 5 };
+// Batches per super-batch of a kind: a window (64 tasks) holds about half as
+// many units as probes, so the short rows' kinds take half; a batch beyond
+// the window's end costs as much as a full one (ER, n = 30000, 400000 pairs:
+// 58 us with 8, 43 us with 4).
+constexpr int kPacks16U = 4, kBitsU = 4;
+constexpr int kind_batches(int kind) { return kind == TK_MULTI16 ? kPacks16U : kind == TK_BITS ? kBitsU : kU; }
 constexpr uint32_t kEmpty16 = 0xFFFFu;  // empty 16-bit slot: above every distance (kShortSpan)
 
 // A hit: k = col[pos] was found in U_b at `where` (an LDS slot, or for the HBM
@@ -297,7 +303,16 @@ __device__ __forceinline__ void credit16(const Args& A, const TableRef& t, uint3
 // lane j adds the difference of its task's word and the one before to the
 // task's edge with one global atomic. A batch without a task end costs only
 // its ballot and a scalar add. A task cut between waves gets one atomic from
-// each.
+// each. (kEndCounts; packs of 32-bit rows, whose windows are one super-batch of
+// short tasks, mask every batch's ballot to the lanes of each task instead:
+// oriented support of an ER graph, n = 10^6: 582 us against 625 us.)
+__device__ __forceinline__ uint64_t lane_range_mask(int lo, int hi) {
+  lo = lo < 0 ? 0 : (lo > 64 ? 64 : lo);
+  hi = hi < 0 ? 0 : (hi > 64 ? 64 : hi);
+  if (hi <= lo) return 0;
+  const uint64_t below_hi = hi >= 64 ? ~0ull : ((1ull << hi) - 1ull);
+  return below_hi & ~((1ull << lo) - 1ull);
+}
 
 // Count mode needs only whether the bucket holds k: an OR of four compares
 // (no slot index, no branch).
@@ -328,22 +343,22 @@ __device__ __forceinline__ int match_slot16(const uint2& b, uint32_t v) {
 // column distances of batch u; 0 is no key. Hits of
 // the first and the second probe of batch u set bit u of f0 and f1 (support
 // modes).
-template <int MODE, int KIND>
-__device__ __forceinline__ void probe_units(const Args& A, const TableRef& tr, const int32_t (&w)[kU],
-                                            const uint32_t (&bbase)[kU], const uint32_t (&bmask)[kU],
+template <int MODE, int KIND, int U>
+__device__ __forceinline__ void probe_units(const Args& A, const TableRef& tr, const int32_t (&w)[U],
+                                            const uint32_t (&bbase)[U], const uint32_t (&bmask)[U],
                                             uint32_t& hits, uint32_t& f0, uint32_t& f1) {
   constexpr bool kMask = MODE == MODE_SUPPORT_FULL || MODE == MODE_SUPPORT_ORIENTED;
   constexpr bool FULL = MODE == MODE_SUPPORT_FULL;
   if constexpr (KIND == TK_BITS) {
     const uint32_t* bits = reinterpret_cast<const uint32_t*>(tr.tab);
-    uint32_t x0[kU], x1[kU];
+    uint32_t x0[U], x1[U];
 #pragma unroll
-    for (int u = 0; u < kU; ++u) {
+    for (int u = 0; u < U; ++u) {
       x0[u] = bits[((uint32_t)w[u] >> 5) & 0x7FFu];
       x1[u] = bits[(uint32_t)w[u] >> 21];
     }
 #pragma unroll
-    for (int u = 0; u < kU; ++u) {
+    for (int u = 0; u < U; ++u) {
       const uint32_t b0 = __builtin_amdgcn_ubfe(x0[u], (uint32_t)w[u] & 31u, 1);
       const uint32_t b1 = __builtin_amdgcn_ubfe(x1[u], ((uint32_t)w[u] >> 16) & 31u, 1);
       hits += b0 + b1;
@@ -360,7 +375,7 @@ __device__ __forceinline__ void probe_units(const Args& A, const TableRef& tr, c
     const uint2* tab2 = reinterpret_cast<const uint2*>(tr.tab);
     constexpr int kG = 4;  // batches whose buckets are read together
 #pragma unroll
-    for (int g0 = 0; g0 < kU; g0 += kG) {
+    for (int g0 = 0; g0 < U; g0 += kG) {
       uint2 x[2 * kG];
 #pragma unroll
       for (int u = g0; u < g0 + kG; ++u) {
@@ -391,7 +406,7 @@ __device__ __forceinline__ void probe_units(const Args& A, const TableRef& tr, c
     }
   } else {
 #pragma unroll
-    for (int u = 0; u < kU; ++u) {
+    for (int u = 0; u < U; ++u) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const uint32_t v = h ? (uint32_t)w[u] >> 16 : (uint32_t)w[u] & 0xFFFFu;
@@ -442,7 +457,9 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
   constexpr bool MULTI = KIND == TK_MULTI || KIND == TK_MULTI16;
   constexpr bool MH = VAR == VAR_MUL, WIDE = VAR == VAR_WIDE && !SHORT;
   constexpr bool kTaskHits = MODE == MODE_SUPPORT_FULL || MODE == MODE_SUPPORT_ORIENTED;
-  constexpr uint32_t SB = 64u * kU;
+  constexpr bool kEndCounts = kTaskHits && KIND != TK_MULTI;
+  constexpr int U = kind_batches(KIND);
+  constexpr uint32_t SB = 64u * U;
   const int lane = lane_id();
   const int64_t T = A.T;
   const __amdgpu_buffer_rsrc_t rsrc =
@@ -495,17 +512,18 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
     uint32_t ntsj = 0;
     if (more) fetch((int64_t)t + 64 + lane, nPe, ntsj);  // next window, in flight meanwhile
 
-    uint32_t run = 0;  // support modes: the window's hits so far (uniform)
+    uint32_t run = 0;   // kEndCounts: the window's hits so far (uniform)
+    uint32_t tcnt = 0;  // otherwise: hits of this lane's window task
     for (uint32_t sb = 0; sb < lim; sb += SB) {
       const uint32_t c0 = (uint32_t)__popcll(__ballot(e <= sb));
       const bool inner = e > sb && e <= sb + SB;
-      uint32_t jl[kU];
-      uint64_t ends[kU];  // support modes: lanes of batch u that hold a task's last probe
+      uint32_t jl[U];
+      uint64_t ends[U];  // kEndCounts: lanes of batch u that hold a task's last probe
       if (__ballot(inner) == 0) {
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
+        for (int u = 0; u < U; ++u) {
           jl[u] = c0;
-          if (kTaskHits) ends[u] = 0;
+          if (kEndCounts) ends[u] = 0;
         }
       } else {
         // bit p set <=> some task ends right after probe sb + p
@@ -513,24 +531,24 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
         wave_sync_lds();
         uint32_t pre = c0;
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
+        for (int u = 0; u < U; ++u) {
           const uint32_t lo = __builtin_amdgcn_readfirstlane(bm[2 * u]);
           const uint32_t hi = __builtin_amdgcn_readfirstlane(bm[2 * u + 1]);
           jl[u] = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, pre));
           pre += (uint32_t)__builtin_popcount(lo) + (uint32_t)__builtin_popcount(hi);
-          if (kTaskHits) ends[u] = ((uint64_t)hi << 32) | lo;
+          if (kEndCounts) ends[u] = ((uint64_t)hi << 32) | lo;
         }
         wave_sync_lds();
         if (lane < (int)(SB / 32)) bm[lane] = 0;
         wave_sync_lds();
       }
-      uint32_t pos[kU], bbase[kU], bmask[kU];
-      int32_t k[kU];
-      bool ok[kU];
+      uint32_t pos[U], bbase[U], bmask[U];
+      int32_t k[U];
+      bool ok[U];
       uint32_t fmask = 0;  // support modes: bit u = this lane's probe of batch u hit
       uint32_t fmask1 = 0;  // short rows: its second probe (bits of fmask: the first)
 #pragma unroll
-      for (int u = 0; u < kU; ++u) {
+      for (int u = 0; u < U; ++u) {
         // ds_bpermute uses lane index bits only, so lanes past the window
         // (jl >= 64, never used) wrap harmlessly
         const uint32_t r = sb + 64u * u + (uint32_t)lane;
@@ -546,22 +564,22 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
         }
       }
 #pragma unroll
-      for (int u = 0; u < kU; ++u) {
+      for (int u = 0; u < U; ++u) {
         if constexpr (WIDE) k[u] = ok[u] ? A.col[(uint64_t)pos[u]] : 0;
         else k[u] = col_load(rsrc, ok[u] ? pos[u] * 4u : kOffNone);
       }
 
       if constexpr (SHORT) {
-        probe_units<MODE, KIND>(A, tr, k, bbase, bmask, hits, fmask, fmask1);
+        probe_units<MODE, KIND, U>(A, tr, k, bbase, bmask, hits, fmask, fmask1);
       } else if constexpr (!GLOBAL) {
         // buckets are read in groups of kG so that the 16-byte results of one
         // group fit the register budget of 8 waves per SIMD
         constexpr int kG = 2;
-        uint32_t bk[kU];
-        bool unres[kU];
+        uint32_t bk[U];
+        bool unres[U];
         bool any_unres = false;
 #pragma unroll
-        for (int g0 = 0; g0 < kU; g0 += kG) {
+        for (int g0 = 0; g0 < U; g0 += kG) {
           int4 v[kG];
 #pragma unroll
           for (int u = g0; u < g0 + kG; ++u) {
@@ -587,7 +605,7 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
         // full first bucket: continue into the next ones (bounded by D)
         if (tr.D > 0 && __ballot(any_unres)) {
 #pragma unroll
-          for (int u = 0; u < kU; ++u) {
+          for (int u = 0; u < U; ++u) {
             uint32_t b2 = bk[u] - bbase[u];
             for (int i = 1; i <= tr.D && unres[u]; ++i) {
               b2 = (b2 + 1) & bmask[u];
@@ -608,7 +626,7 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
         }
       } else {
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
+        for (int u = 0; u < U; ++u) {
           const int64_t where = ok[u] ? hbm_find(A.hcol, tr.rs, tr.d, k[u]) : -1;
           if (where >= 0) {
             ++hits;
@@ -617,9 +635,21 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
           }
         }
       }
-      if constexpr (kTaskHits) {
+      if constexpr (kTaskHits && !kEndCounts) {
+        // this lane's task covers the relative probes [s_rel, e) (s_rel may
+        // be below 0 for lane 0); add the hits of batch u that fall there
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
+        for (int u = 0; u < U; ++u) {
+          const uint64_t hm = __ballot((fmask >> u) & 1u);
+          if (hm) {
+            const int base = (int)(sb + 64u * (uint32_t)u);
+            tcnt += (uint32_t)__popcll(hm & lane_range_mask((int)s_rel - base, (int)e - base));
+          }
+        }
+      }
+      if constexpr (kEndCounts) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
           const uint64_t hm = __ballot((fmask >> u) & 1u);
           const uint64_t hm1 = SHORT ? __ballot((fmask1 >> u) & 1u) : 0;
           if (MODE == MODE_SUPPORT_FULL && SHORT && (hm | hm1)) credit_probed(A, pos[u], hm, hm1);
@@ -637,7 +667,8 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
         }
       }
     }
-    if constexpr (kTaskHits) {
+    if (kTaskHits && !kEndCounts && tcnt && tsj - 1u < A.m) atomicAdd(&A.support[tsj - 1u], (int)tcnt);
+    if constexpr (kEndCounts) {
       wave_sync_lds();
       if (run) {
         // (a task without probes here ends where the one before it does, and
@@ -1122,9 +1153,9 @@ void k_count_items(Args A, const CountItem* __restrict__ items) {
 // but 7 waves per SIMD with spill-free registers run faster; wg_huge tables
 // (32 KiB) allow 4-5 work-groups per CU and wg_giant tables (64 KiB) 2.
 // Support modes hold more state per probe and run at 4.
-constexpr int kOccBits = 7, kOccBitsOriented = 5, kOccBitsFull = 4;  // (bitmaps take at most 8 KiB: registers limit the waves)
+constexpr int kOccBits = 8, kOccBitsOriented = 6, kOccBitsFull = 5;  // (bitmaps take at most 8 KiB: registers limit the waves)
 constexpr int kOccPacks16 = 7;
-constexpr uint32_t kPacks16Waves = 512;  // packs up to which 16 waves share one
+constexpr uint32_t kPacks16Waves = 1024;  // packs up to which 16 waves share one
 constexpr int kOccSmall = 7, kOccLarge = 7, kOccHuge = 5, kOccGiant = 4, kOccSupport = 5;
 
 template <int MODE, bool GLOBAL, int VAR>

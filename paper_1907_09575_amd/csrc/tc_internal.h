@@ -125,8 +125,15 @@ constexpr int64_t kMaxBufferEdges = (1ll << 30) - 64;  // below: probe reads by 
 // of U_b, so no half needs a mask.
 constexpr int64_t kShortSpan = 65534;
 constexpr int64_t kMaxShortEdges = (1ll << 31) - 64;  // units by 32-bit byte offsets
-inline int64_t short_rows_begin(int64_t n, int64_t m) {
-  return m > kMaxShortEdges ? n : (n > kShortSpan ? n - kShortSpan : 0);
+// A graph of more ranks than the span whose degrees are even (largest
+// out-degree within 8 times the average: Erdos-Renyi) has no short rows: they
+// would hold little more than their share of the ranks, and its packs of
+// both kinds would each end on a tail of their own (ER, n = 300000: 118 us
+// without them, 143 us with).
+inline int64_t short_rows_begin(int64_t n, int64_t m, int64_t max_out_degree) {
+  if (m > kMaxShortEdges) return n;
+  if (n <= kShortSpan) return 0;
+  return max_out_degree * n > 8 * m ? n - kShortSpan : n;
 }
 // Probes a task of a short row is charged for in the work decomposition (two
 // per unit), and its units.

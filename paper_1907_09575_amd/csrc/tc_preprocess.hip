@@ -1137,7 +1137,6 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
   g->row_ptr = g->owned.alloc<int64_t>(n + 1);
   g->col = g->owned.alloc<int32_t>(m);
   g->col16 = g->owned.alloc<uint16_t>(m + 2);
-  const int64_t b16 = short_rows_begin(n, m);
   const uint64_t* okey = obuf.as<uint64_t>();
   {
     if (m > 0) {
@@ -1217,16 +1216,17 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
         tl.val.swap(tv);
       }
     }
-    finish_tasks(tl, n, b16, st);
     g->wedges_plus = (int64_t)h.wplus;
     g->max_dplus = (int64_t)h.maxd;
+    finish_tasks(tl, n, short_rows_begin(n, m, g->max_dplus), st);
   }
   ka.release();
   kb.release();
 
   // ---- 6: work classes ------------------------------------------------------
   build_work(g->w, g->owned, n, g->row_ptr, tl.T, tl.row.as<uint32_t>(), tl.ptr.as<int64_t>(),
-             tl.val.as<uint64_t>(), tl.prefix.as<uint64_t>(), b16, default_work_params(m), st);
+             tl.val.as<uint64_t>(), tl.prefix.as<uint64_t>(), short_rows_begin(n, m, g->max_dplus),
+             default_work_params(m), st);
   check_sorts(st);
   finish_work(g->w);
   g->arena_bytes = g->owned.bytes;
@@ -1299,7 +1299,7 @@ Graph* build_variant(const Graph& base, int flags, const WorkParams& wp, hipStre
   const int64_t n = g->n, m = g->m;
   // (<i,j,k> looks up whole rows, first entries included, and the hashing
   // ablation compares 32-bit tables: no short rows there)
-  const int64_t b16 = ijk || g->hash ? n : short_rows_begin(n, m);
+  const int64_t b16 = ijk || g->hash ? n : short_rows_begin(n, m, base.max_dplus);
   TaskLists tl;
   if (m > 0) {
     DevBuf erow(sizeof(uint32_t) * (size_t)m);
