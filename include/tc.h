@@ -180,11 +180,9 @@ tc_status tc_graph_variant(const tc_graph* g, int32_t flags, void* stream, tc_gr
 /*
  * tc_vertex_triangles - number of triangles through every vertex, indexed by
  * original vertex id: d_tri is device int64[n] (caller-owned, overwritten).
- * Computed from the per-edge support of TC_SUPPORT_FULL: the two edges a
- * triangle has at v each count it once, so t(v) is half their sum. The sum
- * over all vertices is 3T. Asynchronous on `stream` except for one
- * synchronisation after the internal column sort; allocates temporaries
- * (the support array and U's column lists: about 16 m + 8 n bytes).
+ * Every triangle is credited to its three vertices; the sum over all vertices
+ * is 3T. Asynchronous on `stream`; allocates temporaries (about 4 m + 8 n
+ * bytes).
  */
 tc_status tc_vertex_triangles(const tc_graph* g, int64_t* d_tri, void* stream);
 

@@ -67,10 +67,17 @@ using Args = CountArgs;
 constexpr int kU = 8;                   // 64-probe batches per super-batch
 constexpr int kBmWords = 2 * kU;        // per-wave task-end bitmap (64 * kU bits)
 
+// Modes that count the hits of every task, and those that count the hits of
+// every key of U_b.
+__host__ __device__ constexpr bool mode_tasks(int mode) {
+  return mode == MODE_SUPPORT_FULL || mode == MODE_SUPPORT_ORIENTED || mode == MODE_VERTEX;
+}
+__host__ __device__ constexpr bool mode_keys(int mode) { return mode == MODE_SUPPORT_FULL || mode == MODE_VERTEX; }
+
 // LDS words of one wave: its task-end bitmap and, in the support modes, the
 // running hit count at the end of each of its window's tasks.
 __host__ __device__ constexpr int wave_words(int mode) {
-  return kBmWords + (mode == MODE_SUPPORT_FULL || mode == MODE_SUPPORT_ORIENTED ? 64 : 0);
+  return kBmWords + (mode_tasks(mode) ? 64 : 0);
 }
 
 constexpr int32_t kEmpty = -1;
@@ -204,6 +211,7 @@ struct TableRef {
   const uint32_t* row_desc;
   int nrows;
   int lds_hits;  // packs, FULL: the (b, k) credits are counted in LDS
+  uint32_t* row_hits;  // packs, VERTEX: hits of every row
   // bitmaps, FULL: keys of smaller distance than each word's (pfx), hits per
   // key in order of distance (cnt; null: credited to U directly)
   const uint16_t* pfx;
@@ -229,8 +237,14 @@ __device__ unsigned int* shift_counters() {
   return s_shift;
 }
 
+// VERTEX: c triangles at vertex v (a rank).
+__device__ __forceinline__ void credit_vertex(const Args& A, uint32_t v, uint32_t c) {
+  if (v < (uint32_t)A.n) atomicAdd(&A.vcount[v], (unsigned long long)c);
+}
+
 // The per-hit credits other than the task's own edge (a, b), which goes
-// through the wave's per-task counters (wave_probe). BLOCK: the shift
+// through the wave's per-task counters (wave_probe). VERTEX: like FULL for the
+// keys k of U_b, whose hits go to the vertex k. BLOCK: the shift
 // counter of k; FULL: the probed entry (a, k) of U_a and k's entry (b, k) of
 // U_b.
 template <int MODE, int KIND>
@@ -241,8 +255,8 @@ __device__ __forceinline__ void credit(const Args& A, const TableRef& t, int whe
     int z = (int)((uint32_t)k % (uint32_t)A.q) - A.xy;
     if (z < 0) z += A.q;
     atomicAdd(&shift_counters()[z], 1u);
-  } else if (MODE == MODE_SUPPORT_FULL) {
-    if (pos < A.m) atomicAdd(&A.support[pos], 1);  // edge (a, k): probed entry of U_a
+  } else if (mode_keys(MODE)) {
+    if (MODE == MODE_SUPPORT_FULL && pos < A.m) atomicAdd(&A.support[pos], 1);  // edge (a, k): probed entry of U_a
     // edge (b, k): k's entry in U_b. A single-row table counts it in the
     // slot's LDS word (added to the array once per work-group, after the
     // probe loop of items_body).
@@ -250,6 +264,8 @@ __device__ __forceinline__ void credit(const Args& A, const TableRef& t, int whe
       atomicAdd(&t.val[where], 1 << kValBits);
     } else if (KIND == TK_MULTI && t.lds_hits) {
       atomicAdd(reinterpret_cast<unsigned int*>(&t.val[where]), 1u << kPackValBits);
+    } else if (MODE == MODE_VERTEX) {
+      credit_vertex(A, (uint32_t)k, 1u);
     } else {
       const uint32_t other = (uint32_t)(KIND == TK_GLOBAL ? where : t.val[where]);
       if (other < A.m) atomicAdd(&A.support[other], 1);
@@ -277,19 +293,23 @@ __device__ __forceinline__ void credit_probed(const Args& A, uint32_t pos, uint6
 // A short row's hit (FULL) with a key of distance v of U_b: its (b, k) credit.
 // `where` is the key's slot (packs), its bitmap word's contents (bitmaps) or
 // its position in U (HBM).
-template <int KIND>
+template <int MODE, int KIND>
 __device__ __forceinline__ void credit16(const Args& A, const TableRef& t, uint32_t where, uint32_t v) {
   if (KIND == TK_BITS) {
     // keys of smaller distance come after k in U_b
     const uint32_t r = (uint32_t)t.pfx[v >> 5] + (uint32_t)__builtin_popcount(where & ((1u << (v & 31)) - 1u));
     if (t.cnt) {
       atomicAdd(&t.cnt[r], 1u);
+    } else if (MODE == MODE_VERTEX) {
+      credit_vertex(A, (uint32_t)A.n - v, 1u);
     } else {
       const uint64_t p = (uint64_t)(t.rs + t.d - 1) - r;
       if (p < A.m) atomicAdd(&A.support[p], 1);
     }
   } else if (KIND == TK_MULTI16 && t.lds_hits) {
     atomicAdd(reinterpret_cast<unsigned int*>(&t.val[where]), 1u << kPackValBits);
+  } else if (MODE == MODE_VERTEX) {
+    credit_vertex(A, (uint32_t)A.n - v, 1u);
   } else {
     const uint32_t other = KIND == TK_GLOBAL16 ? where : (uint32_t)t.val[where];
     if (other < A.m) atomicAdd(&A.support[other], 1);
@@ -347,8 +367,8 @@ template <int MODE, int KIND, int U>
 __device__ __forceinline__ void probe_units(const Args& A, const TableRef& tr, const int32_t (&w)[U],
                                             const uint32_t (&bbase)[U], const uint32_t (&bmask)[U],
                                             uint32_t& hits, uint32_t& f0, uint32_t& f1) {
-  constexpr bool kMask = MODE == MODE_SUPPORT_FULL || MODE == MODE_SUPPORT_ORIENTED;
-  constexpr bool FULL = MODE == MODE_SUPPORT_FULL;
+  constexpr bool kMask = mode_tasks(MODE);
+  constexpr bool FULL = mode_keys(MODE);
   if constexpr (KIND == TK_BITS) {
     const uint32_t* bits = reinterpret_cast<const uint32_t*>(tr.tab);
     uint32_t x0[U], x1[U];
@@ -367,8 +387,8 @@ __device__ __forceinline__ void probe_units(const Args& A, const TableRef& tr, c
         f1 |= b1 << u;
       }
       if (FULL) {
-        if (b0) credit16<KIND>(A, tr, x0[u], (uint32_t)w[u] & 0xFFFFu);
-        if (b1) credit16<KIND>(A, tr, x1[u], (uint32_t)w[u] >> 16);
+        if (b0) credit16<MODE, KIND>(A, tr, x0[u], (uint32_t)w[u] & 0xFFFFu);
+        if (b1) credit16<MODE, KIND>(A, tr, x1[u], (uint32_t)w[u] >> 16);
       }
     }
   } else if constexpr (KIND == TK_MULTI16) {
@@ -400,7 +420,7 @@ __device__ __forceinline__ void probe_units(const Args& A, const TableRef& tr, c
           hits += found ? 1u : 0u;
           if (kMask) (h ? f1 : f0) |= (found ? 1u : 0u) << u;
           if (FULL && found)
-            credit16<KIND>(A, tr, (bbase[u] + bk) * kBucket + (uint32_t)match_slot16(b, v), v);
+            credit16<MODE, KIND>(A, tr, (bbase[u] + bk) * kBucket + (uint32_t)match_slot16(b, v), v);
         }
       }
     }
@@ -414,7 +434,7 @@ __device__ __forceinline__ void probe_units(const Args& A, const TableRef& tr, c
         if (where < 0) continue;
         ++hits;
         if (kMask) (h ? f1 : f0) |= 1u << u;
-        if (FULL) credit16<KIND>(A, tr, (uint32_t)where, v);
+        if (FULL) credit16<MODE, KIND>(A, tr, (uint32_t)where, v);
       }
     }
   }
@@ -440,6 +460,19 @@ __device__ __forceinline__ Window window_first(const Args& A, uint32_t t, uint64
   return w;
 }
 
+// c hits of the task whose first probe is ts: to its own edge, or (VERTEX) to
+// its row a and, in a pack, to its hashed row's counter.
+template <int MODE, bool MULTI>
+__device__ __forceinline__ void credit_task(const Args& A, const TableRef& tr, uint32_t ts, int row, uint32_t c) {
+  if (ts - 1u >= A.m) return;
+  if constexpr (MODE == MODE_VERTEX) {
+    credit_vertex(A, A.erow[ts - 1u], c);
+    if (MULTI) atomicAdd(&tr.row_hits[row], c);
+  } else {
+    atomicAdd(&A.support[ts - 1u], (int)c);
+  }
+}
+
 // One wave processes the probes [q, q + len) of the tasks of one hashed row;
 // task t contains probe q; w0 = window_first(A, t, q, len).
 template <int MODE, int KIND, int VAR>
@@ -456,7 +489,7 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
   constexpr bool SHORT = KIND == TK_MULTI16 || KIND == TK_BITS || KIND == TK_GLOBAL16;  // probes are units
   constexpr bool MULTI = KIND == TK_MULTI || KIND == TK_MULTI16;
   constexpr bool MH = VAR == VAR_MUL, WIDE = VAR == VAR_WIDE && !SHORT;
-  constexpr bool kTaskHits = MODE == MODE_SUPPORT_FULL || MODE == MODE_SUPPORT_ORIENTED;
+  constexpr bool kTaskHits = mode_tasks(MODE);
   constexpr bool kEndCounts = kTaskHits && KIND != TK_MULTI;
   constexpr int U = kind_batches(KIND);
   constexpr uint32_t SB = 64u * U;
@@ -497,6 +530,7 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
     if (lim == 0) break;  // unreachable when every task has a probe; guards progress
     // packs: the table of the lane's task (last row whose first task <= it)
     uint32_t tdesc = 0;
+    int trow = 0;
     if constexpr (MULTI) {
       const uint32_t tj = t + (uint32_t)lane;
       int lo = 0, hi = tr.nrows;  // row_t0[lo] <= tj (lanes past the pack clamp to the last row)
@@ -506,6 +540,7 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
         else hi = mid;
       }
       tdesc = tr.row_desc[lo];
+      trow = lo;
     }
     const bool more = lim < rem;
     uint32_t nPe = 0;
@@ -589,7 +624,7 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
 #pragma unroll
           for (int u = g0; u < g0 + kG; ++u) {
             bool found;
-            if constexpr (MODE == MODE_COUNT || MODE == MODE_SUPPORT_ORIENTED) {
+            if constexpr (MODE != MODE_BLOCK && !mode_keys(MODE)) {
               found = bucket_has(v[u - g0], k[u]);
             } else {
               const int j = match_slot(v[u - g0], k[u]);
@@ -611,7 +646,7 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
               b2 = (b2 + 1) & bmask[u];
               const int4 w = tab4[bbase[u] + b2];
               bool found;
-              if constexpr (MODE == MODE_COUNT || MODE == MODE_SUPPORT_ORIENTED) {
+              if constexpr (MODE != MODE_BLOCK && !mode_keys(MODE)) {
                 found = bucket_has(w, k[u]);
               } else {
                 const int j = match_slot(w, k[u]);
@@ -667,7 +702,7 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
         }
       }
     }
-    if (kTaskHits && !kEndCounts && tcnt && tsj - 1u < A.m) atomicAdd(&A.support[tsj - 1u], (int)tcnt);
+    if (kTaskHits && !kEndCounts && tcnt) credit_task<MODE, MULTI>(A, tr, tsj, trow, tcnt);
     if constexpr (kEndCounts) {
       wave_sync_lds();
       if (run) {
@@ -677,7 +712,7 @@ __device__ void wave_probe(const Args& A, const TableRef& tr, uint32_t t, uint64
         const uint32_t cp = (uint32_t)__shfl_up((int)ce, 1, 64);
         const uint32_t c = ce - (lane == 0 ? 0u : cp);
         const bool any = lane == 0 ? e > 0 : e != e_prev;
-        if (any && c && tsj - 1u < A.m) atomicAdd(&A.support[tsj - 1u], (int)c);
+        if (any && c) credit_task<MODE, MULTI>(A, tr, tsj, trow, c);
         wave_sync_lds();
       }
     }
@@ -737,6 +772,12 @@ __device__ __forceinline__ int insert16(uint32_t* tab, uint32_t bk, uint32_t v) 
   return -1;
 }
 
+// VERTEX: a wave's hits of hashed row b.
+__device__ __forceinline__ void credit_row(const Args& A, int32_t b, uint32_t hits) {
+  const uint32_t h = wave_sum(hits);  // (a work-group holds fewer than 2^18 probes)
+  if (lane_id() == 0 && h) credit_vertex(A, (uint32_t)b, h);
+}
+
 // Packs of light rows (one work-group each): up to kPackRows rows, one per
 // thread for its metadata; all their tables are built together in LDS (keys
 // flattened over the work-group), then the pack's probe range - the tasks of
@@ -747,7 +788,7 @@ constexpr int kPackMetaWords = 3 * kPackRows + 1;  // row_t0, row_desc, key pref
 // LDS words before a pack's tables (a multiple of four: buckets are read as
 // 16 bytes).
 __host__ __device__ constexpr int pack_head_words(int mode, int waves) {
-  return (waves * wave_words(mode) + kPackMetaWords + 3) & ~3;
+  return (waves * wave_words(mode) + kPackMetaWords + (mode == MODE_VERTEX ? kPackRows : 0) + 3) & ~3;
 }
 
 // Exclusive scan over the first kPackRows threads of a work-group (the others
@@ -776,7 +817,7 @@ __device__ __forceinline__ unsigned long long pack_body(const Args& A, const Pac
                                           uint32_t pack_slots, int32_t* smem) {
   __shared__ int s_D;
   __shared__ uint32_t s_w[4], s_w2[4];
-  constexpr bool VALS = MODE == MODE_SUPPORT_FULL;
+  constexpr bool VALS = mode_keys(MODE);
   constexpr int NT = 64 * WAVES;
   static_assert(kPackWavesMax % WAVES == 0 && NT >= kPackRows, "pack work-group shape");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -784,6 +825,7 @@ __device__ __forceinline__ unsigned long long pack_body(const Args& A, const Pac
   uint32_t* row_t0 = reinterpret_cast<uint32_t*>(smem) + WAVES * wave_words(MODE);
   uint32_t* row_desc = row_t0 + kPackRows;
   uint32_t* row_k0 = row_desc + kPackRows;  // kPackRows + 1 entries
+  uint32_t* row_hits = row_k0 + kPackRows + 1;  // VERTEX
   int32_t* tab = smem + pack_head_words(MODE, WAVES);
   int32_t* val = tab + (SHORT ? pack_slots / 2 : pack_slots);  // (short rows: 16-bit slots)
   if (lane < kBmWords) bm[lane] = 0;
@@ -829,6 +871,7 @@ __device__ __forceinline__ unsigned long long pack_body(const Args& A, const Pac
   // this thread also remembers its own row's start (rows are few per thread)
   __shared__ uint32_t s_rs[kPackRows];
   if (tid < nr) s_rs[tid] = rs;
+  if (MODE == MODE_VERTEX && tid < kPackRows) row_hits[tid] = 0;
   __syncthreads();
   int md = 0;
   for (uint32_t x = tid; x < K_tot; x += NT) {
@@ -866,7 +909,7 @@ __device__ __forceinline__ unsigned long long pack_body(const Args& A, const Pac
   if (md) atomicMax(&s_D, md);
   __syncthreads();
 
-  TableRef tr{tab, val, 0, s_D, 0, 0, row_t0, row_desc, nr, lds_hits ? 1 : 0, nullptr, nullptr};
+  TableRef tr{tab, val, 0, s_D, 0, 0, row_t0, row_desc, nr, lds_hits ? 1 : 0, row_hits, nullptr, nullptr};
   uint32_t hits = 0;
   if (wlen > 0) wave_probe<MODE, SHORT ? TK_MULTI16 : TK_MULTI, VAR>(A, tr, wt, wq0, wlen, bm, hits, w0);
   if constexpr (VALS) {
@@ -887,9 +930,15 @@ __device__ __forceinline__ unsigned long long pack_body(const Args& A, const Pac
           else hi = mid;
         }
         const uint32_t p = s_rs[lo] + (x - row_k0[lo]);
-        if (p < A.m) atomicAdd(&A.support[p], (int)c);
+        if (MODE == MODE_VERTEX) credit_vertex(A, (uint32_t)A.hcol[p], c);
+        else if (p < A.m) atomicAdd(&A.support[p], (int)c);
       }
     }
+  }
+  if constexpr (MODE == MODE_VERTEX) {
+    __syncthreads();
+    // (the hashed row is the column of the entry before its first task's first probe)
+    if (tid < nr && row_hits[tid]) credit_vertex(A, (uint32_t)A.hcol[A.tstart[row_t0[tid]] - 1u], row_hits[tid]);
   }
   return block_flush<MODE>(hits, A);
 }
@@ -926,7 +975,7 @@ template <int MODE, bool GLOBAL, int VAR>
 __device__ __forceinline__ unsigned long long items_body(const Args& A, const CountItem* __restrict__ grp,
                                                          int32_t* smem) {
   __shared__ int s_D;
-  constexpr bool VALS = MODE == MODE_SUPPORT_FULL;
+  constexpr bool VALS = mode_keys(MODE);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   uint32_t* bm = reinterpret_cast<uint32_t*>(smem) + wave * wave_words(MODE);
   const int64_t rs = grp[0].rs, d = grp[0].d;
@@ -936,7 +985,7 @@ __device__ __forceinline__ unsigned long long items_body(const Args& A, const Co
   if (lane < kBmWords) bm[lane] = 0;
   block_init<MODE>();
   uint32_t hits = 0;
-  TableRef tr{nullptr, nullptr, 0, 0, rs, d, nullptr, nullptr, 0, 0, nullptr, nullptr};
+  TableRef tr{nullptr, nullptr, 0, 0, rs, d, nullptr, nullptr, 0, 0, nullptr, nullptr, nullptr};
   if (GLOBAL) {
     __syncthreads();  // shift counters cleared before any credit
   } else {
@@ -966,9 +1015,11 @@ __device__ __forceinline__ unsigned long long items_body(const Args& A, const Co
       const uint32_t w = (uint32_t)tr.val[i];
       const uint32_t c = w >> kValBits;
       const int64_t p = rs + (int64_t)(w & ((1u << kValBits) - 1u));
-      if (c && p < (int64_t)A.m) atomicAdd(&A.support[p], (int)c);
+      if (MODE == MODE_VERTEX && c) credit_vertex(A, (uint32_t)A.hcol[p], c);
+      else if (c && p < (int64_t)A.m) atomicAdd(&A.support[p], (int)c);
     }
   }
+  if constexpr (MODE == MODE_VERTEX) credit_row(A, grp[0].b, hits);
   return block_flush<MODE>(hits, A);
 }
 
@@ -1007,7 +1058,7 @@ __device__ __forceinline__ void bits_keys(const Args& A, const CountItem& it, in
 template <int MODE>
 __device__ __forceinline__ void bits_build(const Args& A, const BitsLds& L, const CountItem& it, uint32_t max_keys,
                                            const int32_t (&key)[kKeyRegs]) {
-  constexpr bool FULL = MODE == MODE_SUPPORT_FULL;
+  constexpr bool FULL = mode_keys(MODE);
   constexpr uint32_t NT = 64 * kWaves;
   const uint32_t words = ((uint32_t)(A.n - it.b) >> 5) + 1;
   for (uint32_t i = threadIdx.x; i < words; i += NT) L.bits[i] = 0;
@@ -1034,9 +1085,9 @@ __device__ __forceinline__ void bits_build(const Args& A, const BitsLds& L, cons
 template <int MODE>
 __device__ __forceinline__ void bits_probe(const Args& A, const BitsLds& L, const CountItem& it, uint32_t max_keys,
                                            const Window& w0, uint32_t& hits) {
-  constexpr bool FULL = MODE == MODE_SUPPORT_FULL;
+  constexpr bool FULL = mode_keys(MODE);
   TableRef tr{reinterpret_cast<const int32_t*>(L.bits), nullptr, 0, 0, (int64_t)it.rs, (int64_t)it.d, nullptr,
-              nullptr, 0, 0, L.pfx, it.d <= max_keys ? L.cnt : nullptr};
+              nullptr, 0, 0, nullptr, L.pfx, it.d <= max_keys ? L.cnt : nullptr};
   if (it.len) wave_probe<MODE, TK_BITS, VAR_BASE>(A, tr, it.t0, it.q0, it.len, L.bm, hits, w0);
   if constexpr (FULL) {
     // the (b, k) credits of the work-group: one atomic per key that was hit
@@ -1045,10 +1096,12 @@ __device__ __forceinline__ void bits_probe(const Args& A, const BitsLds& L, cons
       for (uint32_t i = threadIdx.x; i < it.d; i += 64 * kWaves) {
         const uint32_t c = L.cnt[i];
         const uint64_t p = (uint64_t)it.rs + it.d - 1 - i;
-        if (c && p < (uint64_t)A.m) atomicAdd(&A.support[p], (int)c);
+        if (MODE == MODE_VERTEX && c) credit_vertex(A, (uint32_t)A.hcol[p], c);
+        else if (c && p < (uint64_t)A.m) atomicAdd(&A.support[p], (int)c);
       }
     }
   }
+  if constexpr (MODE == MODE_VERTEX) credit_row(A, it.b, hits);
 }
 
 // The groups [g, end) of one class's short rows (items: the first of them),
@@ -1097,7 +1150,7 @@ __device__ __forceinline__ unsigned long long bits_groups_hbm(const Args& A, con
   unsigned long long sum = 0;
   for (; g < end; ++g) {
     const CountItem it = items[(uint64_t)g * kWaves + wave];
-    TableRef tr{nullptr, nullptr, 0, 0, (int64_t)it.rs, (int64_t)it.d, nullptr, nullptr, 0, 0, nullptr, nullptr};
+    TableRef tr{nullptr, nullptr, 0, 0, (int64_t)it.rs, (int64_t)it.d, nullptr, nullptr, 0, 0, nullptr, nullptr, nullptr};
     uint32_t hits = 0;
     if (it.len)
       wave_probe<MODE, TK_GLOBAL16, VAR_BASE>(A, tr, it.t0, it.q0, it.len, bm, hits,
@@ -1189,7 +1242,7 @@ __global__ void k_zero_i32(int32_t* p, int64_t n) {
 }
 
 // launch names seen by the phase timer: "<mode>:<class>"
-const char* const kLaunchNames[4][NUM_CLASSES] = {
+const char* const kLaunchNames[5][NUM_CLASSES] = {
     {"count:pack_small", "count:pack_large", "count:wg_small", "count:wg_large", "count:wg_huge",
      "count:wg_giant", "count:global"},
     {"support_full:pack_small", "support_full:pack_large", "support_full:wg_small",
@@ -1198,10 +1251,14 @@ const char* const kLaunchNames[4][NUM_CLASSES] = {
      "support_oriented:wg_large", "support_oriented:wg_huge", "support_oriented:wg_giant",
      "support_oriented:global"},
     {"block:pack_small", "block:pack_large", "block:wg_small", "block:wg_large", "block:wg_huge",
-     "block:wg_giant", "block:global"}};
+     "block:wg_giant", "block:global"},
+    {"vertex:pack_small", "vertex:pack_large", "vertex:wg_small", "vertex:wg_large", "vertex:wg_huge",
+     "vertex:wg_giant", "vertex:global"}};
 
-const char* const kBitsNames[3] = {"count:short_items", "support_full:short_items", "support_oriented:short_items"};
-const char* const kPacks16Names[3] = {"count:short_packs", "support_full:short_packs", "support_oriented:short_packs"};
+const char* const kBitsNames[5] = {"count:short_items", "support_full:short_items", "support_oriented:short_items", "",
+                                   "vertex:short_items"};
+const char* const kPacks16Names[5] = {"count:short_packs", "support_full:short_packs", "support_oriented:short_packs", "",
+                                      "vertex:short_packs"};
 
 // Work-groups per launch of one class: a dispatch holds fewer than 2^32
 // work-items (a class of more groups, e.g. small wave items on a very large
@@ -1225,7 +1282,7 @@ void launch_bits(const WorkSet& w, const Args& A, hipStream_t st) {
   if (bundles == 0) return;
   const size_t lds = bits_lds_bytes(A.n, log2S, MODE);
   const uint32_t max_keys = bits_max_keys(log2S, MODE);
-  constexpr int OCC = MODE == MODE_SUPPORT_FULL ? kOccBitsFull : MODE == MODE_COUNT ? kOccBits : kOccBitsOriented;
+  constexpr int OCC = mode_keys(MODE) ? kOccBitsFull : MODE == MODE_COUNT ? kOccBits : kOccBitsOriented;
   TC_LAUNCH(kBitsNames[MODE], (k_count_bits<MODE, OCC>), dim3(bundles), dim3(64 * kWaves), lds, st, A, lists,
             max_keys);
 }
@@ -1244,7 +1301,7 @@ void launch_packs16(const WorkSet& w, const Args& A, hipStream_t st) {
   }
   const uint32_t packs = n[0] + n[1];
   if (packs == 0) return;
-  constexpr int OCC = MODE == MODE_SUPPORT_FULL ? 4 : kOccPacks16;
+  constexpr int OCC = mode_keys(MODE) ? 4 : kOccPacks16;
   const int waves = packs <= kPacks16Waves ? 16 : packs <= 2 * kPacks16Waves ? 8 : kWaves;
   const size_t lds = pack16_lds_bytes(slots, MODE, waves);
   auto* f = waves == 16 ? k_count_packs16<MODE, 4, 16> : waves == 8 ? k_count_packs16<MODE, 4, 8>
@@ -1311,7 +1368,7 @@ constexpr int64_t kSideMinProbes = (int64_t)1 << 24;
 
 template <int MODE, int VAR>
 void launch_mode(const WorkSet& w, const Args& A, hipStream_t st) {
-  constexpr bool VALS = MODE == MODE_SUPPORT_FULL;
+  constexpr bool VALS = mode_keys(MODE);
   const size_t mark_bytes = items_lds_bytes(-1, MODE);
   // the light classes go to the side stream when both sides have work
   bool light = false, heavy = false;
@@ -1439,30 +1496,30 @@ void launch_batch_mode(const Args* d_args, const BatchUnit* d_units, int64_t n_u
 }  // namespace
 
 size_t pack_lds_bytes(uint32_t slots, int mode) {
-  const size_t vals = mode == MODE_SUPPORT_FULL ? 2 : 1;
+  const size_t vals = mode_keys(mode) ? 2 : 1;
   return sizeof(int32_t) * ((size_t)pack_head_words(mode, kWaves) + (size_t)slots * vals);
 }
 
 size_t items_lds_bytes(int log2S, int mode) {
-  const size_t vals = mode == MODE_SUPPORT_FULL ? 2 : 1;
+  const size_t vals = mode_keys(mode) ? 2 : 1;
   return sizeof(int32_t) * ((size_t)kWavesBig * wave_words(mode) + (log2S < 0 ? 0 : ((size_t)1 << log2S) * vals));
 }
 
 size_t pack16_lds_bytes(uint32_t slots, int mode, int waves) {
   return sizeof(int32_t) * ((size_t)pack_head_words(mode, waves) + slots / 2 +
-                            (mode == MODE_SUPPORT_FULL ? (size_t)slots : 0));
+                            (mode_keys(mode) ? (size_t)slots : 0));
 }
 
 // Hit counters of a bitmap work-group (FULL): one per key of the class's
 // longest row, as far as its 32-bit table would fit LDS.
 uint32_t bits_max_keys(int log2S, int mode) {
-  return mode == MODE_SUPPORT_FULL && log2S <= kMaxLog2S ? 1u << (log2S <= 12 ? log2S - 2 : log2S - 1) : 0u;
+  return mode_keys(mode) && log2S <= kMaxLog2S ? 1u << (log2S <= 12 ? log2S - 2 : log2S - 1) : 0u;
 }
 
 size_t bits_lds_bytes(int64_t n, int log2S, int mode) {
   const size_t words = bitmap_words((int32_t)n);
   return sizeof(int32_t) * ((size_t)kWaves * wave_words(mode) + words + bits_max_keys(log2S, mode)) +
-         (mode == MODE_SUPPORT_FULL ? sizeof(uint16_t) * ((words + 1) & ~(size_t)1) : 0);
+         (mode_keys(mode) ? sizeof(uint16_t) * ((words + 1) & ~(size_t)1) : 0);
 }
 
 void launch_batch(CountMode mode, const CountArgs* d_args, const BatchUnit* d_units, int64_t n_units,
@@ -1491,7 +1548,7 @@ void launch_batch(CountMode mode, const CountArgs* d_args, const BatchUnit* d_un
 }
 
 void launch_count(const CountView& v, CountMode mode, int64_t* d_count, int32_t* d_support,
-                  int64_t* d_per_shift, hipStream_t st) {
+                  int64_t* d_per_shift, hipStream_t st, const VertexCounts* vc) {
   const WorkSet& w = *v.w;
   if (d_count) TC_LAUNCH("zero_i64", k_zero_i64, dim3(1), dim3(1), 0, st, d_count);
   if ((mode == MODE_SUPPORT_FULL || mode == MODE_SUPPORT_ORIENTED) && v.pm > 0)
@@ -1508,7 +1565,9 @@ void launch_count(const CountView& v, CountMode mode, int64_t* d_count, int32_t*
   TC_REQUIRE(w.b16 >= w.nrows || v.pcol16 != nullptr, TC_EDEVICE, "launch_count: no short columns");
   Args A{v.hrow_ptr, v.hcol, v.pcol, w.tstart, w.tprefix, w.tbeg, w.tend, w.n_tasks, (uint32_t)v.pm,
          v.pcol16, (int32_t)w.nrows, reinterpret_cast<unsigned long long*>(d_count), d_support,
-         reinterpret_cast<unsigned long long*>(d_per_shift), v.q, v.xy};
+         reinterpret_cast<unsigned long long*>(d_per_shift), v.q, v.xy, vc ? vc->erow : nullptr,
+         vc ? vc->count : nullptr};
+  TC_REQUIRE(mode != MODE_VERTEX || (vc && vc->erow && vc->count), TC_EINVAL, "launch_count: no vertex counters");
   TC_REQUIRE(v.hash == 0 || mode == MODE_COUNT, TC_EINVAL, "launch_count: multiplicative hashing counts only");
   TC_REQUIRE(!(wide && v.hash), TC_EOVERFLOW, "launch_count: multiplicative hashing below 2^30 edges only");
   switch (mode) {
@@ -1526,6 +1585,10 @@ void launch_count(const CountView& v, CountMode mode, int64_t* d_count, int32_t*
       else launch_mode<MODE_SUPPORT_ORIENTED, VAR_BASE>(w, A, st);
       break;
     case MODE_BLOCK: launch_mode<MODE_BLOCK, VAR_BASE>(w, A, st); break;
+    case MODE_VERTEX:
+      if (wide) launch_mode<MODE_VERTEX, VAR_WIDE>(w, A, st);
+      else launch_mode<MODE_VERTEX, VAR_BASE>(w, A, st);
+      break;
   }
 }
 

@@ -315,6 +315,7 @@ struct Graph {
   int64_t* row_ptr = nullptr;  // n + 1, U rows
   int32_t* col = nullptr;      // m, rows sorted ascending
   int32_t* perm = nullptr;     // n, perm[original id] = rank
+  uint32_t* deg = nullptr;     // n, degree of every rank
   uint16_t* col16 = nullptr;   // m (+ padding), short columns
   WorkSet w;
 };
@@ -348,7 +349,8 @@ enum CountMode : int {
   MODE_COUNT = 0,
   MODE_SUPPORT_FULL = 1,
   MODE_SUPPORT_ORIENTED = 2,
-  MODE_BLOCK = 3  // count plus per-shift split of one rank's block (Eq. 5)
+  MODE_BLOCK = 3,  // count plus per-shift split of one rank's block (Eq. 5)
+  MODE_VERTEX = 4  // triangles through every vertex (rank space)
 };
 
 // What the count kernels read: the hash side (rows b, their sorted entries),
@@ -364,8 +366,15 @@ struct CountView {
   const uint16_t* pcol16 = nullptr;  // short columns of the probe side (w->b16 < w->nrows)
 };
 
+// MODE_VERTEX: the row of every probe-side entry and the counters of all
+// vertices, which the caller has cleared.
+struct VertexCounts {
+  const uint32_t* erow;
+  unsigned long long* count;
+};
+
 void launch_count(const CountView& v, CountMode mode, int64_t* d_count, int32_t* d_support,
-                  int64_t* d_per_shift, hipStream_t stream);
+                  int64_t* d_per_shift, hipStream_t stream, const VertexCounts* vc = nullptr);
 
 // Kernel arguments of the count kernels (one hashed side, one probe side and
 // the task arrays of a work set).
@@ -385,6 +394,8 @@ struct CountArgs {
   int32_t* support;
   unsigned long long* per_shift;  // MODE_BLOCK: q counters
   int32_t q, xy;                  // MODE_BLOCK: grid size, (x + y) % q
+  const uint32_t* __restrict__ erow;  // MODE_VERTEX: row of every entry of col
+  unsigned long long* vcount;         // MODE_VERTEX: n counters
 };
 
 // ---- batched persistent count (tc_count.hip kernel, tc_batch.cpp plan) -------

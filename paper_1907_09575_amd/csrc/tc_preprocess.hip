@@ -363,9 +363,13 @@ __global__ void k_rank_keys(const uint32_t* __restrict__ deg, int64_t n, int s,
   if (v < n) rk[v] = ((uint64_t)deg[v] << s) | (uint64_t)v;
 }
 
-__global__ void k_perm(const uint64_t* __restrict__ rk, int64_t n, int s, int32_t* __restrict__ perm) {
+__global__ void k_perm(const uint64_t* __restrict__ rk, int64_t n, int s, int32_t* __restrict__ perm,
+                       uint32_t* __restrict__ deg) {
   int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < n) perm[rk[r] & ((1ull << s) - 1)] = (int32_t)r;
+  if (r >= n) return;
+  const uint64_t k = rk[r];
+  perm[k & ((1ull << s) - 1)] = (int32_t)r;
+  deg[r] = (uint32_t)(k >> s);
 }
 
 // Orientation in two steps, so that no rank is read at random from the
@@ -1076,6 +1080,7 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
 
   // ---- 3: degree order ---------------------------------------------------
   g->perm = g->owned.alloc<int32_t>(n);
+  g->deg = g->owned.alloc<uint32_t>(n);
   const uint32_t* hi_starts = dh + 256 * (hpasses - 1);  // valid once m > 0
   {
     DevBuf ra(sizeof(uint64_t) * (size_t)n), rb(sizeof(uint64_t) * (size_t)n);
@@ -1129,7 +1134,7 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
     bool alt = radix_sort<uint64_t, NoVal>(ra.as<uint64_t>(), rb.as<uint64_t>(), nullptr, nullptr, n,
                                            s, 2 * s, st, "rank");
     TC_LAUNCH("perm", k_perm, dim3(grid_for(n)), dim3(kT), 0, st,
-                       alt ? rb.as<uint64_t>() : ra.as<uint64_t>(), n, s, g->perm);
+                       alt ? rb.as<uint64_t>() : ra.as<uint64_t>(), n, s, g->perm, g->deg);
     TC_HIP(hipGetLastError());
   }
 
@@ -1292,6 +1297,7 @@ Graph* build_variant(const Graph& base, int flags, const WorkParams& wp, hipStre
   g->col = base.col;
   g->perm = base.perm;
   g->col16 = base.col16;
+  g->deg = base.deg;
   g->variant = flags;
   g->hash = (flags & TC_VARIANT_MUL_HASH) ? 1 : 0;
   g->base = &base;
@@ -1303,7 +1309,7 @@ Graph* build_variant(const Graph& base, int flags, const WorkParams& wp, hipStre
   TaskLists tl;
   if (m > 0) {
     DevBuf erow(sizeof(uint32_t) * (size_t)m);
-    TC_LAUNCH("entry_rows", k_entry_rows, dim3(wave_grid(n)), dim3(kT), 0, st, g->row_ptr, n,
+    TC_LAUNCH("entry_rows", k_entry_rows, dim3(entry_rows_grid(n)), dim3(kT), 0, st, g->row_ptr, n,
               erow.as<uint32_t>());
     DevBuf tk, tv;
     VariantTaskPred vp{g->row_ptr, g->col, erow.as<uint32_t>(), ijk, no_dcsr, nullptr, nullptr};

@@ -45,6 +45,7 @@ def check(tc, s, d, n):
         for mode in (oracle.MODE_FULL, oracle.MODE_ORIENTED):
             want = oracle.support(U, mode)[1]
             assert np.array_equal(tc.tc_edge_support(h, mode)[0].cpu().numpy(), want), mode
+        assert np.array_equal(tc.tc_vertex_triangles(h).cpu().numpy(), oracle.vertex_triangles(U))
     for tuning in (None, {"lds_cap_log2": 6}):
         plan = tc.tc_batch_create(handles, tuning=tuning)
         assert tc.tc_batch_count(plan).tolist() == [T] * len(handles)
@@ -84,6 +85,8 @@ def test_rows_longer_than_the_hit_counters(tc):
     assert int(tc.tc_count(g).item()) == comb(n, 3)
     sup, _ = tc.tc_edge_support(g, tc.TC_SUPPORT_FULL)
     assert int(sup.min().item()) == int(sup.max().item()) == n - 2
+    t = tc.tc_vertex_triangles(g)
+    assert int(t.min().item()) == int(t.max().item()) == comb(n - 1, 2)
 
 
 @pytest.mark.parametrize("case", ["star", "path", "one_edge", "K3", "K5_in_65540"])
