@@ -215,7 +215,8 @@ tc_status tc_transitivity(const tc_graph* g, double* out, void* stream);
  * Computed by peeling from the TC_SUPPORT_FULL support: each round removes
  * the edges whose support in the remaining graph is below k - 2 and takes
  * the triangles they close out of their other edges' support. Synchronises
- * `stream` once per round; allocates temporaries (about 28 m + 8 n bytes).
+ * `stream` about once per 32 rounds; allocates temporaries (about 44 m + 8 n
+ * bytes, up to 128 m more where most edges join two vertices of high degree).
  * TC_EOVERFLOW for 2^31 or more edges.
  */
 tc_status tc_truss(const tc_graph* g, int32_t* d_tau, int32_t* kmax, void* stream);

@@ -26,6 +26,7 @@
 // round is taken out once, by its removed edge of smallest id; a triangle
 // with an edge removed in an earlier round is already gone.
 #include <algorithm>
+#include <cstring>
 
 #include "tc_prims.h"
 
@@ -161,17 +162,35 @@ void vertex_counts(const Graph& g, int64_t* d_tri, double* d_cc, int64_t* d_sums
 
 // ---- k-truss ---------------------------------------------------------------------
 
+constexpr unsigned kPeelGrid = 2048;    // work-groups of a round: those resident at 8 waves per SIMD
 constexpr int32_t kAlive = 0x7FFFFFFF;  // state of an edge not yet removed (else: its round)
 
-// Alive edges whose support is below lim (the round's removals).
-struct FrontierPred {
-  const int32_t* state;
-  const int32_t* sup;
-  int32_t lim;
-  int32_t* out;
-  struct Item {};
-  __device__ bool operator()(int64_t i, Item&) const { return state[i] == kAlive && sup[i] < lim; }
-  __device__ void emit(int64_t i, const Item&, uint32_t pos) const { out[pos] = (int32_t)i; }
+// A removed edge's triangles are found by walking the neighbourhood of its
+// endpoint of smaller degree d, cut into work entries of walk_chunk(d)
+// neighbours (one wave each), at most 8 per edge: the longest walk of a round
+// would otherwise be one wave's.
+__host__ __device__ inline uint32_t walk_chunk(uint32_t d) {
+  const uint32_t c = ((d + 7) / 8 + 63) & ~63u;
+  return c < 256 ? 256 : c;
+}
+__device__ __forceinline__ uint32_t walk_entries(uint32_t d) {
+  const uint32_t c = walk_chunk(d);
+  return d ? (d + c - 1) / c : 1;
+}
+
+// The peel's arrays. A work entry is an edge id and, above it, its chunk.
+// Rounds are numbered by the launches of k_truss_peel; round i takes the
+// cnt[i] entries of list i % 2 and appends the edges that its triangles
+// bring below lim to the other list. No list is ever compacted from all
+// edges but at a new level.
+struct TrussArrays {
+  const uint32_t* erow;
+  const int32_t* col;
+  const uint32_t* deg;
+  int32_t* state;  // kAlive, or the round that removes the edge
+  int32_t* sup;
+  int32_t* tau;
+  uint64_t* list[2];
 };
 
 __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
@@ -179,24 +198,118 @@ __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
   if (i < n) p[i] = v;
 }
 
-// Smallest support among alive edges (for the next level with removals).
-__global__ __launch_bounds__(256) void k_min_alive(const int32_t* __restrict__ state, const int32_t* __restrict__ sup,
-                                                   int64_t m, int* __restrict__ out) {
-  int v = kAlive;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x)
-    if (state[i] == kAlive) v = min(v, sup[i]);
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v = min(v, __shfl_xor(v, d, 64));
-  if (lane_id() == 0 && v != kAlive) atomicMin(out, v);
+__device__ __forceinline__ uint32_t min_degree(const TrussArrays& A, int32_t e) {
+  return min(A.deg[A.erow[e]], A.deg[A.col[e]]);
 }
 
-__global__ void k_truss_mark(const int32_t* __restrict__ F, int64_t nF, int32_t round, int32_t tau_val,
-                             int32_t* __restrict__ state, int32_t* __restrict__ tau) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nF) return;
-  const int32_t e = F[i];
-  state[e] = round;
-  tau[e] = tau_val;
+// Work entries of all edges together: what a list must hold.
+__global__ __launch_bounds__(256) void k_truss_entries(TrussArrays A, int64_t m, unsigned long long* __restrict__ out) {
+  __shared__ unsigned long long s_w[4];
+  unsigned long long c = 0;
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x)
+    c += walk_entries(min_degree(A, (int32_t)e));
+  c = wave_sum(c);
+  if (lane_id() == 0) s_w[threadIdx.x >> 6] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) atomicAdd(out, s_w[0] + s_w[1] + s_w[2] + s_w[3]);
+}
+
+// A wave's edges for the next frontier, kept in LDS until there are enough for
+// one atomic on the list's counter (an atomic per 64 edges serialises on it:
+// 12 ns each, 0.76 ms for the first level of 4M edges).
+constexpr uint32_t kPushQueue = 256;
+struct PushQueue {
+  int32_t* q;   // kPushQueue entries of this wave
+  uint32_t n;   // (uniform)
+  int32_t round, tau;
+  uint64_t* list;
+  uint32_t* cnt;
+};
+
+// Removes the queued edges in round Q.round (trussness Q.tau) and appends
+// their work entries to Q.list.
+__device__ __forceinline__ void truss_flush(const TrussArrays& A, PushQueue& Q) {
+  if (Q.n == 0) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  const int lane = lane_id();
+  constexpr int kQ = kPushQueue / 64;
+  uint32_t n[kQ], mine = 0;
+#pragma unroll
+  for (int j = 0; j < kQ; ++j) {
+    const uint32_t i = 64u * j + (uint32_t)lane;
+    n[j] = i < Q.n ? walk_entries(min_degree(A, Q.q[i])) : 0;
+    mine += n[j];
+  }
+  const uint32_t inc = wave_incl_scan(mine);
+  uint32_t base = 0;
+  if (lane == 63) base = atomicAdd(Q.cnt, inc);
+  base = (uint32_t)__shfl((int)base, 63, 64) + inc - mine;
+#pragma unroll
+  for (int j = 0; j < kQ; ++j) {
+    if (n[j] == 0) continue;
+    const int32_t e = Q.q[64 * j + lane];
+    A.state[e] = Q.round;
+    A.tau[e] = Q.tau;
+    for (uint32_t c = 0; c < n[j]; ++c) Q.list[base++] = (uint64_t)(uint32_t)e | ((uint64_t)c << 32);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  Q.n = 0;
+}
+
+// Queues the edge e of the lanes with `take` set.
+__device__ __forceinline__ void truss_push(const TrussArrays& A, PushQueue& Q, bool take, int32_t e) {
+  const uint64_t mask = __ballot(take);
+  if (mask == 0) return;
+  if (take)
+    Q.q[Q.n + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0))] = e;
+  Q.n += (uint32_t)__popcll(mask);
+  if (Q.n > kPushQueue - 64) truss_flush(A, Q);
+}
+
+// A batch of rounds, b: when the frontier cnt[i] of its first round i is
+// empty, k_truss_min finds the smallest support left, and k_truss_level makes
+// the edges that have it the frontier of the next level (lim = it + 1, the
+// trussness of what the level removes). Otherwise both do nothing and the
+// level goes on. mins[b]: kAlive and no edge left end the peel.
+__global__ __launch_bounds__(256) void k_truss_min(TrussArrays A, int64_t m, const uint32_t* __restrict__ cnt,
+                                                   int* __restrict__ mn, int* __restrict__ fresh) {
+  if (*cnt != 0) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *fresh = 1;
+  __shared__ int s_v[4];
+  int v = kAlive;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
+    const int s = A.sup[i];
+    v = A.state[i] == kAlive ? min(v, s) : v;
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) v = min(v, __shfl_xor(v, d, 64));
+  if (lane_id() == 0) s_v[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    v = min(min(s_v[0], s_v[1]), min(s_v[2], s_v[3]));
+    if (v != kAlive) atomicMin(mn, v);
+  }
+}
+
+// (lim, lim_out: the level's bound before and after)
+__global__ __launch_bounds__(256) void k_truss_level(TrussArrays A, int64_t m, const int* __restrict__ fresh,
+                                                     const int* __restrict__ mn, const int* __restrict__ lim,
+                                                     int* __restrict__ lim_out, int32_t round, uint32_t* __restrict__ cnt) {
+  const bool go = *fresh != 0 && *mn != kAlive;
+  const int bound = go ? *mn + 1 : *lim;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *lim_out = bound;
+  if (!go) return;
+  __shared__ int32_t s_q[4][kPushQueue];
+  PushQueue Q{s_q[threadIdx.x >> 6], 0, round, bound + 1, A.list[round & 1], cnt};
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x; i0 < m; i0 += stride) {  // (uniform)
+    const int64_t i = i0 + threadIdx.x;
+    const bool take = i < m && A.state[i] == kAlive && A.sup[i] < bound;
+    truss_push(A, Q, take, (int32_t)i);
+  }
+  truss_flush(A, Q);
 }
 
 // N(v) = L_v followed by U_v (ascending), with the U position of each edge.
@@ -208,74 +321,82 @@ struct FullAdj {
   const int32_t* leid;
 };
 
-// First position in the sorted list a[0, len) holding w, or -1.
-__device__ __forceinline__ int64_t find_sorted(const int32_t* __restrict__ a, int64_t len, int32_t w) {
-  int64_t lo = 0, hi = len;
+// Position in the sorted list a[0, len) holding w, or -1 (distinct entries,
+// len < 2^31).
+__device__ __forceinline__ int32_t find_sorted(const int32_t* __restrict__ a, uint32_t len, int32_t w) {
+  uint32_t lo = 0, hi = len;
   while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
+    const uint32_t mid = (lo + hi) >> 1;
     if (a[mid] < w) lo = mid + 1;
     else hi = mid;
   }
-  return (lo < len && a[lo] == w) ? lo : -1;
+  return lo < len && a[lo] == w ? (int32_t)lo : -1;
 }
 
-// One wave per removed edge e = (a, b) of this round: the lanes walk the
-// neighbourhood of the endpoint of smaller degree and look every w up in the
-// other's (binary search in its L or U part); each triangle (e, e1, e2) still
-// whole before this round, and whose removed edge of smallest id is e, takes
-// one from the support of each of e1, e2 still alive.
-__device__ void truss_peel_one(const FullAdj& A, const uint32_t* __restrict__ erow,
-                               const int32_t* __restrict__ F, int64_t f, int32_t round,
-                               const int32_t* __restrict__ state, int32_t* __restrict__ sup) {
+// One wave per work entry of this round: edge e = (a, b), a chunk of the
+// neighbourhood of the endpoint of smaller degree, whose every w is looked up
+// in the other's (binary search in its L or U part); each triangle (e, e1, e2)
+// still whole before this round, and whose removed edge of smallest id is e,
+// takes one from the support of each of e1, e2 that stays, and an edge that
+// this brings below lim goes to the next round's list (the one subtraction
+// that crosses lim sees it). Edges marked for the next round count as staying.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_truss_peel(TrussArrays T, FullAdj A, int32_t round,
+                                                    const int* __restrict__ limp, const uint32_t* __restrict__ cnt,
+                                                    uint32_t* __restrict__ cnt_next) {
+  const uint32_t nF = *cnt;
+  const uint64_t* __restrict__ F = T.list[round & 1];
+  const int lim = *limp;
+  __shared__ int32_t s_q[4][kPushQueue];
+  PushQueue Q{s_q[threadIdx.x >> 6], 0, round + 1, lim + 1, T.list[(round + 1) & 1], cnt_next};
   const int lane = lane_id();
-  const int32_t e = F[f];
-  const int32_t a = (int32_t)erow[e], b = A.col[e];
-  const int64_t la = A.lptr[a + 1] - A.lptr[a], ua = A.row_ptr[a + 1] - A.row_ptr[a];
-  const int64_t lb = A.lptr[b + 1] - A.lptr[b], ub = A.row_ptr[b + 1] - A.row_ptr[b];
-  const bool a_small = la + ua <= lb + ub;
-  const int32_t x = a_small ? a : b, y = a_small ? b : a;
-  const int64_t lx = a_small ? la : lb, dx = a_small ? la + ua : lb + ub;
-  const int64_t ly = a_small ? lb : la, uy = a_small ? ub : ua;
-  for (int64_t i = lane; i < dx; i += 64) {
-    const bool in_l = i < lx;
-    const int32_t w = in_l ? A.lnbr[A.lptr[x] + i] : A.col[A.row_ptr[x] + (i - lx)];
-    if (w == y) continue;
-    int32_t e2;
-    if (w < y) {
-      const int64_t j = find_sorted(A.lnbr + A.lptr[y], ly, w);
-      if (j < 0) continue;
-      e2 = A.leid[A.lptr[y] + j];
-    } else {
-      const int64_t j = find_sorted(A.col + A.row_ptr[y], uy, w);
-      if (j < 0) continue;
-      e2 = (int32_t)(A.row_ptr[y] + j);
+  const uint32_t stride = gridDim.x * (blockDim.x / 64);
+  for (uint32_t f = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6); f < nF; f += stride) {
+    const uint64_t w0 = F[f];
+    const int32_t e = (int32_t)(uint32_t)w0;
+    const int32_t a = (int32_t)T.erow[e], b = A.col[e];
+    const int64_t lpa = A.lptr[a], lpb = A.lptr[b], rpa = A.row_ptr[a], rpb = A.row_ptr[b];
+    const uint32_t la = (uint32_t)(A.lptr[a + 1] - lpa), lb = (uint32_t)(A.lptr[b + 1] - lpb);
+    const uint32_t da = T.deg[a], db = T.deg[b];
+    const bool a_small = da <= db;
+    const int32_t y = a_small ? b : a;
+    const uint32_t lx = a_small ? la : lb, dx = a_small ? da : db;
+    const uint32_t ly = a_small ? lb : la, uy = (a_small ? db : da) - ly;
+    const int64_t lpx = a_small ? lpa : lpb, rpx = (a_small ? rpa : rpb) - (int64_t)lx;
+    const int64_t lpy = a_small ? lpb : lpa, rpy = a_small ? rpb : rpa;
+    const uint32_t c = walk_chunk(dx), first = (uint32_t)(w0 >> 32) * c;
+    const uint32_t i_end = min(dx, first + c);
+    for (uint32_t i0 = first; i0 < i_end; i0 += 64) {  // (uniform across the wave)
+      const uint32_t i = i0 + (uint32_t)lane;
+      int32_t e1 = -1, e2 = -1;
+      if (i < i_end) {
+        const bool in_l = i < lx;  // (entry i of N(x): L_x, then U_x)
+        const int32_t w = in_l ? A.lnbr[lpx + i] : A.col[rpx + i];
+        if (w < y) {
+          const int32_t j = find_sorted(A.lnbr + lpy, ly, w);
+          if (j >= 0) e2 = A.leid[lpy + j];
+        } else if (w > y) {
+          const int32_t j = find_sorted(A.col + rpy, uy, w);
+          if (j >= 0) e2 = (int32_t)(rpy + j);
+        }
+        if (e2 >= 0) e1 = in_l ? A.leid[lpx + i] : (int32_t)(rpx + i);
+      }
+      bool t1 = false, t2 = false;
+      if (e1 >= 0) {
+        const int32_t s1 = T.state[e1], s2 = T.state[e2];
+        const bool whole = s1 >= round && s2 >= round;  // no edge went in an earlier round
+        int32_t owner = e;
+        if (s1 == round && e1 < owner) owner = e1;
+        if (s2 == round && e2 < owner) owner = e2;
+        if (whole && owner == e) {
+          if (s1 > round) t1 = atomicSub(&T.sup[e1], 1) == lim;
+          if (s2 > round) t2 = atomicSub(&T.sup[e2], 1) == lim;
+        }
+      }
+      truss_push(T, Q, t1, e1);
+      truss_push(T, Q, t2, e2);
     }
-    const int32_t e1 = in_l ? A.leid[A.lptr[x] + i] : (int32_t)(A.row_ptr[x] + (i - lx));
-    const int32_t s1 = state[e1], s2 = state[e2];
-    if (s1 < round || s2 < round) continue;  // an edge went in an earlier round
-    int32_t owner = e;
-    if (s1 == round && e1 < owner) owner = e1;
-    if (s2 == round && e2 < owner) owner = e2;
-    if (owner != e) continue;
-    if (s1 == kAlive) atomicSub(&sup[e1], 1);
-    if (s2 == kAlive) atomicSub(&sup[e2], 1);
   }
-}
-
-__global__ __launch_bounds__(256) void k_truss_peel(FullAdj A, const uint32_t* __restrict__ erow,
-                                                    const int32_t* __restrict__ F, int64_t nF, int32_t round,
-                                                    const int32_t* __restrict__ state, int32_t* __restrict__ sup) {
-  const int64_t stride = (int64_t)gridDim.x * (blockDim.x / 64);
-  for (int64_t f = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6); f < nF; f += stride)
-    truss_peel_one(A, erow, F, f, round, state, sup);
-}
-
-template <class T>
-T read_scalar(const T* d, hipStream_t st) {
-  T h{};
-  TC_HIP(hipMemcpyAsync(&h, d, sizeof(T), hipMemcpyDeviceToHost, st));
-  TC_HIP(hipStreamSynchronize(st));
-  return h;
+  truss_flush(T, Q);
 }
 
 int32_t truss(const Graph& g, int32_t* d_tau, hipStream_t st) {
@@ -284,45 +405,64 @@ int32_t truss(const Graph& g, int32_t* d_tau, hipStream_t st) {
   const int64_t m = g.m;
   if (m == 0) return 0;
   TC_REQUIRE(m < ((int64_t)1 << 31), TC_EOVERFLOW, "tc_truss: 2^31 or more edges");
-  DevBuf sup(sizeof(int32_t) * (size_t)m), state(sizeof(int32_t) * (size_t)m), F(sizeof(int32_t) * (size_t)m);
-  DevBuf dmin(sizeof(int));
+  DevBuf sup(sizeof(int32_t) * (size_t)m), state(sizeof(int32_t) * (size_t)m);
   launch_count(graph_view(g), MODE_SUPPORT_FULL, nullptr, sup.as<int32_t>(), nullptr, st);
   Lower L;
   build_lower(L, g, st);
   TC_LAUNCH("truss_fill", k_fill_i32, dim3(grid_threads(m)), dim3(kAT), 0, st, state.as<int32_t>(), m, kAlive);
-  TC_LAUNCH("truss_fill", k_fill_i32, dim3(grid_threads(m)), dim3(kAT), 0, st, d_tau, m, 0);
-  check_sorts(st);
+  TrussArrays T{L.erow.as<uint32_t>(), g.col, g.deg, state.as<int32_t>(), sup.as<int32_t>(), d_tau, {}};
+  const unsigned sweep = (unsigned)std::min<int64_t>(2048, grid_threads(m));  // (whole-array kernels)
+  DevBuf total(sizeof(unsigned long long));
+  TC_HIP(hipMemsetAsync(total.p, 0, total.bytes, st));
+  TC_LAUNCH("truss_entries", k_truss_entries, dim3(sweep), dim3(kAT), 0, st, T, m, total.as<unsigned long long>());
+  unsigned long long entries = 0;
+  TC_HIP(hipMemcpyAsync(&entries, total.p, sizeof(entries), hipMemcpyDeviceToHost, st));
+  check_sorts(st);  // (synchronises st)
+  TC_REQUIRE(entries < 0xFFFFFFFFull, TC_EOVERFLOW, "tc_truss: 2^32 or more work entries");
+  DevBuf l0(sizeof(uint64_t) * (size_t)entries), l1(sizeof(uint64_t) * (size_t)entries);
+  T.list[0] = l0.as<uint64_t>();
+  T.list[1] = l1.as<uint64_t>();
   const FullAdj A{g.row_ptr, g.col, L.ptr.as<int64_t>(), L.nbr.as<int32_t>(), L.eid.as<int32_t>()};
-  int64_t alive = m;
-  int64_t k = 3;
-  int32_t round = 0, kmax = 0;
-  while (alive > 0) {
-    FrontierPred fp{state.as<int32_t>(), sup.as<int32_t>(), (int32_t)(k - 2), F.as<int32_t>()};
-    const int64_t nF = compact("truss_frontier", m, fp, [](int64_t, FrontierPred&) {}, st);
-    if (nF == 0) {
-      // no alive edge is below k - 2: the next level that removes one
-      const int big = kAlive;
-      TC_HIP(hipMemcpyAsync(dmin.p, &big, sizeof(int), hipMemcpyHostToDevice, st));
-      TC_LAUNCH("truss_min", k_min_alive, dim3((unsigned)std::min<int64_t>(1024, grid_threads(m))), dim3(kAT), 0,
-                st, state.as<int32_t>(), sup.as<int32_t>(), m, dmin.as<int>());
-      const int mn = read_scalar(dmin.as<int>(), st);
-      TC_REQUIRE(mn != kAlive && (int64_t)mn + 3 > k, TC_EDEVICE, "tc_truss: no level removes an edge");
-      k = (int64_t)mn + 3;
-      continue;
+
+  // Batches of kRounds rounds, kBatches to a host read-back. Everything a
+  // round decides (its frontier, the level) stays on the device; a round
+  // with nothing to do costs its launch.
+  constexpr int kRounds = 8, kBatches = 4;
+  struct Ctl {  // of one read-back
+    int mn[kBatches], fresh[kBatches];
+    int lim[kBatches + 1];
+    uint32_t cnt[kBatches * kRounds + 1];
+  };
+  DevBuf ctl(sizeof(Ctl));
+  Ctl h, init;
+  std::memset(&init, 0, sizeof(init));
+  for (int& v : init.mn) v = kAlive;
+  int32_t round = 0;
+  for (;;) {
+    TC_REQUIRE(round < kAlive - 2 * kBatches * kRounds, TC_EOVERFLOW, "tc_truss: too many rounds");
+    TC_HIP(hipMemcpyAsync(ctl.p, &init, sizeof(Ctl), hipMemcpyHostToDevice, st));
+    Ctl* d = ctl.as<Ctl>();
+    for (int b = 0; b < kBatches; ++b) {
+      TC_LAUNCH("truss_min", k_truss_min, dim3(sweep), dim3(kAT), 0, st, T, m, &d->cnt[b * kRounds], &d->mn[b],
+                &d->fresh[b]);
+      TC_LAUNCH("truss_level", k_truss_level, dim3(sweep), dim3(kAT), 0, st, T, m, &d->fresh[b], &d->mn[b],
+                &d->lim[b], &d->lim[b + 1], round, &d->cnt[b * kRounds]);
+      for (int r = 0; r < kRounds; ++r, ++round)
+        TC_LAUNCH("truss_peel", k_truss_peel, dim3(kPeelGrid), dim3(kAT), 0, st, T, A, round, &d->lim[b + 1],
+                  &d->cnt[b * kRounds + r], &d->cnt[b * kRounds + r + 1]);
     }
-    TC_REQUIRE(round < kAlive - 1, TC_EOVERFLOW, "tc_truss: too many rounds");
-    TC_LAUNCH("truss_mark", k_truss_mark, dim3(grid_threads(nF)), dim3(kAT), 0, st, F.as<int32_t>(), nF, round,
-              (int32_t)(k - 1), state.as<int32_t>(), d_tau);
-    TC_LAUNCH("truss_peel", k_truss_peel, dim3(grid_waves(nF)), dim3(kAT), 0, st, A, L.erow.as<uint32_t>(),
-              F.as<int32_t>(), nF, round, state.as<int32_t>(), sup.as<int32_t>());
     TC_HIP(hipGetLastError());
-    kmax = (int32_t)(k - 1);
-    alive -= nF;
-    ++round;
+    TC_HIP(hipMemcpyAsync(&h, ctl.p, sizeof(Ctl), hipMemcpyDeviceToHost, st));
+    TC_HIP(hipStreamSynchronize(st));
+    // (a level that found no edge alive ends the peel)
+    bool done = false;
+    for (int b = 0; b < kBatches; ++b) done = done || (h.fresh[b] && h.mn[b] == kAlive);
+    init.lim[0] = h.lim[kBatches];
+    init.cnt[0] = h.cnt[kBatches * kRounds];
+    if (done) break;
   }
-  TC_HIP(hipStreamSynchronize(st));
   note_use(g, st);
-  return kmax;
+  return init.lim[0] + 1;  // the last level's trussness
 }
 
 template <class F>
