@@ -155,16 +155,12 @@ __host__ __device__ constexpr int class_waves(int c) {
 // rows of up to 8192 keys stay in LDS); at least 64.
 __host__ __device__ inline int table_log2(int64_t d) {
   const int64_t want = d <= 2048 ? 4 * d : 2 * d;
-  int l = 6;
-  while ((1ll << l) < want) ++l;
-  return l;
+  return want <= 64 ? 6 : 64 - __builtin_clzll((unsigned long long)(want - 1));
 }
 
 // Packs of light rows give each row its own table, >= 4 d slots, at least 16.
 __host__ __device__ inline int pack_table_log2(int64_t d) {
-  int l = 4;
-  while ((1ll << l) < 4 * d) ++l;
-  return l;
+  return d <= 4 ? 4 : 64 - __builtin_clzll((unsigned long long)(4 * d - 1));
 }
 
 // ---- device memory (tc_alloc.cpp) ------------------------------------------
@@ -465,7 +461,7 @@ uint32_t bits_max_keys(int log2S, int mode);
 // Slots per pack of short rows: two for each of the pack_slots threshold (they
 // are half as wide), as far as FULL support's value words leave room in LDS
 // (six bytes a slot); a pack's tables take one row's more.
-inline uint32_t short_pack_slots(uint32_t pack_slots) { return pack_slots < 10240 ? 2 * pack_slots : 20480; }
+__host__ __device__ inline uint32_t short_pack_slots(uint32_t pack_slots) { return pack_slots < 10240 ? 2 * pack_slots : 20480; }
 inline uint32_t pack16_slots(uint32_t pack_slots, int log2S) { return short_pack_slots(pack_slots) + (1u << log2S); }
 // Words of the bitmap over a short row's column distances, [0, min(n, kShortSpan)].
 __host__ __device__ inline uint32_t bitmap_words(int32_t n) {

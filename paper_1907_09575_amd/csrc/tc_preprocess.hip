@@ -880,9 +880,10 @@ constexpr uint64_t kShortHeavyMin = 2048;
 // that the GPU holds at once without one each, and no more than 256K, above
 // which the last ones show (scale 22, 7.2G probes: 2662 us in 16384 bundles,
 // 2586 us in 32768).
-inline uint64_t bundle_weight(uint64_t W) {
-  const uint64_t least = std::max<uint64_t>(4096, std::min<uint64_t>(24 << 10, W / 2048));
-  return std::min<uint64_t>(256 << 10, std::max(least, W / 16384));
+__host__ __device__ inline uint64_t bundle_weight(uint64_t W) {
+  const uint64_t fill = W / 2048 < (24 << 10) ? W / 2048 : 24 << 10, least = fill < 4096 ? 4096 : fill;
+  const uint64_t w = W / 16384 < least ? least : W / 16384;
+  return w < (256 << 10) ? w : 256 << 10;
 }
 
 // Bundle boundaries of one class's short groups (items: the first of them;
@@ -968,6 +969,680 @@ __global__ void k_emit_items(const uint32_t* __restrict__ offs, const uint32_t* 
   items[j] = it;
 }
 
+// ---- small graphs -----------------------------------------------------------
+// A graph of at most kSmallN vertices and kSmallRaw raw pairs is bound by its
+// launches and host round trips, not by its bytes: its degrees are counted in
+// LDS from the sorted keys (no partition), its ranks are sorted by one
+// work-group, its edges are oriented by the orient sort's own first pass (the
+// rank map stays in L2: no partition either), and one work-group orders its
+// rows by class and cuts its packs. Up to kBlockSortMax raw pairs every sort
+// is one work-group's too (k_small_dedup, k_small_orient, k_small_tasks): a
+// sort of three passes is 10 launches of 2-16 us otherwise.
+constexpr int64_t kSmallN = 32768, kSmallRaw = 1 << 20;
+constexpr int kSmallThreads = 1024, kSmallWaves = kSmallThreads / 64;
+constexpr int64_t kBlockSortMax = 16 * kSmallThreads;
+
+// (32 keys per thread spill: 105 us for 32768 pairs, against 75 us in passes.)
+
+// LDS of a block sort: the keys, per wave and digit a count, scratch.
+template <int IPT>
+struct BlockSort {
+  uint32_t key[kSmallThreads * IPT];
+  uint32_t cnt[kSmallWaves][256];
+  uint32_t start[256];
+  uint32_t tmp[4];
+};
+
+// Item i of lane l of wave w is element w * 64 IPT + 64 i + l.
+template <int IPT>
+__device__ __forceinline__ int block_item(int i) {
+  return (int)(threadIdx.x >> 6) * 64 * IPT + 64 * i + (int)(threadIdx.x & 63);
+}
+
+// Stable sort of the work-group's keys by bits [bit_lo, bit_hi), ascending
+// (the ranking of k_rs_onesweep, the whole array one tile). On return k[i] is
+// element block_item(i) of the sorted array, and L.key holds it whole.
+template <int IPT>
+__device__ void block_sort(uint32_t (&k)[IPT], int bit_lo, int bit_hi, BlockSort<IPT>& L) {
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const uint64_t lt_mask = (1ull << lane) - 1ull;
+  for (int shift = bit_lo; shift < bit_hi; shift += 8) {
+    const uint32_t dmask = (1u << (bit_hi - shift < 8 ? bit_hi - shift : 8)) - 1u;
+    for (int x = tid; x < kSmallWaves * 256; x += kSmallThreads) (&L.cnt[0][0])[x] = 0;
+    __syncthreads();
+    uint32_t rank[IPT];
+    uint32_t* cnt_w = L.cnt[wave];
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) {
+      const uint32_t d = (k[i] >> shift) & dmask;
+      const uint64_t peers = rs_peers(d, true);
+      const uint32_t before = cnt_w[d];
+      rank[i] = before + (uint32_t)__popcll(peers & lt_mask);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      if ((peers & lt_mask) == 0) cnt_w[d] = before + (uint32_t)__popcll(peers);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    __syncthreads();
+    uint32_t total = 0, inc = 0;
+    if (tid < 256) {
+#pragma unroll
+      for (int w = 0; w < kSmallWaves; ++w) {
+        const uint32_t c = L.cnt[w][tid];
+        L.cnt[w][tid] = total;
+        total += c;
+      }
+      inc = wave_incl_scan(total);
+      if (lane == 63) L.tmp[wave] = inc;
+    }
+    __syncthreads();
+    if (tid < 256) {
+      uint32_t before = 0;
+      for (int w = 0; w < wave; ++w) before += L.tmp[w];
+      L.start[tid] = before + inc - total;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) {
+      const uint32_t d = (k[i] >> shift) & dmask;
+      L.key[L.start[d] + L.cnt[wave][d] + rank[i]] = k[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) k[i] = L.key[block_item<IPT>(i)];
+  }
+}
+
+// The sorted canonical keys S of at most 1024 IPT raw pairs (2 s <= 30 bits).
+// Places past m_raw take all ones, whose sorted bits are the sentinel's: they
+// stay behind the self loops.
+template <int IPT>
+__global__ __launch_bounds__(kSmallThreads) void k_small_dedup(CanonSrc cs, int m_raw, uint64_t* __restrict__ S,
+                                                               int* __restrict__ err) {
+  extern __shared__ int4 smem4[];
+  BlockSort<IPT>& L = *reinterpret_cast<BlockSort<IPT>*>(smem4);
+  uint32_t k[IPT];
+  bool bad_any = false;
+#pragma unroll
+  for (int i = 0; i < IPT; ++i) {
+    const int x = block_item<IPT>(i);
+    bool bad;
+    const uint32_t v = (uint32_t)cs.key(x < m_raw ? x : m_raw - 1, bad);
+    bad_any |= bad;
+    k[i] = x < m_raw ? v : 0xFFFFFFFFu;
+  }
+  if (bad_any) atomicOr(err, 1);
+  block_sort<IPT>(k, 0, 2 * cs.s, L);
+#pragma unroll
+  for (int i = 0; i < IPT; ++i) {
+    const int x = block_item<IPT>(i);
+    if (x < m_raw) S[x] = k[i];
+  }
+}
+
+// Distinct keys of S counted, and the degree of every vertex (deg zeroed
+// before): each work-group counts its share of S in LDS (n counters), lower
+// endpoints a run at a time (see k_degree_hist).
+__global__ __launch_bounds__(kSmallThreads) void k_small_degree(const uint64_t* __restrict__ S, uint64_t sent,
+                                                                int64_t m_raw, int64_t per, int s, int n,
+                                                                uint32_t* __restrict__ deg,
+                                                                unsigned long long* __restrict__ total) {
+  extern __shared__ uint32_t h_deg[];
+  __shared__ uint32_t s_c;
+  const int lane = threadIdx.x & 63;
+  for (int j = threadIdx.x; j < n; j += kSmallThreads) h_deg[j] = 0;
+  if (threadIdx.x == 0) s_c = 0;
+  __syncthreads();
+  const int64_t i0 = (int64_t)blockIdx.x * per, i1 = i0 + per < m_raw ? i0 + per : m_raw;
+  const uint64_t mask = (1ull << s) - 1, below = (1ull << lane) - 1ull;
+  uint32_t c = 0;
+  constexpr int kB = 4;
+  for (int64_t wb = i0 + (int64_t)(threadIdx.x - lane) * kB; wb < i1; wb += (int64_t)kSmallThreads * kB) {
+    uint64_t k[kB], prev[kB];
+#pragma unroll
+    for (int b = 0; b < kB; ++b) {
+      const int64_t i = wb + (int64_t)b * 64 + lane, ic = i < m_raw ? i : m_raw - 1;
+      k[b] = S[ic];
+      prev[b] = S[ic > 0 ? ic - 1 : 0];
+    }
+#pragma unroll
+    for (int b = 0; b < kB; ++b) {
+      const int64_t i = wb + (int64_t)b * 64 + lane;
+      const bool ok = (i < i1) & (k[b] != sent) & ((i == 0) | (prev[b] != k[b]));
+      const uint32_t lo = (uint32_t)(k[b] >> s);
+      const uint32_t plo = (uint32_t)__shfl_up((int)lo, 1);
+      const uint64_t heads = __ballot(lane == 0 || plo != lo), oks = __ballot(ok);
+      if ((heads >> lane) & 1ull) {
+        const uint64_t after = heads & ~below & ~(1ull << lane);
+        const uint64_t run = (after ? (after & (~after + 1ull)) - 1ull : ~0ull) & ~below;
+        const uint32_t r = (uint32_t)__popcll(oks & run);
+        if (r) atomicAdd(&h_deg[lo], r);
+      }
+      if (ok) atomicAdd(&h_deg[k[b] & mask], 1u);
+      if (lane == 0) c += (uint32_t)__popcll(oks);
+    }
+  }
+  if (c) atomicAdd(&s_c, c);
+  __syncthreads();
+  for (int j = threadIdx.x; j < n; j += kSmallThreads)
+    if (h_deg[j]) atomicAdd(&deg[j], h_deg[j]);
+  if (threadIdx.x == 0 && s_c) atomicAdd(total, (unsigned long long)s_c);
+}
+
+// Ranks of at most 1024 IPT vertices: stable by degree (below 2^15).
+template <int IPT>
+__global__ __launch_bounds__(kSmallThreads) void k_small_rank(const uint32_t* __restrict__ deg, int n, int deg_bits,
+                                                              int32_t* __restrict__ perm,
+                                                              uint32_t* __restrict__ deg_rank) {
+  extern __shared__ int4 smem4[];
+  BlockSort<IPT>& L = *reinterpret_cast<BlockSort<IPT>*>(smem4);
+  uint32_t k[IPT];
+#pragma unroll
+  for (int i = 0; i < IPT; ++i) {
+    const int v = block_item<IPT>(i);
+    k[i] = v < n ? (deg[v] << 16) | (uint32_t)v : 0xFFFFFFFFu;
+  }
+  block_sort<IPT>(k, 16, 16 + deg_bits, L);
+#pragma unroll
+  for (int i = 0; i < IPT; ++i) {
+    const int r = block_item<IPT>(i);
+    if (r < n) {
+      perm[k[i] & 0xFFFFu] = r;
+      deg_rank[r] = k[i] >> 16;
+    }
+  }
+}
+
+// The orient sort's source: position i of S as the oriented key of its
+// distinct edge.
+struct OrientSrc {
+  const uint64_t* S;
+  uint64_t sent;
+  const int32_t* perm;
+  int s;
+  __device__ bool operator()(int64_t i, uint64_t& k, char&) const {
+    const uint64_t e = S[i], prev = S[i > 0 ? i - 1 : 0];
+    const bool ok = (e != sent) & ((i == 0) | (prev != e));
+    const uint64_t lo = ok ? e >> s : 0, hi = ok ? e & ((1ull << s) - 1) : 0;
+    const uint64_t a = (uint32_t)perm[lo], b = (uint32_t)perm[hi];
+    k = a < b ? ((a << s) | b) : ((b << s) | a);
+    return ok;
+  }
+};
+
+__global__ __launch_bounds__(256) void k_orient_digits(OrientSrc src, int64_t m_raw, int key_bits,
+                                                       uint32_t* __restrict__ ghist) {
+  extern __shared__ uint32_t h_dyn[];
+  DigitCounter dc;
+  dc.init(h_dyn, 0, key_bits);
+  constexpr int kB = 4;
+  const int64_t stride = (int64_t)gridDim.x * 256 * kB;
+  for (int64_t base = (int64_t)blockIdx.x * 256 * kB + threadIdx.x; base < m_raw; base += stride) {
+    uint64_t k[kB];
+    bool ok[kB];
+#pragma unroll
+    for (int j = 0; j < kB; ++j) {
+      const int64_t i = base + (int64_t)j * 256;
+      char none;
+      ok[j] = src(i < m_raw ? i : m_raw - 1, k[j], none) & (i < m_raw);
+    }
+#pragma unroll
+    for (int j = 0; j < kB; ++j)
+      if (ok[j]) dc.add(k[j]);
+  }
+  dc.flush(ghist);
+}
+
+// The oriented keys and columns of U from at most 1024 IPT positions of S.
+template <int IPT>
+__global__ __launch_bounds__(kSmallThreads) void k_small_orient(OrientSrc src, int m_raw, int m,
+                                                                uint64_t* __restrict__ okey, ColEpi epi) {
+  extern __shared__ int4 smem4[];
+  BlockSort<IPT>& L = *reinterpret_cast<BlockSort<IPT>*>(smem4);
+  uint32_t k[IPT];
+#pragma unroll
+  for (int i = 0; i < IPT; ++i) {
+    const int x = block_item<IPT>(i);
+    uint64_t key;
+    char none;
+    const bool ok = src(x < m_raw ? x : m_raw - 1, key, none) & (x < m_raw);
+    k[i] = ok ? (uint32_t)key : 0xFFFFFFFFu;  // (no oriented key has all 2 s bits set)
+  }
+  block_sort<IPT>(k, 0, 2 * src.s, L);
+#pragma unroll
+  for (int i = 0; i < IPT; ++i) {
+    const int x = block_item<IPT>(i);
+    if (x < m) {
+      okey[x] = k[i];
+      epi((uint64_t)x, (uint64_t)k[i]);
+    }
+  }
+}
+
+// Row pointers, W+, the largest d+, the bitmap of non-empty rows and the
+// zeros of the short columns, in one launch.
+__global__ __launch_bounds__(256) void k_small_rows(const uint64_t* __restrict__ keys, int64_t m, int s, int64_t n,
+                                                    int64_t* __restrict__ row_ptr, uint16_t* __restrict__ col16,
+                                                    uint64_t* __restrict__ bits,
+                                                    unsigned long long* __restrict__ wplus,
+                                                    unsigned int* __restrict__ maxd) {
+  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  auto first = [&](int64_t row) {
+    int64_t lo = 0, hi = m;
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) >> 1;
+      if ((int64_t)(keys[mid] >> s) < row) lo = mid + 1;
+      else hi = mid;
+    }
+    return lo;
+  };
+  uint64_t d = 0;
+  if (r <= n) {
+    const int64_t lo = first(r);
+    row_ptr[r] = lo;
+    col16[lo] = 0;
+    if (r == n) col16[m + 1] = 0;
+    else d = (uint64_t)(first(r + 1) - lo);
+  }
+  const uint64_t ne = __ballot(d > 0);
+  const uint64_t w = wave_sum(d * (d - (d > 0)) / 2);
+  const uint32_t md = wave_max((uint32_t)d);
+  if (lane_id() == 0) {
+    if (r < n) bits[r >> 6] = ne;
+    if (w) atomicAdd(wplus, (unsigned long long)w);
+    if (md) atomicMax(maxd, md);
+  }
+}
+
+// The tasks of at most 1024 IPT entries of U, sorted by row (key: row and the
+// entry, which keeps U's order within a row), and their number.
+template <int IPT>
+__global__ __launch_bounds__(kSmallThreads) void k_small_tasks(TaskSrc src, int m, int s, uint32_t* __restrict__ row,
+                                                               uint64_t* __restrict__ val, uint32_t* __restrict__ total) {
+  extern __shared__ int4 smem4[];
+  BlockSort<IPT>& L = *reinterpret_cast<BlockSort<IPT>*>(smem4);
+  uint32_t k[IPT], c = 0;
+#pragma unroll
+  for (int i = 0; i < IPT; ++i) {
+    const int x = block_item<IPT>(i);
+    uint32_t b;
+    uint64_t v;
+    const bool ok = src(x < m ? x : m - 1, b, v) & (x < m);
+    k[i] = ok ? (b << 15) | (uint32_t)x : 0xFFFFFFFFu;  // (row 2^s - 1 has no task: no key of it follows)
+    c += ok ? 1u : 0u;
+  }
+  block_sort<IPT>(k, 15, 15 + s, L);
+  c = wave_sum(c);
+  if (lane_id() == 0 && c) atomicAdd(total, c);
+#pragma unroll
+  for (int i = 0; i < IPT; ++i) {
+    const int x = block_item<IPT>(i);
+    if (k[i] == 0xFFFFFFFFu) continue;
+    uint32_t b;
+    uint64_t v;
+    (void)src((int64_t)(k[i] & 0x7FFFu), b, v);
+    row[x] = b;
+    val[x] = v;
+  }
+}
+
+// Launches a block-sort kernel template at the smallest size that holds
+// `count` elements.
+#define TC_LAUNCH_BLOCK(name, kern, count, st, ...)                                                             \
+  do {                                                                                                          \
+    if ((count) <= 4 * kSmallThreads) launch_block<4>(name, kern<4>, st, __VA_ARGS__);                          \
+    else if ((count) <= 8 * kSmallThreads) launch_block<8>(name, kern<8>, st, __VA_ARGS__);                     \
+    else launch_block<16>(name, kern<16>, st, __VA_ARGS__);                                                     \
+  } while (0)
+
+// hipFuncSetAttribute for a kernel of more than 64 KiB of dynamic LDS, once
+// per device and kernel.
+void allow_lds(const void* f, size_t lds) {
+  if (lds <= 65536) return;
+  static std::mutex mu;
+  static std::set<std::pair<int, const void*>> done;
+  int dev = 0;
+  TC_HIP(hipGetDevice(&dev));
+  std::lock_guard<std::mutex> lk(mu);
+  if (done.count({dev, f})) return;
+  TC_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  done.insert({dev, f});
+}
+
+template <int IPT, class... P, class... A>
+void launch_block(const char* name, void (*kern)(P...), hipStream_t st, A... args) {
+  allow_lds((const void*)kern, sizeof(BlockSort<IPT>));
+  TC_LAUNCH(name, kern, dim3(1), dim3(kSmallThreads), sizeof(BlockSort<IPT>), st, args...);
+  TC_HIP(hipGetLastError());
+}
+
+// ---- class-major order of a small graph's rows --------------------------------
+// What the compaction, the class sort, the scans and the pack kernels below do
+// for a large row set, by one work-group for at most kSmallN rows: the
+// class-major row order, the prefixes of tasks, units and items along it, and
+// the packs of the two pack classes. (A thread's rows per class, and those
+// before it, are 16-bit fields.)
+struct SmallOrder {
+  ClassBounds cb;
+  unsigned long long stats[NUM_CLASSES][3];  // rows, keys, tasks
+  unsigned long long cw[NUM_CLASSES], cw16[NUM_CLASSES];
+  uint64_t bundle_w;
+  uint32_t chunk16, chunk[NUM_CLASSES];
+  int cl[NUM_CLASSES];
+};
+
+// A class-major row: its units, tasks and keys.
+struct alignas(16) RowRec {
+  uint64_t W;
+  uint32_t tasks, d;
+};
+
+// Exclusive scan over the work-group and the total (two barriers).
+template <class T>
+__device__ __forceinline__ T small_scan(T v, T* s_w, T& total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const T inc = wave_incl_scan(v);
+  if (lane == 63) s_w[wave] = inc;
+  __syncthreads();
+  T before = 0, tot = 0;
+#pragma unroll
+  for (int w = 0; w < kSmallWaves; ++w) {
+    const T x = s_w[w];
+    before += w < wave ? x : T(0);
+    tot += x;
+  }
+  __syncthreads();
+  total = tot;
+  return before + inc - v;
+}
+
+// Probes per wave item of each item class, and of the short rows' bundles.
+__host__ __device__ inline uint32_t class_chunk(uint64_t cw, int c, const WorkParams& wp) {
+  const uint64_t per_group = wp.min_groups ? cw / ((uint64_t)wp.min_groups * class_waves(c)) : ~0ull;
+  return per_group < kWaveChunkMin ? wp.wave_chunk
+                                   : (uint32_t)(per_group < wp.wave_chunk ? per_group : wp.wave_chunk);
+}
+
+__global__ __launch_bounds__(kSmallThreads) void k_small_order(
+    int n, const int8_t* __restrict__ cls, const int64_t* __restrict__ tptr, const uint64_t* __restrict__ tprefix,
+    const int64_t* __restrict__ row_ptr, int64_t b16, WorkParams wp, const unsigned long long* __restrict__ cw,
+    const unsigned long long* __restrict__ cw16, const int* __restrict__ cl, uint32_t* __restrict__ crow,
+    uint32_t* __restrict__ tbeg, uint32_t* __restrict__ tend, uint32_t* __restrict__ cm_pos,
+    uint64_t* __restrict__ wsc, uint32_t* __restrict__ usc, uint32_t* __restrict__ pack_ptr0,
+    uint32_t* __restrict__ pack_ptr1, RowRec* __restrict__ rec, SmallOrder* __restrict__ out) {
+  __shared__ uint64_t s_w64[kSmallWaves];
+  __shared__ unsigned long long s_wu[kSmallWaves];
+  __shared__ uint32_t s_w32[kSmallWaves];
+  __shared__ uint64_t s_flag[kSmallWaves][kSmallN / kSmallWaves / 64];
+  __shared__ unsigned long long s_stat[NUM_CLASSES][3];
+  __shared__ uint32_t s_row[NUM_CLASSES + 1], s_row16[NUM_CLASSES], s_chunk[NUM_CLASSES];
+  __shared__ uint32_t s_item[NUM_CLASSES + 1], s_item16[NUM_CLASSES];
+  __shared__ uint16_t s_crow[kSmallN];
+  const int tid = threadIdx.x;
+  uint64_t cw_short = 0;
+  for (int c = CLS_WG_SMALL; c < NUM_CLASSES; ++c) cw_short += cw16[c];
+  const uint64_t bundle_w = bundle_weight(cw_short);
+  const uint32_t chunk16 = (uint32_t)(bundle_w / kWaves < wp.wave_chunk ? bundle_w / kWaves : wp.wave_chunk);
+  if (tid < NUM_CLASSES) {
+    s_chunk[tid] = class_chunk(cw[tid], tid, wp);
+    for (int j = 0; j < 3; ++j) s_stat[tid][j] = 0;
+  }
+  __syncthreads();
+  // rows per class: of this thread, then before it
+  const int R = (n + kSmallThreads - 1) / kSmallThreads;  // at most 32
+  const int r0 = tid * R < n ? tid * R : n, r1 = r0 + R < n ? r0 + R : n;
+  uint64_t lo = 0, hi = 0;  // 16-bit counts of classes 0-3, 4-6
+  uint32_t cpack[4] = {0, 0, 0, 0};  // the rows' classes + 1, four bits each
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    if (8 * g >= R) break;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int r = r0 + 8 * g + j;
+      const int c = r < r1 ? cls[r] : -1;
+      cpack[g] |= (uint32_t)(c + 1) << (4 * j);
+      lo += c >= 0 && c < 4 ? 1ull << (16 * c) : 0;
+      hi += c >= 4 ? 1ull << (16 * (c - 4)) : 0;
+    }
+  }
+  uint64_t lo_all, hi_all;
+  lo = small_scan(lo, s_w64, lo_all);
+  hi = small_scan(hi, s_w64, hi_all);
+  if (tid == 0) {
+    uint32_t at = 0;
+    for (int c = 0; c <= NUM_CLASSES; ++c) {
+      s_row[c] = at;
+      if (c < NUM_CLASSES) at += (uint32_t)((c < 4 ? lo_all >> (16 * c) : hi_all >> (16 * (c - 4))) & 0xFFFFu);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 32; ++j) {
+    if (j >= R) break;
+    const int r = r0 + j;
+    const int c = (int)((cpack[j / 8] >> (4 * (j % 8))) & 15u) - 1;
+    if (c < 0) {
+      if (r < r1) {  // a row without work: an empty task range
+        tbeg[r] = 0;
+        tend[r] = 0;
+      }
+      continue;
+    }
+    uint32_t p;
+    if (c < 4) {
+      p = (uint32_t)(lo >> (16 * c)) & 0xFFFFu;
+      lo += 1ull << (16 * c);
+    } else {
+      p = (uint32_t)(hi >> (16 * (c - 4))) & 0xFFFFu;
+      hi += 1ull << (16 * (c - 4));
+    }
+    s_crow[s_row[c] + p] = (uint16_t)r;
+  }
+  __syncthreads();
+  const int Rt = (int)s_row[NUM_CLASSES];
+  auto class_of = [&](int i) {
+    int c = 0;
+    while (i >= (int)s_row[c + 1]) ++c;
+    return c;
+  };
+  if (tid < NUM_CLASSES) {  // first short row of each class
+    uint32_t a = s_row[tid], z = s_row[tid + 1];
+    while (a < z) {
+      const uint32_t mid = (a + z) >> 1;
+      if ((int64_t)s_crow[mid] < b16) a = mid + 1;
+      else z = mid;
+    }
+    s_row16[tid] = a;
+  }
+  // prefixes along the class-major rows: each wave takes a contiguous share,
+  // 64 rows at a time (consecutive lanes read and write consecutive rows: one
+  // CU moves a cache line per cycle, and with consecutive rows per thread the
+  // lines alone took 130 us of 16384 rows)
+  auto items_of = [&](uint32_t b, int c, uint64_t W) -> uint32_t {
+    if (c <= CLS_PACK_LARGE) return 0;
+    return (int64_t)b >= b16 ? wg_parts(2 * W, kWaves, chunk16) : wg_parts(W, class_waves(c), s_chunk[c]);
+  };
+  const int lane = tid & 63, wave = tid >> 6;
+  const int C = ((Rt + kSmallWaves - 1) / kSmallWaves + 63) & ~63;
+  const int i0 = wave * C < Rt ? wave * C : Rt, i1 = i0 + C < Rt ? i0 + C : Rt;
+  uint32_t tasks = 0, items = 0;
+  uint64_t units = 0;
+  {
+    int c_run = -1;
+    unsigned long long st[3] = {0, 0, 0};
+    auto flush = [&]() {
+      if (c_run >= 0)
+        for (int j = 0; j < 3; ++j) atomicAdd(&s_stat[c_run][j], st[j]);
+    };
+    constexpr int kB = 4;
+    for (int ib = i0 + lane; ib < i1; ib += 64 * kB) {
+      RowRec q[kB];
+      int64_t p0[kB], p1[kB];
+#pragma unroll
+      for (int j = 0; j < kB; ++j) {
+        const uint32_t b = s_crow[ib + 64 * j < i1 ? ib + 64 * j : i1 - 1];
+        p0[j] = tptr[b];
+        p1[j] = tptr[b + 1];
+        q[j].d = (uint32_t)(row_ptr[b + 1] - row_ptr[b]);
+      }
+#pragma unroll
+      for (int j = 0; j < kB; ++j) {
+        q[j].W = tprefix[p1[j]] - tprefix[p0[j]];
+        q[j].tasks = (uint32_t)(p1[j] - p0[j]);
+      }
+#pragma unroll
+      for (int j = 0; j < kB; ++j) {
+        const int i = ib + 64 * j;
+        if (i >= i1) break;
+        rec[i] = q[j];
+        const int c = class_of(i);
+        if (c != c_run) {
+          flush();
+          c_run = c;
+          st[0] = st[1] = st[2] = 0;
+        }
+        st[0] += 1;
+        st[1] += q[j].d;
+        st[2] += q[j].tasks;
+        tasks += q[j].tasks;
+        units += q[j].W;
+        items += items_of(s_crow[i], c, q[j].W);
+      }
+    }
+    flush();
+  }
+  // (small_scan of the waves' totals: lane 63 brings them, the others 0)
+  auto wave_base = [&](auto v, auto* s_w, auto& all) {
+    const auto sum = wave_sum(v);
+    const auto ex = small_scan(lane == 63 ? sum : decltype(v)(0), s_w, all);
+    return __shfl(ex, 0, 64);
+  };
+  uint32_t tasks_all, items_all;
+  unsigned long long units_all;
+  tasks = wave_base(tasks, s_w32, tasks_all);
+  items = wave_base(items, s_w32, items_all);
+  unsigned long long ubase = wave_base((unsigned long long)units, s_wu, units_all);
+  for (int ib = i0; ib < i1; ib += 64) {
+    const int i = ib + lane;
+    const bool in = i < i1;
+    const RowRec q = rec[in ? i : i1 - 1];
+    const uint32_t b = s_crow[in ? i : i1 - 1];
+    const int c = class_of(in ? i : i1 - 1);
+    const uint32_t it = in ? items_of(b, c, q.W) : 0;
+    const uint32_t ts = wave_incl_scan(in ? q.tasks : 0u), is = wave_incl_scan(it);
+    const unsigned long long us = wave_incl_scan((unsigned long long)(in ? q.W : 0));
+    if (in) {
+      crow[i] = b;
+      cm_pos[b] = (uint32_t)i;
+      tbeg[b] = tasks + ts - q.tasks;
+      tend[b] = tasks + ts;
+      wsc[i] = ubase + us - q.W;
+      usc[i] = items + is - it;
+      if (i == (int)s_row[c]) s_item[c] = items + is - it;
+      if (i == (int)s_row16[c]) s_item16[c] = items + is - it;
+    }
+    tasks += (uint32_t)__shfl((int)ts, 63, 64);
+    items += (uint32_t)__shfl((int)is, 63, 64);
+    ubase += __shfl(us, 63, 64);
+  }
+  if (tid == 0) {
+    wsc[Rt] = units_all;
+    usc[Rt] = items_all;
+    s_item[NUM_CLASSES] = items_all;
+  }
+  __syncthreads();
+  // packs: a boundary where the running weight, the running slots or the row
+  // enters a new multiple of its budget, and at the first short row
+  const double inv_target = 1.0 / (double)wp.pack_target;
+  auto target_of = [&](unsigned long long x) {  // x / pack_target (x < 2^53)
+    unsigned long long q = (unsigned long long)((double)x * inv_target);
+    if (q * wp.pack_target > x) --q;
+    if ((q + 1) * wp.pack_target <= x) ++q;
+    return q;
+  };
+#pragma unroll 1
+  for (int c = CLS_PACK_SMALL; c <= CLS_PACK_LARGE; ++c) {
+    const int c0 = (int)s_row[c], nr = (int)s_row[c + 1] - c0, i16 = (int)s_row16[c] - c0;
+    const int P = ((nr + kSmallWaves - 1) / kSmallWaves + 63) & ~63;
+    const int a = wave * P < nr ? wave * P : nr, z = a + P < nr ? a + P : nr;
+    auto weigh = [&](int i, unsigned long long& w, uint32_t& sl) {
+      const RowRec q = rec[c0 + i];
+      w = row_weight(q.W, s_crow[c0 + i], b16);
+      sl = 1u << pack_table_log2(q.tasks ? q.d : 0);
+    };
+    unsigned long long w = 0, all64;
+    uint32_t sl = 0, all32, np;
+    for (int i = a + lane; i < z; i += 64) {
+      unsigned long long wi;
+      uint32_t si;
+      weigh(i, wi, si);
+      w += wi;
+      sl += si;
+    }
+    unsigned long long pw = wave_base(w, s_wu, all64);
+    uint32_t ps = wave_base(sl, s_w32, all32);
+    uint32_t count = 0;  // (uniform)
+    for (int ib = a; ib < z; ib += 64) {
+      const int i = ib + lane;
+      unsigned long long wi = 0, lw = 0;
+      uint32_t si = 0, ls = 0;  // l: the row before
+      if (i < z) weigh(i, wi, si);
+      if (i > 0 && i < z) weigh(i - 1, lw, ls);
+      const unsigned long long wx = pw + wave_incl_scan(wi) - wi;
+      const uint32_t sx = ps + wave_incl_scan(si) - si;
+      const uint32_t budget = i >= i16 ? short_pack_slots(wp.pack_slots) : wp.pack_slots;
+      const bool start = i < z && (i == 0 || i == i16 || target_of(wx) != target_of(wx - lw) ||
+                                   sx / budget != (sx - ls) / budget || i % kPackRows == 0);
+      const uint64_t f = __ballot(start);
+      if (lane == 0) s_flag[wave][(ib - a) >> 6] = f;
+      count += (uint32_t)__popcll(f);
+      pw = __shfl(wx + wi, 63, 64);
+      ps = (uint32_t)__shfl((int)(sx + si), 63, 64);
+    }
+    uint32_t at = wave_base(lane == 63 ? count : 0u, s_w32, np);
+    uint32_t* ptr = c == 0 ? pack_ptr0 : pack_ptr1;
+    for (int ib = a; ib < z; ib += 64) {
+      const int i = ib + lane;
+      const uint64_t f = s_flag[wave][(ib - a) >> 6];
+      const uint32_t p = at + (uint32_t)__popcll(f & ((1ull << lane) - 1ull));
+      if (i < z && i == i16) out->cb.packs32[c] = p;
+      if ((f >> lane) & 1ull) ptr[p] = (uint32_t)i;
+      at += (uint32_t)__popcll(f);
+    }
+    if (tid == 0) {
+      ptr[np] = (uint32_t)nr;
+      if (i16 >= nr) out->cb.packs32[c] = np;
+      out->cb.packs[c] = np;
+    }
+    __syncthreads();  // (s_flag is written again)
+  }
+  if (tid == 0) {
+    // (an empty class, and one without short rows, end where the next begins)
+    for (int c = NUM_CLASSES - 1; c >= 0; --c) {
+      if (s_row[c] == s_row[c + 1]) s_item[c] = s_item[c + 1];
+      if (s_row16[c] == s_row[c + 1]) s_item16[c] = s_item[c + 1];
+    }
+    for (int c = 0; c <= NUM_CLASSES; ++c) {
+      out->cb.row[c] = s_row[c];
+      out->cb.item[c] = s_item[c];
+      if (c == NUM_CLASSES) break;
+      out->cb.row16[c] = s_row16[c];
+      out->cb.item16[c] = s_item16[c];
+      for (int j = 0; j < 3; ++j) out->stats[c][j] = s_stat[c][j];
+      out->cw[c] = cw[c];
+      out->cw16[c] = cw16[c];
+      out->cl[c] = cl[c];
+      out->chunk[c] = s_chunk[c];
+    }
+    out->cb.tasks = tasks_all;
+    out->bundle_w = bundle_w;
+    out->chunk16 = chunk16;
+  }
+}
+
 }  // namespace
 
 struct GraphImpl : Graph {
@@ -1006,9 +1681,16 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
   // 28: two host reads of 16 bytes), then the digit counts of the degree
   // partition (2 x 256), of the canonical keys, of the oriented keys and of
   // the tasks (kSortPassesMax x 256 each).
+  // A small graph's vertex degrees follow, and the look-back words of its
+  // sorts.
+  const bool small = n <= kSmallN && m_raw <= kSmallRaw;
+  const bool block_sorts = small && m_raw <= kBlockSortMax;
   constexpr size_t kHistWords = 256 * kSortPassesMax;
-  DevBuf zs(64 + sizeof(uint32_t) * (256 * 2 + 3 * kHistWords));
+  const size_t deg_at = 64 + sizeof(uint32_t) * (256 * 2 + 3 * kHistWords);
+  const size_t pool_at = deg_at + (small ? (sizeof(uint32_t) * (size_t)n + 255) & ~(size_t)255 : 0);
+  DevBuf zs(pool_at + (small ? kZeroPool : 0));
   TC_HIP(hipMemsetAsync(zs.p, 0, zs.bytes, st));
+  if (small) temps.zero_pool(zs.as<char>() + pool_at, kZeroPool);
   char* const zb = zs.as<char>();
   int* d_err = reinterpret_cast<int*>(zb);
   unsigned long long* d_m = reinterpret_cast<unsigned long long*>(zb + 8);
@@ -1043,7 +1725,9 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
     // waves per SIMD); one read of the pairs before it counts their digits
     // and checks the ids
     const CanonSrc csrc{d_src, d_dst, n, s, sent};
-    if (m_raw > 0) {
+    if (m_raw > 0 && block_sorts) {
+      TC_LAUNCH_BLOCK("small_dedup", k_small_dedup, m_raw, st, csrc, (int)m_raw, ka.as<uint64_t>(), d_err);
+    } else if (m_raw > 0) {
       TC_LAUNCH("canon_digits", k_canon_digits,
                 dim3((unsigned)std::min<int64_t>(kProducerBlocks, div_up(m_raw, kT * kDigitBatch))), dim3(kT),
                 digit_lds_bytes(0, 2 * s), st, csrc, m_raw, 2 * s, ch, d_err);
@@ -1051,6 +1735,15 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
       salt = radix_sort_from<uint64_t, NoVal, CanonSrc, 28>(csrc, m_raw, ka.as<uint64_t>(), kb.as<uint64_t>(),
                                                             nullptr, nullptr, m_raw, 0, 2 * s, ch,
                                                             st, "dedup");
+    }
+    if (m_raw > 0 && small) {
+      const int64_t per = std::max<int64_t>(8192, div_up(m_raw, 64));
+      allow_lds((const void*)k_small_degree, sizeof(uint32_t) * (size_t)n);
+      TC_LAUNCH("small_degree", k_small_degree, dim3((unsigned)div_up(m_raw, per)), dim3(kSmallThreads),
+                sizeof(uint32_t) * (size_t)n, st, salt ? kb.as<uint64_t>() : ka.as<uint64_t>(), sent, m_raw, per, s,
+                (int)n, reinterpret_cast<uint32_t*>(zb + deg_at), d_m);
+      TC_HIP(hipGetLastError());
+    } else if (m_raw > 0) {
       // duplicates marked, distinct keys counted, with their upper
       // endpoints' partition digits
       TC_LAUNCH("distinct_mark", k_distinct_mark,
@@ -1082,16 +1775,23 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
   g->perm = g->owned.alloc<int32_t>(n);
   g->deg = g->owned.alloc<uint32_t>(n);
   const uint32_t* hi_starts = dh + 256 * (hpasses - 1);  // valid once m > 0
-  {
+  if (small && n <= kBlockSortMax) {
+    TC_LAUNCH_BLOCK("small_rank", k_small_rank, n, st, reinterpret_cast<const uint32_t*>(zb + deg_at), (int)n, s,
+                    g->perm, g->deg);
+  } else {
     DevBuf ra(sizeof(uint64_t) * (size_t)n), rb(sizeof(uint64_t) * (size_t)n);
-    if (m > 0) {
+    if (small) {
+      TC_LAUNCH("rank_keys", k_rank_keys, dim3(grid_for(n)), dim3(kT), 0, st,
+                reinterpret_cast<const uint32_t*>(zb + deg_at), n, s, ra.as<uint64_t>());
+      TC_HIP(hipGetLastError());
+    } else if (m > 0) {
       // upper endpoints partitioned by their top bits (read from S through
       // the distinct keys) and counted per bucket in LDS with the lower
       // endpoints (k_degree_hist, which writes the rank keys)
       DevBuf hb(sizeof(uint32_t) * (size_t)m), hb2(hpasses > 1 ? sizeof(uint32_t) * (size_t)m : 0);
       const bool halt = radix_sort_from<uint32_t, NoVal>(DistinctHiSrc{dsel, s}, m_raw, hb.as<uint32_t>(),
                                                          hb2.as<uint32_t>(), nullptr, nullptr, m, hshift, s,
-                                                         dh, st, "degree");
+                                                         dh, st, "degree", NoEpi{}, false, true);
       const uint32_t* hsorted = halt ? hb2.as<uint32_t>() : hb.as<uint32_t>();
       const int64_t span = (int64_t)1 << hshift;  // vertices per bucket
       const int sub = (int)div_up(span, kDegBins);
@@ -1143,7 +1843,28 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
   g->col = g->owned.alloc<int32_t>(m);
   g->col16 = g->owned.alloc<uint16_t>(m + 2);
   const uint64_t* okey = obuf.as<uint64_t>();
-  {
+  DevBuf ne;  // bitmap of U's non-empty rows
+  const ColEpi col_epi{g->col, g->col16, n, s};
+  if (small && m > 0) {
+    ne.alloc(sizeof(uint64_t) * (size_t)div_up(n, 64));
+    const OrientSrc osrc{sbuf.as<uint64_t>(), sent, g->perm, s};
+    if (block_sorts) {
+      TC_LAUNCH_BLOCK("small_orient", k_small_orient, m_raw, st, osrc, (int)m_raw, (int)m, obuf.as<uint64_t>(),
+                      col_epi);
+    } else {
+      TC_LAUNCH("orient_digits", k_orient_digits, dim3((unsigned)std::min<int64_t>(256, div_up(m_raw, kT * 4))),
+                dim3(kT), digit_lds_bytes(0, 2 * s), st, osrc, m_raw, 2 * s, ohist);
+      TC_HIP(hipGetLastError());
+      // (S is read by the first pass alone: its buffer is the partner of the others)
+      if (radix_sort_from<uint64_t, NoVal, OrientSrc, 28, ColEpi>(osrc, m_raw, obuf.as<uint64_t>(),
+                                                                  sbuf.as<uint64_t>(), nullptr, nullptr, m, 0, 2 * s,
+                                                                  ohist, st, "orient", col_epi))
+        okey = sbuf.as<uint64_t>();
+    }
+    TC_LAUNCH("small_rows", k_small_rows, dim3(grid_for(n + 1)), dim3(kT), 0, st, okey, m, s, n, g->row_ptr,
+              g->col16, ne.as<uint64_t>(), d_wplus, d_maxd);
+    TC_HIP(hipGetLastError());
+  } else {
     if (m > 0) {
       // partition by the top 8 bits of hi (one pass from S into the free
       // buffer), then the oriented keys in place
@@ -1160,7 +1881,7 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
       // S's buffer is the ping-pong partner (S is not read after the
       // partition); the last pass also writes each key's column: U's col
       bool alt = radix_sort<uint64_t, NoVal, ColEpi>(obuf.as<uint64_t>(), sbuf.as<uint64_t>(), nullptr, nullptr,
-                                                     m, 0, 2 * s, st, "orient", ColEpi{g->col, g->col16, n, s},
+                                                     m, 0, 2 * s, st, "orient", col_epi,
                                                      ohist);
       if (alt) okey = sbuf.as<uint64_t>();
       TC_LAUNCH("row_bounds", k_row_bounds, dim3(grid_for(n + 1)), dim3(kT), 0, st, okey, m, s, n, g->row_ptr,
@@ -1186,13 +1907,22 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
   // is written in U order)
   TaskLists tl;
   {
-    DevBuf ne;
     TaskSrc src{};
     if (m > 0) {
-      ne.alloc(sizeof(uint64_t) * (size_t)div_up(n, 64));
-      TC_LAUNCH("nonempty_bits", k_nonempty_bits, dim3(grid_for(n)), dim3(kT), 0, st, g->row_ptr, n,
-                ne.as<uint64_t>());
+      if (!small) {
+        ne.alloc(sizeof(uint64_t) * (size_t)div_up(n, 64));
+        TC_LAUNCH("nonempty_bits", k_nonempty_bits, dim3(grid_for(n)), dim3(kT), 0, st, g->row_ptr, n,
+                  ne.as<uint64_t>());
+      }
       src.p = TaskPred{okey, s, g->row_ptr, ne.as<uint64_t>(), nullptr, nullptr};
+    }
+    const bool block_tasks = block_sorts && m > 0;  // (m <= m_raw)
+    if (block_tasks) {
+      tl.row.alloc(sizeof(uint32_t) * (size_t)m);
+      tl.val.alloc(sizeof(uint64_t) * (size_t)m);
+      TC_LAUNCH_BLOCK("small_tasks", k_small_tasks, m, st, src, (int)m, s, tl.row.as<uint32_t>(),
+                      tl.val.as<uint64_t>(), d_T);
+    } else if (m > 0) {
       TC_LAUNCH("task_digits", k_task_digits,
                 dim3((unsigned)std::min<int64_t>(kProducerBlocks, div_up(m, kT * kDigitBatch))), dim3(kT),
                 digit_lds_bytes(0, s), st, src, m, s, th, d_T);
@@ -1209,7 +1939,7 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
     const int64_t T = h.T;
     tl.T = T;
     tl.ptr.alloc(sizeof(int64_t) * (size_t)(n + 1));
-    if (T > 0) {
+    if (T > 0 && !block_tasks) {
       tl.row.alloc(sizeof(uint32_t) * (size_t)T);
       tl.val.alloc(sizeof(uint64_t) * (size_t)T);
       DevBuf tk(sizeof(uint32_t) * (size_t)T), tv(sizeof(uint64_t) * (size_t)T);
@@ -1378,6 +2108,79 @@ void sort_tasks(TaskLists& tl, DevBuf& tk, DevBuf& tv, int64_t T, int64_t nrows,
   finish_tasks(tl, nrows, b16, st);
 }
 
+namespace {
+
+// Bundles of class c's short rows (cw16: their weight), whose items are there.
+void make_bundles(WorkSet& w, Owned& own, int c, uint64_t cw16, hipStream_t st) {
+  const int64_t groups = (w.n_items[c] - w.n_items32[c]) / kWaves;
+  if (groups == 0) return;
+  const uint64_t per = w.bundle_w / 2;  // units
+  w.n_bundles[c] = div_up((int64_t)(cw16 / 2), (int64_t)per);
+  w.bundle[c] = own.alloc<uint32_t>(w.n_bundles[c] + 1);
+  TC_LAUNCH("bundles", k_bundles, dim3(grid_for(groups)), dim3(kT), 0, st, w.items[c] + w.n_items32[c], groups, per,
+            w.n_bundles[c], w.bundle[c]);
+  TC_HIP(hipGetLastError());
+}
+
+// The rest of build_work for at most kSmallN rows (k_small_order).
+void build_work_small(WorkSet& w, Owned& own, int64_t n, const int64_t* hrow_ptr, int64_t T, const uint32_t* tb_row,
+                      const int64_t* tb_ptr, const uint64_t* tb_val, const uint64_t* tb_prefix, hipStream_t st,
+                      const int8_t* cls, unsigned long long* d_cp, const unsigned long long* d_cw, const int* d_cl) {
+  uint32_t* crow = reinterpret_cast<uint32_t*>(own.alloc<int32_t>(n));
+  uint32_t* pack_ptr[2] = {own.alloc<uint32_t>(n + 1), own.alloc<uint32_t>(n + 1)};
+  DevBuf cm_pos(sizeof(uint32_t) * (size_t)n), wsc(sizeof(uint64_t) * (size_t)(n + 1));
+  DevBuf usc(sizeof(uint32_t) * (size_t)(n + 1)), so(sizeof(SmallOrder)), rec(sizeof(RowRec) * (size_t)n);
+  TC_LAUNCH("small_order", k_small_order, dim3(1), dim3(kSmallThreads), 0, st, (int)n, cls, tb_ptr, tb_prefix,
+            hrow_ptr, w.b16, w.wp, d_cw, d_cw + NUM_CLASSES, d_cl, crow, w.tbeg, w.tend, cm_pos.as<uint32_t>(),
+            wsc.as<uint64_t>(), usc.as<uint32_t>(), pack_ptr[0], pack_ptr[1], rec.as<RowRec>(), so.as<SmallOrder>());
+  TC_LAUNCH("task_permute", k_task_permute, dim3((unsigned)div_up(T, kT * kPermuteTasks)), dim3(kT), 0, st, T,
+            tb_row, tb_ptr, tb_val, tb_prefix, cls, w.tbeg, cm_pos.as<uint32_t>(), wsc.as<uint64_t>(), w.tstart,
+            w.tprefix, d_cp);
+  TC_HIP(hipGetLastError());
+  TC_HIP(hipMemcpyAsync(w.tprefix + T, tb_prefix + T, sizeof(uint64_t), hipMemcpyDeviceToDevice, st));
+  SmallOrder h;
+  TC_HIP(hipMemcpyAsync(&h, so.p, sizeof(h), hipMemcpyDeviceToHost, st));
+  TC_HIP(hipMemcpyAsync(w.cls_probes, d_cp, sizeof(w.cls_probes), hipMemcpyDeviceToHost, st));
+  TC_HIP(hipStreamSynchronize(st));
+  TC_REQUIRE((int64_t)h.cb.tasks == T && h.cb.row[NUM_CLASSES] > 0, TC_EDEVICE,
+             "build_work: class-major task order lost tasks");
+  w.bundle_w = h.bundle_w;
+  for (int c = 0; c < NUM_CLASSES; ++c) {
+    for (int j = 0; j < 3; ++j) w.cls_stats[c][j] = (int64_t)h.stats[c][j];
+    w.cls_log2S[c] = h.cl[c];
+    w.cls_chunk[c] = h.chunk[c];
+    const int64_t r0 = h.cb.row[c], nr = h.cb.row[c + 1] - r0;
+    if (nr == 0) continue;
+    if (c <= CLS_PACK_LARGE) {
+      const int64_t np = h.cb.packs[c];
+      w.pack_rows[c] = reinterpret_cast<int32_t*>(crow + r0);
+      w.pack_ptr[c] = pack_ptr[c];
+      w.pack_recs[c] = own.alloc<PackRow>(nr);
+      w.pack_info[c] = own.alloc<PackInfo>(np);
+      TC_LAUNCH("pack_recs", k_pack_recs, dim3(grid_for(nr)), dim3(kT), 0, st, w.pack_rows[c], nr, hrow_ptr, w.tbeg,
+                w.tend, w.pack_recs[c]);
+      TC_LAUNCH("pack_info", k_pack_info, dim3(grid_for(np * kPackWavesMax)), dim3(kT), 0, st, pack_ptr[c], np,
+                w.pack_recs[c], w.tprefix, w.pack_info[c]);
+      w.n_pack_rows[c] = nr;
+      w.n_packs[c] = np;
+      w.n_packs32[c] = h.cb.packs32[c];
+      w.pack_log2S[c] = h.cl[c];
+    } else {
+      const int64_t total = (int64_t)h.cb.item[c + 1] - (int64_t)h.cb.item[c];
+      if (total == 0) continue;
+      w.items[c] = own.alloc<CountItem>(total);
+      w.n_items[c] = total;
+      w.n_items32[c] = (int64_t)h.cb.item16[c] - (int64_t)h.cb.item[c];
+      TC_LAUNCH("emit_items", k_emit_items, dim3(grid_for(total)), dim3(kT), 0, st, usc.as<uint32_t>() + r0,
+                crow + r0, nr, total, w.tbeg, w.tend, w.tprefix, hrow_ptr, w.items[c]);
+      make_bundles(w, own, c, h.cw16[c], st);
+    }
+    TC_HIP(hipGetLastError());
+  }
+}
+
+}  // namespace
+
 void build_work(WorkSet& w, Owned& own, int64_t n, const int64_t* hrow_ptr, int64_t T,
                 const uint32_t* tb_row, const int64_t* tb_ptr, const uint64_t* tb_val,
                 const uint64_t* tb_prefix, int64_t b16, const WorkParams& wp, hipStream_t st, bool all_rows) {
@@ -1392,9 +2195,12 @@ void build_work(WorkSet& w, Owned& own, int64_t n, const int64_t* hrow_ptr, int6
   DevBuf dscal(64);
   uint32_t* d_tot32 = dscal.as<uint32_t>();
   uint64_t* d_tot64 = reinterpret_cast<uint64_t*>(dscal.as<char>() + 32);
-  // rows without tasks keep the empty range [0, 0)
-  TC_LAUNCH("fill_u32", k_fill_u32, dim3(grid_for(n)), dim3(kT), 0, st, w.tbeg, n, 0u);
-  TC_LAUNCH("fill_u32", k_fill_u32, dim3(grid_for(n)), dim3(kT), 0, st, w.tend, n, 0u);
+  const bool small = T > 0 && n <= kSmallN;
+  if (!small) {
+    // rows without tasks keep the empty range [0, 0)
+    TC_LAUNCH("fill_u32", k_fill_u32, dim3(grid_for(n)), dim3(kT), 0, st, w.tbeg, n, 0u);
+    TC_LAUNCH("fill_u32", k_fill_u32, dim3(grid_for(n)), dim3(kT), 0, st, w.tend, n, 0u);
+  }
   if (T == 0) {
     TC_HIP(hipMemsetAsync(w.tprefix, 0, sizeof(uint64_t), st));
     w.probes = 0;
@@ -1411,6 +2217,11 @@ void build_work(WorkSet& w, Owned& own, int64_t n, const int64_t* hrow_ptr, int6
   TC_LAUNCH("classify", k_classify, dim3(grid_reduce(n)), dim3(kT), 0, st, tb_ptr, tb_prefix, hrow_ptr, n,
             all_rows, wp.heavy_min, std::min(wp.heavy_min, kShortHeavyMin), b16, cls.as<int8_t>(), d_cl, d_cw);
   TC_HIP(hipGetLastError());
+  if (small) {
+    build_work_small(w, own, n, hrow_ptr, T, tb_row, tb_ptr, tb_val, tb_prefix, st, cls.as<int8_t>(), d_cp, d_cw,
+                     d_cl);
+    return;
+  }
   struct {
     unsigned long long cw[NUM_CLASSES], cw16[NUM_CLASSES];
     int cl[NUM_CLASSES];
@@ -1461,12 +2272,7 @@ void build_work(WorkSet& w, Owned& own, int64_t n, const int64_t* hrow_ptr, int6
     for (int c = CLS_WG_SMALL; c < NUM_CLASSES; ++c) cw16 += hc.cw16[c];
     const uint64_t bundle_w = w.bundle_w = bundle_weight(cw16);
     cmi.chunk16 = (uint32_t)std::min<uint64_t>(wp.wave_chunk, bundle_w / kWaves);
-    for (int c = 0; c < NUM_CLASSES; ++c) {
-      const uint64_t per_group = wp.min_groups ? h_cw[c] / ((uint64_t)wp.min_groups * class_waves(c)) : ~0ull;
-      cmi.chunk[c] = per_group < kWaveChunkMin ? wp.wave_chunk
-                                                : (uint32_t)std::min<uint64_t>(wp.wave_chunk, per_group);
-      w.cls_chunk[c] = cmi.chunk[c];
-    }
+    for (int c = 0; c < NUM_CLASSES; ++c) w.cls_chunk[c] = cmi.chunk[c] = class_chunk(h_cw[c], c, wp);
     device_excl_scan_f<uint32_t>(cmi, usc.as<uint32_t>(), R,
                                  usc.as<uint32_t>() + R, st);
     DevBuf cm_pos(sizeof(uint32_t) * (size_t)n);
@@ -1565,15 +2371,7 @@ void build_work(WorkSet& w, Owned& own, int64_t n, const int64_t* hrow_ptr, int6
         w.items[c] = items;
         w.n_items[c] = total;
         w.n_items32[c] = (int64_t)h.item16[c] - (int64_t)h.item[c];
-        const int64_t groups = (total - w.n_items32[c]) / kWaves;
-        if (groups > 0) {
-          const uint64_t per = bundle_w / 2;  // units
-          w.n_bundles[c] = div_up((int64_t)(hc.cw16[c] / 2), (int64_t)per);
-          w.bundle[c] = own.alloc<uint32_t>(w.n_bundles[c] + 1);
-          TC_LAUNCH("bundles", k_bundles, dim3(grid_for(groups)), dim3(kT), 0, st, items + w.n_items32[c], groups,
-                    per, w.n_bundles[c], w.bundle[c]);
-          TC_HIP(hipGetLastError());
-        }
+        make_bundles(w, own, c, hc.cw16[c], st);
       }
     }
   }

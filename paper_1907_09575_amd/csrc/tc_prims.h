@@ -5,6 +5,7 @@
 // All kernels use 256-thread work-groups (4 wave64 waves).
 #pragma once
 
+#include <algorithm>
 #include <string>
 #include <type_traits>
 #include <utility>
@@ -220,6 +221,8 @@ struct TempCtx {
   bool active = false;
   hipStream_t st = nullptr;
   int* fail = nullptr;
+  char* zero = nullptr;  // device memory already cleared on st, for the sorts' look-back words
+  size_t zero_left = 0;
 };
 TempCtx& temp_ctx();
 
@@ -228,6 +231,12 @@ struct TempStream {
   void* fail_word = nullptr;
   explicit TempStream(hipStream_t st);
   ~TempStream();
+  // `bytes` at p, cleared on the scope's stream and kept until it ends: small
+  // sorts take their look-back words from it instead of clearing their own.
+  void zero_pool(char* p, size_t bytes) {
+    temp_ctx().zero = p;
+    temp_ctx().zero_left = bytes;
+  }
   TempStream(const TempStream&) = delete;
   TempStream& operator=(const TempStream&) = delete;
 };
@@ -427,7 +436,9 @@ constexpr int kSortPassesMax = 8;
 // Look-back words of all passes of a sort up to this size are cleared by
 // one memset (see radix_sort_cfg).
 constexpr size_t kLbClearOnceBytes = (size_t)4 << 20;
+constexpr size_t kZeroPool = (size_t)2 << 20;  // look-back words of a small graph's sorts
 constexpr uint32_t kLbSpinMax = 1u << 16;
+constexpr int64_t kRawCountTiles = 256;
 constexpr int kLbWin = 4;  // predecessors read per look-back step
 
 template <class W>
@@ -559,7 +570,7 @@ __global__ __launch_bounds__(256) void k_rs_onesweep(const K* __restrict__ kin, 
                                                      const uint32_t* __restrict__ bucket,
                                                      W* __restrict__ status,
                                                      uint32_t* __restrict__ ticket, int* __restrict__ fail,
-                                                     Epi epi, Src src = Src{}) {
+                                                     bool raw_counts, Epi epi, Src src = Src{}) {
   constexpr int TILE = 256 * KPT;
   constexpr int WCH = 64 * KPT;  // keys of the tile each wave ranks (a contiguous quarter)
   constexpr bool HV = !std::is_same<V, NoVal>::value;
@@ -572,6 +583,7 @@ __global__ __launch_bounds__(256) void k_rs_onesweep(const K* __restrict__ kin, 
   __shared__ uint32_t s_tmp[4];
   __shared__ uint32_t s_tile;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  uint32_t my_bucket = bucket[tid];  // where digit tid starts (raw_counts: how many there are)
   if (tid == 0) s_tile = atomicAdd(ticket, 1u);
 #pragma unroll
   for (int w = 0; w < 4; ++w) s_cnt[w][tid] = 0;
@@ -640,6 +652,10 @@ __global__ __launch_bounds__(256) void k_rs_onesweep(const K* __restrict__ kin, 
   __hip_atomic_store(my, tile == 0 ? (TOP | (W)cnt) : (W)cnt + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   uint32_t tot;
   s_tstart[tid] = block_excl_scan(cnt, s_tmp, tot);
+  if (raw_counts) {
+    uint32_t all;
+    my_bucket = block_excl_scan(my_bucket, s_tmp, all);
+  }
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < KPT; ++i) {
@@ -651,7 +667,7 @@ __global__ __launch_bounds__(256) void k_rs_onesweep(const K* __restrict__ kin, 
     }
   }
   if (tile == 0) {
-    s_goff[tid] = bucket[tid];
+    s_goff[tid] = my_bucket;
   } else {
     // walk back WIN predecessors per step (their words are read together):
     // add counts from the nearest one until an inclusive prefix; stop at a
@@ -688,7 +704,7 @@ __global__ __launch_bounds__(256) void k_rs_onesweep(const K* __restrict__ kin, 
       }
     }
     __hip_atomic_store(my, TOP | (W)(excl + cnt), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_goff[tid] = bucket[tid] + (uint32_t)excl;
+    s_goff[tid] = my_bucket + (uint32_t)excl;
   }
   __syncthreads();
   // keys of the tile
@@ -731,7 +747,8 @@ constexpr int rs_default_kpt() {
 // buffers. The last pass calls epi(final position, key) for every key (no
 // pass runs, and epi is not called, when n <= 1). hist: the keys' digit
 // counts ([passes][256], from a DigitCounter in the producing kernel; it is
-// scanned in place; hist_scanned: it already holds each pass's exclusive
+// scanned in place, except by a sort of at most kRawCountTiles tiles
+// without leave_starts; hist_scanned: it already holds each pass's exclusive
 // digit starts, as a sort leaves them), or nullptr to count them here.
 //
 // With a source (src != nullptr), the n keys are those that *src selects
@@ -746,7 +763,8 @@ template <class K, class V, int KPT, class W, int WIN = kLbWin, class Epi = NoEp
           int KPT_SRC = KPT>
 bool radix_sort_cfg(K* keys, K* keys_alt, V* vals, V* vals_alt, int64_t n, int bit_lo, int bit_hi,
                     hipStream_t st, const char* name, Epi epi = Epi{}, uint32_t* hist = nullptr,
-                    const Src* src = nullptr, int64_t n_in = 0, bool hist_scanned = false) {
+                    const Src* src = nullptr, int64_t n_in = 0, bool hist_scanned = false,
+                    bool leave_starts = false) {
   constexpr int TILE = 256 * KPT;
   const char* n_digits = intern_name(std::string("rs_digits:") + name);
   const char* n_pass = intern_name(std::string("rs_pass:") + name);
@@ -775,18 +793,32 @@ bool radix_sort_cfg(K* keys, K* keys_alt, V* vals, V* vals_alt, int64_t n, int b
   const size_t region = sizeof(W) * (size_t)pass_words;
   const bool clear_once = (size_t)passes * region <= kLbClearOnceBytes;
   const size_t hist_bytes = hist ? 0 : sizeof(uint32_t) * 256 * kSortPassesMax;
-  DevBuf work(hist_bytes + (clear_once ? (size_t)passes : 1) * region);
-  char* lb0 = work.as<char>() + hist_bytes;
-  if (clear_once) TC_HIP(hipMemsetAsync(work.p, 0, work.bytes, st));
+  const size_t work_bytes = hist_bytes + (clear_once ? (size_t)passes : 1) * region;
+  DevBuf work;
+  char* wp = nullptr;
+  if (clear_once && work_bytes <= temp_ctx().zero_left) {
+    wp = temp_ctx().zero;
+    const size_t taken = std::min(temp_ctx().zero_left, (work_bytes + 255) & ~(size_t)255);
+    temp_ctx().zero += taken;
+    temp_ctx().zero_left -= taken;
+  } else {
+    work.alloc(work_bytes);
+    wp = work.as<char>();
+    if (clear_once) TC_HIP(hipMemsetAsync(wp, 0, work_bytes, st));
+  }
+  char* lb0 = wp + hist_bytes;
   uint32_t* gh = hist;
   if (!gh) {
-    gh = work.as<uint32_t>();
+    gh = reinterpret_cast<uint32_t*>(wp);
     if (!clear_once) TC_HIP(hipMemsetAsync(gh, 0, sizeof(uint32_t) * 256 * (size_t)passes, st));
     const unsigned dgrid = (unsigned)std::min<int64_t>(2048, div_up(n, 256 * 16));
     TC_LAUNCH(n_digits, (k_rs_digits<K>), dim3(dgrid), dim3(256), digit_lds_bytes(bit_lo, bit_hi), st, keys,
               n, bit_lo, bit_hi, gh);
   }
-  if (!hist_scanned) TC_LAUNCH("rs_buckets", k_rs_buckets, dim3(1), dim3(256), 0, st, gh, passes);
+  // the digit starts: scanned by a kernel of their own, or, in a sort of few
+  // tiles, by every tile for itself (one launch less)
+  const bool raw_counts = !hist_scanned && !leave_starts && std::max(ntiles, ntiles_in) <= kRawCountTiles;
+  if (!hist_scanned && !raw_counts) TC_LAUNCH("rs_buckets", k_rs_buckets, dim3(1), dim3(256), 0, st, gh, passes);
   K* ka = keys;
   K* kb = keys_alt;
   V* va = vals;
@@ -803,20 +835,20 @@ bool radix_sort_cfg(K* keys, K* keys_alt, V* vals, V* vals_alt, int64_t n, int b
     if (p == 0 && src) {  // from the source into keys/vals
       if (last)
         TC_LAUNCH(n_pass, (k_rs_onesweep<K, V, KPT_SRC, W, WIN, Epi, Src>), dim3((unsigned)ntiles_in), dim3(256), 0,
-                  st, nullptr, ka, nullptr, va, n_in, shift, dmask, gh, words + pad, ticket, fail, epi, *src);
+                  st, nullptr, ka, nullptr, va, n_in, shift, dmask, gh, words + pad, ticket, fail, raw_counts, epi, *src);
       else
         TC_LAUNCH(n_pass, (k_rs_onesweep<K, V, KPT_SRC, W, WIN, NoEpi, Src>), dim3((unsigned)ntiles_in), dim3(256),
-                  0, st, nullptr, ka, nullptr, va, n_in, shift, dmask, gh, words + pad, ticket, fail, NoEpi{},
-                  *src);
+                  0, st, nullptr, ka, nullptr, va, n_in, shift, dmask, gh, words + pad, ticket, fail, raw_counts,
+                  NoEpi{}, *src);
       TC_HIP(hipGetLastError());
       continue;
     }
     if (!last)
       TC_LAUNCH(n_pass, (k_rs_onesweep<K, V, KPT, W, WIN, NoEpi>), dim3((unsigned)ntiles), dim3(256), 0, st, ka,
-                kb, va, vb, n, shift, dmask, gh + 256 * p, words + pad, ticket, fail, NoEpi{});
+                kb, va, vb, n, shift, dmask, gh + 256 * p, words + pad, ticket, fail, raw_counts, NoEpi{});
     else
       TC_LAUNCH(n_pass, (k_rs_onesweep<K, V, KPT, W, WIN, Epi>), dim3((unsigned)ntiles), dim3(256), 0, st, ka,
-                kb, va, vb, n, shift, dmask, gh + 256 * p, words + pad, ticket, fail, epi);
+                kb, va, vb, n, shift, dmask, gh + 256 * p, words + pad, ticket, fail, raw_counts, epi);
     TC_HIP(hipGetLastError());
     std::swap(ka, kb);
     std::swap(va, vb);
@@ -851,15 +883,15 @@ bool radix_sort(K* keys, K* keys_alt, V* vals, V* vals_alt, int64_t n, int bit_l
 template <class K, class V, class Src, int KPT_SRC = rs_default_kpt<K, V>(), class Epi = NoEpi>
 bool radix_sort_from(const Src& src, int64_t n_in, K* keys, K* keys_alt, V* vals, V* vals_alt, int64_t n,
                      int bit_lo, int bit_hi, uint32_t* hist, hipStream_t st, const char* name,
-                     Epi epi = Epi{}, bool hist_scanned = false) {
+                     Epi epi = Epi{}, bool hist_scanned = false, bool leave_starts = false) {
   constexpr int KPT = rs_default_kpt<K, V>();
   if (n < ((int64_t)1 << 31) && !sort_wide_words_forced())
     return radix_sort_cfg<K, V, KPT, uint32_t, kLbWin, Epi, Src, KPT_SRC>(keys, keys_alt, vals, vals_alt, n,
                                                                           bit_lo, bit_hi, st, name, epi, hist,
-                                                                          &src, n_in, hist_scanned);
+                                                                          &src, n_in, hist_scanned, leave_starts);
   return radix_sort_cfg<K, V, KPT, uint64_t, kLbWin, Epi, Src, KPT_SRC>(keys, keys_alt, vals, vals_alt, n,
                                                                         bit_lo, bit_hi, st, name, epi, hist,
-                                                                        &src, n_in, hist_scanned);
+                                                                        &src, n_in, hist_scanned, leave_starts);
 }
 
 // Throws TC_EDEVICE if a sort of the current TempStream scope gave up waiting
