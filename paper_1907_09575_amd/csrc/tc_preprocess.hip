@@ -1,12 +1,14 @@
 // tc_preprocess.hip - device preprocessing (Section 5.3 of the paper, on one GPU).
 //
 // Pipeline, all on the caller's stream:
-//   1. canonical keys: each pair {u, v}, u != v, becomes min(u,v) * 2^s + max(u,v)
-//      (s = ceil(log2 n)); self loops and invalid ids become a sentinel.
-//   2. stable LSD radix sort of the 2s-bit keys: the distinct keys (those
-//      that differ from their predecessor and are not the sentinel) are the
-//      simple undirected graph of Section 2 / Section 6.1; they are selected
-//      from the sorted keys by each later reader, never copied out.
+//   1. keys: each pair {u, v}, u != v, becomes a 2s-bit key of min(u,v) and
+//      max(u,v) (s = ceil(log2 n)); self loops are marked (small graphs: a
+//      sentinel).
+//   2. stable LSD radix sort of the keys by as many of their top bits as leave
+//      groups that fit a hash set in LDS, which finds the duplicates (small
+//      graphs: by all bits, and by comparing neighbours): the distinct keys
+//      are the simple undirected graph of Section 2 / Section 6.1; they are
+//      selected from the sorted keys by each later reader, never copied out.
 //   3. degrees counted in LDS per vertex range: lower endpoints from the
 //      sorted keys, upper endpoints from a radix partition of them by their
 //      top bits; rank = position in the order (degree, id)
@@ -67,14 +69,71 @@ struct CanonSrc {
   }
 };
 
-// Digit counts of the canonical keys for every pass of the dedup sort, and
-// the id check, in one read of the raw pairs (grid-stride, kDigitBatch pairs
-// in flight per thread; one LDS histogram flush per work-group).
-__global__ __launch_bounds__(256) void k_canon_digits(CanonSrc cs, int64_t m, int key_bits,
+// Keys take at most 62 bits (s <= 31); bit 63 marks one that is no distinct
+// edge (a duplicate, a self loop).
+constexpr uint64_t kDupMark = 1ull << 63;
+
+// The edge {lo, hi} as a 2s-bit key for a sort that only has to bring equal
+// edges close together: the upper s - low bits of lo, then s bits that mix hi
+// with the low bits of lo (x = hi c1 + lo_low c2 mod 2^s, c1 odd: hi is
+// recovered from x and lo_low), then the low bits of lo. Sorted by its top
+// bits alone, such a key is grouped by an interval of lo (the degree count
+// finds its lower endpoints by it) and, within it, by a hash that spreads
+// any vertex's edges evenly.
+struct MixCode {
+  static constexpr uint32_t c1 = 0x9E3779B1u, c2 = 0x6A09E667u;  // 2^32 / golden ratio (odd); fraction of sqrt 2
+  static constexpr uint32_t inverse(uint32_t c) {  // mod 2^32 (Newton: bits double)
+    uint32_t x = c;
+    for (int i = 0; i < 5; ++i) x *= 2u - c * x;
+    return x;
+  }
+  int s, low;
+  __device__ uint64_t key(uint32_t lo, uint32_t hi) const {
+    const uint32_t l = lo & ((1u << low) - 1u), mask = (1u << s) - 1u;
+    return ((uint64_t)(lo >> low) << (s + low)) | ((uint64_t)((hi * c1 + l * c2) & mask) << low) | l;
+  }
+  __device__ uint32_t lo(uint64_t k) const {  // (of a marked key too)
+    return ((uint32_t)((k & ~kDupMark) >> (s + low)) << low) | ((uint32_t)k & ((1u << low) - 1u));
+  }
+  __device__ uint32_t hi(uint64_t k) const {
+    constexpr uint32_t c1inv = inverse(c1);
+    static_assert(c1 * c1inv == 1u, "inverse of c1");
+    const uint32_t l = (uint32_t)k & ((1u << low) - 1u);
+    return (((uint32_t)(k >> low) - l * c2) * c1inv) & ((1u << s) - 1u);
+  }
+};
+
+// The dedup sort's source beyond small graphs: raw pair i as its mixed key,
+// marked if it is a self loop (which spread over the groups like any edge)
+// or holds an id outside [0, n) (reported by the digit counts).
+struct MixSrc {
+  const int32_t* src;
+  const int32_t* dst;
+  int64_t n;
+  MixCode mc;
+  __device__ uint64_t key(int64_t i, bool& bad) const {
+    const int64_t u = src[i], v = dst[i];
+    bad = (u < 0) | (u >= n) | (v < 0) | (v >= n);
+    const uint64_t k = mc.key((uint32_t)(u < v ? u : v), (uint32_t)(u < v ? v : u));
+    return bad ? kDupMark : u == v ? k | kDupMark : k;
+  }
+  __device__ bool operator()(int64_t i, uint64_t& k, char&) const {
+    bool bad;
+    k = key(i, bad);
+    return true;
+  }
+};
+
+// Digit counts of the keys for every pass of the dedup sort (bits [bit_lo,
+// bit_hi)), and the id check, in one read of the raw pairs (grid-stride,
+// kDigitBatch pairs in flight per thread; one LDS histogram flush per
+// work-group).
+template <class Src>
+__global__ __launch_bounds__(256) void k_canon_digits(Src cs, int64_t m, int bit_lo, int bit_hi,
                                                       uint32_t* __restrict__ ghist, int* __restrict__ err) {
   extern __shared__ uint32_t h_dyn[];
   DigitCounter dc;
-  dc.init(h_dyn, 0, key_bits);
+  dc.init(h_dyn, bit_lo, bit_hi);
   bool bad_any = false;
   const int64_t stride = (int64_t)gridDim.x * 256 * kDigitBatch;
   for (int64_t base = (int64_t)blockIdx.x * 256 * kDigitBatch + threadIdx.x; base < m; base += stride) {
@@ -96,51 +155,45 @@ __global__ __launch_bounds__(256) void k_canon_digits(CanonSrc cs, int64_t m, in
   dc.flush(ghist);
 }
 
-// Distinct keys of the sorted canonical keys S (duplicates adjacent, the
-// sentinel for dropped self loops last): position i holds one iff S[i] is
-// not the sentinel and differs from S[i - 1]. The distinct keys are never
-// written out. k_distinct_mark finds them by comparing neighbours and marks
-// every other key with bit 63 (keys take at most 62 bits: s <= 31); later
-// readers (the degree count, its partition and the orientation) then select
-// a key by its own word alone (DistinctSel) and mask the mark off where
-// they use an unselected key's bits.
-constexpr uint64_t kDupMark = 1ull << 63;
-
+// Distinct edges of S, the mixed keys sorted by their top bits or by all of
+// them: the unmarked ones. They are never copied out: k_distinct_groups (or
+// k_distinct_mark) marks duplicates with kDupMark, and later readers (the
+// degree count, its partition and the orientation) select a key by its own
+// word alone and mask the mark off where they use an unselected key's bits.
 struct DistinctSel {
   const uint64_t* S;
-  uint64_t sent;
   __device__ bool operator()(int64_t i, uint64_t& k) const {
     k = S[i];
-    return ((k & kDupMark) == 0) & (k != sent);
+    return (k & kDupMark) == 0;
   }
 };
 
 // The degree partition's source: the upper endpoint of each distinct key.
 struct DistinctHiSrc {
   DistinctSel d;
-  int s;
+  MixCode mc;
   __device__ bool operator()(int64_t i, uint32_t& hi, char&) const {
     uint64_t k;
     const bool ok = d(i, k);
-    hi = (uint32_t)(k & ((1ull << s) - 1));
+    hi = mc.hi(k);
     return ok;
   }
 };
 
-// Distinct keys of S marked (see above) and counted, with the digit counts
-// of their upper endpoints for the degree partition's passes (bits
-// [bit_lo, s)), in one read of S. A neighbour may have marked S[i - 1]
-// already: keys are compared with the mark masked off.
-__global__ __launch_bounds__(256) void k_distinct_mark(uint64_t* __restrict__ S, uint64_t sent, int64_t m_raw,
-                                                       int bit_lo, int s, uint32_t* __restrict__ ghist,
+// Duplicates of a fully sorted S marked (a key that equals its predecessor),
+// distinct keys counted, with the digit counts of their upper endpoints for
+// the degree partition's passes (bits [bit_lo, s)), in one read of S. A
+// neighbour may have marked S[i - 1] already: keys are compared with the
+// mark masked off.
+__global__ __launch_bounds__(256) void k_distinct_mark(uint64_t* __restrict__ S, MixCode mc, int64_t m_raw,
+                                                       int bit_lo, uint32_t* __restrict__ ghist,
                                                        unsigned long long* __restrict__ total) {
   extern __shared__ uint32_t h_dyn[];
   __shared__ uint32_t s_c;
   if (threadIdx.x == 0) s_c = 0;
   DigitCounter dc;
-  dc.init(h_dyn, bit_lo, s);  // (ends with a barrier)
+  dc.init(h_dyn, bit_lo, mc.s);  // (ends with a barrier)
   uint32_t c = 0;
-  const uint64_t mask = (1ull << s) - 1;
   const int64_t stride = (int64_t)gridDim.x * 256 * kDigitBatch;
   for (int64_t base = (int64_t)blockIdx.x * 256 * kDigitBatch + threadIdx.x; base < m_raw; base += stride) {
     uint64_t k[kDigitBatch], prev[kDigitBatch];
@@ -154,9 +207,9 @@ __global__ __launch_bounds__(256) void k_distinct_mark(uint64_t* __restrict__ S,
 #pragma unroll
     for (int j = 0; j < kDigitBatch; ++j) {
       const int64_t i = base + (int64_t)j * 256;
-      if (i < m_raw && k[j] != sent) {
+      if (i < m_raw && !(k[j] & kDupMark)) {
         if (i == 0 || (prev[j] & ~kDupMark) != k[j]) {
-          dc.add((uint32_t)(k[j] & mask));
+          dc.add(mc.hi(k[j]));
           ++c;
         } else {
           S[i] = k[j] | kDupMark;
@@ -167,6 +220,116 @@ __global__ __launch_bounds__(256) void k_distinct_mark(uint64_t* __restrict__ S,
   if (c) atomicAdd(&s_c, c);
   dc.flush(ghist);  // (starts with a barrier: s_c is complete)
   if (threadIdx.x == 0 && s_c) atomicAdd(total, (unsigned long long)s_c);
+}
+
+// The same for an S that is sorted by the bits from gshift up only: keys that
+// agree there (a group) are adjacent, in any order. A tile's work-group takes
+// the groups that begin in its kGrpTile keys (the first may have begun
+// before: skipped; the last may run on past the tile: read on) and enters
+// their keys into a hash set in LDS, whose words are 11 bits of the key's
+// hash and its position in the tile + 1: the first to claim a word is the
+// distinct key, and one whose word already holds an equal key is marked.
+// What a group may hold: the sort's bits are chosen so that even edges that
+// all share one interval of lo average at most kGrpMean keys a group, so a
+// tile and a group fit the set; a group of more than kGrpMax keys (one edge
+// that often), or a set that is full all the same, sets *fail, and the host
+// sorts by all bits instead.
+// Two or three passes of the sort, of 1.28 ms each at scale 24 (256 M pairs),
+// become LDS work of the read that the mark needs anyway.
+constexpr int kGrpThreads = 1024;
+constexpr int kGrpKeys = 4;  // per thread
+constexpr int kGrpTile = kGrpThreads * kGrpKeys;
+constexpr int kGrpSlots = 16384;  // 64 KiB: two work-groups a CU
+constexpr int kGrpMeanLog2 = 13;
+constexpr int64_t kGrpMax = (int64_t)1 << 20;  // (positions take 21 bits)
+constexpr int kGrpAhead = 64;  // keys past the tile read with it
+
+__global__ __launch_bounds__(kGrpThreads, 8) void k_distinct_groups(uint64_t* S, MixCode mc, int64_t m_raw, int gshift,
+                                                                    int bit_lo, uint32_t* __restrict__ ghist,
+                                                                    unsigned long long* __restrict__ total,
+                                                                    int* __restrict__ fail) {
+  extern __shared__ uint32_t h_dyn[];
+  __shared__ int4 s_tab4[kGrpSlots / 4];
+  __shared__ uint32_t s_c;
+  uint32_t* const tab = reinterpret_cast<uint32_t*>(s_tab4);
+  const int tid = threadIdx.x;
+  if (tid == 0) s_c = 0;
+  DigitCounter dc;
+  dc.init(h_dyn, bit_lo, mc.s);
+  uint32_t c = 0;
+  auto group = [&](uint64_t k) -> uint64_t { return (k & ~kDupMark) >> gshift; };
+  auto at = [&](int64_t i) -> uint64_t { return S[i < m_raw ? i : m_raw - 1]; };
+  const int64_t ntiles = (m_raw + kGrpTile - 1) / kGrpTile;
+  int64_t t = blockIdx.x;
+  uint64_t nk[kGrpKeys], n_ahead, n_before, n_last, n_far;  // the next tile's loads
+  auto load = [&](int64_t tt) {
+    const int64_t i0 = tt * kGrpTile;
+#pragma unroll
+    for (int j = 0; j < kGrpKeys; ++j) nk[j] = at(i0 + j * kGrpThreads + tid);
+    n_ahead = at(i0 + kGrpTile + (tid & (kGrpAhead - 1)));
+    n_before = S[i0 > 0 ? i0 - 1 : 0];
+    n_last = at(i0 + kGrpTile - 1);
+    n_far = at(i0 + kGrpTile + kGrpAhead - 1);
+  };
+  if (t < ntiles) load(t);
+  for (; t < ntiles; t += gridDim.x) {
+    const int64_t i0 = t * kGrpTile;
+    uint64_t k[kGrpKeys];
+#pragma unroll
+    for (int j = 0; j < kGrpKeys; ++j) k[j] = nk[j];
+    const uint64_t ahead = n_ahead, last = group(n_last), far = group(n_far);
+    // (no group is all ones: it would need lo = 2^s - 1)
+    const uint64_t before = t == 0 ? ~0ull : group(n_before);
+    if (t + gridDim.x < ntiles) load(t + gridDim.x);
+#pragma unroll
+    for (int j = 0; j < kGrpSlots / 4 / kGrpThreads; ++j) s_tab4[j * kGrpThreads + tid] = make_int4(0, 0, 0, 0);
+    __syncthreads();
+    auto enter = [&](uint64_t key, int64_t i) {
+      uint32_t h = (uint32_t)key * 0x9E3779B1u ^ (uint32_t)(key >> 32) * 0x6A09E667u;
+      h = (h ^ (h >> 15)) * 0x510E527Fu;
+      h ^= h >> 16;
+      uint32_t slot = h >> 18;
+      const uint32_t word = (h << 21) | (uint32_t)(i - i0 + 1);
+      for (int probes = 0; probes < kGrpSlots; ++probes, slot = (slot + 1) & (kGrpSlots - 1)) {
+        const uint32_t old = atomicCAS(&tab[slot], 0u, word);
+        if (old == 0) {
+          dc.add(mc.hi(key));
+          ++c;
+          return;
+        }
+        // (the owner of a word is never marked)
+        if (((old ^ word) >> 21) == 0 && S[i0 + (old & 0x1FFFFFu) - 1] == key) {
+          S[i] = key | kDupMark;
+          return;
+        }
+      }
+      atomicOr(fail, 1);
+    };
+#pragma unroll
+    for (int j = 0; j < kGrpKeys; ++j) {
+      const int64_t i = i0 + j * kGrpThreads + tid;
+      if (i < m_raw && !(k[j] & kDupMark) && group(k[j]) != before) enter(k[j], i);
+    }
+    if (last != before) {  // the tile's last group, past the tile
+      int64_t i = i0 + kGrpTile + tid;
+      if (tid < kGrpAhead && i < m_raw && !(ahead & kDupMark) && group(ahead) == last) enter(ahead, i);
+      bool on = far == last;  // (uniform)
+      for (int64_t base = i0 + kGrpTile + kGrpAhead; on && base < m_raw; base += kGrpThreads) {
+        if (base - i0 > kGrpMax) {
+          if (tid == 0) atomicOr(fail, 1);
+          break;
+        }
+        i = base + tid;
+        const uint64_t key = at(i);
+        on = group(at(base + kGrpThreads - 1)) == last;
+        if (i < m_raw && !(key & kDupMark) && group(key) == last) enter(key, i);
+      }
+    }
+    __syncthreads();
+  }
+  if (c) atomicAdd(&s_c, c);
+  dc.flush(ghist);  // (starts with a barrier: s_c is complete)
+  if (tid == 0 && s_c) atomicAdd(total, (unsigned long long)s_c);
 }
 
 // Entry i of U (row a, column b) starts a task iff U_a has entries after i
@@ -266,11 +429,12 @@ __global__ void k_fill_i64(int64_t* p, int64_t n, int64_t v) {
 // hshift; bucket j at [start(j), start(j + 1)), start(j) = bs32[j] or bs64[j]
 // for j < nbs, m beyond). Each work-group counts one range [v0, v1) of at
 // most kDegBins vertices of one bucket in LDS: the upper endpoints from that
-// bucket's entries, the lower endpoints from the distinct keys of S in
-// [v0 << s, v1 << s) (S is sorted by lower endpoint; the range is found by
-// binary search), with kDegBatch loads in flight per thread before they are
-// counted. It writes the rank keys deg(v) << s | v of its vertices.
-constexpr int kDegBins = 32768;   // LDS counters of one work-group (128 KiB)
+// bucket's entries, the lower endpoints from the distinct keys of S whose lo
+// lies in [v0, v1) (S is sorted by lo >> mc.low, and v0 is a multiple of
+// 2^mc.low; the range is found by binary search), with kDegBatch loads in
+// flight per thread before they are counted. It writes the rank keys deg(v) << s | v of its vertices.
+constexpr int kDegBinsLog2 = 15;
+constexpr int kDegBins = 1 << kDegBinsLog2;   // LDS counters of one work-group (128 KiB)
 constexpr int kDegThreads = 1024;
 constexpr int kDegBatch = 8;
 
@@ -290,7 +454,7 @@ __global__ __launch_bounds__(kDegThreads) void k_degree_hist(const uint32_t* __r
                                                              const uint32_t* __restrict__ bs32,
                                                              const int64_t* __restrict__ bs64, int64_t nbs, int64_t m,
                                                              int hshift, int sub, DistinctSel d, int64_t m_raw,
-                                                             int64_t n, int s, uint64_t* __restrict__ rk) {
+                                                             int64_t n, MixCode mc, uint64_t* __restrict__ rk) {
   extern __shared__ uint32_t h_deg[];
   __shared__ int64_t s_r[2];
   const uint32_t bucket = blockIdx.x / (uint32_t)sub, part = blockIdx.x % (uint32_t)sub;
@@ -300,7 +464,11 @@ __global__ __launch_bounds__(kDegThreads) void k_degree_hist(const uint32_t* __r
   if (v0 >= v1) return;  // (uniform per work-group)
   const int nv = (int)(v1 - v0);
   for (int j = threadIdx.x; j < nv; j += blockDim.x) h_deg[j] = 0;
-  if (threadIdx.x < 2) s_r[threadIdx.x] = lower_bound_u64(d.S, m_raw, (uint64_t)(threadIdx.x ? v1 : v0) << s);
+  if (threadIdx.x < 2) {
+    // (v1 = n: up to the end of its interval, where no lo lies past it)
+    const uint64_t v = (uint64_t)(threadIdx.x ? v1 : v0) + ((1ull << mc.low) - 1);
+    s_r[threadIdx.x] = lower_bound_u64(d.S, m_raw, (v >> mc.low) << (mc.s + mc.low));
+  }
   __syncthreads();
   // upper endpoints
   auto start = [&](int64_t j) -> int64_t { return j >= nbs ? m : bs64 ? bs64[j] : (int64_t)bs32[j]; };
@@ -319,12 +487,11 @@ __global__ __launch_bounds__(kDegThreads) void k_degree_hist(const uint32_t* __r
     }
   }
   // lower endpoints: the distinct keys among S[r0, r1) all have lo in [v0, v1).
-  // A wave's 64 consecutive positions hold runs of equal lo (S is sorted):
-  // the first lane of each run adds the run's distinct keys with one atomic
-  // (one atomic per lane would serialise on a high-degree vertex's counter).
+  // The keys of a wave that share the first one's lo are added with one
+  // atomic (a vertex that most of a range's edges start at would otherwise
+  // take one lane at a time).
   const int64_t r0 = s_r[0], r1 = s_r[1];
   const int lane = threadIdx.x & 63;
-  const uint64_t below = (1ull << lane) - 1ull;  // lanes before this one
   // (wb, a wave's first position, is uniform across the wave: every lane
   // takes part in the ballots; lanes past r1 read S[r1 - 1] and select nothing)
   for (int64_t wb = r0 + (int64_t)(threadIdx.x - lane) * kDegBatch; wb < r1;
@@ -338,22 +505,20 @@ __global__ __launch_bounds__(kDegThreads) void k_degree_hist(const uint32_t* __r
     }
 #pragma unroll
     for (int b = 0; b < kDegBatch; ++b) {
-      const uint32_t lo = (uint32_t)((k[b] & ~kDupMark) >> s);
-      const uint32_t prev = (uint32_t)__shfl_up((int)lo, 1);
-      const uint64_t heads = __ballot(lane == 0 || prev != lo);
-      const uint64_t oks = __ballot(ok[b]);
-      if ((heads >> lane) & 1ull) {
-        const uint64_t after = heads & ~below & ~(1ull << lane);  // later heads
-        const uint64_t run = (after ? (after & (~after + 1ull)) - 1ull : ~0ull) & ~below;
-        const uint32_t c = (uint32_t)__popcll(oks & run);
-        if (c) atomicAdd(&h_deg[(int64_t)lo - v0], c);
+      const uint32_t lo = mc.lo(k[b]);
+      const uint32_t lead = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
+      const uint64_t same = __ballot(ok[b] && lo == lead);
+      if (lane == 0) {
+        if (same) atomicAdd(&h_deg[(int64_t)lo - v0], (uint32_t)__popcll(same));
+      } else if (ok[b] && lo != lead) {
+        atomicAdd(&h_deg[(int64_t)lo - v0], 1u);
       }
     }
   }
   __syncthreads();
   for (int j = threadIdx.x; j < nv; j += blockDim.x) {
     const int64_t v = v0 + j;
-    rk[v] = ((uint64_t)h_deg[j] << s) | (uint64_t)v;
+    rk[v] = ((uint64_t)h_deg[j] << mc.s) | (uint64_t)v;
   }
 }
 
@@ -376,21 +541,20 @@ __global__ void k_perm(const uint64_t* __restrict__ rk, int64_t n, int s, int32_
 // whole rank map. (1) One radix pass partitions the distinct edges by the
 // top 8 bits of their upper endpoint (the last digit pass of the degree
 // count's partition, whose scanned digit starts it reuses); its source reads
-// S in order, so the lower endpoints' ranks are read in nondecreasing vertex
-// order: element = rank(lo) << 32 | hi. (2) k_orient_hi reads the ranks of
+// S in order, so the lower endpoints' ranks are read interval by interval of
+// at most 32768 vertices (128 KiB of the map): element = rank(lo) << 32 | hi. (2) k_orient_hi reads the ranks of
 // the upper endpoints bucket by bucket (a bucket spans 2^(s-8) vertices: a
 // 256 KiB slice of the rank map at s = 24, 1 MiB at s = 26, which stays in
 // L2) and writes the oriented key in place.
 struct LoRankSrc {
   DistinctSel d;
   const int32_t* perm;
-  int s;
+  MixCode mc;
   __device__ bool operator()(int64_t i, uint64_t& k, char&) const {
     uint64_t e;
     const bool ok = d(i, e);
-    // (an unselected position may hold the sentinel, whose lower endpoint
-    // 2^s - 1 can lie past the rank map: read vertex 0 for it instead)
-    k = ((uint64_t)(uint32_t)perm[ok ? e >> s : 0] << 32) | (e & ((1ull << s) - 1));
+    // (an unselected key's lower endpoint is a vertex too)
+    k = ((uint64_t)(uint32_t)perm[mc.lo(e)] << 32) | mc.hi(e);
     return ok;
   }
 };
@@ -1676,7 +1840,7 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
   const uint64_t sent = (2 * s >= 64) ? ~0ull : ((1ull << (2 * s)) - 1);
 
   // Everything below that starts at zero, in one buffer cleared by one
-  // memset: 64 bytes of scalars (id error (int) at 0, distinct count m
+  // memset: 64 bytes of scalars (id error (int) at 0, dedup refused (int) at 4, distinct count m
   // (u64) at 8, W+ (u64) at 16, largest d+ (u32) at 24, task count (u32) at
   // 28: two host reads of 16 bytes), then the digit counts of the degree
   // partition (2 x 256), of the canonical keys, of the oriented keys and of
@@ -1693,6 +1857,7 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
   if (small) temps.zero_pool(zs.as<char>() + pool_at, kZeroPool);
   char* const zb = zs.as<char>();
   int* d_err = reinterpret_cast<int*>(zb);
+  int* d_refused = reinterpret_cast<int*>(zb + 4);
   unsigned long long* d_m = reinterpret_cast<unsigned long long*>(zb + 8);
   unsigned long long* d_wplus = reinterpret_cast<unsigned long long*>(zb + 16);
   unsigned int* d_maxd = reinterpret_cast<unsigned int*>(zb + 24);
@@ -1703,11 +1868,11 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
   uint32_t* const th = ohist + kHistWords;
 
   // ---- 1-2: simple graph -------------------------------------------------
-  // The canonical keys are sorted (duplicates adjacent, self loops as the
-  // sentinel, which sorts last) into S; the distinct keys are never written
-  // out: the degree count, its partition and the orientation select them
-  // from S (DistinctSel). The other sort buffer later holds the oriented
-  // keys, and S's buffer is the orient sort's ping-pong partner.
+  // The keys are sorted (duplicates close together) into S; the distinct keys
+  // are never written out: the degree count, its partition and the
+  // orientation select them from S (DistinctSel). The other sort buffer later
+  // holds the oriented keys, and S's buffer is the orient sort's ping-pong
+  // partner.
   int64_t m = 0;
   DevBuf ka(sizeof(uint64_t) * (size_t)std::max<int64_t>(m_raw, 1));
   DevBuf kb(sizeof(uint64_t) * (size_t)std::max<int64_t>(m_raw, 1));
@@ -1719,43 +1884,68 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
   // the orientation's partition)
   const int hshift = s <= 8 ? 0 : s <= 24 ? s - 8 : s - 16;
   const int hpasses = digit_passes(hshift, s);
-  {
-    // canonical keys are built by the first pass of the dedup sort from the
-    // raw pairs (7168-pair tiles: the largest whose registers allow two
-    // waves per SIMD); one read of the pairs before it counts their digits
-    // and checks the ids
+  // mixed keys: intervals of lo as the degree count's ranges begin at
+  const MixCode mc{s, std::min(hshift, kDegBinsLog2)};
+  // Passes over the top 8 bits each that leave at most 2^kGrpMeanLog2 keys a
+  // group on average if all edges shared one interval of lo (the mixed bits
+  // are even). Preprocessing and count: 53.6 -> 50.6 ms at scale 24 (3 passes
+  // instead of 6), 4031 -> 3819 us at scale 20 and 2564 -> 2449 us for a
+  // million vertices of equal degree (3 instead of 5).
+  int gpasses = digit_passes(0, s - mc.low);
+  while (8 * gpasses < 2 * s && m_raw > (int64_t)1 << std::min(62, 8 * gpasses + kGrpMeanLog2 - (s - mc.low)))
+    ++gpasses;
+  for (bool grouped = !small && 8 * gpasses < 2 * s;; grouped = false) {
+    // the keys are built by the first pass of the dedup sort from the raw
+    // pairs (7168-pair tiles: the largest whose registers allow two waves per
+    // SIMD); one read of the pairs before it counts their digits and checks
+    // the ids
     const CanonSrc csrc{d_src, d_dst, n, s, sent};
+    const MixSrc msrc{d_src, d_dst, n, mc};
+    const int bit_lo = grouped ? 2 * s - 8 * gpasses : 0;
+    const unsigned pblocks = (unsigned)std::min<int64_t>(kProducerBlocks, div_up(m_raw, kT * kDigitBatch));
     if (m_raw > 0 && block_sorts) {
       TC_LAUNCH_BLOCK("small_dedup", k_small_dedup, m_raw, st, csrc, (int)m_raw, ka.as<uint64_t>(), d_err);
-    } else if (m_raw > 0) {
-      TC_LAUNCH("canon_digits", k_canon_digits,
-                dim3((unsigned)std::min<int64_t>(kProducerBlocks, div_up(m_raw, kT * kDigitBatch))), dim3(kT),
-                digit_lds_bytes(0, 2 * s), st, csrc, m_raw, 2 * s, ch, d_err);
+    } else if (m_raw > 0 && small) {
+      TC_LAUNCH("canon_digits", (k_canon_digits<CanonSrc>), dim3(pblocks), dim3(kT), digit_lds_bytes(0, 2 * s), st,
+                csrc, m_raw, 0, 2 * s, ch, d_err);
       TC_HIP(hipGetLastError());
       salt = radix_sort_from<uint64_t, NoVal, CanonSrc, 28>(csrc, m_raw, ka.as<uint64_t>(), kb.as<uint64_t>(),
                                                             nullptr, nullptr, m_raw, 0, 2 * s, ch,
                                                             st, "dedup");
+    } else if (m_raw > 0) {
+      TC_LAUNCH("canon_digits", (k_canon_digits<MixSrc>), dim3(pblocks), dim3(kT), digit_lds_bytes(bit_lo, 2 * s), st,
+                msrc, m_raw, bit_lo, 2 * s, ch, d_err);
+      TC_HIP(hipGetLastError());
+      salt = radix_sort_from<uint64_t, NoVal, MixSrc, 28>(msrc, m_raw, ka.as<uint64_t>(), kb.as<uint64_t>(),
+                                                          nullptr, nullptr, m_raw, bit_lo, 2 * s, ch,
+                                                          st, "dedup");
     }
+    uint64_t* const S = salt ? kb.as<uint64_t>() : ka.as<uint64_t>();
     if (m_raw > 0 && small) {
       const int64_t per = std::max<int64_t>(8192, div_up(m_raw, 64));
       allow_lds((const void*)k_small_degree, sizeof(uint32_t) * (size_t)n);
       TC_LAUNCH("small_degree", k_small_degree, dim3((unsigned)div_up(m_raw, per)), dim3(kSmallThreads),
-                sizeof(uint32_t) * (size_t)n, st, salt ? kb.as<uint64_t>() : ka.as<uint64_t>(), sent, m_raw, per, s,
-                (int)n, reinterpret_cast<uint32_t*>(zb + deg_at), d_m);
+                sizeof(uint32_t) * (size_t)n, st, S, sent, m_raw, per, s, (int)n,
+                reinterpret_cast<uint32_t*>(zb + deg_at), d_m);
       TC_HIP(hipGetLastError());
     } else if (m_raw > 0) {
       // duplicates marked, distinct keys counted, with their upper
       // endpoints' partition digits
-      TC_LAUNCH("distinct_mark", k_distinct_mark,
-                dim3((unsigned)std::min<int64_t>(kProducerBlocks, div_up(m_raw, kT * kDigitBatch))), dim3(kT),
-                digit_lds_bytes(hshift, s), st, salt ? kb.as<uint64_t>() : ka.as<uint64_t>(), sent, m_raw, hshift,
-                s, dh, d_m);
+      const size_t lds = digit_lds_bytes(hshift, s);
+      if (grouped) {
+        allow_lds((const void*)k_distinct_groups, lds);
+        TC_LAUNCH("distinct_groups", k_distinct_groups,
+                  dim3((unsigned)std::min<int64_t>(512, div_up(m_raw, kGrpTile))), dim3(kGrpThreads), lds, st, S, mc,
+                  m_raw, bit_lo, hshift, dh, d_m, d_refused);
+      } else {
+        TC_LAUNCH("distinct_mark", k_distinct_mark, dim3(pblocks), dim3(kT), lds, st, S, mc, m_raw, hshift, dh, d_m);
+      }
       TC_HIP(hipGetLastError());
     }
     // the id check and the distinct count: one host sync for both
     struct {
       int err;
-      int pad;
+      int refused;
       unsigned long long m;
     } h;
     static_assert(sizeof(h) == 16, "scalar layout");
@@ -1763,13 +1953,18 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
     TC_HIP(hipStreamSynchronize(st));
     const unsigned long long h_m = h.m;
     TC_REQUIRE(h.err == 0, TC_EINVAL, "tc_preprocess: vertex id outside [0, n)");
+    if (h.refused) {  // (a group too large for its hash set: all counts again, from a full sort)
+      TC_HIP(hipMemsetAsync(zs.p, 0, zs.bytes, st));
+      continue;
+    }
     TC_REQUIRE(h_m < (unsigned long long)kMaxEdges, TC_EOVERFLOW, "tc_preprocess: 2^32 - 256 or more edges");
     m = (int64_t)h_m;
+    break;
   }
   g->m = m;
   DevBuf& sbuf = salt ? kb : ka;     // S
   DevBuf& obuf = salt ? ka : kb;     // free: the oriented keys go here
-  const DistinctSel dsel{sbuf.as<uint64_t>(), sent};
+  const DistinctSel dsel{sbuf.as<uint64_t>()};
 
   // ---- 3: degree order ---------------------------------------------------
   g->perm = g->owned.alloc<int32_t>(n);
@@ -1789,7 +1984,7 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
       // the distinct keys) and counted per bucket in LDS with the lower
       // endpoints (k_degree_hist, which writes the rank keys)
       DevBuf hb(sizeof(uint32_t) * (size_t)m), hb2(hpasses > 1 ? sizeof(uint32_t) * (size_t)m : 0);
-      const bool halt = radix_sort_from<uint32_t, NoVal>(DistinctHiSrc{dsel, s}, m_raw, hb.as<uint32_t>(),
+      const bool halt = radix_sort_from<uint32_t, NoVal>(DistinctHiSrc{dsel, mc}, m_raw, hb.as<uint32_t>(),
                                                          hb2.as<uint32_t>(), nullptr, nullptr, m, hshift, s,
                                                          dh, st, "degree", NoEpi{}, false, true);
       const uint32_t* hsorted = halt ? hb2.as<uint32_t>() : hb.as<uint32_t>();
@@ -1822,7 +2017,7 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
         nbs = nbuckets + 1;
       }
       TC_LAUNCH("degree_hist", k_degree_hist, dim3((unsigned)groups), dim3(kDegThreads), lds, st, hsorted, bs32,
-                bs32 ? nullptr : bp.as<int64_t>(), nbs, m, hshift, sub, dsel, m_raw, n, s, ra.as<uint64_t>());
+                bs32 ? nullptr : bp.as<int64_t>(), nbs, m, hshift, sub, dsel, m_raw, n, mc, ra.as<uint64_t>());
       TC_HIP(hipGetLastError());
     } else {
       DevBuf deg(sizeof(uint32_t) * (size_t)n);
@@ -1871,7 +2066,7 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
       // (28 edges per thread, as the canonicalising pass: a source that
       // loads twice per element needs the registers)
       const bool palt = radix_sort_from<uint64_t, NoVal, LoRankSrc, 28>(
-          LoRankSrc{dsel, g->perm, s}, m_raw, obuf.as<uint64_t>(), nullptr, nullptr, nullptr, m,
+          LoRankSrc{dsel, g->perm, mc}, m_raw, obuf.as<uint64_t>(), nullptr, nullptr, nullptr, m,
           s > 8 ? s - 8 : 0, s, const_cast<uint32_t*>(hi_starts), st, "orient_part", NoEpi{}, true);
       TC_REQUIRE(!palt, TC_EDEVICE, "tc_preprocess: the orientation partition is one pass");
       const int64_t og = std::min<int64_t>(kProducerBlocks, div_up(m, kT * 2 * kEw));
