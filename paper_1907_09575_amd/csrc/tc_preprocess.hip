@@ -1896,7 +1896,7 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
     ++gpasses;
   for (bool grouped = !small && 8 * gpasses < 2 * s;; grouped = false) {
     // the keys are built by the first pass of the dedup sort from the raw
-    // pairs (7168-pair tiles: the largest whose registers allow two waves per
+    // pairs (7168-pair tiles: the largest whose registers allow four waves per
     // SIMD); one read of the pairs before it counts their digits and checks
     // the ids
     const CanonSrc csrc{d_src, d_dst, n, s, sent};
@@ -1909,14 +1909,14 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
       TC_LAUNCH("canon_digits", (k_canon_digits<CanonSrc>), dim3(pblocks), dim3(kT), digit_lds_bytes(0, 2 * s), st,
                 csrc, m_raw, 0, 2 * s, ch, d_err);
       TC_HIP(hipGetLastError());
-      salt = radix_sort_from<uint64_t, NoVal, CanonSrc, 28>(csrc, m_raw, ka.as<uint64_t>(), kb.as<uint64_t>(),
+      salt = radix_sort_from<uint64_t, NoVal, CanonSrc, 14>(csrc, m_raw, ka.as<uint64_t>(), kb.as<uint64_t>(),
                                                             nullptr, nullptr, m_raw, 0, 2 * s, ch,
                                                             st, "dedup");
     } else if (m_raw > 0) {
       TC_LAUNCH("canon_digits", (k_canon_digits<MixSrc>), dim3(pblocks), dim3(kT), digit_lds_bytes(bit_lo, 2 * s), st,
                 msrc, m_raw, bit_lo, 2 * s, ch, d_err);
       TC_HIP(hipGetLastError());
-      salt = radix_sort_from<uint64_t, NoVal, MixSrc, 28>(msrc, m_raw, ka.as<uint64_t>(), kb.as<uint64_t>(),
+      salt = radix_sort_from<uint64_t, NoVal, MixSrc, 14>(msrc, m_raw, ka.as<uint64_t>(), kb.as<uint64_t>(),
                                                           nullptr, nullptr, m_raw, bit_lo, 2 * s, ch,
                                                           st, "dedup");
     }
@@ -2051,7 +2051,7 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
                 dim3(kT), digit_lds_bytes(0, 2 * s), st, osrc, m_raw, 2 * s, ohist);
       TC_HIP(hipGetLastError());
       // (S is read by the first pass alone: its buffer is the partner of the others)
-      if (radix_sort_from<uint64_t, NoVal, OrientSrc, 28, ColEpi>(osrc, m_raw, obuf.as<uint64_t>(),
+      if (radix_sort_from<uint64_t, NoVal, OrientSrc, 14, ColEpi>(osrc, m_raw, obuf.as<uint64_t>(),
                                                                   sbuf.as<uint64_t>(), nullptr, nullptr, m, 0, 2 * s,
                                                                   ohist, st, "orient", col_epi))
         okey = sbuf.as<uint64_t>();
@@ -2063,9 +2063,9 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
     if (m > 0) {
       // partition by the top 8 bits of hi (one pass from S into the free
       // buffer), then the oriented keys in place
-      // (28 edges per thread, as the canonicalising pass: a source that
+      // (14 edges per thread, as the canonicalising pass: a source that
       // loads twice per element needs the registers)
-      const bool palt = radix_sort_from<uint64_t, NoVal, LoRankSrc, 28>(
+      const bool palt = radix_sort_from<uint64_t, NoVal, LoRankSrc, 14>(
           LoRankSrc{dsel, g->perm, mc}, m_raw, obuf.as<uint64_t>(), nullptr, nullptr, nullptr, m,
           s > 8 ? s - 8 : 0, s, const_cast<uint32_t*>(hi_starts), st, "orient_part", NoEpi{}, true);
       TC_REQUIRE(!palt, TC_EDEVICE, "tc_preprocess: the orientation partition is one pass");
@@ -2138,7 +2138,7 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
       tl.row.alloc(sizeof(uint32_t) * (size_t)T);
       tl.val.alloc(sizeof(uint64_t) * (size_t)T);
       DevBuf tk(sizeof(uint32_t) * (size_t)T), tv(sizeof(uint64_t) * (size_t)T);
-      const bool alt = radix_sort_from<uint32_t, uint64_t>(src, m, tl.row.as<uint32_t>(), tk.as<uint32_t>(),
+      const bool alt = radix_sort_from<uint32_t, uint64_t, TaskSrc, 11>(src, m, tl.row.as<uint32_t>(), tk.as<uint32_t>(),
                                                            tl.val.as<uint64_t>(), tv.as<uint64_t>(), T, 0, s,
                                                            th, st, "tasks");
       if (alt) {

@@ -433,6 +433,7 @@ struct NoEpi {
 };
 
 constexpr int kSortPassesMax = 8;
+constexpr int kRsThreads = 512;  // of a sort tile's work-group (see k_rs_onesweep)
 // Look-back words of all passes of a sort up to this size are cleared by
 // one memset (see radix_sort_cfg).
 constexpr size_t kLbClearOnceBytes = (size_t)4 << 20;
@@ -563,45 +564,75 @@ static __global__ __launch_bounds__(256) void k_rs_buckets(uint32_t* __restrict_
   }
 }
 
+// Exclusive scan across the first 256 threads of a work-group (the others
+// pass 0 and take no result); s_wave needs 4 entries. Contains two barriers.
+template <class T>
+__device__ __forceinline__ T digit_excl_scan(T v, T* s_wave, T& total) {
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  const T inc = wave_incl_scan(v);
+  if (wave < 4 && lane == 63) s_wave[wave] = inc;
+  __syncthreads();
+  T woff = 0, tot = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const T x = s_wave[w];
+    if (w < wave) woff += x;
+    tot += x;
+  }
+  __syncthreads();
+  total = tot;
+  return woff + inc - v;
+}
+
 // Two work-groups of a tile fit a CU (LDS), so the registers are held to two
 // waves a SIMD: a few more than 256 in the 12-byte pass with a source leave one
 // tile a CU (preprocessing and count at scale 24: 54.4 ms against 53.6 ms).
+// Two work-groups of a tile fit a CU (LDS). A tile's phases (loads, ranking,
+// look-back, scattered stores) leave the memory or the vector units idle in
+// turn, so a tile of 8192 8-byte keys is spread over 512 threads of 16 rather
+// than 256 of 32: at most 128 registers each, four waves a SIMD instead of
+// two. A pass over 256 M 8-byte keys (scale 24): 1268 -> 1138 us (copy rate:
+// 855); 1024 threads of 8: 1186 us (spills); three work-groups of smaller
+// tiles: 1284 us (shorter runs, more look-back).
 template <class K, class V, int KPT, class W, int WIN, class Epi, class Src = NoSrc>
-__global__ __launch_bounds__(256, 2) void k_rs_onesweep(const K* __restrict__ kin, K* __restrict__ kout,
-                                                        const V* __restrict__ vin, V* __restrict__ vout,
-                                                        int64_t n, int shift, uint32_t dmask,
-                                                        const uint32_t* __restrict__ bucket,
-                                                        W* __restrict__ status,
-                                                        uint32_t* __restrict__ ticket, int* __restrict__ fail,
-                                                        bool raw_counts, Epi epi, Src src = Src{}) {
-  constexpr int TILE = 256 * KPT;
-  constexpr int WCH = 64 * KPT;  // keys of the tile each wave ranks (a contiguous quarter)
+__global__ __launch_bounds__(kRsThreads, kRsThreads / 128) void k_rs_onesweep(
+    const K* __restrict__ kin, K* __restrict__ kout,
+    const V* __restrict__ vin, V* __restrict__ vout,
+    int64_t n, int shift, uint32_t dmask,
+    const uint32_t* __restrict__ bucket,
+    W* __restrict__ status,
+    uint32_t* __restrict__ ticket, int* __restrict__ fail,
+    bool raw_counts, Epi epi, Src src = Src{}) {
+  constexpr int TILE = kRsThreads * KPT;
+  constexpr int NW = kRsThreads / 64;
+  constexpr int WCH = 64 * KPT;  // keys of the tile each wave ranks (contiguous)
   constexpr bool HV = !std::is_same<V, NoVal>::value;
   constexpr W TOP = lb_top<W>();
   using VS = typename std::conditional<HV, V, char>::type;
   __shared__ K s_k[TILE];
   __shared__ VS s_v[HV ? TILE : 1];
-  __shared__ uint32_t s_cnt[4][256];  // per wave and digit: count, then the wave's offset
+  __shared__ uint16_t s_cnt[NW][256];  // per wave and digit: count, then the wave's offset
   __shared__ uint32_t s_goff[256], s_tstart[256];
   __shared__ uint32_t s_tmp[4];
   __shared__ uint32_t s_tile;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (tid == 0) s_tile = atomicAdd(ticket, 1u);
 #pragma unroll
-  for (int w = 0; w < 4; ++w) s_cnt[w][tid] = 0;
+  for (int x = tid; x < NW * 256; x += kRsThreads) (&s_cnt[0][0])[x] = 0;
   // where digit tid starts (raw_counts: how many there are); kept in LDS,
   // and scanned before the tile is in registers
-  uint32_t first = bucket[tid];
+  const bool dig = tid < 256;  // (thread d keeps digit d)
+  uint32_t first = dig ? bucket[tid] : 0;
   if (raw_counts) {
     uint32_t all;
-    first = block_excl_scan(first, s_tmp, all);
+    first = digit_excl_scan(first, s_tmp, all);
   }
-  s_goff[tid] = first;
+  if (dig) s_goff[tid] = first;
   __syncthreads();
   const uint32_t tile = s_tile;
   const int64_t wbase = (int64_t)tile * TILE + (int64_t)wave * WCH;
 
-  // the wave's quarter in registers: item i of lane l is input position
+  // the wave's part in registers: item i of lane l is input position
   // wbase + 64 i + l; with a source, bit i of vmask says whether the item is
   // a key of the sort (without one, the positions below n are)
   constexpr bool FROM_SRC = !std::is_same<Src, NoSrc>::value;
@@ -626,11 +657,11 @@ __global__ __launch_bounds__(256, 2) void k_rs_onesweep(const K* __restrict__ ki
     if constexpr (FROM_SRC) return (vmask >> i) & 1u;
     else return wbase + 64 * i + lane < n;
   };
-  // stable rank within the wave's quarter; the wave's own LDS counters carry
+  // stable rank within the wave's part; the wave's own LDS counters carry
   // the counts from item to item (a wave's LDS accesses complete in order)
   uint32_t rank[KPT];
   const uint64_t lt_mask = (1ull << lane) - 1ull;
-  uint32_t* cnt_w = s_cnt[wave];
+  uint16_t* cnt_w = s_cnt[wave];
 #pragma unroll
   for (int i = 0; i < KPT; ++i) {
     const bool valid = is_key(i);
@@ -641,7 +672,7 @@ __global__ __launch_bounds__(256, 2) void k_rs_onesweep(const K* __restrict__ ki
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (valid && (peers & lt_mask) == 0) cnt_w[d] = before + (uint32_t)__popcll(peers);
+    if (valid && (peers & lt_mask) == 0) cnt_w[d] = (uint16_t)(before + (uint32_t)__popcll(peers));
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -649,19 +680,23 @@ __global__ __launch_bounds__(256, 2) void k_rs_onesweep(const K* __restrict__ ki
   __syncthreads();
   // digit `tid`: offsets of the waves within the tile's run, the tile's count
   uint32_t cnt = 0;
+  if (dig) {
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const uint32_t c = s_cnt[w][tid];
-    s_cnt[w][tid] = cnt;
-    cnt += c;
+    for (int w = 0; w < NW; ++w) {
+      const uint32_t c = s_cnt[w][tid];
+      s_cnt[w][tid] = (uint16_t)cnt;
+      cnt += c;
+    }
   }
   // publish the tile's count; put the tile in digit order in LDS (while the
   // predecessors publish theirs); then look back for the earlier tiles'
   // total and publish the inclusive prefix
   W* my = status + (uint64_t)tile * 256 + tid;
-  __hip_atomic_store(my, tile == 0 ? (TOP | (W)cnt) : (W)cnt + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (dig)
+    __hip_atomic_store(my, tile == 0 ? (TOP | (W)cnt) : (W)cnt + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   uint32_t tot;
-  s_tstart[tid] = block_excl_scan(cnt, s_tmp, tot);
+  const uint32_t tstart = digit_excl_scan(cnt, s_tmp, tot);
+  if (dig) s_tstart[tid] = tstart;
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < KPT; ++i) {
@@ -672,7 +707,7 @@ __global__ __launch_bounds__(256, 2) void k_rs_onesweep(const K* __restrict__ ki
       if constexpr (HV) s_v[lp] = v[i];
     }
   }
-  if (tile != 0) {
+  if (tile != 0 && dig) {
     // walk back WIN predecessors per step (their words are read together):
     // add counts from the nearest one until an inclusive prefix; stop at a
     // tile that has published nothing yet and read again from there
@@ -721,7 +756,7 @@ __global__ __launch_bounds__(256, 2) void k_rs_onesweep(const K* __restrict__ ki
   }
 #pragma unroll
   for (int i = 0; i < KPT; ++i) {
-    const int lp = i * 256 + tid;
+    const int lp = i * kRsThreads + tid;
     if (lp < tile_n) {
       const K kk = s_k[lp];
       const uint32_t d = rs_digit(kk, shift, dmask);
@@ -741,7 +776,7 @@ __global__ __launch_bounds__(256, 2) void k_rs_onesweep(const K* __restrict__ ki
 template <class K, class V>
 constexpr int rs_default_kpt() {
   constexpr int e = (int)sizeof(K) + (std::is_same<V, NoVal>::value ? 0 : (int)sizeof(V));
-  return e <= 4 ? 24 : e <= 8 ? 32 : e <= 12 ? 24 : 16;
+  return (e <= 4 ? 24 : e <= 8 ? 32 : e <= 12 ? 24 : 16) * 256 / kRsThreads;
 }
 
 // Sorts keys[0..n) by bits [bit_lo, bit_hi) (stable), carrying vals if V is
@@ -769,7 +804,7 @@ bool radix_sort_cfg(K* keys, K* keys_alt, V* vals, V* vals_alt, int64_t n, int b
                     hipStream_t st, const char* name, Epi epi = Epi{}, uint32_t* hist = nullptr,
                     const Src* src = nullptr, int64_t n_in = 0, bool hist_scanned = false,
                     bool leave_starts = false) {
-  constexpr int TILE = 256 * KPT;
+  constexpr int TILE = kRsThreads * KPT;
   const char* n_digits = intern_name(std::string("rs_digits:") + name);
   const char* n_pass = intern_name(std::string("rs_pass:") + name);
   if (src) {
@@ -784,7 +819,7 @@ bool radix_sort_cfg(K* keys, K* keys_alt, V* vals, V* vals_alt, int64_t n, int b
   TC_REQUIRE(bit_hi - bit_lo <= 8 * kSortPassesMax, TC_EINVAL, "radix_sort: key range too wide");
   const int passes = (bit_hi - bit_lo + 7) / 8;
   const int64_t ntiles = div_up(n, TILE);
-  const int64_t ntiles_in = src ? div_up(n_in, 256 * KPT_SRC) : ntiles;  // (the source pass: KPT_SRC per thread)
+  const int64_t ntiles_in = src ? div_up(n_in, kRsThreads * KPT_SRC) : ntiles;  // (the source pass: KPT_SRC per thread)
   int* fail = temp_ctx().fail;
   TC_REQUIRE(fail != nullptr, TC_EDEVICE, "radix_sort: called outside a TempStream scope");
   // per pass: ticket counter (padded to 256 bytes) + tiles * 256 look-back
@@ -838,20 +873,20 @@ bool radix_sort_cfg(K* keys, K* keys_alt, V* vals, V* vals_alt, int64_t n, int b
     uint32_t* ticket = reinterpret_cast<uint32_t*>(words);
     if (p == 0 && src) {  // from the source into keys/vals
       if (last)
-        TC_LAUNCH(n_pass, (k_rs_onesweep<K, V, KPT_SRC, W, WIN, Epi, Src>), dim3((unsigned)ntiles_in), dim3(256), 0,
+        TC_LAUNCH(n_pass, (k_rs_onesweep<K, V, KPT_SRC, W, WIN, Epi, Src>), dim3((unsigned)ntiles_in), dim3(kRsThreads), 0,
                   st, nullptr, ka, nullptr, va, n_in, shift, dmask, gh, words + pad, ticket, fail, raw_counts, epi, *src);
       else
-        TC_LAUNCH(n_pass, (k_rs_onesweep<K, V, KPT_SRC, W, WIN, NoEpi, Src>), dim3((unsigned)ntiles_in), dim3(256),
+        TC_LAUNCH(n_pass, (k_rs_onesweep<K, V, KPT_SRC, W, WIN, NoEpi, Src>), dim3((unsigned)ntiles_in), dim3(kRsThreads),
                   0, st, nullptr, ka, nullptr, va, n_in, shift, dmask, gh, words + pad, ticket, fail, raw_counts,
                   NoEpi{}, *src);
       TC_HIP(hipGetLastError());
       continue;
     }
     if (!last)
-      TC_LAUNCH(n_pass, (k_rs_onesweep<K, V, KPT, W, WIN, NoEpi>), dim3((unsigned)ntiles), dim3(256), 0, st, ka,
+      TC_LAUNCH(n_pass, (k_rs_onesweep<K, V, KPT, W, WIN, NoEpi>), dim3((unsigned)ntiles), dim3(kRsThreads), 0, st, ka,
                 kb, va, vb, n, shift, dmask, gh + 256 * p, words + pad, ticket, fail, raw_counts, NoEpi{});
     else
-      TC_LAUNCH(n_pass, (k_rs_onesweep<K, V, KPT, W, WIN, Epi>), dim3((unsigned)ntiles), dim3(256), 0, st, ka,
+      TC_LAUNCH(n_pass, (k_rs_onesweep<K, V, KPT, W, WIN, Epi>), dim3((unsigned)ntiles), dim3(kRsThreads), 0, st, ka,
                 kb, va, vb, n, shift, dmask, gh + 256 * p, words + pad, ticket, fail, raw_counts, epi);
     TC_HIP(hipGetLastError());
     std::swap(ka, kb);
