@@ -103,23 +103,34 @@ void build_lower(Lower& L, const Graph& g, hipStream_t st) {
 // Per original vertex u (rank r = perm[u]): t, the local clustering
 // coefficient t / C(d, 2) (0 if d < 2; one correctly rounded division of two
 // exact integers) and the sums of t (= 3T) and of C(d, 2) over all vertices.
+// (every work-group ends on two atomics to the sums, of 12 ns each: few
+// work-groups)
+constexpr unsigned kVertexOutGrid = 1024;
 __global__ __launch_bounds__(256) void k_vertex_out(const int32_t* __restrict__ perm, int64_t n,
                                                     const unsigned long long* __restrict__ t_rank,
                                                     const uint32_t* __restrict__ deg, int64_t* __restrict__ t_orig,
                                                     double* __restrict__ cc, unsigned long long* __restrict__ sums) {
   __shared__ unsigned long long s_t[4], s_w[4];
-  const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  uint64_t t = 0, pairs = 0;
-  if (u < n) {
-    const int64_t r = perm[u];
-    t = t_rank[r];
+  uint64_t t_all = 0, pairs_all = 0;
+  const uint32_t hot = vertex_hot(n);
+  for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t r = perm[u], top = n - 1 - r;
+    uint64_t t = 0;
+    if (top >= hot) {
+      t = t_rank[r];
+    } else {
+#pragma unroll
+      for (uint32_t c = 0; c < kVertexCopies; ++c) t += t_rank[n + (int64_t)c * hot + top];
+    }
     const uint64_t d = deg[r];
-    pairs = d * (d - (d > 0)) / 2;
+    const uint64_t pairs = d * (d - (d > 0)) / 2;
     if (t_orig) t_orig[u] = (int64_t)t;
     if (cc) cc[u] = pairs ? (double)t / (double)pairs : 0.0;
+    t_all += t;
+    pairs_all += pairs;
   }
   if (!sums) return;
-  const unsigned long long wt = wave_sum((unsigned long long)t), ww = wave_sum((unsigned long long)pairs);
+  const unsigned long long wt = wave_sum((unsigned long long)t_all), ww = wave_sum((unsigned long long)pairs_all);
   if (lane_id() == 0) {
     s_t[threadIdx.x >> 6] = wt;
     s_w[threadIdx.x >> 6] = ww;
@@ -147,14 +158,15 @@ void vertex_counts(const Graph& g, int64_t* d_tri, double* d_cc, int64_t* d_sums
   const int64_t n = g.n;
   auto* sums = reinterpret_cast<unsigned long long*>(d_sums);
   if (sums) TC_LAUNCH("zero_sums", k_zero_u64x2, dim3(1), dim3(64), 0, st, sums);
-  DevBuf t_rank(sizeof(unsigned long long) * (size_t)n), erow(sizeof(uint32_t) * (size_t)std::max<int64_t>(g.m, 1));
-  TC_LAUNCH("fill_i64", k_fill_i64v, dim3(grid_threads(n)), dim3(kAT), 0, st, t_rank.as<int64_t>(), n, (int64_t)0);
+  const int64_t nc = vertex_counters(n);
+  DevBuf t_rank(sizeof(unsigned long long) * (size_t)nc), erow(sizeof(uint32_t) * (size_t)std::max<int64_t>(g.m, 1));
+  TC_LAUNCH("fill_i64", k_fill_i64v, dim3(grid_threads(nc)), dim3(kAT), 0, st, t_rank.as<int64_t>(), nc, (int64_t)0);
   if (g.m > 0)
     TC_LAUNCH("entry_rows", k_entry_rows, dim3(entry_rows_grid(n)), dim3(kAT), 0, st, g.row_ptr, n,
               erow.as<uint32_t>());
   const VertexCounts vc{erow.as<uint32_t>(), t_rank.as<unsigned long long>()};
   launch_count(graph_view(g), MODE_VERTEX, nullptr, nullptr, nullptr, st, &vc);
-  TC_LAUNCH("vertex_out", k_vertex_out, dim3(grid_threads(n)), dim3(kAT), 0, st, g.perm, n,
+  TC_LAUNCH("vertex_out", k_vertex_out, dim3(std::min(grid_threads(n), kVertexOutGrid)), dim3(kAT), 0, st, g.perm, n,
             t_rank.as<unsigned long long>(), g.deg, d_tri, d_cc, sums);
   TC_HIP(hipGetLastError());
   note_use(g, st);

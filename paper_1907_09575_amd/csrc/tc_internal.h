@@ -362,8 +362,13 @@ struct CountView {
   const uint16_t* pcol16 = nullptr;  // short columns of the probe side (w->b16 < w->nrows)
 };
 
-// MODE_VERTEX: the row of every probe-side entry and the counters of all
-// vertices, which the caller has cleared.
+// MODE_VERTEX: the row of every probe-side entry and vertex_counters(n)
+// counters, which the caller has cleared. The count of rank v is count[v], or,
+// for the vertex_hot(n) highest ranks, the sum over copies c of
+// count[n + c * vertex_hot(n) + n - 1 - v].
+constexpr uint32_t kVertexCopies = 16;
+__host__ __device__ inline uint32_t vertex_hot(int64_t n) { return (uint32_t)(n < 8192 ? n : 8192); }
+inline int64_t vertex_counters(int64_t n) { return n + (int64_t)kVertexCopies * vertex_hot(n); }
 struct VertexCounts {
   const uint32_t* erow;
   unsigned long long* count;
@@ -391,7 +396,7 @@ struct CountArgs {
   unsigned long long* per_shift;  // MODE_BLOCK: q counters
   int32_t q, xy;                  // MODE_BLOCK: grid size, (x + y) % q
   const uint32_t* __restrict__ erow;  // MODE_VERTEX: row of every entry of col
-  unsigned long long* vcount;         // MODE_VERTEX: n counters
+  unsigned long long* vcount;         // MODE_VERTEX: vertex_counters(n) counters
 };
 
 // ---- batched persistent count (tc_count.hip kernel, tc_batch.cpp plan) -------
