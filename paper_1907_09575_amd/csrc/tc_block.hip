@@ -178,6 +178,12 @@ void gather_pair(LocalRows& H, LocalRows& P, const Graph& g, int32_t q, int32_t 
 void block_count(const Graph& g, int32_t q, int32_t x, int32_t y, int64_t* d_count, int64_t* d_per_shift,
                  hipStream_t st) {
   TempStream temps(st);
+  DevBuf words;  // of the scans below: cleared once
+  if (g.n / q > 2048) {
+    words.alloc(kScanPool);
+    TC_HIP(hipMemsetAsync(words.p, 0, kScanPool, st));
+    temps.scan_pool(words.as<char>(), kScanPool);
+  }
   Owned own;
   own.st = st;
   LocalRows H, P;  // hash side: rows j == x; probe side: rows i == y

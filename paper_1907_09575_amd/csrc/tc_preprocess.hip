@@ -1852,9 +1852,12 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
   constexpr size_t kHistWords = 256 * kSortPassesMax;
   const size_t deg_at = 64 + sizeof(uint32_t) * (256 * 2 + 3 * kHistWords);
   const size_t pool_at = deg_at + (small ? (sizeof(uint32_t) * (size_t)n + 255) & ~(size_t)255 : 0);
-  DevBuf zs(pool_at + (small ? kZeroPool : 0));
+  // (and of the scans)
+  const size_t scan_at = pool_at + (small ? kZeroPool : 0);
+  DevBuf zs(scan_at + kScanPool);
   TC_HIP(hipMemsetAsync(zs.p, 0, zs.bytes, st));
   if (small) temps.zero_pool(zs.as<char>() + pool_at, kZeroPool);
+  temps.scan_pool(zs.as<char>() + scan_at, kScanPool);
   char* const zb = zs.as<char>();
   int* d_err = reinterpret_cast<int*>(zb);
   int* d_refused = reinterpret_cast<int*>(zb + 4);

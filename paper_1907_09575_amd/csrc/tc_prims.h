@@ -69,9 +69,10 @@ __device__ __forceinline__ T block_excl_scan(T v, T* s_wave, T& total) {
 
 // ---------------------------------------------------------------------------
 // Exclusive scan of a device array: out[i] = sum_{j<i} in[j]; optionally
-// *total = sum of all. Three kernels: tile reduce, scan of tile sums (one
-// block), tile scan with carry-in; one (k_scan_small) for at most
-// kScanSmallTiles tiles.
+// *total = sum of all. Up to kScanLong elements one kernel (k_scan): every
+// tile publishes its sum and finds the sum of the tiles before it by decoupled
+// look-back; beyond, three: tile reduce, scan of tile sums (one block), tile
+// scan with carry-in.
 // ---------------------------------------------------------------------------
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kPrimThreads * kScanItems;
@@ -166,48 +167,99 @@ __global__ __launch_bounds__(256) void k_scan_final(L load, int64_t n, const Tou
   }
 }
 
-// Exclusive scan of at most kScanSmallTiles tiles by one work-group: the
-// tiles of k_scan_final in order, each with the running total of the ones
-// before it as its carry-in; writes the grand total too. One launch instead
-// of three for the short arrays (tile counts, per-class rows, the vertices
-// of a small graph) that most scans of a small graph's preprocessing cover.
-constexpr int kScanSmallTiles = 4;
+// Tile words of a scan: a sum of at most 62 bits and, above it, what it is.
+constexpr uint64_t kScanSum = 1ull << 62;     // of the tile
+constexpr uint64_t kScanPrefix = 2ull << 62;  // of all tiles up to it
+constexpr uint64_t kScanValue = kScanSum - 1;
+constexpr uint32_t kLbSpinMax = 1u << 16;  // look-back waits (scans and sorts) give up after as many tries
 
+// One tile per work-group as in k_scan_final, tiles in the order the
+// work-groups begin (a ticket), so that a tile waits only for tiles that run
+// or have run. The first wave looks back over 64 tiles at a time. words (ticket, then a word per tile; cleared): not used by
+// a scan of one tile.
 template <class L, class Tout>
-__global__ __launch_bounds__(256) void k_scan_small(L load, int64_t n, Tout* __restrict__ out,
-                                                    Tout* __restrict__ total) {
-  __shared__ Tout s_w[kScanItems][4];
-  const int lane = lane_id(), wave = threadIdx.x >> 6;
-  Tout off = 0;  // the same in every thread
-  for (int64_t base = 0; base < n; base += kScanTile) {
-    Tout v[kScanItems], inc[kScanItems];
-#pragma unroll
-    for (int i = 0; i < kScanItems; ++i) {
-      const int64_t idx = base + (int64_t)i * kPrimThreads + threadIdx.x;
-      v[i] = idx < n ? load(idx) : Tout(0);
-    }
-#pragma unroll
-    for (int i = 0; i < kScanItems; ++i) {
-      inc[i] = wave_incl_scan(v[i]);
-      if (lane == 63) s_w[i][wave] = inc[i];
-    }
+__global__ __launch_bounds__(256) void k_scan(L load, int64_t n, unsigned long long* __restrict__ words,
+                                             Tout* __restrict__ out, Tout* __restrict__ total,
+                                             int* __restrict__ fail) {
+  constexpr int NT = 256, ITEMS = kScanItems, NW = NT / 64;
+  __shared__ Tout s_w[ITEMS][NW];
+  __shared__ Tout s_before;
+  __shared__ uint32_t s_tile;
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+  uint32_t tile = 0;
+  if (gridDim.x > 1) {
+    if (tid == 0) s_tile = (uint32_t)atomicAdd(words, 1ull);
     __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kScanItems; ++i) {
-      Tout before = 0, row = 0;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const Tout x = s_w[i][w];
-        if (w < wave) before += x;
-        row += x;
-      }
-      const int64_t idx = base + (int64_t)i * kPrimThreads + threadIdx.x;
-      if (idx < n) out[idx] = off + before + inc[i] - v[i];
-      off += row;
-    }
-    __syncthreads();  // s_w is written again by the next tile
+    tile = s_tile;
   }
-  if (total && threadIdx.x == 0) *total = off;
+  const int64_t base = (int64_t)tile * NT * ITEMS;
+  Tout v[ITEMS], inc[ITEMS];
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) {
+    const int64_t idx = base + (int64_t)i * NT + tid;
+    v[i] = idx < n ? load(idx) : Tout(0);
+  }
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) {
+    inc[i] = wave_incl_scan(v[i]);
+    if (lane == 63) s_w[i][wave] = inc[i];
+  }
+  __syncthreads();
+  if (wave == 0) {
+    Tout own = 0;
+    for (int x = lane; x < ITEMS * NW; x += 64) own += (&s_w[0][0])[x];
+    own = wave_sum(own);
+    Tout before = 0;
+    if (gridDim.x > 1) {
+      unsigned long long* const mine = words + 1 + tile;
+      if (lane == 0)
+        __hip_atomic_store(mine, (tile ? kScanSum : kScanPrefix) | (uint64_t)own, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+      uint32_t spins = 0;
+      int64_t j = (int64_t)tile - 1;  // the nearest tile not yet added
+      while (j >= 0) {
+        // (before tile 0: a prefix of 0)
+        const uint64_t w = j - lane >= 0 ? __hip_atomic_load(words + 1 + (j - lane), __ATOMIC_RELAXED,
+                                                             __HIP_MEMORY_SCOPE_AGENT)
+                                         : kScanPrefix;
+        const uint64_t prefixes = __ballot(w >= kScanPrefix), empty = __ballot(w < kScanSum);
+        // lanes up to the nearest prefix, or all
+        const uint64_t use = prefixes ? prefixes ^ (prefixes - 1) : ~0ull;
+        if (empty & use) {
+          if (++spins > kLbSpinMax) {  // never expected: give up rather than hang
+            if (lane == 0) atomicExch(fail, 1);
+            break;
+          }
+          __builtin_amdgcn_s_sleep(1);
+          continue;
+        }
+        before += wave_sum((use >> lane) & 1ull ? (Tout)(w & kScanValue) : Tout(0));
+        if (prefixes) break;
+        j -= 64;
+      }
+      if (tile && lane == 0)
+        __hip_atomic_store(mine, kScanPrefix | (uint64_t)(before + own), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (lane == 0) {
+      s_before = before;
+      if (total && (int64_t)(tile + 1) * NT * ITEMS >= n) *total = before + own;
+    }
+  }
+  __syncthreads();
+  Tout off = s_before;
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) {
+    Tout before = 0, row = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const Tout x = s_w[i][w];
+      if (w < wave) before += x;
+      row += x;
+    }
+    const int64_t idx = base + (int64_t)i * NT + tid;
+    if (idx < n) out[idx] = off + before + inc[i] - v[i];
+    off += row;
+  }
 }
 
 // Stream that preprocessing temporaries are ordered on (set by TempStream).
@@ -221,8 +273,12 @@ struct TempCtx {
   bool active = false;
   hipStream_t st = nullptr;
   int* fail = nullptr;
-  char* zero = nullptr;  // device memory already cleared on st, for the sorts' look-back words
+  // device memory already cleared on st, for the look-back words of sorts and
+  // of scans
+  char* zero = nullptr;
   size_t zero_left = 0;
+  char* scan_zero = nullptr;
+  size_t scan_zero_left = 0;
 };
 TempCtx& temp_ctx();
 
@@ -232,10 +288,15 @@ struct TempStream {
   explicit TempStream(hipStream_t st);
   ~TempStream();
   // `bytes` at p, cleared on the scope's stream and kept until it ends: small
-  // sorts take their look-back words from it instead of clearing their own.
+  // sorts (scans: those that it has room for) take their look-back words from
+  // it instead of clearing their own.
   void zero_pool(char* p, size_t bytes) {
     temp_ctx().zero = p;
     temp_ctx().zero_left = bytes;
+  }
+  void scan_pool(char* p, size_t bytes) {
+    temp_ctx().scan_zero = p;
+    temp_ctx().scan_zero_left = bytes;
   }
   TempStream(const TempStream&) = delete;
   TempStream& operator=(const TempStream&) = delete;
@@ -282,24 +343,50 @@ inline int64_t div_up(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // Exclusive scan of the n elements load(0..n-1) into out; if total !=
 // nullptr, the grand total is written there (device pointer). out may alias
 // what load reads only if element i depends on position i alone.
+//
+// One kernel instead of three saves two launches, which is what a scan of a
+// few thousand to a few million elements costs (block of a 13 x 13 grid, RMAT
+// scale 24, 14 scans: 2.50 -> 2.41 ms). A long one is bound by its reads and
+// writes, and there the ticket (one atomic on one address, 12 ns) and the
+// look-back of every tile cost more than a second read: 256 M edges, all scans
+// of the preprocessing 2.7 ms against 1.8 ms.
+constexpr size_t kScanPool = (size_t)128 << 10;  // words of the scans of a call, cleared at once
+constexpr int64_t kScanLong = (int64_t)1 << 22;
+
 template <class Tout, class L>
 void device_excl_scan_f(L load, Tout* out, int64_t n, Tout* total, hipStream_t st) {
   if (n <= 0) {
     if (total) TC_HIP(hipMemsetAsync(total, 0, sizeof(Tout), st));
     return;
   }
-  int64_t nb = div_up(n, kScanTile);
-  if (nb <= kScanSmallTiles) {
-    TC_LAUNCH("scan_small", (k_scan_small<L, Tout>), dim3(1), dim3(256), 0, st, load, n, out, total);
+  const int64_t nb = div_up(n, kScanTile);
+  if (n >= kScanLong) {
+    DevBuf part(sizeof(Tout) * (size_t)nb);
+    TC_LAUNCH("scan_reduce", (k_scan_reduce<L, Tout>), dim3((unsigned)nb), dim3(256), 0, st, load, n,
+              part.as<Tout>());
+    TC_LAUNCH("scan_partials", (k_scan_partials<Tout>), dim3(1), dim3(256), 0, st, part.as<Tout>(), nb, total);
+    TC_LAUNCH("scan_final", (k_scan_final<L, Tout>), dim3((unsigned)nb), dim3(256), 0, st, load, n,
+              part.as<Tout>(), out);
     TC_HIP(hipGetLastError());
     return;
   }
-  DevBuf part(sizeof(Tout) * (size_t)nb);
-  TC_LAUNCH("scan_reduce", (k_scan_reduce<L, Tout>), dim3((unsigned)nb), dim3(256), 0, st, load, n,
-            part.as<Tout>());
-  TC_LAUNCH("scan_partials", (k_scan_partials<Tout>), dim3(1), dim3(256), 0, st, part.as<Tout>(), nb, total);
-  TC_LAUNCH("scan_final", (k_scan_final<L, Tout>), dim3((unsigned)nb), dim3(256), 0, st, load, n,
-            part.as<Tout>(), out);
+  TempCtx& ctx = temp_ctx();
+  unsigned long long* words = nullptr;
+  DevBuf own;
+  if (nb > 1) {
+    TC_REQUIRE(ctx.fail != nullptr, TC_EDEVICE, "scan: called outside a TempStream scope");
+    const size_t bytes = (sizeof(unsigned long long) * (size_t)(nb + 1) + 255) & ~(size_t)255;
+    if (bytes <= ctx.scan_zero_left) {
+      words = reinterpret_cast<unsigned long long*>(ctx.scan_zero);
+      ctx.scan_zero += bytes;
+      ctx.scan_zero_left -= bytes;
+    } else {
+      own.alloc(bytes);
+      words = own.as<unsigned long long>();
+      TC_HIP(hipMemsetAsync(words, 0, bytes, st));
+    }
+  }
+  TC_LAUNCH("scan", (k_scan<L, Tout>), dim3((unsigned)nb), dim3(256), 0, st, load, n, words, out, total, ctx.fail);
   TC_HIP(hipGetLastError());
 }
 
@@ -438,7 +525,6 @@ constexpr int kRsThreads = 512;  // of a sort tile's work-group (see k_rs_oneswe
 // one memset (see radix_sort_cfg).
 constexpr size_t kLbClearOnceBytes = (size_t)4 << 20;
 constexpr size_t kZeroPool = (size_t)2 << 20;  // look-back words of a small graph's sorts
-constexpr uint32_t kLbSpinMax = 1u << 16;
 constexpr int64_t kRawCountTiles = 256;
 constexpr int kLbWin = 4;  // predecessors read per look-back step
 
