@@ -406,14 +406,6 @@ __global__ __launch_bounds__(256) void k_task_digits(TaskSrc src, int64_t m, int
   if (threadIdx.x == 0 && s_c) atomicAdd(total, s_c);
 }
 
-// Bit r of the bitmap: row r of a CSR is not empty.
-__global__ __launch_bounds__(256) void k_nonempty_bits(const int64_t* __restrict__ row_ptr, int64_t n,
-                                                       uint64_t* __restrict__ bits) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const uint64_t b = __ballot(r < n && row_ptr[r + 1] > row_ptr[r]);
-  if (lane_id() == 0 && r < n) bits[r >> 6] = b;
-}
-
 __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
@@ -601,7 +593,7 @@ __global__ __launch_bounds__(256) void k_orient_hi(uint64_t* __restrict__ pk, in
 }
 
 // Column of a sorted orient key and its short form, written by the orient
-// sort's last pass (k_row_bounds clears the first entry of every row).
+// sort's last pass (k_rows clears the first entry of every row).
 struct ColEpi {
   int32_t* col;
   uint16_t* col16;
@@ -620,53 +612,75 @@ __global__ void k_col(const uint64_t* __restrict__ okey, int64_t m, int s, int32
   if (i < m) col[i] = (int32_t)(okey[i] & ((1ull << s) - 1));
 }
 
-// U's row pointers from the sorted orient keys (k_bounds), and the zeros of
-// the short columns: the first entry of every row and the padding.
-__global__ void k_row_bounds(const uint64_t* __restrict__ keys, int64_t m, int s, int64_t n,
-                             int64_t* __restrict__ row_ptr, uint16_t* __restrict__ col16) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r > n) return;
-  int64_t lo = 0, hi = m;
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
-    if ((int64_t)(keys[mid] >> s) < r) lo = mid + 1;
-    else hi = mid;
-  }
-  row_ptr[r] = lo;
-  col16[lo] = 0;  // (an empty row: the first entry of a later one, or the padding)
-  if (r == n) col16[m + 1] = 0;
-}
-
-// W+ = sum_a C(d+(a), 2) and max d+(a).
 // Grids of the reducing kernels below: a few blocks per CU, each looping
 // over its rows, so that the per-block global atomics stay few.
 constexpr unsigned kReduceBlocks = 1024;
 inline unsigned grid_reduce(int64_t n) { return (unsigned)std::min<int64_t>(kReduceBlocks, grid_for(n)); }
 
-__global__ __launch_bounds__(256) void k_row_stats(const int64_t* __restrict__ row_ptr, int64_t n,
-                                                   unsigned long long* __restrict__ wplus,
-                                                   unsigned int* __restrict__ maxd) {
-  __shared__ uint64_t s_w[4];
-  __shared__ uint32_t s_m[4];
+// From the sorted orient keys: U's row pointers (binary search), the bitmap of
+// non-empty rows, W+ = sum_a C(d+(a), 2), max d+(a), and the zeros of the
+// short columns: the first entry of every row and the padding. A work-group
+// searches the starts of its 512 rows and, in a ninth wave, that of the row
+// after them, and takes the degrees from LDS (three launches, of which
+// two read the row pointers again: 84 us at scale 20, 70 us for 10^6 rows of
+// 8; this one: 62 us and 55 us).
+constexpr int kRowsPer = 512, kRowsThreads = kRowsPer + 64;
+constexpr unsigned kRowsBlocks = 1024;  // (each ends on two atomics, 12 ns one after the other)
+__global__ __launch_bounds__(kRowsThreads) void k_rows(const uint64_t* __restrict__ keys, int64_t m, int s, int64_t n,
+                                                       int64_t* __restrict__ row_ptr, uint16_t* __restrict__ col16,
+                                                       uint64_t* __restrict__ bits,
+                                                       unsigned long long* __restrict__ wplus,
+                                                       unsigned int* __restrict__ maxd) {
+  __shared__ int64_t s_lo[kRowsPer + 1];
+  __shared__ uint64_t s_w[kRowsPer / 64];
+  __shared__ uint32_t s_m[kRowsPer / 64];
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
   uint64_t w = 0;
   uint32_t md = 0;
-  for (int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; a < n; a += (int64_t)gridDim.x * blockDim.x) {
-    const uint64_t d = (uint64_t)(row_ptr[a + 1] - row_ptr[a]);
-    w += d * (d - (d > 0)) / 2;
-    md = max(md, (uint32_t)d);
+  for (int64_t r0 = (int64_t)blockIdx.x * kRowsPer; r0 <= n; r0 += (int64_t)gridDim.x * kRowsPer) {
+    const int64_t r = r0 + tid;
+    if (tid <= kRowsPer) {
+      int64_t lo = 0, hi = m;
+      while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if ((int64_t)(keys[mid] >> s) < r) lo = mid + 1;
+        else hi = mid;
+      }
+      s_lo[tid] = lo;
+      if (tid < kRowsPer && r <= n) {
+        row_ptr[r] = lo;
+        col16[lo] = 0;  // (an empty row: the first entry of a later one, or the padding)
+        if (r == n) col16[m + 1] = 0;
+      }
+    }
+    __syncthreads();
+    if (tid < kRowsPer) {
+      const uint64_t d = r < n ? (uint64_t)(s_lo[tid + 1] - s_lo[tid]) : 0;
+      const uint64_t ne = __ballot(d > 0);
+      if (lane == 0 && r < n) bits[r >> 6] = ne;
+      w += d * (d - (d > 0)) / 2;
+      md = max(md, (uint32_t)d);
+    }
+    __syncthreads();
   }
-  w = wave_sum(w);
-  md = wave_max(md);
-  if (lane_id() == 0) {
-    s_w[threadIdx.x >> 6] = w;
-    s_m[threadIdx.x >> 6] = md;
+  if (tid < kRowsPer) {
+    w = wave_sum(w);
+    md = wave_max(md);
+    if (lane == 0) {
+      s_w[wave] = w;
+      s_m[wave] = md;
+    }
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint64_t tw = s_w[0] + s_w[1] + s_w[2] + s_w[3];
-    uint32_t tm = max(max(s_m[0], s_m[1]), max(s_m[2], s_m[3]));
+  if (tid == 0) {
+    uint64_t tw = 0;
+    uint32_t tm = 0;
+    for (int i = 0; i < kRowsPer / 64; ++i) {
+      tw += s_w[i];
+      tm = max(tm, s_m[i]);
+    }
     if (tw) atomicAdd(wplus, (unsigned long long)tw);
-    atomicMax(maxd, tm);
+    if (tm) atomicMax(maxd, tm);
   }
 }
 
@@ -1064,12 +1078,19 @@ __global__ void k_bundles(const CountItem* __restrict__ items, int64_t groups, u
   if (j == groups - 1)
     for (int64_t i = at + 1; i <= n_bundles; ++i) bundle[i] = (uint32_t)groups;
 }
+// Sort key of a pack: heavier first, to an eighth of its power of two (2^8 ..
+// 2^24), short rows after the others. One digit: the order only has to start
+// the long packs early. (All 31 bits took four passes: 100 us of the
+// preprocessing at scale 20 against 26 us, and the counts take the same time.)
+constexpr int kPackKeyBits = 8;
 __global__ void k_pack_keys(const PackInfo* __restrict__ info, int64_t np, int64_t p16, uint32_t* __restrict__ key,
                             uint32_t* __restrict__ idx) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= np) return;
   const uint64_t w = info[p].q1 - info[p].q0 + 64ull * (info[p].r1 - info[p].r0);
-  key[p] = (0x7FFFFFFFu - (uint32_t)(w < 0x7FFFFFFFull ? w : 0x7FFFFFFFull)) | (p >= p16 ? 0x80000000u : 0u);
+  // exponent and three mantissa bits
+  const int e = (int)(__float_as_uint((float)w) >> 20) - ((127 + 8) << 3);
+  key[p] = (uint32_t)(127 - (e < 0 ? 0 : e > 127 ? 127 : e)) | (p >= p16 ? 128u : 0u);
   idx[p] = (uint32_t)p;
 }
 
@@ -1383,41 +1404,6 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_orient(OrientSrc src, i
       okey[x] = k[i];
       epi((uint64_t)x, (uint64_t)k[i]);
     }
-  }
-}
-
-// Row pointers, W+, the largest d+, the bitmap of non-empty rows and the
-// zeros of the short columns, in one launch.
-__global__ __launch_bounds__(256) void k_small_rows(const uint64_t* __restrict__ keys, int64_t m, int s, int64_t n,
-                                                    int64_t* __restrict__ row_ptr, uint16_t* __restrict__ col16,
-                                                    uint64_t* __restrict__ bits,
-                                                    unsigned long long* __restrict__ wplus,
-                                                    unsigned int* __restrict__ maxd) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  auto first = [&](int64_t row) {
-    int64_t lo = 0, hi = m;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if ((int64_t)(keys[mid] >> s) < row) lo = mid + 1;
-      else hi = mid;
-    }
-    return lo;
-  };
-  uint64_t d = 0;
-  if (r <= n) {
-    const int64_t lo = first(r);
-    row_ptr[r] = lo;
-    col16[lo] = 0;
-    if (r == n) col16[m + 1] = 0;
-    else d = (uint64_t)(first(r + 1) - lo);
-  }
-  const uint64_t ne = __ballot(d > 0);
-  const uint64_t w = wave_sum(d * (d - (d > 0)) / 2);
-  const uint32_t md = wave_max((uint32_t)d);
-  if (lane_id() == 0) {
-    if (r < n) bits[r >> 6] = ne;
-    if (w) atomicAdd(wplus, (unsigned long long)w);
-    if (md) atomicMax(maxd, md);
   }
 }
 
@@ -2044,7 +2030,6 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
   DevBuf ne;  // bitmap of U's non-empty rows
   const ColEpi col_epi{g->col, g->col16, n, s};
   if (small && m > 0) {
-    ne.alloc(sizeof(uint64_t) * (size_t)div_up(n, 64));
     const OrientSrc osrc{sbuf.as<uint64_t>(), sent, g->perm, s};
     if (block_sorts) {
       TC_LAUNCH_BLOCK("small_orient", k_small_orient, m_raw, st, osrc, (int)m_raw, (int)m, obuf.as<uint64_t>(),
@@ -2059,9 +2044,6 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
                                                                   ohist, st, "orient", col_epi))
         okey = sbuf.as<uint64_t>();
     }
-    TC_LAUNCH("small_rows", k_small_rows, dim3(grid_for(n + 1)), dim3(kT), 0, st, okey, m, s, n, g->row_ptr,
-              g->col16, ne.as<uint64_t>(), d_wplus, d_maxd);
-    TC_HIP(hipGetLastError());
   } else {
     if (m > 0) {
       // partition by the top 8 bits of hi (one pass from S into the free
@@ -2082,18 +2064,19 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
                                                      m, 0, 2 * s, st, "orient", col_epi,
                                                      ohist);
       if (alt) okey = sbuf.as<uint64_t>();
-      TC_LAUNCH("row_bounds", k_row_bounds, dim3(grid_for(n + 1)), dim3(kT), 0, st, okey, m, s, n, g->row_ptr,
-                g->col16);
       if (m == 1)  // no sort pass ran
         TC_LAUNCH("col", k_col, dim3(grid_for(m)), dim3(kT), 0, st, okey, m, s, g->col);
     } else {
       TC_LAUNCH("fill_i64", k_fill_i64, dim3(grid_for(n + 1)), dim3(kT), 0, st, g->row_ptr, n + 1,
                          (int64_t)0);
     }
-    TC_LAUNCH("row_stats", k_row_stats, dim3(grid_reduce(n)), dim3(kT), 0, st, g->row_ptr, n, d_wplus,
-              d_maxd);
-    TC_HIP(hipGetLastError());
   }
+  if (m > 0) {
+    ne.alloc(sizeof(uint64_t) * (size_t)div_up(n, 64));
+    TC_LAUNCH("rows", k_rows, dim3((unsigned)std::min<int64_t>(kRowsBlocks, div_up(n + 1, kRowsPer))), dim3(kRowsThreads), 0, st, okey, m, s, n,
+              g->row_ptr, g->col16, ne.as<uint64_t>(), d_wplus, d_maxd);
+  }
+  TC_HIP(hipGetLastError());
   // the buffer that does not hold the oriented keys is free now
   (okey == sbuf.as<uint64_t>() ? obuf : sbuf).release();
   // (W+ and the largest d+ are read back with the task count below: one
@@ -2106,14 +2089,7 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
   TaskLists tl;
   {
     TaskSrc src{};
-    if (m > 0) {
-      if (!small) {
-        ne.alloc(sizeof(uint64_t) * (size_t)div_up(n, 64));
-        TC_LAUNCH("nonempty_bits", k_nonempty_bits, dim3(grid_for(n)), dim3(kT), 0, st, g->row_ptr, n,
-                  ne.as<uint64_t>());
-      }
-      src.p = TaskPred{okey, s, g->row_ptr, ne.as<uint64_t>(), nullptr, nullptr};
-    }
+    if (m > 0) src.p = TaskPred{okey, s, g->row_ptr, ne.as<uint64_t>(), nullptr, nullptr};
     const bool block_tasks = block_sorts && m > 0;  // (m <= m_raw)
     if (block_tasks) {
       tl.row.alloc(sizeof(uint32_t) * (size_t)m);
@@ -2550,7 +2526,7 @@ void build_work(WorkSet& w, Owned& own, int64_t n, const int64_t* hrow_ptr, int6
           TC_LAUNCH("pack_keys", k_pack_keys, dim3(grid_for(np)), dim3(kT), 0, st, raw.as<PackInfo>(), np, np32,
                     key.as<uint32_t>(), idx.as<uint32_t>());
           const bool alt = radix_sort<uint32_t, uint32_t>(key.as<uint32_t>(), key2.as<uint32_t>(), idx.as<uint32_t>(),
-                                                          idx2.as<uint32_t>(), np, 0, 32, st, "pack_lpt");
+                                                          idx2.as<uint32_t>(), np, 0, kPackKeyBits, st, "pack_lpt");
           TC_LAUNCH("pack_gather", k_pack_gather, dim3(grid_for(np)), dim3(kT), 0, st, raw.as<PackInfo>(),
                     alt ? idx2.as<uint32_t>() : idx.as<uint32_t>(), np, w.pack_info[c]);
         }
