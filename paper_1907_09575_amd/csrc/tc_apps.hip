@@ -174,19 +174,25 @@ void vertex_counts(const Graph& g, int64_t* d_tri, double* d_cc, int64_t* d_sums
 
 // ---- k-truss ---------------------------------------------------------------------
 
-constexpr unsigned kPeelGrid = 2048;    // work-groups of a round: those resident at 8 waves per SIMD
+constexpr int kPeelWaves = 8, kPeelThreads = 64 * kPeelWaves;
+constexpr unsigned kPeelGrid = 1024;    // work-groups of a round: those resident at 8 waves per SIMD
 constexpr int32_t kAlive = 0x7FFFFFFF;  // state of an edge not yet removed (else: its round)
 
 // A removed edge's triangles are found by walking the neighbourhood of its
 // endpoint of smaller degree d, cut into work entries of walk_chunk(d)
-// neighbours (one wave each), at most 8 per edge: the longest walk of a round
-// would otherwise be one wave's.
-__host__ __device__ inline uint32_t walk_chunk(uint32_t d) {
-  const uint32_t c = ((d + 7) / 8 + 63) & ~63u;
-  return c < 256 ? 256 : c;
+// neighbours (one wave each): the longest walk of a round would otherwise be
+// one wave's, and a round is as long as its chain of dependent loads. At most
+// 16 entries per edge of no fewer than 64 neighbours (RMAT scale 18, 1251
+// rounds: 46.5 ms with 8 of 256, 40.6 ms with 16 of 128, 38.2 ms so); from
+// 2^27 edges on, where rounds are bound by their loads and the lists by
+// memory, 8 of 256.
+constexpr int64_t kFineWalks = (int64_t)1 << 27;
+__host__ __device__ inline uint32_t walk_chunk(uint32_t d, bool fine) {
+  const uint32_t c = (fine ? (d + 15) / 16 + 63 : (d + 7) / 8 + 63) & ~63u, least = fine ? 64 : 256;
+  return c < least ? least : c;
 }
-__device__ __forceinline__ uint32_t walk_entries(uint32_t d) {
-  const uint32_t c = walk_chunk(d);
+__device__ __forceinline__ uint32_t walk_entries(uint32_t d, bool fine) {
+  const uint32_t c = walk_chunk(d, fine);
   return d ? (d + c - 1) / c : 1;
 }
 
@@ -203,6 +209,7 @@ struct TrussArrays {
   int32_t* sup;
   int32_t* tau;
   uint64_t* list[2];
+  bool fine;  // walk_chunk
 };
 
 __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
@@ -219,7 +226,7 @@ __global__ __launch_bounds__(256) void k_truss_entries(TrussArrays A, int64_t m,
   __shared__ unsigned long long s_w[4];
   unsigned long long c = 0;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x)
-    c += walk_entries(min_degree(A, (int32_t)e));
+    c += walk_entries(min_degree(A, (int32_t)e), A.fine);
   c = wave_sum(c);
   if (lane_id() == 0) s_w[threadIdx.x >> 6] = c;
   __syncthreads();
@@ -239,9 +246,10 @@ struct PushQueue {
 };
 
 // Removes the queued edges in round Q.round (trussness Q.tau) and appends
-// their work entries to Q.list.
-__device__ __forceinline__ void truss_flush(const TrussArrays& A, PushQueue& Q) {
-  if (Q.n == 0) return;
+// their work entries to Q.list, at the place that reserve(entries of the
+// wave, held by lane 63) returns (to every lane).
+template <class F>
+__device__ __forceinline__ void truss_take(const TrussArrays& A, PushQueue& Q, F&& reserve) {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
   const int lane = lane_id();
@@ -250,13 +258,11 @@ __device__ __forceinline__ void truss_flush(const TrussArrays& A, PushQueue& Q) 
 #pragma unroll
   for (int j = 0; j < kQ; ++j) {
     const uint32_t i = 64u * j + (uint32_t)lane;
-    n[j] = i < Q.n ? walk_entries(min_degree(A, Q.q[i])) : 0;
+    n[j] = i < Q.n ? walk_entries(min_degree(A, Q.q[i]), A.fine) : 0;
     mine += n[j];
   }
   const uint32_t inc = wave_incl_scan(mine);
-  uint32_t base = 0;
-  if (lane == 63) base = atomicAdd(Q.cnt, inc);
-  base = (uint32_t)__shfl((int)base, 63, 64) + inc - mine;
+  uint32_t base = reserve(inc) + inc - mine;
 #pragma unroll
   for (int j = 0; j < kQ; ++j) {
     if (n[j] == 0) continue;
@@ -268,6 +274,35 @@ __device__ __forceinline__ void truss_flush(const TrussArrays& A, PushQueue& Q) 
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
   Q.n = 0;
+}
+
+// One wave's queue, when it is full.
+__device__ __forceinline__ void truss_flush(const TrussArrays& A, PushQueue& Q) {
+  truss_take(A, Q, [&](uint32_t inc) {
+    uint32_t base = 0;
+    if (lane_id() == 63) base = atomicAdd(Q.cnt, inc);
+    return (uint32_t)__shfl((int)base, 63, 64);
+  });
+}
+
+// What is left in the queues of all waves of a work-group at its end, with
+// one atomic (one per wave: 40 us for a round of 3000 edges, whose walks take
+// 15). Call from all threads.
+__device__ __forceinline__ void truss_flush_all(const TrussArrays& A, PushQueue& Q) {
+  __shared__ uint32_t s_n[kPeelWaves], s_base;
+  const int wave = threadIdx.x >> 6;
+  truss_take(A, Q, [&](uint32_t inc) {
+    if (lane_id() == 63) s_n[wave] = inc;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+    for (int w = 0; w < kPeelWaves; ++w) {
+      if (w < wave) before += s_n[w];
+      all += s_n[w];
+    }
+    if (threadIdx.x == 0 && all) s_base = atomicAdd(Q.cnt, all);
+    __syncthreads();
+    return (all ? s_base : 0u) + before;
+  });
 }
 
 // Queues the edge e of the lanes with `take` set.
@@ -301,19 +336,20 @@ __global__ __launch_bounds__(256) void k_truss_min(TrussArrays A, int64_t m, con
   __syncthreads();
   if (threadIdx.x == 0) {
     v = min(min(s_v[0], s_v[1]), min(s_v[2], s_v[3]));
-    if (v != kAlive) atomicMin(mn, v);
+    // (most work-groups find what another has written)
+    if (v < __hip_atomic_load(mn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(mn, v);
   }
 }
 
 // (lim, lim_out: the level's bound before and after)
-__global__ __launch_bounds__(256) void k_truss_level(TrussArrays A, int64_t m, const int* __restrict__ fresh,
+__global__ __launch_bounds__(kPeelThreads) void k_truss_level(TrussArrays A, int64_t m, const int* __restrict__ fresh,
                                                      const int* __restrict__ mn, const int* __restrict__ lim,
                                                      int* __restrict__ lim_out, int32_t round, uint32_t* __restrict__ cnt) {
   const bool go = *fresh != 0 && *mn != kAlive;
   const int bound = go ? *mn + 1 : *lim;
   if (blockIdx.x == 0 && threadIdx.x == 0) *lim_out = bound;
   if (!go) return;
-  __shared__ int32_t s_q[4][kPushQueue];
+  __shared__ int32_t s_q[kPeelWaves][kPushQueue];
   PushQueue Q{s_q[threadIdx.x >> 6], 0, round, bound + 1, A.list[round & 1], cnt};
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x; i0 < m; i0 += stride) {  // (uniform)
@@ -321,7 +357,7 @@ __global__ __launch_bounds__(256) void k_truss_level(TrussArrays A, int64_t m, c
     const bool take = i < m && A.state[i] == kAlive && A.sup[i] < bound;
     truss_push(A, Q, take, (int32_t)i);
   }
-  truss_flush(A, Q);
+  truss_flush_all(A, Q);
 }
 
 // N(v) = L_v followed by U_v (ascending), with the U position of each edge.
@@ -336,13 +372,19 @@ struct FullAdj {
 // Position in the sorted list a[0, len) holding w, or -1 (distinct entries,
 // len < 2^31).
 __device__ __forceinline__ int32_t find_sorted(const int32_t* __restrict__ a, uint32_t len, int32_t w) {
-  uint32_t lo = 0, hi = len;
-  while (lo < hi) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (a[mid] < w) lo = mid + 1;
-    else hi = mid;
+  // three pivots a step, read together: a walk is a chain of these loads
+  uint32_t lo = 0, hi = len;  // the first entry >= w lies in [lo, hi]
+  while (hi - lo > 3) {
+    const uint32_t q = (hi - lo) >> 2, p1 = lo + q, p2 = p1 + q, p3 = p2 + q;
+    const int32_t v1 = a[p1], v2 = a[p2], v3 = a[p3];
+    hi = v1 >= w ? p1 : v2 >= w ? p2 : v3 >= w ? p3 : hi;
+    lo = v3 < w ? p3 + 1 : v2 < w ? p2 + 1 : v1 < w ? p1 + 1 : lo;
   }
-  return lo < len && a[lo] == w ? (int32_t)lo : -1;
+  int32_t at = -1;
+#pragma unroll
+  for (uint32_t j = 0; j < 4; ++j)
+    if (lo + j < len && lo + j <= hi && a[lo + j] == w) at = (int32_t)(lo + j);
+  return at;
 }
 
 // One wave per work entry of this round: edge e = (a, b), a chunk of the
@@ -352,13 +394,14 @@ __device__ __forceinline__ int32_t find_sorted(const int32_t* __restrict__ a, ui
 // takes one from the support of each of e1, e2 that stays, and an edge that
 // this brings below lim goes to the next round's list (the one subtraction
 // that crosses lim sees it). Edges marked for the next round count as staying.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_truss_peel(TrussArrays T, FullAdj A, int32_t round,
-                                                    const int* __restrict__ limp, const uint32_t* __restrict__ cnt,
-                                                    uint32_t* __restrict__ cnt_next) {
+__global__ __launch_bounds__(kPeelThreads) __attribute__((amdgpu_waves_per_eu(8)))
+void k_truss_peel(TrussArrays T, FullAdj A, int32_t round, const int* __restrict__ limp,
+                  const uint32_t* __restrict__ cnt, uint32_t* __restrict__ cnt_next) {
   const uint32_t nF = *cnt;
+  if (blockIdx.x * kPeelWaves >= nF) return;
   const uint64_t* __restrict__ F = T.list[round & 1];
   const int lim = *limp;
-  __shared__ int32_t s_q[4][kPushQueue];
+  __shared__ int32_t s_q[kPeelWaves][kPushQueue];
   PushQueue Q{s_q[threadIdx.x >> 6], 0, round + 1, lim + 1, T.list[(round + 1) & 1], cnt_next};
   const int lane = lane_id();
   const uint32_t stride = gridDim.x * (blockDim.x / 64);
@@ -375,7 +418,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
     const uint32_t ly = a_small ? lb : la, uy = (a_small ? db : da) - ly;
     const int64_t lpx = a_small ? lpa : lpb, rpx = (a_small ? rpa : rpb) - (int64_t)lx;
     const int64_t lpy = a_small ? lpb : lpa, rpy = a_small ? rpb : rpa;
-    const uint32_t c = walk_chunk(dx), first = (uint32_t)(w0 >> 32) * c;
+    const uint32_t c = walk_chunk(dx, T.fine), first = (uint32_t)(w0 >> 32) * c;
     const uint32_t i_end = min(dx, first + c);
     for (uint32_t i0 = first; i0 < i_end; i0 += 64) {  // (uniform across the wave)
       const uint32_t i = i0 + (uint32_t)lane;
@@ -408,7 +451,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
       truss_push(T, Q, t2, e2);
     }
   }
-  truss_flush(T, Q);
+  truss_flush_all(T, Q);
 }
 
 int32_t truss(const Graph& g, int32_t* d_tau, hipStream_t st) {
@@ -422,7 +465,7 @@ int32_t truss(const Graph& g, int32_t* d_tau, hipStream_t st) {
   Lower L;
   build_lower(L, g, st);
   TC_LAUNCH("truss_fill", k_fill_i32, dim3(grid_threads(m)), dim3(kAT), 0, st, state.as<int32_t>(), m, kAlive);
-  TrussArrays T{L.erow.as<uint32_t>(), g.col, g.deg, state.as<int32_t>(), sup.as<int32_t>(), d_tau, {}};
+  TrussArrays T{L.erow.as<uint32_t>(), g.col, g.deg, state.as<int32_t>(), sup.as<int32_t>(), d_tau, {}, m < kFineWalks};
   const unsigned sweep = (unsigned)std::min<int64_t>(2048, grid_threads(m));  // (whole-array kernels)
   DevBuf total(sizeof(unsigned long long));
   TC_HIP(hipMemsetAsync(total.p, 0, total.bytes, st));
@@ -457,10 +500,10 @@ int32_t truss(const Graph& g, int32_t* d_tau, hipStream_t st) {
     for (int b = 0; b < kBatches; ++b) {
       TC_LAUNCH("truss_min", k_truss_min, dim3(sweep), dim3(kAT), 0, st, T, m, &d->cnt[b * kRounds], &d->mn[b],
                 &d->fresh[b]);
-      TC_LAUNCH("truss_level", k_truss_level, dim3(sweep), dim3(kAT), 0, st, T, m, &d->fresh[b], &d->mn[b],
+      TC_LAUNCH("truss_level", k_truss_level, dim3((sweep + 1) / 2), dim3(kPeelThreads), 0, st, T, m, &d->fresh[b], &d->mn[b],
                 &d->lim[b], &d->lim[b + 1], round, &d->cnt[b * kRounds]);
       for (int r = 0; r < kRounds; ++r, ++round)
-        TC_LAUNCH("truss_peel", k_truss_peel, dim3(kPeelGrid), dim3(kAT), 0, st, T, A, round, &d->lim[b + 1],
+        TC_LAUNCH("truss_peel", k_truss_peel, dim3(kPeelGrid), dim3(kPeelThreads), 0, st, T, A, round, &d->lim[b + 1],
                   &d->cnt[b * kRounds + r], &d->cnt[b * kRounds + r + 1]);
     }
     TC_HIP(hipGetLastError());
