@@ -10,13 +10,14 @@ pairs per second over whole steps; the count phase alone (the paper's tct) and
 preprocessing (ppt) are reported beside it.
 
 Roofline: every library launch in the timed steps is bracketed by HIP events
-(tc_timer_attach) on the stream it runs on; the dominant kernel is the count
-class with the most algorithmic bytes per launch (4 per probe + 4 per
-hashed-row key + 12 per task + 32 per row of its class), and those bytes over
-its average event time give `achieved`. (The light count classes run on a
-side stream beside the heavy ones, so per-kernel event times overlap; the
-count phase's own wall time, `count_ms`, comes from events around tc_count.) `count_median_ms` times tc_count alone on the resident graph
-(2 warm-ups, median of 11).
+(tc_timer_attach) on the stream it runs on. The dominant kernels are those of
+the count; rows of all classes share launches and the light ones run on a side
+stream beside the heavy ones, so their event times overlap and the count is
+priced as a whole: its algorithmic bytes (2 per probe of a short row, whose
+16-bit columns it reads, 4 per other probe, + 4 per hashed-row key + 12 per
+task + 32 per row) over the wall time of its phase (`count_ms`, events around
+tc_count) give `achieved`. `count_median_ms` times tc_count alone on the
+resident graph (2 warm-ups, median of 11).
 
 Beside the step: one rank's block of the 13 x 13 grid (`block`), the
 ablations of Section 7.3 and the per-rank tables of Section 7.2
@@ -90,26 +91,70 @@ def parse():
 
 
 def count_kernel_bytes(stats: dict, cls: str) -> int:
-    """Algorithmic bytes of one launch of count:<cls>: every probe reads one
-    int32 of U (4 B); every hashed row is read once to build its table (4 B per
+    """Algorithmic bytes of the rows of one class with 32-bit columns: every
+    probe reads one int32 of U (4 B); every hashed row is read once to build its table (4 B per
     key) and its row bounds and task range once (32 B); every task reads its
     start (4 B) and its prefix entry (8 B)."""
     s = stats[cls]
     return 4 * s["probes"] + 4 * s["table_keys"] + 12 * s["tasks"] + 32 * s["rows"]
 
 
+def short_row_probes(tc, g) -> int:
+    """Probes of the short rows of g (those counted from 16-bit columns): all
+    with at most 65534 vertices; else those of the last 65534 ranks, unless the
+    out-degrees are even (the largest at most 8 times the average)."""
+    import torch
+    info = g.info()
+    n, m, span = info["n"], info["m"], 65534
+    if m == 0 or m > (1 << 31) - 64:
+        return 0
+    if n <= span:
+        return info["probes"]
+    if info["max_out_degree"] * n <= 8 * m:
+        return 0
+    rp, col, _ = tc.tc_graph_export(g)
+    total = 0
+    for i0 in range(0, m, 1 << 26):
+        i = torch.arange(i0, min(m, i0 + (1 << 26)), device=rp.device)
+        b = col[i0:i0 + (1 << 26)].long()
+        left = rp[torch.searchsorted(rp, i, right=True)] - i - 1
+        total += int(left[(b >= n - span) & (rp[b + 1] > rp[b])].sum().item())
+    return total
+
+
+def count_bytes(tc, g, stats: dict) -> int:
+    """Algorithmic bytes of the whole count of g."""
+    return (sum(count_kernel_bytes(stats, c) for c in stats if stats[c]["rows"])
+            - 2 * short_row_probes(tc, g))
+
+
+def dedup_passes(n: int, m_raw: int) -> int:
+    """Passes of the dedup sort: all bits of the keys up to 32768 vertices and
+    2^20 pairs, else as many top bits as leave 8192 keys a group if all edges
+    shared one interval of the lower endpoint."""
+    s = max(1, (n - 1).bit_length())
+    full = (2 * s + 7) // 8
+    if n <= 32768 and m_raw <= 1 << 20:
+        return full
+    top = s - min(0 if s <= 8 else s - 8 if s <= 24 else s - 16, 15)
+    p = (top + 7) // 8
+    while 8 * p < 2 * s and m_raw > 1 << min(62, 8 * p + 13 - top):
+        p += 1
+    return min(p, full)
+
+
 def preprocess_bytes(n: int, m_raw: int, m: int, tasks: int) -> int:
     """Algorithmic bytes of tc_preprocess (the paper's ppt): read the raw pairs
     once (8 per pair); an LSD radix sort moves 16 bytes per key per 8-bit
-    pass (read + write of an 8-byte key) over ceil(2 log2 n / 8) passes: the
-    dedup sort over the raw pairs and the orient sort over the simple edges;
-    the rank sort over the n vertices takes ceil(log2 n / 8) passes; then the
-    CSR (4 per edge, 8 per row pointer, 4 per rank-map entry) and the task
-    lists (4 + 8 per task) are written once."""
+    pass (read + write of an 8-byte key): the dedup sort over the raw pairs
+    (dedup_passes) and the orient sort over the simple edges (ceil(2 log2 n /
+    8) passes); the rank sort over the n vertices takes ceil(log2 n / 8)
+    passes; then the CSR (4 per edge, 8 per row pointer, 4 per rank-map entry)
+    and the task lists (4 + 8 per task) are written once."""
     s = max(1, (n - 1).bit_length())
     p_edge = (2 * s + 7) // 8
     p_rank = (s + 7) // 8
-    return (8 * m_raw + 16 * p_edge * m_raw + 16 * p_rank * n + 16 * p_edge * m
+    return (8 * m_raw + 16 * dedup_passes(n, m_raw) * m_raw + 16 * p_rank * n + 16 * p_edge * m
             + 4 * m + 8 * (n + 1) + 4 * n + 12 * tasks)
 
 
@@ -329,8 +374,8 @@ def bench_ablation(tc, g, T, qs):
 def bench_large(tc, args):
     """RMAT scale 26 (2^30 raw pairs, the shape of the paper's g500-s26
     input): one warm-up, then one timed preprocess + count step, the count
-    alone on the resident graph (median of 5, HIP events) and the dominant
-    count kernel against the HBM roofline. T is checked against the value the
+    alone on the resident graph (median of 5, HIP events) and the count
+    against the HBM roofline. T is checked against the value the
     oracle stored for this input (tests/golden)."""
     import numpy as np
     import torch
@@ -375,25 +420,21 @@ def bench_large(tc, args):
         assert int(out.item()) == T
         if r >= 2:
             runs.append(e0.elapsed_time(e1))
+    alg = count_bytes(tc, g, cstats)
     g.free()
     del src, dst
     torch.cuda.empty_cache()
     step_ms = (t1 - t0) * 1e3
     count_ms = ev[1].elapsed_time(ev[2])  # wall time of the count phase on the stream
-    counts = {k: v for k, v in kern.items() if k.startswith("count:")}
-    dom = max((k for k in counts if cstats[k.split(":", 1)[1]]["rows"]),
-              key=lambda k: count_kernel_bytes(cstats, k.split(":", 1)[1]))
-    cls = dom.split(":", 1)[1]
-    achieved = count_kernel_bytes(cstats, cls) / (counts[dom]["avg_ms"] / 1e3) / 1e9
+    achieved = alg / (count_ms / 1e3) / 1e9
     res = {"workload": "rmat%d_ef%d_preprocess_count" % (scale, args.edge_factor), "n": n, "m_raw": m_raw,
            "m": info["m"], "triangles": T, "wedges_plus": info["wedges_plus"], "step_ms": round(step_ms, 3),
            "edges_per_s": m_raw / (step_ms / 1e3), "preprocess_ms": round(step_ms - count_ms, 3),
            "count_ms": round(count_ms, 3), "count_median_ms": round(float(np.median(runs)), 3),
            "count_median_edges_per_s": info["m"] / (float(np.median(runs)) / 1e3),
-           "roofline": {"bound": "hbm", "kernel": dom, "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS,
+           "roofline": {"bound": "hbm", "kernel": "count", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS,
                         "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                        "avg_launch_ms": round(counts[dom]["avg_ms"], 4),
-                        "algorithmic_bytes_per_launch": count_kernel_bytes(cstats, cls)},
+                        "avg_launch_ms": round(count_ms, 4), "algorithmic_bytes_per_launch": alg},
            "kernels_top": {k: {"total_ms": round(v["total_ms"], 3), "launches": v["launches"]}
                            for k, v in sorted(((k, v) for k, v in kern.items() if not k.startswith("_")),
                                               key=lambda kv: -kv[1]["total_ms"])[:10]}}
@@ -411,8 +452,7 @@ def bench_support(tc, args):
     the support workload): tc_count, then tc_edge_support in FULL and ORIENTED
     mode, each 2 warm-ups and the median of 5 (HIP events around the call on
     the current stream). Every run is checked: sum of FULL = 3T, sum of
-    ORIENTED = T. Algorithmic bytes: the count's (count_kernel_bytes over the
-    classes), plus 4m to clear the support array and 4m to write it back, plus
+    ORIENTED = T. Algorithmic bytes: the count's (count_bytes), plus 4m to clear the support array and 4m to write it back, plus
     for FULL the H_b edge ids read from the tables (4m) and two remote int32
     read-modify-writes per triangle (16 T)."""
     import numpy as np
@@ -435,7 +475,7 @@ def bench_support(tc, args):
     T = int(cnt.item())
     m = g.info()["m"]
     cstats = tc.tc_graph_class_stats(g)
-    b_count = sum(count_kernel_bytes(cstats, c) for c in cstats if cstats[c]["rows"])
+    b_count = count_bytes(tc, g, cstats)
     sup = torch.empty(max(m, 1), dtype=torch.int32, device=dev)
     out = {"workload": "rmat%d_ef%d_support" % (scale, args.edge_factor), "n": 1 << scale,
            "m_raw": m_raw, "m": m, "triangles": T}
@@ -568,7 +608,7 @@ def bench_batch(tc, args):
     bytes_total = 0
     for g in graphs:
         cs = tc.tc_graph_class_stats(g)
-        bytes_total += sum(count_kernel_bytes(cs, c) for c in cs if cs[c]["rows"])
+        bytes_total += count_bytes(tc, g, cs)
     plain_s = min(plain_times)
     res = {
         "graphs": n, "m_raw": m_raw, "m": m_total, "triangles": int(out.sum().item()),
@@ -811,9 +851,10 @@ def main():
     count_kernel_sum_ms = sum(v["total_ms"] for k, v in kern.items() if k.startswith("count:")) / args.steps
     # count alone on the resident graph: 2 warm-ups, median of 11 (HIP events
     # around tc_count on the current stream)
-    count_runs = []
+    count_runs, alg = [], None
     if not args.copy_calibration:
         g = tc.tc_preprocess(src, dst, n)
+        alg = count_bytes(tc, g, cstats)
         for r in range(13):
             e0 = torch.cuda.Event(enable_timing=True)
             e1 = torch.cuda.Event(enable_timing=True)
@@ -830,33 +871,14 @@ def main():
                         if not k.startswith("count:") and not k.startswith("_") and k != "zero_i64") / args.steps
     pre_ms = step_s * 1e3 - count_ms  # wall time of the step outside the count phase
     launches = {k: v for k, v in kern.items() if not k.startswith("_")}
-    # the dominant kernel: the count class with the most algorithmic bytes
-    # (the light classes run on a side stream beside the heavy ones, so the
-    # event-timed durations of kernels overlap and their sum exceeds the
-    # phase's wall time)
-    dom = max((k for k in launches if k.startswith("count:") and k.split(":", 1)[1] in cstats
-               and cstats[k.split(":", 1)[1]]["rows"]),
-              key=lambda k: count_kernel_bytes(cstats, k.split(":", 1)[1]))
-    roofline = None
-    if dom.startswith("count:"):
-        cls = dom.split(":", 1)[1]
-        bytes_per_launch = count_kernel_bytes(cstats, cls)
-        avg_s = launches[dom]["avg_ms"] / 1e3
-        achieved = bytes_per_launch / avg_s / 1e9
-        roofline = {"bound": "hbm", "kernel": dom, "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS,
-                    "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                    "traffic": load_traffic(dom), "traffic_kind": "fabric (L2 misses: Infinity Cache or HBM)",
-                    "algorithmic_bytes_per_launch": bytes_per_launch,
-                    "avg_launch_ms": round(launches[dom]["avg_ms"], 4),
-                    "copy_GBps": copy_gbs,
-                    "frac_of_copy": round(achieved / copy_gbs, 4) if copy_gbs else None}
-    else:
-        roofline = {"bound": "hbm", "kernel": dom, "achieved": None, "peak": HBM_PEAK_GBS,
-                    "unit": "GB/s", "frac": None, "traffic": None, "copy_GBps": copy_gbs,
-                    "note": "dominant kernel is not a count kernel"}
-
-    # whole count phase against the same roofline
-    count_bytes = sum(count_kernel_bytes(cstats, c) for c in cstats if cstats[c]["rows"])
+    # the count against the roofline (its launches overlap on two streams)
+    achieved = alg / (count_ms / 1e3) / 1e9 if alg else None
+    roofline = {"bound": "hbm", "kernel": "count", "achieved": round(achieved, 2) if alg else None,
+                "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4) if alg else None,
+                "traffic": load_traffic("count"), "traffic_kind": "fabric (L2 misses: Infinity Cache or HBM)",
+                "algorithmic_bytes_per_launch": alg, "avg_launch_ms": round(count_ms, 4),
+                "copy_GBps": copy_gbs,
+                "frac_of_copy": round(achieved / copy_gbs, 4) if alg and copy_gbs else None}
     result = {
         "metric": METRIC,
         "value": m_raw / step_s,
@@ -895,7 +917,7 @@ def main():
         "count_edges_per_s": info["m"] / (count_ms / 1e3) if count_ms > 0 else None,
         "count_raw_edges_per_s": m_raw / (count_ms / 1e3) if count_ms > 0 else None,
         "count_probes_per_s": info["probes"] / (count_ms / 1e3) if count_ms > 0 else None,
-        "count_phase_alg_GBps": count_bytes / (count_ms / 1e3) / 1e9 if count_ms > 0 else None,
+        "count_phase_alg_GBps": achieved,
         "classes": {c: {"probes": v["probes"], "rows": v["rows"], "tasks": v["tasks"],
                         "workgroups": v["workgroups"], "table_slots": v["table_slots"]}
                     for c, v in cstats.items() if v["rows"]},
