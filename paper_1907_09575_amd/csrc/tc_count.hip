@@ -50,8 +50,8 @@
 //   - in buckets of four 16-bit slots (packs): one 8-byte LDS read.
 // The 32-bit kernels are bound by HBM at 4 bytes per probe; these move half
 // of that and are bound by vector issue (about 8 instructions per probe and
-// lane of which half is the lookup). tc_count, RMAT: scale 20 1215 -> 660 us,
-// scale 22 5422 -> 3440 us (of which 690 us are its 32-bit packs), scale 14
+// lane of which half is the lookup). tc_count, RMAT: scale 20 1215 -> 645 us,
+// scale 22 5427 -> 3300 us, scale 24 29.9 -> 19.1 ms, scale 14
 // (n = 16384, all rows short) 170 -> 57 us.
 // Reductions: per-lane 32-bit hit counters, wave reduction by xor shuffles,
 // one 64-bit atomic per work-group into the caller's counter (order-free and
