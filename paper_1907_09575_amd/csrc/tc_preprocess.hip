@@ -1166,6 +1166,18 @@ __global__ void k_emit_items(const uint32_t* __restrict__ offs, const uint32_t* 
 constexpr int64_t kSmallN = 32768, kSmallRaw = 1 << 20;
 constexpr int kSmallThreads = 1024, kSmallWaves = kSmallThreads / 64;
 constexpr int64_t kBlockSortMax = 16 * kSmallThreads;
+// Look-back words of a small graph's sorts (two bytes a pair hold those of its
+// three sorts of up to four passes) and scans.
+inline size_t sort_pool_bytes(int64_t m_raw) { return ((size_t)64 << 10) + ((2 * (size_t)m_raw + 255) & ~(size_t)255); }
+constexpr size_t kSmallScanPool = (size_t)32 << 10;
+// Up to as many pairs a small graph's temporaries are carved from one block:
+// taking each from the cache and returning it records an event, and some 25 of
+// them were a seventh of a small call (4096 vertices, 32768 pairs,
+// preprocessing and count: 533 us, 460 us so). Past
+// this, what a block without reuse holds beyond the peak would show in a
+// server's memory budget.
+constexpr int64_t kArenaRaw = (int64_t)1 << 16;
+inline size_t arena_bytes_of(int64_t m_raw, int64_t n) { return (size_t)(48 * m_raw + 48 * n) + ((size_t)256 << 10); }
 
 // (32 keys per thread spill: 105 us for 32768 pairs, against 75 us in passes.)
 
@@ -1839,11 +1851,18 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
   const size_t deg_at = 64 + sizeof(uint32_t) * (256 * 2 + 3 * kHistWords);
   const size_t pool_at = deg_at + (small ? (sizeof(uint32_t) * (size_t)n + 255) & ~(size_t)255 : 0);
   // (and of the scans)
-  const size_t scan_at = pool_at + (small ? kZeroPool : 0);
-  DevBuf zs(scan_at + kScanPool);
+  const size_t pool_bytes = small && !block_sorts ? sort_pool_bytes(m_raw) : 0;
+  // (every part begins at a multiple of 64 bytes: the scan words are 64-bit)
+  const size_t scan_at = pool_at + pool_bytes, scan_bytes = small ? kSmallScanPool : kScanPool;
+  DevBuf arena;
+  if (small && m_raw <= kArenaRaw) {
+    arena.alloc(arena_bytes_of(m_raw, n));
+    temps.carve_from(arena.as<char>(), arena.bytes);
+  }
+  DevBuf zs(scan_at + scan_bytes);
   TC_HIP(hipMemsetAsync(zs.p, 0, zs.bytes, st));
-  if (small) temps.zero_pool(zs.as<char>() + pool_at, kZeroPool);
-  temps.scan_pool(zs.as<char>() + scan_at, kScanPool);
+  if (pool_bytes) temps.zero_pool(zs.as<char>() + pool_at, pool_bytes);
+  temps.scan_pool(zs.as<char>() + scan_at, scan_bytes);
   char* const zb = zs.as<char>();
   int* d_err = reinterpret_cast<int*>(zb);
   int* d_refused = reinterpret_cast<int*>(zb + 4);

@@ -279,6 +279,9 @@ struct TempCtx {
   size_t zero_left = 0;
   char* scan_zero = nullptr;
   size_t scan_zero_left = 0;
+  // one block that the scope's DevBufs are carved from while it lasts
+  char* arena = nullptr;
+  size_t arena_left = 0;
 };
 TempCtx& temp_ctx();
 
@@ -298,6 +301,13 @@ struct TempStream {
     temp_ctx().scan_zero = p;
     temp_ctx().scan_zero_left = bytes;
   }
+  // `bytes` at p: DevBufs allocated from now on in this scope lie there, one
+  // after the other (their places are not used again), while they fit. The
+  // caller's buffer, which must outlive them.
+  void carve_from(char* p, size_t bytes) {
+    temp_ctx().arena = p;
+    temp_ctx().arena_left = bytes;
+  }
   TempStream(const TempStream&) = delete;
   TempStream& operator=(const TempStream&) = delete;
 };
@@ -307,17 +317,26 @@ struct DevBuf {
   void* p = nullptr;
   size_t bytes = 0;
   hipStream_t st = nullptr;
+  bool carved = false;  // from the scope's arena
   DevBuf() = default;
   explicit DevBuf(size_t b) { alloc(b); }
   void alloc(size_t b) {
     release();
     bytes = b;
     if (!b) return;
-    st = temp_ctx().st;
-    p = cache_alloc(b, st);
+    TempCtx& ctx = temp_ctx();
+    st = ctx.st;
+    carved = ((b + 255) & ~(size_t)255) <= ctx.arena_left;
+    if (carved) {
+      p = ctx.arena;
+      ctx.arena += (b + 255) & ~(size_t)255;
+      ctx.arena_left -= (b + 255) & ~(size_t)255;
+    } else {
+      p = cache_alloc(b, st);
+    }
   }
   void release() {
-    if (p) cache_free(p, st, false);
+    if (p && !carved) cache_free(p, st, false);
     p = nullptr;
     bytes = 0;
   }
@@ -326,6 +345,7 @@ struct DevBuf {
     std::swap(p, o.p);
     std::swap(bytes, o.bytes);
     std::swap(st, o.st);
+    std::swap(carved, o.carved);
   }
   DevBuf(const DevBuf&) = delete;
   DevBuf& operator=(const DevBuf&) = delete;
@@ -524,7 +544,6 @@ constexpr int kRsThreads = 512;  // of a sort tile's work-group (see k_rs_oneswe
 // Look-back words of all passes of a sort up to this size are cleared by
 // one memset (see radix_sort_cfg).
 constexpr size_t kLbClearOnceBytes = (size_t)4 << 20;
-constexpr size_t kZeroPool = (size_t)2 << 20;  // look-back words of a small graph's sorts
 constexpr int64_t kRawCountTiles = 256;
 constexpr int kLbWin = 4;  // predecessors read per look-back step
 

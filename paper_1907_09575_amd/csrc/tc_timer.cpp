@@ -42,6 +42,7 @@ TempCtx& temp_ctx() {
 TempStream::TempStream(hipStream_t st) : prev(temp_ctx()) {
   fail_word = cache_alloc(sizeof(int), st);
   TC_HIP(hipMemsetAsync(fail_word, 0, sizeof(int), st));
+  temp_ctx() = TempCtx{};  // (pools and arena belong to the scope that set them)
   temp_ctx().active = true;
   temp_ctx().st = st;
   temp_ctx().fail = static_cast<int*>(fail_word);
