@@ -232,7 +232,8 @@ __global__ __launch_bounds__(256) void k_distinct_mark(uint64_t* __restrict__ S,
 // What a group may hold: the sort's bits are chosen so that even edges that
 // all share one interval of lo average at most kGrpMean keys a group, so a
 // tile and a group fit the set; a group of more than kGrpMax keys (one edge
-// that often), or a set that is full all the same, sets *fail, and the host
+// that often), or a set that is so full that a key finds no word in
+// kGrpProbes, sets *fail: what is left of the launch is skipped, and the host
 // sorts by all bits instead.
 // Two or three passes of the sort, of 1.28 ms each at scale 24 (256 M pairs),
 // become LDS work of the read that the mark needs anyway.
@@ -243,6 +244,7 @@ constexpr int kGrpSlots = 16384;  // 64 KiB: two work-groups a CU
 constexpr int kGrpMeanLog2 = 13;
 constexpr int64_t kGrpMax = (int64_t)1 << 20;  // (positions take 21 bits)
 constexpr int kGrpAhead = 64;  // keys past the tile read with it
+constexpr int kGrpProbes = 1024;
 
 __global__ __launch_bounds__(kGrpThreads, 8) void k_distinct_groups(uint64_t* S, MixCode mc, int64_t m_raw, int gshift,
                                                                     int bit_lo, uint32_t* __restrict__ ghist,
@@ -251,6 +253,7 @@ __global__ __launch_bounds__(kGrpThreads, 8) void k_distinct_groups(uint64_t* S,
   extern __shared__ uint32_t h_dyn[];
   __shared__ int4 s_tab4[kGrpSlots / 4];
   __shared__ uint32_t s_c;
+  __shared__ int s_stop;
   uint32_t* const tab = reinterpret_cast<uint32_t*>(s_tab4);
   const int tid = threadIdx.x;
   if (tid == 0) s_c = 0;
@@ -283,14 +286,16 @@ __global__ __launch_bounds__(kGrpThreads, 8) void k_distinct_groups(uint64_t* S,
     if (t + gridDim.x < ntiles) load(t + gridDim.x);
 #pragma unroll
     for (int j = 0; j < kGrpSlots / 4 / kGrpThreads; ++j) s_tab4[j * kGrpThreads + tid] = make_int4(0, 0, 0, 0);
+    if (tid == 0) s_stop = __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
+    if (s_stop) break;  // (uniform: it is written again after the barrier below)
     auto enter = [&](uint64_t key, int64_t i) {
       uint32_t h = (uint32_t)key * 0x9E3779B1u ^ (uint32_t)(key >> 32) * 0x6A09E667u;
       h = (h ^ (h >> 15)) * 0x510E527Fu;
       h ^= h >> 16;
       uint32_t slot = h >> 18;
       const uint32_t word = (h << 21) | (uint32_t)(i - i0 + 1);
-      for (int probes = 0; probes < kGrpSlots; ++probes, slot = (slot + 1) & (kGrpSlots - 1)) {
+      for (int probes = 0; probes < kGrpProbes; ++probes, slot = (slot + 1) & (kGrpSlots - 1)) {
         const uint32_t old = atomicCAS(&tab[slot], 0u, word);
         if (old == 0) {
           dc.add(mc.hi(key));
@@ -319,6 +324,8 @@ __global__ __launch_bounds__(kGrpThreads, 8) void k_distinct_groups(uint64_t* S,
           if (tid == 0) atomicOr(fail, 1);
           break;
         }
+        // (no barrier in this loop: a wave may leave it when it sees the flag)
+        if (__hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
         i = base + tid;
         const uint64_t key = at(i);
         on = group(at(base + kGrpThreads - 1)) == last;
