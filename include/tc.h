@@ -27,7 +27,9 @@
  *    any call is TC_ENOMEM and leaves the library usable.
  *  - Environment: TC_SORT_WIDE_WORDS=1 makes every internal radix sort use
  *    the 64-bit look-back words that sorts of 2^31 keys or more take (a test
- *    switch; results are identical).
+ *    switch; results are identical). TC_SCAN_SPINS=k lets a scan's work-group
+ *    wait for its predecessors k tries instead of 65536 before it adds their
+ *    elements itself (a test switch too).
  */
 #ifndef TC_H
 #define TC_H

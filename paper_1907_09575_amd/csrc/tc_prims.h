@@ -171,16 +171,21 @@ __global__ __launch_bounds__(256) void k_scan_final(L load, int64_t n, const Tou
 constexpr uint64_t kScanSum = 1ull << 62;     // of the tile
 constexpr uint64_t kScanPrefix = 2ull << 62;  // of all tiles up to it
 constexpr uint64_t kScanValue = kScanSum - 1;
-constexpr uint32_t kLbSpinMax = 1u << 16;  // look-back waits (scans and sorts) give up after as many tries
+constexpr uint32_t kLbSpinMax = 1u << 16;  // look-back waits (scans and sorts) end after as many tries
+// Tries of a scan's wait: kLbSpinMax, or the environment variable TC_SCAN_SPINS
+// (so that tests reach what a tile does past them).
+uint32_t scan_spins();
 
 // One tile per work-group as in k_scan_final, tiles in the order the
 // work-groups begin (a ticket), so that a tile waits only for tiles that run
-// or have run. The first wave looks back over 64 tiles at a time. words (ticket, then a word per tile; cleared): not used by
-// a scan of one tile.
+// or have run. The first wave looks back over 64 tiles at a time. A wait of
+// more than `spins` tries ends: the wave then adds the elements before its tile
+// itself (slower, the same sum), so that no wrong offset is ever written.
+// words (ticket, then a word per tile; cleared): not used by a scan of one
+// tile. out may not alias what load reads.
 template <class L, class Tout>
 __global__ __launch_bounds__(256) void k_scan(L load, int64_t n, unsigned long long* __restrict__ words,
-                                             Tout* __restrict__ out, Tout* __restrict__ total,
-                                             int* __restrict__ fail) {
+                                             Tout* __restrict__ out, Tout* __restrict__ total, uint32_t spins) {
   constexpr int NT = 256, ITEMS = kScanItems, NW = NT / 64;
   __shared__ Tout s_w[ITEMS][NW];
   __shared__ Tout s_before;
@@ -215,7 +220,7 @@ __global__ __launch_bounds__(256) void k_scan(L load, int64_t n, unsigned long l
       if (lane == 0)
         __hip_atomic_store(mine, (tile ? kScanSum : kScanPrefix) | (uint64_t)own, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
-      uint32_t spins = 0;
+      uint32_t tries = 0;
       int64_t j = (int64_t)tile - 1;  // the nearest tile not yet added
       while (j >= 0) {
         // (before tile 0: a prefix of 0)
@@ -226,8 +231,10 @@ __global__ __launch_bounds__(256) void k_scan(L load, int64_t n, unsigned long l
         // lanes up to the nearest prefix, or all
         const uint64_t use = prefixes ? prefixes ^ (prefixes - 1) : ~0ull;
         if (empty & use) {
-          if (++spins > kLbSpinMax) {  // never expected: give up rather than hang
-            if (lane == 0) atomicExch(fail, 1);
+          if (++tries > spins) {
+            Tout all = 0;
+            for (int64_t i = lane; i < base; i += 64) all += load(i);
+            before = wave_sum(all);
             break;
           }
           __builtin_amdgcn_s_sleep(1);
@@ -361,8 +368,8 @@ const char* intern_name(const std::string& s);
 inline int64_t div_up(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Exclusive scan of the n elements load(0..n-1) into out; if total !=
-// nullptr, the grand total is written there (device pointer). out may alias
-// what load reads only if element i depends on position i alone.
+// nullptr, the grand total is written there (device pointer). out may not
+// alias what load reads.
 //
 // One kernel instead of three saves two launches, which is what a scan of a
 // few thousand to a few million elements costs (block of a 13 x 13 grid, RMAT
@@ -394,7 +401,6 @@ void device_excl_scan_f(L load, Tout* out, int64_t n, Tout* total, hipStream_t s
   unsigned long long* words = nullptr;
   DevBuf own;
   if (nb > 1) {
-    TC_REQUIRE(ctx.fail != nullptr, TC_EDEVICE, "scan: called outside a TempStream scope");
     const size_t bytes = (sizeof(unsigned long long) * (size_t)(nb + 1) + 255) & ~(size_t)255;
     if (bytes <= ctx.scan_zero_left) {
       words = reinterpret_cast<unsigned long long*>(ctx.scan_zero);
@@ -406,11 +412,11 @@ void device_excl_scan_f(L load, Tout* out, int64_t n, Tout* total, hipStream_t s
       TC_HIP(hipMemsetAsync(words, 0, bytes, st));
     }
   }
-  TC_LAUNCH("scan", (k_scan<L, Tout>), dim3((unsigned)nb), dim3(256), 0, st, load, n, words, out, total, ctx.fail);
+  TC_LAUNCH("scan", (k_scan<L, Tout>), dim3((unsigned)nb), dim3(256), 0, st, load, n, words, out, total, scan_spins());
   TC_HIP(hipGetLastError());
 }
 
-// Exclusive scan of n array elements; out may alias in.
+// Exclusive scan of n array elements.
 template <class Tin, class Tout>
 void device_excl_scan(const Tin* in, Tout* out, int64_t n, Tout* total, hipStream_t st) {
   device_excl_scan_f<Tout>(ArrayLoad<Tin, Tout>{in}, out, n, total, st);

@@ -34,6 +34,11 @@ bool sort_wide_words_forced() {
   return v != nullptr && v[0] != '\0' && !(v[0] == '0' && v[1] == '\0');
 }
 
+uint32_t scan_spins() {
+  const char* v = std::getenv("TC_SCAN_SPINS");
+  return v != nullptr && v[0] != '\0' ? (uint32_t)std::strtoul(v, nullptr, 10) : kLbSpinMax;
+}
+
 TempCtx& temp_ctx() {
   static thread_local TempCtx c;
   return c;
