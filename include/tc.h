@@ -29,7 +29,8 @@
  *    the 64-bit look-back words that sorts of 2^31 keys or more take (a test
  *    switch; results are identical). TC_SCAN_SPINS=k lets a scan's work-group
  *    wait for its predecessors k tries instead of 65536 before it adds their
- *    elements itself (a test switch too).
+ *    elements itself, and TC_TRUSS_WALKS=k cuts tc_truss's walks into at most
+ *    k (1 .. 16) entries per edge (test switches too).
  */
 #ifndef TC_H
 #define TC_H
@@ -217,8 +218,10 @@ tc_status tc_transitivity(const tc_graph* g, double* out, void* stream);
  * Computed by peeling from the TC_SUPPORT_FULL support: each round removes
  * the edges whose support in the remaining graph is below k - 2 and takes
  * the triangles they close out of their other edges' support. Synchronises
- * `stream` about once per 32 rounds; allocates temporaries (about 44 m + 8 n
- * bytes, up to 128 m more where most edges join two vertices of high degree).
+ * `stream` about once per 32 rounds; allocates temporaries: about 44 m + 8 n
+ * bytes, and 8 m to 128 m for the list of work entries (up to 16 per edge, the
+ * most where its endpoints have a thousand neighbours or more; fewer per edge
+ * where the memory left does not hold them).
  * TC_EOVERFLOW for 2^31 or more edges.
  */
 tc_status tc_truss(const tc_graph* g, int32_t* d_tau, int32_t* kmax, void* stream);

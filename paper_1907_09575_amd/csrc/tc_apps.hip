@@ -26,6 +26,7 @@
 // round is taken out once, by its removed edge of smallest id; a triangle
 // with an edge removed in an earlier round is already gone.
 #include <algorithm>
+#include <cstdlib>
 #include <cstring>
 
 #include "tc_prims.h"
@@ -182,25 +183,33 @@ constexpr int32_t kAlive = 0x7FFFFFFF;  // state of an edge not yet removed (els
 // endpoint of smaller degree d, cut into work entries of walk_chunk(d)
 // neighbours (one wave each): the longest walk of a round would otherwise be
 // one wave's, and a round is as long as its chain of dependent loads. At most
-// 16 entries per edge of no fewer than 64 neighbours (RMAT scale 18, 1251
-// rounds: 46.5 ms with 8 of 256, 40.6 ms with 16 of 128, 38.2 ms so); from
-// 2^27 edges on, where rounds are bound by their loads and the lists by
-// memory, 8 of 256.
-constexpr int64_t kFineWalks = (int64_t)1 << 27;
-__host__ __device__ inline uint32_t walk_chunk(uint32_t d, bool fine) {
-  const uint32_t c = (fine ? (d + 15) / 16 + 63 : (d + 7) / 8 + 63) & ~63u, least = fine ? 64 : 256;
+// `parts` entries per edge, 1 .. kWalkParts, of no fewer than 1024 / parts
+// neighbours (RMAT scale 18, 1251 rounds: 46.5 ms with 8 of 256, 40.6 ms with
+// 16 of 128, 38.2 ms with 16 of 64).
+constexpr uint32_t kWalkParts = 16;
+constexpr int kWalkChoices = 5;  // parts 16, 8, 4, 2, 1
+__host__ __device__ inline uint32_t walk_chunk(uint32_t d, uint32_t parts) {
+  const uint32_t c = ((d + parts - 1) / parts + 63) & ~63u, least = 1024 / parts;
   return c < least ? least : c;
 }
-__device__ __forceinline__ uint32_t walk_entries(uint32_t d, bool fine) {
-  const uint32_t c = walk_chunk(d, fine);
+__device__ __forceinline__ uint32_t walk_entries(uint32_t d, uint32_t parts) {
+  const uint32_t c = walk_chunk(d, parts);
   return d ? (d + c - 1) / c : 1;
 }
 
-// The peel's arrays. A work entry is an edge id and, above it, its chunk.
-// Rounds are numbered by the launches of k_truss_peel; round i takes the
-// cnt[i] entries of list i % 2 and appends the edges that its triangles
-// bring below lim to the other list. No list is ever compacted from all
-// edges but at a new level.
+// Entries per edge at most: kWalkParts, or less by the environment variable
+// TC_TRUSS_WALKS (so that tests reach the coarser walks at small sizes).
+uint32_t truss_walks() {
+  const char* v = std::getenv("TC_TRUSS_WALKS");
+  return v != nullptr && v[0] != '\0' ? (uint32_t)std::strtoul(v, nullptr, 10) : kWalkParts;
+}
+
+// The peel's arrays. A work entry is an edge id and, above it, its chunk. Every
+// edge is appended once in the whole peel, so one list of all entries holds
+// them, round after round: rounds are numbered by the launches of
+// k_truss_peel, round i takes the cnt[i] entries from start[i] on and appends
+// the edges that its triangles bring below lim after them. No list is ever
+// compacted from all edges but at a new level.
 struct TrussArrays {
   const uint32_t* erow;
   const int32_t* col;
@@ -208,8 +217,8 @@ struct TrussArrays {
   int32_t* state;  // kAlive, or the round that removes the edge
   int32_t* sup;
   int32_t* tau;
-  uint64_t* list[2];
-  bool fine;  // walk_chunk
+  uint64_t* list;
+  uint32_t parts;  // entries of an edge at most (walk_chunk)
 };
 
 __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
@@ -221,16 +230,28 @@ __device__ __forceinline__ uint32_t min_degree(const TrussArrays& A, int32_t e) 
   return min(A.deg[A.erow[e]], A.deg[A.col[e]]);
 }
 
-// Work entries of all edges together: what a list must hold.
+// Work entries of all edges together, for 16, 8, 4, 2 and 1 entries per edge
+// at most: what the list must hold. (Every work-group ends on five atomics to
+// one line, 12 ns each: few work-groups.)
 __global__ __launch_bounds__(256) void k_truss_entries(TrussArrays A, int64_t m, unsigned long long* __restrict__ out) {
-  __shared__ unsigned long long s_w[4];
-  unsigned long long c = 0;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x)
-    c += walk_entries(min_degree(A, (int32_t)e), A.fine);
-  c = wave_sum(c);
-  if (lane_id() == 0) s_w[threadIdx.x >> 6] = c;
+  __shared__ unsigned long long s_w[4][kWalkChoices];
+  unsigned long long c[kWalkChoices] = {};
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x) {
+    const uint32_t d = min_degree(A, (int32_t)e);
+#pragma unroll
+    for (int i = 0; i < kWalkChoices; ++i) c[i] += walk_entries(d, kWalkParts >> i);
+  }
+#pragma unroll
+  for (int i = 0; i < kWalkChoices; ++i) {
+    c[i] = wave_sum(c[i]);
+    if (lane_id() == 0) s_w[threadIdx.x >> 6][i] = c[i];
+  }
   __syncthreads();
-  if (threadIdx.x == 0) atomicAdd(out, s_w[0] + s_w[1] + s_w[2] + s_w[3]);
+  if (threadIdx.x < kWalkChoices) {
+    unsigned long long t = 0;
+    for (int w = 0; w < 4; ++w) t += s_w[w][threadIdx.x];
+    atomicAdd(&out[threadIdx.x], t);
+  }
 }
 
 // A wave's edges for the next frontier, kept in LDS until there are enough for
@@ -241,7 +262,7 @@ struct PushQueue {
   int32_t* q;   // kPushQueue entries of this wave
   uint32_t n;   // (uniform)
   int32_t round, tau;
-  uint64_t* list;
+  uint64_t* list;  // the round's first entry
   uint32_t* cnt;
 };
 
@@ -258,7 +279,7 @@ __device__ __forceinline__ void truss_take(const TrussArrays& A, PushQueue& Q, F
 #pragma unroll
   for (int j = 0; j < kQ; ++j) {
     const uint32_t i = 64u * j + (uint32_t)lane;
-    n[j] = i < Q.n ? walk_entries(min_degree(A, Q.q[i]), A.fine) : 0;
+    n[j] = i < Q.n ? walk_entries(min_degree(A, Q.q[i]), A.parts) : 0;
     mine += n[j];
   }
   const uint32_t inc = wave_incl_scan(mine);
@@ -341,16 +362,18 @@ __global__ __launch_bounds__(256) void k_truss_min(TrussArrays A, int64_t m, con
   }
 }
 
-// (lim, lim_out: the level's bound before and after)
+// (lim, lim_out: the level's bound before and after; start: the first entry of
+// the round)
 __global__ __launch_bounds__(kPeelThreads) void k_truss_level(TrussArrays A, int64_t m, const int* __restrict__ fresh,
                                                      const int* __restrict__ mn, const int* __restrict__ lim,
-                                                     int* __restrict__ lim_out, int32_t round, uint32_t* __restrict__ cnt) {
+                                                     int* __restrict__ lim_out, int32_t round, const uint32_t* __restrict__ start,
+                                                     uint32_t* __restrict__ cnt) {
   const bool go = *fresh != 0 && *mn != kAlive;
   const int bound = go ? *mn + 1 : *lim;
   if (blockIdx.x == 0 && threadIdx.x == 0) *lim_out = bound;
   if (!go) return;
   __shared__ int32_t s_q[kPeelWaves][kPushQueue];
-  PushQueue Q{s_q[threadIdx.x >> 6], 0, round, bound + 1, A.list[round & 1], cnt};
+  PushQueue Q{s_q[threadIdx.x >> 6], 0, round, bound + 1, A.list + *start, cnt};
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x; i0 < m; i0 += stride) {  // (uniform)
     const int64_t i = i0 + threadIdx.x;
@@ -396,13 +419,14 @@ __device__ __forceinline__ int32_t find_sorted(const int32_t* __restrict__ a, ui
 // that crosses lim sees it). Edges marked for the next round count as staying.
 __global__ __launch_bounds__(kPeelThreads) __attribute__((amdgpu_waves_per_eu(8)))
 void k_truss_peel(TrussArrays T, FullAdj A, int32_t round, const int* __restrict__ limp,
-                  const uint32_t* __restrict__ cnt, uint32_t* __restrict__ cnt_next) {
+                  uint32_t* __restrict__ start, const uint32_t* __restrict__ cnt, uint32_t* __restrict__ cnt_next) {
   const uint32_t nF = *cnt;
+  if (blockIdx.x == 0 && threadIdx.x == 0) start[1] = start[0] + nF;  // of the next round
   if (blockIdx.x * kPeelWaves >= nF) return;
-  const uint64_t* __restrict__ F = T.list[round & 1];
+  const uint64_t* const F = T.list + start[0];
   const int lim = *limp;
   __shared__ int32_t s_q[kPeelWaves][kPushQueue];
-  PushQueue Q{s_q[threadIdx.x >> 6], 0, round + 1, lim + 1, T.list[(round + 1) & 1], cnt_next};
+  PushQueue Q{s_q[threadIdx.x >> 6], 0, round + 1, lim + 1, T.list + start[0] + nF, cnt_next};
   const int lane = lane_id();
   const uint32_t stride = gridDim.x * (blockDim.x / 64);
   for (uint32_t f = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6); f < nF; f += stride) {
@@ -418,7 +442,7 @@ void k_truss_peel(TrussArrays T, FullAdj A, int32_t round, const int* __restrict
     const uint32_t ly = a_small ? lb : la, uy = (a_small ? db : da) - ly;
     const int64_t lpx = a_small ? lpa : lpb, rpx = (a_small ? rpa : rpb) - (int64_t)lx;
     const int64_t lpy = a_small ? lpb : lpa, rpy = a_small ? rpb : rpa;
-    const uint32_t c = walk_chunk(dx, T.fine), first = (uint32_t)(w0 >> 32) * c;
+    const uint32_t c = walk_chunk(dx, T.parts), first = (uint32_t)(w0 >> 32) * c;
     const uint32_t i_end = min(dx, first + c);
     for (uint32_t i0 = first; i0 < i_end; i0 += 64) {  // (uniform across the wave)
       const uint32_t i = i0 + (uint32_t)lane;
@@ -465,18 +489,29 @@ int32_t truss(const Graph& g, int32_t* d_tau, hipStream_t st) {
   Lower L;
   build_lower(L, g, st);
   TC_LAUNCH("truss_fill", k_fill_i32, dim3(grid_threads(m)), dim3(kAT), 0, st, state.as<int32_t>(), m, kAlive);
-  TrussArrays T{L.erow.as<uint32_t>(), g.col, g.deg, state.as<int32_t>(), sup.as<int32_t>(), d_tau, {}, m < kFineWalks};
+  TrussArrays T{L.erow.as<uint32_t>(), g.col, g.deg, state.as<int32_t>(), sup.as<int32_t>(), d_tau, nullptr, kWalkParts};
   const unsigned sweep = (unsigned)std::min<int64_t>(2048, grid_threads(m));  // (whole-array kernels)
-  DevBuf total(sizeof(unsigned long long));
+  DevBuf total(sizeof(unsigned long long) * kWalkChoices);
   TC_HIP(hipMemsetAsync(total.p, 0, total.bytes, st));
-  TC_LAUNCH("truss_entries", k_truss_entries, dim3(sweep), dim3(kAT), 0, st, T, m, total.as<unsigned long long>());
-  unsigned long long entries = 0;
-  TC_HIP(hipMemcpyAsync(&entries, total.p, sizeof(entries), hipMemcpyDeviceToHost, st));
+  TC_LAUNCH("truss_entries", k_truss_entries, dim3(std::min(sweep, 512u)), dim3(kAT), 0, st, T, m, total.as<unsigned long long>());
+  unsigned long long entries[kWalkChoices];
+  TC_HIP(hipMemcpyAsync(entries, total.p, sizeof(entries), hipMemcpyDeviceToHost, st));
   check_sorts(st);  // (synchronises st)
-  TC_REQUIRE(entries < 0xFFFFFFFFull, TC_EOVERFLOW, "tc_truss: 2^32 or more work entries");
-  DevBuf l0(sizeof(uint64_t) * (size_t)entries), l1(sizeof(uint64_t) * (size_t)entries);
-  T.list[0] = l0.as<uint64_t>();
-  T.list[1] = l1.as<uint64_t>();
+  // the most entries per edge whose list is indexed by 31 bits and fits the
+  // memory left (one per edge: m < 2^31 of them)
+  DevBuf list;
+  for (int i = 0; T.list == nullptr; ++i) {
+    const bool last = i + 1 == kWalkChoices;
+    if (!last && (entries[i] >> 31 || (kWalkParts >> i) > truss_walks())) continue;
+    try {
+      list.alloc(sizeof(uint64_t) * (size_t)entries[i]);
+    } catch (const Error& e) {
+      if (last || e.status != TC_ENOMEM) throw;
+      continue;
+    }
+    T.list = list.as<uint64_t>();
+    T.parts = kWalkParts >> i;
+  }
   const FullAdj A{g.row_ptr, g.col, L.ptr.as<int64_t>(), L.nbr.as<int32_t>(), L.eid.as<int32_t>()};
 
   // Batches of kRounds rounds, kBatches to a host read-back. Everything a
@@ -486,7 +521,7 @@ int32_t truss(const Graph& g, int32_t* d_tau, hipStream_t st) {
   struct Ctl {  // of one read-back
     int mn[kBatches], fresh[kBatches];
     int lim[kBatches + 1];
-    uint32_t cnt[kBatches * kRounds + 1];
+    uint32_t cnt[kBatches * kRounds + 1], start[kBatches * kRounds + 1];
   };
   DevBuf ctl(sizeof(Ctl));
   Ctl h, init;
@@ -501,10 +536,10 @@ int32_t truss(const Graph& g, int32_t* d_tau, hipStream_t st) {
       TC_LAUNCH("truss_min", k_truss_min, dim3(sweep), dim3(kAT), 0, st, T, m, &d->cnt[b * kRounds], &d->mn[b],
                 &d->fresh[b]);
       TC_LAUNCH("truss_level", k_truss_level, dim3((sweep + 1) / 2), dim3(kPeelThreads), 0, st, T, m, &d->fresh[b], &d->mn[b],
-                &d->lim[b], &d->lim[b + 1], round, &d->cnt[b * kRounds]);
+                &d->lim[b], &d->lim[b + 1], round, &d->start[b * kRounds], &d->cnt[b * kRounds]);
       for (int r = 0; r < kRounds; ++r, ++round)
         TC_LAUNCH("truss_peel", k_truss_peel, dim3(kPeelGrid), dim3(kPeelThreads), 0, st, T, A, round, &d->lim[b + 1],
-                  &d->cnt[b * kRounds + r], &d->cnt[b * kRounds + r + 1]);
+                  &d->start[b * kRounds + r], &d->cnt[b * kRounds + r], &d->cnt[b * kRounds + r + 1]);
     }
     TC_HIP(hipGetLastError());
     TC_HIP(hipMemcpyAsync(&h, ctl.p, sizeof(Ctl), hipMemcpyDeviceToHost, st));
@@ -514,6 +549,7 @@ int32_t truss(const Graph& g, int32_t* d_tau, hipStream_t st) {
     for (int b = 0; b < kBatches; ++b) done = done || (h.fresh[b] && h.mn[b] == kAlive);
     init.lim[0] = h.lim[kBatches];
     init.cnt[0] = h.cnt[kBatches * kRounds];
+    init.start[0] = h.start[kBatches * kRounds];
     if (done) break;
   }
   note_use(g, st);
