@@ -148,13 +148,19 @@ __global__ void k_zero_u64x2(unsigned long long* p) {
   if (threadIdx.x < 2) p[threadIdx.x] = 0;
 }
 
-void vertex_counts(const Graph& g, int64_t* d_tri, double* d_cc, int64_t* d_sums, hipStream_t st) {
-  require_plain(g, "per-vertex triangle counts");
-  // (its temporaries go back to the cache when it returns: a captured graph
-  // could not replay it)
+// Per-vertex counts are not for a stream that is being captured: their
+// temporaries go back to the cache when the call returns, so a replay would
+// write into memory of others. Checked before anything is recorded (the fill of
+// a first temporary would be).
+void require_no_capture(hipStream_t st) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   TC_HIP(hipStreamIsCapturing(st, &cs));
   TC_REQUIRE(cs == hipStreamCaptureStatusNone, TC_EDEVICE, "per-vertex triangle counts: the stream is being captured");
+}
+
+void vertex_counts(const Graph& g, int64_t* d_tri, double* d_cc, int64_t* d_sums, hipStream_t st) {
+  require_plain(g, "per-vertex triangle counts");
+  require_no_capture(st);
   TempStream temps(st);
   const int64_t n = g.n;
   auto* sums = reinterpret_cast<unsigned long long*>(d_sums);
@@ -599,6 +605,7 @@ tc_status tc_transitivity(const tc_graph* gh, double* out, void* stream) {
   return tc::guarded("tc_transitivity", [&] {
     TC_REQUIRE(gh != nullptr && out != nullptr, TC_EINVAL, "tc_transitivity: null argument");
     hipStream_t st = static_cast<hipStream_t>(stream);
+    tc::require_no_capture(st);
     tc::TempStream temps(st);
     tc::DevBuf sums(2 * sizeof(int64_t));
     tc::vertex_counts(*tc::G(gh), nullptr, nullptr, sums.as<int64_t>(), st);
