@@ -27,9 +27,9 @@
 //      of consecutive light rows, owns one contiguous task range; light rows
 //      are packed, heavy rows are cut into per-wave probe ranges.
 #include <algorithm>
+#include <map>
 #include <memory>
 #include <mutex>
-#include <set>
 
 #include "tc_prims.h"
 
@@ -1467,18 +1467,20 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_tasks(TaskSrc src, int 
     else launch_block<16>(name, kern<16>, st, __VA_ARGS__);                                                     \
   } while (0)
 
-// hipFuncSetAttribute for a kernel of more than 64 KiB of dynamic LDS, once
-// per device and kernel.
+// hipFuncSetAttribute for a kernel of more than 64 KiB of dynamic LDS: once per
+// device and kernel, and again when a launch takes more than the launches
+// before it.
 void allow_lds(const void* f, size_t lds) {
   if (lds <= 65536) return;
   static std::mutex mu;
-  static std::set<std::pair<int, const void*>> done;
+  static std::map<std::pair<int, const void*>, size_t> allowed;
   int dev = 0;
   TC_HIP(hipGetDevice(&dev));
   std::lock_guard<std::mutex> lk(mu);
-  if (done.count({dev, f})) return;
+  size_t& most = allowed[{dev, f}];
+  if (lds <= most) return;
   TC_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  done.insert({dev, f});
+  most = lds;
 }
 
 template <int IPT, class... P, class... A>
@@ -2008,17 +2010,7 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
       const int64_t nbuckets = div_up(n, span);
       const int64_t groups = nbuckets * sub;
       const size_t lds = sizeof(uint32_t) * kDegBins;
-      {
-        // (the attribute is set once per device)
-        static std::mutex mu;
-        static std::set<int> done;
-        std::lock_guard<std::mutex> lk(mu);
-        if (!done.count(g->device)) {
-          TC_HIP(hipFuncSetAttribute((const void*)k_degree_hist, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)lds));
-          done.insert(g->device);
-        }
-      }
+      allow_lds((const void*)k_degree_hist, lds);
       // bucket starts: with one digit pass, its digit starts as the sort
       // scanned them (256 exclusive starts); else found by binary search
       DevBuf bp;
