@@ -47,16 +47,6 @@ struct DeviceCache {
 std::mutex g_mu;
 std::map<int, DeviceCache> g_dev;
 
-size_t round_size(size_t b) {
-  if (b <= ((size_t)1 << 20)) {
-    size_t r = 512;
-    while (r < b) r <<= 1;
-    return r;
-  }
-  const size_t g = (size_t)2 << 20;
-  return (b + g - 1) / g * g;
-}
-
 DeviceCache& cache_for(int dev) {
   DeviceCache& c = g_dev[dev];
   if (c.cap == 0) {
@@ -88,6 +78,16 @@ void trim_locked(DeviceCache& c, size_t keep) {
 
 }  // namespace
 
+size_t cache_block_bytes(size_t b) {
+  if (b <= ((size_t)1 << 20)) {
+    size_t r = 512;
+    while (r < b) r <<= 1;
+    return r;
+  }
+  const size_t g = (size_t)2 << 20;
+  return (b + g - 1) / g * g;
+}
+
 // Cached blocks of one size looked at for one last used on the requesting
 // stream before the smallest fitting one is taken.
 constexpr int kReuseScan = 32;
@@ -95,7 +95,7 @@ constexpr int kReuseScan = 32;
 void* cache_alloc(size_t bytes, hipStream_t st) {
   int dev = 0;
   TC_HIP(hipGetDevice(&dev));
-  const size_t rb = round_size(bytes ? bytes : 1);
+  const size_t rb = cache_block_bytes(bytes ? bytes : 1);
   Block b;
   {
     std::lock_guard<std::mutex> lk(g_mu);

@@ -171,6 +171,8 @@ __host__ __device__ inline int pack_table_log2(int64_t d) {
 void* cache_alloc(size_t bytes, hipStream_t st);
 void cache_free(void* p, hipStream_t st, bool idle);
 void cache_release_all();
+// Bytes of the block that a request of b bytes takes.
+size_t cache_block_bytes(size_t b);
 // Call before destroying a stream that blocks were freed on: synchronises it
 // and makes its cached blocks idle, so that no cached event refers to it.
 void cache_retire_stream(hipStream_t st);
@@ -319,8 +321,14 @@ struct Graph {
 extern const char* const kClassNames[NUM_CLASSES];
 
 // Build a graph from a device edge list on `st` (tc_preprocess without the
-// argument checks; synchronises st) and free one.
-Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, int64_t n, hipStream_t st);
+// argument checks; synchronises st) and free one. lean: without the block that a
+// small graph's temporaries are carved from.
+Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, int64_t n, hipStream_t st,
+                   bool lean = false);
+// Device bytes held at once while an edge list is uploaded and build_graph runs
+// on it, the resident graph among them (an estimate from above: graphs of more
+// probes per edge take more work units than it counts).
+size_t build_graph_bytes(int64_t m_raw, int64_t n);
 // destroy_graph returns the graph's memory once the work of every stream that
 // used it (its UseLog) is done; destroy_graph_idle is for callers that know
 // no such work is pending.

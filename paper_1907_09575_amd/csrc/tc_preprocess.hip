@@ -1182,7 +1182,7 @@ constexpr size_t kSmallScanPool = (size_t)32 << 10;
 // them were a seventh of a small call (4096 vertices, 32768 pairs,
 // preprocessing and count: 533 us, 460 us so). Past
 // this, what a block without reuse holds beyond the peak would show in a
-// server's memory budget.
+// server's memory budget (build_graph_bytes).
 constexpr int64_t kArenaRaw = (int64_t)1 << 16;
 inline size_t arena_bytes_of(int64_t m_raw, int64_t n) { return (size_t)(48 * m_raw + 48 * n) + ((size_t)256 << 10); }
 
@@ -1835,7 +1835,7 @@ void destroy_graph(Graph* g) {
 }
 
 Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, int64_t n,
-                   hipStream_t st) {
+                   hipStream_t st, bool lean) {
   std::unique_ptr<GraphImpl> g(new GraphImpl());
   g->owned.st = st;
   TC_HIP(hipGetDevice(&g->device));
@@ -1864,7 +1864,7 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
   // (every part begins at a multiple of 64 bytes: the scan words are 64-bit)
   const size_t scan_at = pool_at + pool_bytes, scan_bytes = small ? kSmallScanPool : kScanPool;
   DevBuf arena;
-  if (small && m_raw <= kArenaRaw) {
+  if (small && m_raw <= kArenaRaw && !lean) {
     arena.alloc(arena_bytes_of(m_raw, n));
     temps.carve_from(arena.as<char>(), arena.bytes);
   }
@@ -2159,6 +2159,29 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
   g->arena_bytes = g->owned.bytes;
   note_use(*g, st);
   return g.release();
+}
+
+// The blocks of build_graph that live together, phase by phase, as the cache
+// rounds them; m <= m_raw, at most as many tasks, rows with work at most that
+// many and at most n.
+size_t build_graph_bytes(int64_t m_raw, int64_t n) {
+  const int64_t m = std::max<int64_t>(m_raw, 1), r = std::min(n, m);
+  auto B = [](int64_t bytes) { return cache_block_bytes((size_t)bytes); };
+  const size_t upload = B(8 * m);
+  const size_t ranks = 2 * B(4 * n), u = B(8 * (n + 1)) + B(4 * m) + B(2 * m + 4);
+  // task arrays, row order, pack pointers and records; work units: 8 bytes an
+  // edge up to 2^20 of them, 1 beyond
+  const size_t work = 2 * B(4 * n) + B(4 * m) + B(8 * (m + 1)) + B(4 * n) + 2 * B(4 * (n + 1)) + 2 * B(8 * r) +
+                      B(8 * std::min(m, (int64_t)1 << 20) + m);
+  const size_t fixed = (size_t)1 << 20;  // zeroed words, scalars, rounding of the classes' arrays
+  if (m_raw <= kArenaRaw && n <= kSmallN) return upload + B((int64_t)arena_bytes_of(m_raw, n)) + ranks + u + work + fixed;
+  const size_t words = B(m / 4);  // look-back words of a sort
+  const size_t dedup = 2 * B(8 * m) + words;
+  const size_t degree = dedup + ranks + 2 * B(8 * n) + B(4 * m) + (n > (1 << 24) ? B(4 * m) : 0);
+  const size_t tasks = B(8 * m) + ranks + u + B(8 * (n + 1)) + 2 * (B(4 * m) + B(8 * m)) + words;
+  const size_t rows = B(n) + B(4 * n) + 5 * B(4 * r) + 4 * B(8 * r) + 4 * B(4 * r);
+  const size_t order = ranks + u + B(8 * (n + 1)) + B(4 * m) + 2 * B(8 * m) + work + rows;
+  return upload + std::max(std::max(degree, tasks), order) + fixed;
 }
 
 void check_task_sorts(hipStream_t st) { check_sorts(st); }

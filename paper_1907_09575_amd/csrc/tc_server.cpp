@@ -67,6 +67,7 @@ struct CacheEntry {
   int refs = 0;       // admitted requests using it
   uint64_t last_use = 0;
   bool building = true;
+  bool lean = false;  // build with the least memory
   tc_status status = TC_OK;
   std::string err;
   // build input (host)
@@ -76,12 +77,10 @@ struct CacheEntry {
   int32_t n = 0;
 };
 
-// Device bytes reserved while a graph is preprocessed: the uploaded edge list,
-// the sort keys and flags of deduplication, the edge set, and the resident
-// graph (CSR, rank map, tasks and work units).
-size_t prep_estimate(int64_t m_raw, int64_t n) {
-  return (size_t)(56 * m_raw + 40 * n) + ((size_t)1 << 20);
-}
+// Device bytes of a build without a block of temporaries: the uploaded edge
+// list, the sort keys of deduplication, and the resident graph (CSR, rank map,
+// tasks and work units), without the rounding of blocks.
+size_t lean_bytes(int64_t m_raw, int64_t n) { return (size_t)(56 * m_raw + 40 * n) + ((size_t)1 << 20); }
 
 // Device bytes of a graph's share of a tick's batch plan: its kernel
 // arguments and unit sources, and its work units (the plan's units and, while
@@ -193,7 +192,12 @@ struct Server {
       CacheEntry* e = find(q->r.graph_key);
       const int64_t sup_entries = e && !e->building ? e->g->m : q->r.m_raw;
       const size_t sup = q->r.op == TC_REQ_COUNT ? 0 : (size_t)4 * (size_t)sup_entries;
-      const size_t need = sup + (e ? 0 : prep_estimate(q->r.m_raw, q->r.n));
+      // a graph that would go past the budget even alone is built with the
+      // least memory (no block of temporaries) if that fits
+      size_t est = e ? 0 : build_graph_bytes(q->r.m_raw, q->r.n);
+      const bool lean = active.empty() && sup + est > (size_t)budget;
+      if (lean) est = std::min(est, lean_bytes(q->r.m_raw, q->r.n));
+      const size_t need = sup + est;
       if (!e && q->r.m_raw > 0 && (!q->r.src || !q->r.dst)) {
         pending.pop_front();
         finish(q, TC_EINVAL, "tc_server: graph_key not resident and no edge list given");
@@ -222,7 +226,8 @@ struct Server {
       } else {
         auto ne = std::make_unique<CacheEntry>();
         ne->key = q->r.graph_key;
-        ne->est = prep_estimate(q->r.m_raw, q->r.n);
+        ne->est = est;
+        ne->lean = lean;
         ne->src = q->r.src;
         ne->dst = q->r.dst;
         ne->m_raw = q->r.m_raw;
@@ -265,7 +270,7 @@ struct Server {
           TC_HIP(hipMemcpyAsync(d_edges, e->src, bytes, hipMemcpyHostToDevice, st));
           TC_HIP(hipMemcpyAsync(d_edges + e->m_raw, e->dst, bytes, hipMemcpyHostToDevice, st));
         }
-        g = build_graph(d_edges, d_edges + e->m_raw, e->m_raw, e->n, st);
+        g = build_graph(d_edges, d_edges + e->m_raw, e->m_raw, e->n, st, e->lean);
       } catch (const Error& x) {
         status = x.status;
         err = x.what();
