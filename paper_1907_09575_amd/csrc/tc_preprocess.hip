@@ -231,10 +231,14 @@ __global__ __launch_bounds__(256) void k_distinct_mark(uint64_t* __restrict__ S,
 // distinct key, and one whose word already holds an equal key is marked.
 // What a group may hold: the sort's bits are chosen so that even edges that
 // all share one interval of lo average at most kGrpMean keys a group, so a
-// tile and a group fit the set; a group of more than kGrpMax keys (one edge
-// that often), or a set that is so full that a key finds no word in
-// kGrpProbes, sets *fail: what is left of the launch is skipped, and the host
-// sorts by all bits instead.
+// tile and a group fit the set; a group of more than `most` keys (one edge
+// that often; seen before any of it is read), or a set that is so full that a
+// key finds no word in kGrpProbes, sets *fail: what is left of the launch is
+// skipped, and the host sorts by all bits instead.
+// A group that runs far past its tile is one edge many times over, and one
+// work-group reads it: kGrpFar keys a thread at a time, and a key equal to one
+// that its wave has entered is marked without a look at the set (2^20 copies of
+// an edge: 1.87 ms with a key a thread and every one looked up, 0.6 ms so).
 // Two or three passes of the sort, of 1.28 ms each at scale 24 (256 M pairs),
 // become LDS work of the read that the mark needs anyway.
 constexpr int kGrpThreads = 1024;
@@ -242,12 +246,18 @@ constexpr int kGrpKeys = 4;  // per thread
 constexpr int kGrpTile = kGrpThreads * kGrpKeys;
 constexpr int kGrpSlots = 16384;  // 64 KiB: two work-groups a CU
 constexpr int kGrpMeanLog2 = 13;
-constexpr int64_t kGrpMax = (int64_t)1 << 20;  // (positions take 21 bits)
+// Keys of a group at most: its work-group reads 2^20 of them in 0.6 ms, and a
+// sort by all bits costs as much at 16M pairs, 0.15 ms at 2M (positions take
+// 21 bits).
+inline int64_t group_max(int64_t m_raw) {
+  return std::min<int64_t>((int64_t)1 << 20, std::max<int64_t>((int64_t)1 << 17, m_raw / 16));
+}
 constexpr int kGrpAhead = 64;  // keys past the tile read with it
+constexpr int kGrpFar = 4;     // keys per thread and step beyond those
 constexpr int kGrpProbes = 1024;
 
 __global__ __launch_bounds__(kGrpThreads, 8) void k_distinct_groups(uint64_t* S, MixCode mc, int64_t m_raw, int gshift,
-                                                                    int bit_lo, uint32_t* __restrict__ ghist,
+                                                                    int64_t most, int bit_lo, uint32_t* __restrict__ ghist,
                                                                     unsigned long long* __restrict__ total,
                                                                     int* __restrict__ fail) {
   extern __shared__ uint32_t h_dyn[];
@@ -318,18 +328,41 @@ __global__ __launch_bounds__(kGrpThreads, 8) void k_distinct_groups(uint64_t* S,
     if (last != before) {  // the tile's last group, past the tile
       int64_t i = i0 + kGrpTile + tid;
       if (tid < kGrpAhead && i < m_raw && !(ahead & kDupMark) && group(ahead) == last) enter(ahead, i);
-      bool on = far == last;  // (uniform)
-      for (int64_t base = i0 + kGrpTile + kGrpAhead; on && base < m_raw; base += kGrpThreads) {
-        if (base - i0 > kGrpMax) {
+      const int64_t far0 = i0 + kGrpTile + kGrpAhead;
+      if (far == last && far0 < m_raw) {  // (uniform)
+        if (i0 + most < m_raw && group(at(i0 + most)) == last) {
           if (tid == 0) atomicOr(fail, 1);
-          break;
+        } else {
+          bool on = true;
+          uint64_t known = 0;  // an edge that this wave has entered (0: none; it is no unmarked key)
+          for (int64_t base = far0; on && base < m_raw; base += (int64_t)kGrpThreads * kGrpFar) {
+            // (no barrier in this loop: a wave may leave it when it sees the flag)
+            if (__hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
+            uint64_t key[kGrpFar];
+#pragma unroll
+            for (int j = 0; j < kGrpFar; ++j) key[j] = at(base + j * kGrpThreads + tid);
+            on = group(at(base + (int64_t)kGrpThreads * kGrpFar - 1)) == last;
+            uint32_t rest = 0;  // items to enter
+#pragma unroll
+            for (int j = 0; j < kGrpFar; ++j) {
+              i = base + j * kGrpThreads + tid;
+              const bool mine = i < m_raw && !(key[j] & kDupMark) && group(key[j]) == last;
+              if (mine && key[j] == known) S[i] = key[j] | kDupMark;
+              else rest |= mine ? 1u << j : 0u;
+            }
+            if (__ballot(rest != 0)) {
+              for (; rest; rest &= rest - 1) {
+                i = base + (__ffs((int)rest) - 1) * kGrpThreads + tid;
+                known = S[i];  // (not marked: its own thread marks it)
+                enter(known, i);
+              }
+              known = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(known >> 32)) << 32) |
+                      (uint32_t)__builtin_amdgcn_readfirstlane((int)known);
+            }
+          }
+          // (again: nothing of the next tile is held in registers through the loop)
+          if (t + gridDim.x < ntiles) load(t + gridDim.x);
         }
-        // (no barrier in this loop: a wave may leave it when it sees the flag)
-        if (__hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
-        i = base + tid;
-        const uint64_t key = at(i);
-        on = group(at(base + kGrpThreads - 1)) == last;
-        if (i < m_raw && !(key & kDupMark) && group(key) == last) enter(key, i);
       }
     }
     __syncthreads();
@@ -1953,7 +1986,7 @@ Graph* build_graph(const int32_t* d_src, const int32_t* d_dst, int64_t m_raw, in
         allow_lds((const void*)k_distinct_groups, lds);
         TC_LAUNCH("distinct_groups", k_distinct_groups,
                   dim3((unsigned)std::min<int64_t>(512, div_up(m_raw, kGrpTile))), dim3(kGrpThreads), lds, st, S, mc,
-                  m_raw, bit_lo, hshift, dh, d_m, d_refused);
+                  m_raw, bit_lo, group_max(m_raw), hshift, dh, d_m, d_refused);
       } else {
         TC_LAUNCH("distinct_mark", k_distinct_mark, dim3(pblocks), dim3(kT), lds, st, S, mc, m_raw, hshift, dh, d_m);
       }
