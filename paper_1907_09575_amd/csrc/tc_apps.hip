@@ -27,7 +27,6 @@
 // with an edge removed in an earlier round is already gone.
 #include <algorithm>
 #include <cstdlib>
-#include <cstring>
 
 #include "tc_prims.h"
 
@@ -224,7 +223,8 @@ struct TrussArrays {
   int32_t* sup;
   int32_t* tau;
   uint64_t* list;
-  uint32_t parts;  // entries of an edge at most (walk_chunk)
+  uint32_t parts;    // entries of an edge at most (walk_chunk)
+  uint32_t entries;  // of all edges: a list that holds them has every edge removed
 };
 
 __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
@@ -236,27 +236,46 @@ __device__ __forceinline__ uint32_t min_degree(const TrussArrays& A, int32_t e) 
   return min(A.deg[A.erow[e]], A.deg[A.col[e]]);
 }
 
-// Work entries of all edges together, for 16, 8, 4, 2 and 1 entries per edge
-// at most: what the list must hold. (Every work-group ends on five atomics to
-// one line, 12 ns each: few work-groups.)
-__global__ __launch_bounds__(256) void k_truss_entries(TrussArrays A, int64_t m, unsigned long long* __restrict__ out) {
+// What the peel starts from: the work entries of all edges together, for 16, 8,
+// 4, 2 and 1 entries per edge at most (what the list must hold), and the
+// largest value of kAlive less the support and of the support. (Every
+// work-group ends on seven atomics to one line, 12 ns each: few work-groups.)
+struct TrussStart {
+  unsigned long long entries[kWalkChoices];
+  int room, top;
+};
+__global__ __launch_bounds__(256) void k_truss_start(TrussArrays A, int64_t m, TrussStart* __restrict__ out) {
   __shared__ unsigned long long s_w[4][kWalkChoices];
+  __shared__ int s_room[4], s_top[4];
   unsigned long long c[kWalkChoices] = {};
+  int room = 0, top = 0;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x) {
     const uint32_t d = min_degree(A, (int32_t)e);
+    const int s = A.sup[e];
+    room = max(room, kAlive - s);
+    top = max(top, s);
 #pragma unroll
     for (int i = 0; i < kWalkChoices; ++i) c[i] += walk_entries(d, kWalkParts >> i);
   }
+  room = wave_max(room);
+  top = wave_max(top);
 #pragma unroll
   for (int i = 0; i < kWalkChoices; ++i) {
     c[i] = wave_sum(c[i]);
     if (lane_id() == 0) s_w[threadIdx.x >> 6][i] = c[i];
   }
+  if (lane_id() == 0) {
+    s_room[threadIdx.x >> 6] = room;
+    s_top[threadIdx.x >> 6] = top;
+  }
   __syncthreads();
   if (threadIdx.x < kWalkChoices) {
     unsigned long long t = 0;
     for (int w = 0; w < 4; ++w) t += s_w[w][threadIdx.x];
-    atomicAdd(&out[threadIdx.x], t);
+    atomicAdd(&out->entries[threadIdx.x], t);
+  } else if (threadIdx.x == kWalkChoices) {
+    atomicMax(&out->room, max(max(s_room[0], s_room[1]), max(s_room[2], s_room[3])));
+    atomicMax(&out->top, max(max(s_top[0], s_top[1]), max(s_top[2], s_top[3])));
   }
 }
 
@@ -346,10 +365,11 @@ __device__ __forceinline__ void truss_push(const TrussArrays& A, PushQueue& Q, b
 // empty, k_truss_min finds the smallest support left, and k_truss_level makes
 // the edges that have it the frontier of the next level (lim = it + 1, the
 // trussness of what the level removes). Otherwise both do nothing and the
-// level goes on. mins[b]: kAlive and no edge left end the peel.
-__global__ __launch_bounds__(256) void k_truss_min(TrussArrays A, int64_t m, const uint32_t* __restrict__ cnt,
-                                                   int* __restrict__ mn, int* __restrict__ fresh) {
-  if (*cnt != 0) return;
+// level goes on. room: kAlive less the smallest support (cleared: none found).
+__global__ __launch_bounds__(256) void k_truss_min(TrussArrays A, int64_t m, const uint32_t* __restrict__ start,
+                                                   const uint32_t* __restrict__ cnt, int* __restrict__ room,
+                                                   int* __restrict__ fresh) {
+  if (*cnt != 0 || *start == A.entries) return;
   if (blockIdx.x == 0 && threadIdx.x == 0) *fresh = 1;
   __shared__ int s_v[4];
   int v = kAlive;
@@ -364,18 +384,18 @@ __global__ __launch_bounds__(256) void k_truss_min(TrussArrays A, int64_t m, con
   if (threadIdx.x == 0) {
     v = min(min(s_v[0], s_v[1]), min(s_v[2], s_v[3]));
     // (most work-groups find what another has written: 16.9 -> 11.7 us)
-    if (v < __hip_atomic_load(mn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(mn, v);
+    if (kAlive - v > __hip_atomic_load(room, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(room, kAlive - v);
   }
 }
 
 // (lim, lim_out: the level's bound before and after; start: the first entry of
 // the round)
 __global__ __launch_bounds__(kPeelThreads) void k_truss_level(TrussArrays A, int64_t m, const int* __restrict__ fresh,
-                                                     const int* __restrict__ mn, const int* __restrict__ lim,
+                                                     const int* __restrict__ room, const int* __restrict__ lim,
                                                      int* __restrict__ lim_out, int32_t round, const uint32_t* __restrict__ start,
                                                      uint32_t* __restrict__ cnt) {
-  const bool go = *fresh != 0 && *mn != kAlive;
-  const int bound = go ? *mn + 1 : *lim;
+  const bool go = *fresh != 0;  // (then an edge is left)
+  const int bound = go ? kAlive - *room + 1 : *lim;
   if (blockIdx.x == 0 && threadIdx.x == 0) *lim_out = bound;
   if (!go) return;
   __shared__ int32_t s_q[kPeelWaves][kPushQueue];
@@ -425,14 +445,16 @@ __device__ __forceinline__ int32_t find_sorted(const int32_t* __restrict__ a, ui
 // that crosses lim sees it). Edges marked for the next round count as staying.
 __global__ __launch_bounds__(kPeelThreads) __attribute__((amdgpu_waves_per_eu(8)))
 void k_truss_peel(TrussArrays T, FullAdj A, int32_t round, const int* __restrict__ limp,
-                  uint32_t* __restrict__ start, const uint32_t* __restrict__ cnt, uint32_t* __restrict__ cnt_next) {
-  const uint32_t nF = *cnt;
-  if (blockIdx.x == 0 && threadIdx.x == 0) start[1] = start[0] + nF;  // of the next round
-  if (blockIdx.x * kPeelWaves >= nF) return;
-  const uint64_t* const F = T.list + start[0];
+                  const uint32_t* __restrict__ start, uint32_t* __restrict__ start_next,
+                  const uint32_t* __restrict__ cnt, uint32_t* __restrict__ cnt_next) {
+  const uint32_t nF = *cnt, end = *start + nF;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *start_next = end;
+  // (with the last edges listed, none stays whose support would matter)
+  if (blockIdx.x * kPeelWaves >= nF || end == T.entries) return;
+  const uint64_t* const F = T.list + (end - nF);
   const int lim = *limp;
   __shared__ int32_t s_q[kPeelWaves][kPushQueue];
-  PushQueue Q{s_q[threadIdx.x >> 6], 0, round + 1, lim + 1, T.list + start[0] + nF, cnt_next};
+  PushQueue Q{s_q[threadIdx.x >> 6], 0, round + 1, lim + 1, T.list + end, cnt_next};
   const int lane = lane_id();
   const uint32_t stride = gridDim.x * (blockDim.x / 64);
   for (uint32_t f = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6); f < nF; f += stride) {
@@ -495,28 +517,38 @@ int32_t truss(const Graph& g, int32_t* d_tau, hipStream_t st) {
   Lower L;
   build_lower(L, g, st);
   TC_LAUNCH("truss_fill", k_fill_i32, dim3(grid_threads(m)), dim3(kAT), 0, st, state.as<int32_t>(), m, kAlive);
-  TrussArrays T{L.erow.as<uint32_t>(), g.col, g.deg, state.as<int32_t>(), sup.as<int32_t>(), d_tau, nullptr, kWalkParts};
+  TrussArrays T{L.erow.as<uint32_t>(), g.col, g.deg, state.as<int32_t>(), sup.as<int32_t>(), d_tau, nullptr, kWalkParts, 0};
   const unsigned sweep = (unsigned)std::min<int64_t>(2048, grid_threads(m));  // (whole-array kernels)
-  DevBuf total(sizeof(unsigned long long) * kWalkChoices);
-  TC_HIP(hipMemsetAsync(total.p, 0, total.bytes, st));
-  TC_LAUNCH("truss_entries", k_truss_entries, dim3(std::min(sweep, 512u)), dim3(kAT), 0, st, T, m, total.as<unsigned long long>());
-  unsigned long long entries[kWalkChoices];
-  TC_HIP(hipMemcpyAsync(entries, total.p, sizeof(entries), hipMemcpyDeviceToHost, st));
+  DevBuf total(sizeof(TrussStart));
+  zero_i32(total.as<int32_t>(), sizeof(TrussStart) / 4, st, true);
+  TC_LAUNCH("truss_start", k_truss_start, dim3(std::min(sweep, 512u)), dim3(kAT), 0, st, T, m, total.as<TrussStart>());
+  TrussStart first;
+  TC_HIP(hipMemcpyAsync(&first, total.p, sizeof(first), hipMemcpyDeviceToHost, st));
   check_sorts(st);  // (synchronises st)
+  if (kAlive - first.room == first.top) {
+    // all supports are the same (no triangles, or a clique): one level removes
+    // every edge at once
+    TC_LAUNCH("truss_fill", k_fill_i32, dim3(grid_threads(m)), dim3(kAT), 0, st, d_tau, m, first.top + 2);
+    TC_HIP(hipGetLastError());
+    TC_HIP(hipStreamSynchronize(st));
+    note_use(g, st);
+    return first.top + 2;
+  }
   // the most entries per edge whose list is indexed by 31 bits and fits the
   // memory left (one per edge: m < 2^31 of them)
   DevBuf list;
   for (int i = 0; T.list == nullptr; ++i) {
     const bool last = i + 1 == kWalkChoices;
-    if (!last && (entries[i] >> 31 || (kWalkParts >> i) > truss_walks())) continue;
+    if (!last && (first.entries[i] >> 31 || (kWalkParts >> i) > truss_walks())) continue;
     try {
-      list.alloc(sizeof(uint64_t) * (size_t)entries[i]);
+      list.alloc(sizeof(uint64_t) * (size_t)first.entries[i]);
     } catch (const Error& e) {
       if (last || e.status != TC_ENOMEM) throw;
       continue;
     }
     T.list = list.as<uint64_t>();
     T.parts = kWalkParts >> i;
+    T.entries = (uint32_t)first.entries[i];
   }
   const FullAdj A{g.row_ptr, g.col, L.ptr.as<int64_t>(), L.nbr.as<int32_t>(), L.eid.as<int32_t>()};
 
@@ -524,42 +556,45 @@ int32_t truss(const Graph& g, int32_t* d_tau, hipStream_t st) {
   // round decides (its frontier, the level) stays on the device; a round
   // with nothing to do costs its launch.
   constexpr int kRounds = 8, kBatches = 4;
-  struct Ctl {  // of one read-back
-    int mn[kBatches], fresh[kBatches];
-    int lim[kBatches + 1];
-    uint32_t cnt[kBatches * kRounds + 1], start[kBatches * kRounds + 1];
+  struct Ctl {  // of one read-back (cleared before it)
+    int room[kBatches], fresh[kBatches];
+    int lim[kBatches];
+    uint32_t cnt[kBatches * kRounds], start[kBatches * kRounds];
   };
-  DevBuf ctl(sizeof(Ctl));
-  Ctl h, init;
-  std::memset(&init, 0, sizeof(init));
-  for (int& v : init.mn) v = kAlive;
+  // (the last bound, frontier and its place are read where the read-back before
+  // left them)
+  DevBuf ctl(3 * sizeof(Ctl));
+  Ctl* const ring = ctl.as<Ctl>();
+  zero_i32(ctl.as<int32_t>(), 3 * sizeof(Ctl) / 4, st, true);
+  int* lim = &ring[2].lim[0];
+  uint32_t *cnt = &ring[2].cnt[0], *start = &ring[2].start[0];
   int32_t round = 0;
-  for (;;) {
+  Ctl h;
+  for (int trip = 0;; ++trip) {
     TC_REQUIRE(round < kAlive - 2 * kBatches * kRounds, TC_EOVERFLOW, "tc_truss: too many rounds");
-    TC_HIP(hipMemcpyAsync(ctl.p, &init, sizeof(Ctl), hipMemcpyHostToDevice, st));
-    Ctl* d = ctl.as<Ctl>();
+    Ctl* d = &ring[trip % 2];
+    if (trip >= 2) zero_i32(reinterpret_cast<int32_t*>(d), sizeof(Ctl) / 4, st, true);
+    int i = 0;  // round of this read-back
     for (int b = 0; b < kBatches; ++b) {
-      TC_LAUNCH("truss_min", k_truss_min, dim3(sweep), dim3(kAT), 0, st, T, m, &d->cnt[b * kRounds], &d->mn[b],
-                &d->fresh[b]);
-      TC_LAUNCH("truss_level", k_truss_level, dim3((sweep + 1) / 2), dim3(kPeelThreads), 0, st, T, m, &d->fresh[b], &d->mn[b],
-                &d->lim[b], &d->lim[b + 1], round, &d->start[b * kRounds], &d->cnt[b * kRounds]);
-      for (int r = 0; r < kRounds; ++r, ++round)
-        TC_LAUNCH("truss_peel", k_truss_peel, dim3(kPeelGrid), dim3(kPeelThreads), 0, st, T, A, round, &d->lim[b + 1],
-                  &d->start[b * kRounds + r], &d->cnt[b * kRounds + r], &d->cnt[b * kRounds + r + 1]);
+      TC_LAUNCH("truss_min", k_truss_min, dim3(sweep), dim3(kAT), 0, st, T, m, start, cnt, &d->room[b], &d->fresh[b]);
+      TC_LAUNCH("truss_level", k_truss_level, dim3((sweep + 1) / 2), dim3(kPeelThreads), 0, st, T, m, &d->fresh[b],
+                &d->room[b], lim, &d->lim[b], round, start, cnt);
+      lim = &d->lim[b];
+      for (int r = 0; r < kRounds; ++r, ++round, ++i) {
+        TC_LAUNCH("truss_peel", k_truss_peel, dim3(kPeelGrid), dim3(kPeelThreads), 0, st, T, A, round, lim, start,
+                  &d->start[i], cnt, &d->cnt[i]);
+        start = &d->start[i];
+        cnt = &d->cnt[i];
+      }
     }
     TC_HIP(hipGetLastError());
-    TC_HIP(hipMemcpyAsync(&h, ctl.p, sizeof(Ctl), hipMemcpyDeviceToHost, st));
+    TC_HIP(hipMemcpyAsync(&h, d, sizeof(Ctl), hipMemcpyDeviceToHost, st));
     TC_HIP(hipStreamSynchronize(st));
-    // (a level that found no edge alive ends the peel)
-    bool done = false;
-    for (int b = 0; b < kBatches; ++b) done = done || (h.fresh[b] && h.mn[b] == kAlive);
-    init.lim[0] = h.lim[kBatches];
-    init.cnt[0] = h.cnt[kBatches * kRounds];
-    init.start[0] = h.start[kBatches * kRounds];
-    if (done) break;
+    if (h.start[i - 1] + h.cnt[i - 1] == T.entries) {  // every edge is removed
+      note_use(g, st);
+      return h.lim[kBatches - 1] + 1;  // the last level's trussness
+    }
   }
-  note_use(g, st);
-  return init.lim[0] + 1;  // the last level's trussness
 }
 
 template <class F>
