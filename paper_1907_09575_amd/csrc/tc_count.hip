@@ -1474,23 +1474,23 @@ void k_count_batch(const Args* __restrict__ gargs, const BatchUnit* __restrict__
       const BatchUnit bu = units[u];
       Args A = gargs[bu.graph];
       A.count = counts + bu.graph;
+      const auto* recs = static_cast<const PackRow*>(bu.p0);
+      const auto* info = static_cast<const PackInfo*>(bu.p1);
+      const auto* items = static_cast<const CountItem*>(bu.p0);
       if (bu.kind == BK_PACK16) {
-        pack_body<MODE, VAR_BASE, true, kWaves>(A, static_cast<const PackRow*>(bu.p0), static_cast<const PackInfo*>(bu.p1),
-                                        bu.index, bu.slots, smem);
-      } else if (bu.kind == BK_PACK) {
-        pack_body<MODE, VAR_BASE, false, kWaves>(A, static_cast<const PackRow*>(bu.p0), static_cast<const PackInfo*>(bu.p1),
-                                         bu.index, bu.slots, smem);
+        pack_body<MODE, VAR_BASE, true, kWaves>(A, recs, info, bu.index, bu.slots, smem);
       } else if (ONLY16 || bu.kind == BK_BITS) {
         if (bu.index < bu.end)
-          block_flush<MODE>(bits_groups<MODE>(A, static_cast<const CountItem*>(bu.p0), bu.index, (uint32_t)bu.end,
-                                              bu.slots, smem), A);
-      } else if (bu.kind == BK_BITS_HBM) {
-        block_flush<MODE>(bits_groups_hbm<MODE>(A, static_cast<const CountItem*>(bu.p0), bu.index, (uint32_t)bu.end,
-                                                smem), A);
-      } else if (bu.kind == BK_ITEMS) {
-        items_body<MODE, false, VAR_BASE>(A, static_cast<const CountItem*>(bu.p0), smem);
-      } else {
-        items_body<MODE, true, VAR_BASE>(A, static_cast<const CountItem*>(bu.p0), smem);
+          block_flush<MODE>(bits_groups<MODE>(A, items, bu.index, (uint32_t)bu.end, bu.slots, smem), A);
+      } else if constexpr (!ONLY16) {
+        if (bu.kind == BK_PACK)
+          pack_body<MODE, VAR_BASE, false, kWaves>(A, recs, info, bu.index, bu.slots, smem);
+        else if (bu.kind == BK_BITS_HBM)
+          block_flush<MODE>(bits_groups_hbm<MODE>(A, items, bu.index, (uint32_t)bu.end, smem), A);
+        else if (bu.kind == BK_ITEMS)
+          items_body<MODE, false, VAR_BASE>(A, items, smem);
+        else
+          items_body<MODE, true, VAR_BASE>(A, items, smem);
       }
     }
   }
