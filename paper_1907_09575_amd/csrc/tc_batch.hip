@@ -88,8 +88,19 @@ Tuning parse_tuning(const char* js) {
 constexpr int kItemClasses = NUM_CLASSES - CLS_WG_SMALL;  // wg_small .. global
 
 // Probes of a unit of short rows' groups: a small graph's bundles are sized to
-// spread that one graph over the GPU, and merged up to this for a batch.
-constexpr uint64_t kUnitProbes = 65536;
+// spread that one graph over the GPU, and merged for a batch, up to kUnitProbes
+// but no further than leaves kFillUnits units per CU. A batch of few units also
+// cuts its packs of short rows in two or four (each part builds the pack's
+// tables and takes its share of the probes), as far as kFillUnits per CU and if
+// a graph's packs hold kCutProbes on average: a pack is a chain of windows, as
+// long as its launch when nothing else runs. One RMAT graph of 1000 vertices:
+// 97 us with whole packs and merged bundles, 54 us so; 8 ER graphs of 500 to
+// 1200 vertices: 71 and 45 us; one clique of 400: 71 and 54 us (79 us with four
+// units per CU: every unit ends on an atomic to its graph's count and begins
+// with one to the queue, 12 ns each).
+constexpr uint64_t kUnitProbes = 65536, kUnitProbesMin = 4096;
+constexpr uint64_t kCutProbes = 2048;
+constexpr int64_t kFillUnits = 2;
 
 // Per graph entry of the plan: where its units come from (device copy).
 struct BatchSrc {
@@ -110,7 +121,10 @@ struct BatchSrc {
   const uint32_t* bundle[kItemClasses];
   uint32_t n_bundles[kItemClasses], n_units16[kItemClasses];
   uint32_t merge;
+  uint32_t cut;  // log2 of the units of a pack of short rows
   uint64_t unit_off;
+
+  __host__ __device__ uint32_t pack_units(int c) const { return n_packs32[c] + ((n_packs[c] - n_packs32[c]) << cut); }
 };
 
 // One work-group per graph entry: emit its units and their weights (probes
@@ -119,7 +133,7 @@ struct BatchSrc {
 __global__ __launch_bounds__(256) void k_batch_units(const BatchSrc* __restrict__ src, BatchUnit* __restrict__ units,
                                                      uint32_t* __restrict__ key, uint32_t* __restrict__ idx) {
   const BatchSrc& s = src[blockIdx.x];
-  const uint32_t np0 = s.n_packs[0], np1 = s.n_packs[1];
+  const uint32_t np0 = s.pack_units(0), np1 = s.pack_units(1);
   uint32_t total = np0 + np1;
   for (int c = 0; c < kItemClasses; ++c) total += s.n_groups32[c] + s.n_units16[c];
   for (uint32_t j = threadIdx.x; j < total; j += blockDim.x) {
@@ -128,15 +142,16 @@ __global__ __launch_bounds__(256) void k_batch_units(const BatchSrc* __restrict_
     u.graph = (int32_t)blockIdx.x;
     if (j < np0 + np1) {
       const int c = j < np0 ? 0 : 1;
-      const uint32_t p = j < np0 ? j : j - np0;
+      const uint32_t i = j < np0 ? j : j - np0, n32 = s.n_packs32[c];
+      const bool s16 = i >= n32;
+      const uint32_t p = s16 ? n32 + ((i - n32) >> s.cut) : i;
       const PackInfo& pi = s.pack_info[c][p];
-      const bool s16 = p >= s.n_packs32[c];
-      wgt = (pi.q1 - pi.q0) * (s16 ? 2 : 1) + 64ull * (pi.r1 - pi.r0);
+      wgt = (s16 ? (2 * (pi.q1 - pi.q0)) >> s.cut : pi.q1 - pi.q0) + 64ull * (pi.r1 - pi.r0);
       u.p0 = s.pack_recs[c];
       u.p1 = s.pack_info[c];
       u.index = p;
       u.slots = s16 ? s.pack_slots16[c] : s.pack_slots[c];
-      u.kind = s16 ? BK_PACK16 : BK_PACK;
+      u.kind = s16 ? (int32_t)(BK_PACK16 | ((i - n32) & ((1u << s.cut) - 1)) << 8 | s.cut << 16) : BK_PACK;
     } else {
       uint32_t r = j - np0 - np1;
       int c = 0;
@@ -194,7 +209,7 @@ struct BatchPlan {
   uint32_t chunk = 1;  // units per queue atomic
   unsigned grid = 0;
   size_t lds = 0;
-  bool only16 = false;
+  BatchBodies bodies = BATCH_ALL;
   int cus = 0;
   Tuning tun;
   Owned own;
@@ -237,16 +252,44 @@ struct PlanHost {
   size_t lds = 0;
   uint64_t units = 0;
   int64_t hbm_units = 0;
-  bool only16 = true;  // all units are short rows' with their tables in LDS
+  bool any_short = false, any_long = false, any_short_hbm = false;  // units of short rows (tables in LDS, in HBM), of others
+  BatchBodies bodies() const {
+    return any_short_hbm || (any_short && any_long) ? BATCH_ALL : any_long ? BATCH_LONG : BATCH_SHORT;
+  }
 };
 
 void plan_host(PlanHost& H, const PlanEntry* entries, int64_t num, CountMode mode, const Tuning& t,
-               int device, std::vector<std::pair<int32_t*, int64_t>>* support) {
+               int device, int cus, std::vector<std::pair<int32_t*, int64_t>>* support) {
   H.args.assign((size_t)std::max<int64_t>(num, 1), CountArgs{});
   H.srcs.assign((size_t)std::max<int64_t>(num, 1), BatchSrc{});
   size_t lds = 0;
   uint64_t off = 0;
   int64_t hbm_units = 0;
+  // how far to merge bundles and cut packs
+  uint64_t probes = 0;
+  for (int64_t i = 0; i < num; ++i) probes += entries[i].g ? (uint64_t)entries[i].g->w.probes : 0;
+  const int64_t fill = kFillUnits * cus;
+  const uint64_t unit_probes = std::min(kUnitProbes, std::max(kUnitProbesMin, probes / (uint64_t)fill));
+  auto merge_of = [&](const WorkSet& w) { return std::max<uint64_t>(1, unit_probes / w.bundle_w); };
+  // (a pack of few probes is mostly the building of its tables)
+  auto cut = [](const WorkSet& w) {
+    const int64_t packs = w.n_packs[0] + w.n_packs[1];
+    return w.n_packs32[0] + w.n_packs32[1] < packs &&
+           w.cls_probes[0] + w.cls_probes[1] >= kCutProbes * (uint64_t)packs;
+  };
+  int64_t packs16 = 0, others = 0;
+  for (int64_t i = 0; i < num; ++i) {
+    if (!entries[i].g) continue;
+    const WorkSet& w = entries[i].g->w;
+    for (int c = 0; c < 2; ++c) {
+      others += w.n_packs32[c];
+      (cut(w) ? packs16 : others) += w.n_packs[c] - w.n_packs32[c];
+    }
+    for (int c = CLS_WG_SMALL; c < NUM_CLASSES; ++c)
+      others += w.n_items32[c] / kWaves + div_up(w.n_bundles[c], (int64_t)merge_of(w));
+  }
+  uint32_t log2_parts = 0;
+  while ((kWaves << log2_parts) < kPackWavesMax && (packs16 << (log2_parts + 1)) + others <= fill) ++log2_parts;
   for (int64_t i = 0; i < num; ++i) {
     TC_REQUIRE(entries[i].g != nullptr, TC_EINVAL, "batch plan: null graph handle");
     const Graph& g = *entries[i].g;
@@ -281,6 +324,7 @@ void plan_host(PlanHost& H, const PlanEntry* entries, int64_t num, CountMode mod
     s.tprefix = w.tprefix;
     s.row_ptr = g.row_ptr;
     s.unit_off = off;
+    s.cut = cut(w) ? log2_parts : 0;
     if (w.n_tasks == 0) continue;  // no units: the count stays 0
     for (int c = 0; c < 2; ++c) {
       s.pack_recs[c] = w.pack_recs[c];
@@ -292,10 +336,13 @@ void plan_host(PlanHost& H, const PlanEntry* entries, int64_t num, CountMode mod
       s.pack_slots16[c] = pack16_slots(w.wp.pack_slots, w.pack_log2S[c]);
       if (w.n_packs32[c] > 0) {
         lds = std::max(lds, pack_lds_bytes(s.pack_slots[c], mode));
-        H.only16 = false;
+        H.any_long = true;
       }
-      if (w.n_packs32[c] < w.n_packs[c]) lds = std::max(lds, pack16_lds_bytes(s.pack_slots16[c], mode, kWaves));
-      off += (uint64_t)w.n_packs[c];
+      if (w.n_packs32[c] < w.n_packs[c]) {
+        lds = std::max(lds, pack16_lds_bytes(s.pack_slots16[c], mode, kWaves));
+        H.any_short = true;
+      }
+      off += s.pack_units(c);
     }
     for (int c = 0; c < kItemClasses; ++c) {
       const int cls = CLS_WG_SMALL + c;
@@ -307,7 +354,7 @@ void plan_host(PlanHost& H, const PlanEntry* entries, int64_t num, CountMode mod
         s.kind[c] = hbm ? BK_ITEMS_HBM : BK_ITEMS;
         lds = std::max(lds, items_lds_bytes(hbm ? -1 : w.cls_log2S[cls], mode));
         if (hbm) hbm_units += s.n_groups32[c];
-        H.only16 = false;
+        H.any_long = true;
       }
       if (w.n_bundles[cls] > 0) {
         // (a bitmap serves any row; the cap still names the rows by the
@@ -317,13 +364,11 @@ void plan_host(PlanHost& H, const PlanEntry* entries, int64_t num, CountMode mod
         s.max_keys[c] = bits_max_keys(w.cls_log2S[cls], mode);
         s.bundle[c] = w.bundle[cls];
         s.n_bundles[c] = (uint32_t)w.n_bundles[cls];
-        s.merge = (uint32_t)std::max<uint64_t>(1, kUnitProbes / w.bundle_w);
+        s.merge = (uint32_t)merge_of(w);
         s.n_units16[c] = (uint32_t)div_up(s.n_bundles[c], s.merge);
         lds = std::max(lds, hbm ? items_lds_bytes(-1, mode) : bits_lds_bytes(g.n, w.cls_log2S[cls], mode));
-        if (hbm) {
-          hbm_units += s.n_units16[c];
-          H.only16 = false;
-        }
+        if (hbm) hbm_units += s.n_units16[c];
+        (hbm ? H.any_short_hbm : H.any_short) = true;
       }
       off += s.n_groups32[c] + s.n_units16[c];
     }
@@ -383,7 +428,7 @@ BatchPlan* make_plan(const PlanEntry* entries, int64_t num, CountMode mode, cons
     }
   }
   PlanHost H;
-  plan_host(H, ents.data(), num, mode, t, P->device, &P->support);
+  plan_host(H, ents.data(), num, mode, t, P->device, P->cus, &P->support);
   std::vector<CountArgs>& args = H.args;
   std::vector<BatchSrc>& srcs = H.srcs;
   const uint64_t off = H.units;
@@ -391,9 +436,9 @@ BatchPlan* make_plan(const PlanEntry* entries, int64_t num, CountMode mode, cons
   P->n_units = (int64_t)off;
   P->hbm_units = H.hbm_units;
   P->lds = H.lds;
-  P->only16 = H.only16;
+  P->bodies = H.bodies();
   plan_grid(t, P->lds, P->n_units, P->cus, P->bpc, P->grid, P->chunk);
-  batch_kernel_lds(mode, P->lds, P->only16);
+  batch_kernel_lds(mode, P->lds, P->bodies);
 
   P->d_args = P->own.alloc<CountArgs>(std::max<int64_t>(num, 1));
   P->d_units = P->own.alloc<BatchUnit>(std::max<int64_t>(P->n_units, 1));
@@ -433,7 +478,7 @@ namespace {
 void plan_launch(BatchPlan& P, int64_t* d_counts, hipStream_t st, bool timed) {
   for (const auto& z : P.support) zero_i32(z.first, z.second, st, timed);
   launch_batch(P.mode, P.d_args, P.d_units, P.n_units, P.chunk, P.n_graphs, P.d_queue, d_counts, P.grid, P.lds,
-               P.only16, st, timed);
+               P.bodies, st, timed);
 }
 
 }  // namespace
@@ -586,7 +631,7 @@ void count_batched_noalloc(const PlanEntry* entries, int64_t num, int64_t* d_cou
   Tuning t;  // the default schedule, graph order (no sort: sorting needs temporaries)
   t.lpt = false;
   PlanHost H;
-  plan_host(H, entries, num, MODE_COUNT, t, device, nullptr);
+  plan_host(H, entries, num, MODE_COUNT, t, device, cus, nullptr);
   TC_REQUIRE(H.units < 0xFFFFFFF0ull, TC_EOVERFLOW, "tc_count_batched_noalloc: more than 2^32 work units");
   const ScratchLayout L(num, (int64_t)H.units);
   if (L.total > kScratchBytes)
@@ -597,7 +642,7 @@ void count_batched_noalloc(const PlanEntry* entries, int64_t num, int64_t* d_cou
   unsigned grid = 0;
   uint32_t chunk = 1;
   plan_grid(t, H.lds, (int64_t)H.units, cus, bpc, grid, chunk);
-  batch_kernel_lds(MODE_COUNT, H.lds, H.only16);
+  batch_kernel_lds(MODE_COUNT, H.lds, H.bodies());
   auto* d_queue = reinterpret_cast<unsigned int*>(base);
   auto* d_args = reinterpret_cast<CountArgs*>(base + L.args);
   auto* d_srcs = reinterpret_cast<BatchSrc*>(base + L.srcs);
@@ -611,7 +656,7 @@ void count_batched_noalloc(const PlanEntry* entries, int64_t num, int64_t* d_cou
   }
   // clears the counts and the queue counter (a kernel), then the persistent launch
   launch_batch(MODE_COUNT, d_args, d_units, (int64_t)H.units, chunk, num, d_queue, d_counts, grid, H.lds,
-               H.only16, st, true);
+               H.bodies(), st, true);
   // the host copies above read H's vectors: they must be done before H goes
   TC_HIP(hipStreamSynchronize(st));
 }

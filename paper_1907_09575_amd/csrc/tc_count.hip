@@ -819,11 +819,13 @@ __device__ __forceinline__ uint32_t pack_scan(uint32_t v, uint32_t* s_w, uint32_
 }
 
 // WAVES: waves of the work-group, which share the pack's probes (4, or more
-// where a class has too few packs to fill the GPU: see launch_short).
+// where a class has too few packs to fill the GPU: see launch_packs16). In a
+// batch the pack may be cut into 2^cut units, of which this is number `part`.
 template <int MODE, int VAR, bool SHORT, int WAVES>
 __device__ __forceinline__ unsigned long long pack_body(const Args& A, const PackRow* __restrict__ recs,
                                           const PackInfo* __restrict__ info, uint32_t pack,
-                                          uint32_t pack_slots, int32_t* smem) {
+                                          uint32_t pack_slots, int32_t* smem, uint32_t part = 0,
+                                          uint32_t cut = 0) {
   __shared__ int s_D;
   __shared__ uint32_t s_w[4], s_w2[4];
   constexpr bool VALS = mode_keys(MODE);
@@ -846,9 +848,10 @@ __device__ __forceinline__ unsigned long long pack_body(const Args& A, const Pac
   // this wave's share of the pack's probes, its first task, and its first
   // window (in flight while the tables are built)
   const uint64_t q0 = pi.q0, W = pi.q1 - pi.q0;
-  const uint64_t wq0 = q0 + pack_share(W, wave * (kPackWavesMax / WAVES));
-  const uint64_t wq1 = q0 + pack_share(W, (wave + 1) * (kPackWavesMax / WAVES));
-  const uint32_t wt = (uint32_t)__builtin_amdgcn_readfirstlane((int)pi.wt[wave * (kPackWavesMax / WAVES)]);
+  const int shares = (kPackWavesMax / WAVES) >> cut, share0 = ((int)part * WAVES + wave) * shares;
+  const uint64_t wq0 = q0 + pack_share(W, share0);
+  const uint64_t wq1 = q0 + pack_share(W, share0 + shares);
+  const uint32_t wt = (uint32_t)__builtin_amdgcn_readfirstlane((int)pi.wt[share0]);
   const uint32_t wlen = (uint32_t)(wq1 - wq0);
   const Window w0 = window_first(A, wt, wq0, wlen);
   const bool lds_hits = VALS && (SHORT ? 2 * W : W) < kPackLdsHitsMax;  // (uniform: the pack's probes)
@@ -1450,12 +1453,18 @@ __global__ void k_batch_clear(unsigned long long* counts, int64_t n, unsigned in
 // atomic takes `chunk` consecutive units (a tuning choice: fewer atomics on
 // the one counter against coarser balance). Each unit runs the same body as
 // its class's own kernel with its graph's arguments.
-// ONLY16: every unit is one of short rows with its table in LDS (all graphs
-// of up to kShortSpan vertices): the other bodies, whose registers would
-// limit the waves, are left out.
-template <int MODE, bool ONLY16>
+// Bodies that a plan needs none of are left out, since all bodies' registers
+// limit the waves: BATCH_SHORT holds those of short rows with their tables in LDS
+// (all graphs of up to kShortSpan vertices), BATCH_LONG those of 32-bit rows,
+// BATCH_ALL everything, at four waves a SIMD, without spills (128 even graphs of
+// 80000 vertices and more, input order: 2956 us with all bodies at five waves,
+// 2677 us with those of 32-bit rows alone).
+template <int MODE, int BODIES>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
-    MODE == MODE_SUPPORT_FULL ? 4 : ONLY16 ? kOccBatch16 : MODE == MODE_COUNT ? kOccBatch : 4)))
+    MODE == MODE_SUPPORT_FULL || BODIES == BATCH_ALL ? 4
+    : BODIES == BATCH_SHORT                           ? kOccBatch16
+    : MODE == MODE_COUNT                              ? kOccBatch
+                                                      : 4)))
 void k_count_batch(const Args* __restrict__ gargs, const BatchUnit* __restrict__ units, uint32_t n_units,
                    uint32_t chunk, unsigned int* __restrict__ queue, unsigned long long* __restrict__ counts) {
   extern __shared__ int4 smem4[];
@@ -1477,20 +1486,31 @@ void k_count_batch(const Args* __restrict__ gargs, const BatchUnit* __restrict__
       const auto* recs = static_cast<const PackRow*>(bu.p0);
       const auto* info = static_cast<const PackInfo*>(bu.p1);
       const auto* items = static_cast<const CountItem*>(bu.p0);
-      if (bu.kind == BK_PACK16) {
-        pack_body<MODE, VAR_BASE, true, kWaves>(A, recs, info, bu.index, bu.slots, smem);
-      } else if (ONLY16 || bu.kind == BK_BITS) {
-        if (bu.index < bu.end)
+      auto short_rows = [&] {
+        if ((bu.kind & 0xFF) == BK_PACK16)
+          pack_body<MODE, VAR_BASE, true, kWaves>(A, recs, info, bu.index, bu.slots, smem, (bu.kind >> 8) & 0xFF,
+                                                  bu.kind >> 16);
+        else if (bu.index < bu.end)
           block_flush<MODE>(bits_groups<MODE>(A, items, bu.index, (uint32_t)bu.end, bu.slots, smem), A);
-      } else if constexpr (!ONLY16) {
+      };
+      auto long_rows = [&] {
         if (bu.kind == BK_PACK)
           pack_body<MODE, VAR_BASE, false, kWaves>(A, recs, info, bu.index, bu.slots, smem);
-        else if (bu.kind == BK_BITS_HBM)
-          block_flush<MODE>(bits_groups_hbm<MODE>(A, items, bu.index, (uint32_t)bu.end, smem), A);
         else if (bu.kind == BK_ITEMS)
           items_body<MODE, false, VAR_BASE>(A, items, smem);
         else
           items_body<MODE, true, VAR_BASE>(A, items, smem);
+      };
+      if constexpr (BODIES == BATCH_SHORT) {
+        short_rows();
+      } else if constexpr (BODIES == BATCH_LONG) {
+        long_rows();
+      } else if ((bu.kind & 0xFF) == BK_PACK16 || bu.kind == BK_BITS) {
+        short_rows();
+      } else if (bu.kind == BK_BITS_HBM) {
+        block_flush<MODE>(bits_groups_hbm<MODE>(A, items, bu.index, (uint32_t)bu.end, smem), A);
+      } else {
+        long_rows();
       }
     }
   }
@@ -1499,10 +1519,12 @@ void k_count_batch(const Args* __restrict__ gargs, const BatchUnit* __restrict__
 template <int MODE>
 void launch_batch_mode(const Args* d_args, const BatchUnit* d_units, int64_t n_units, uint32_t chunk,
                        unsigned int* d_queue, unsigned long long* counts, unsigned grid, size_t lds,
-                       bool only16, hipStream_t st, bool timed) {
+                       BatchBodies bodies, hipStream_t st, bool timed) {
   static const char* const kNames[3] = {"count:batch", "support_full:batch", "support_oriented:batch"};
   if (n_units == 0) return;
-  auto* f = only16 ? k_count_batch<MODE, true> : k_count_batch<MODE, false>;
+  auto* f = bodies == BATCH_SHORT  ? k_count_batch<MODE, BATCH_SHORT>
+            : bodies == BATCH_LONG ? k_count_batch<MODE, BATCH_LONG>
+                                   : k_count_batch<MODE, BATCH_ALL>;
   if (timed)
     TC_LAUNCH(kNames[MODE], f, dim3(grid), dim3(256), lds, st, d_args, d_units, (uint32_t)n_units, chunk, d_queue,
               counts);
@@ -1542,7 +1564,7 @@ size_t bits_lds_bytes(int64_t n, int log2S, int mode) {
 
 void launch_batch(CountMode mode, const CountArgs* d_args, const BatchUnit* d_units, int64_t n_units,
                   uint32_t chunk, int64_t n_out, unsigned int* d_queue, int64_t* d_counts, unsigned grid,
-                  size_t lds, bool only16, hipStream_t st, bool timed) {
+                  size_t lds, BatchBodies bodies, hipStream_t st, bool timed) {
   TC_REQUIRE(chunk >= 1, TC_EINVAL, "launch_batch: chunk must be >= 1");
   TC_REQUIRE(mode == MODE_COUNT || mode == MODE_SUPPORT_FULL || mode == MODE_SUPPORT_ORIENTED, TC_EINVAL,
              "launch_batch: unsupported mode");
@@ -1552,13 +1574,13 @@ void launch_batch(CountMode mode, const CountArgs* d_args, const BatchUnit* d_un
   else hipLaunchKernelGGL(k_batch_clear, dim3(cg), dim3(256), 0, st, counts, n_out, d_queue);
   switch (mode) {
     case MODE_COUNT:
-      launch_batch_mode<MODE_COUNT>(d_args, d_units, n_units, chunk, d_queue, counts, grid, lds, only16, st, timed);
+      launch_batch_mode<MODE_COUNT>(d_args, d_units, n_units, chunk, d_queue, counts, grid, lds, bodies, st, timed);
       break;
     case MODE_SUPPORT_FULL:
-      launch_batch_mode<MODE_SUPPORT_FULL>(d_args, d_units, n_units, chunk, d_queue, counts, grid, lds, only16, st, timed);
+      launch_batch_mode<MODE_SUPPORT_FULL>(d_args, d_units, n_units, chunk, d_queue, counts, grid, lds, bodies, st, timed);
       break;
     default:
-      launch_batch_mode<MODE_SUPPORT_ORIENTED>(d_args, d_units, n_units, chunk, d_queue, counts, grid, lds, only16,
+      launch_batch_mode<MODE_SUPPORT_ORIENTED>(d_args, d_units, n_units, chunk, d_queue, counts, grid, lds, bodies,
                                                st, timed);
       break;
   }
@@ -1610,17 +1632,19 @@ void launch_count(const CountView& v, CountMode mode, int64_t* d_count, int32_t*
   }
 }
 
-template <bool ONLY16>
+template <int BODIES>
 static const void* batch_kernel(CountMode mode) {
-  return mode == MODE_COUNT          ? (const void*)k_count_batch<MODE_COUNT, ONLY16>
-         : mode == MODE_SUPPORT_FULL ? (const void*)k_count_batch<MODE_SUPPORT_FULL, ONLY16>
-                                     : (const void*)k_count_batch<MODE_SUPPORT_ORIENTED, ONLY16>;
+  return mode == MODE_COUNT          ? (const void*)k_count_batch<MODE_COUNT, BODIES>
+         : mode == MODE_SUPPORT_FULL ? (const void*)k_count_batch<MODE_SUPPORT_FULL, BODIES>
+                                     : (const void*)k_count_batch<MODE_SUPPORT_ORIENTED, BODIES>;
 }
 
-void batch_kernel_lds(CountMode mode, size_t lds, bool only16) {
+void batch_kernel_lds(CountMode mode, size_t lds, BatchBodies bodies) {
   if (lds <= 65536) return;
-  TC_HIP(hipFuncSetAttribute(only16 ? batch_kernel<true>(mode) : batch_kernel<false>(mode),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  const void* f = bodies == BATCH_SHORT  ? batch_kernel<BATCH_SHORT>(mode)
+                  : bodies == BATCH_LONG ? batch_kernel<BATCH_LONG>(mode)
+                                         : batch_kernel<BATCH_ALL>(mode);
+  TC_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
 }
 
 void zero_i32(int32_t* p, int64_t n, hipStream_t st, bool timed) {

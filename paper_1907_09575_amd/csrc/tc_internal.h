@@ -413,6 +413,11 @@ struct CountArgs {
 // in HBM; the same three of short rows.
 enum BatchKind : int32_t { BK_PACK = 0, BK_ITEMS = 1, BK_ITEMS_HBM = 2, BK_PACK16 = 3, BK_BITS = 4, BK_BITS_HBM = 5 };
 
+// What the units of a plan are: a mixture, or all of one sort (the kernel then
+// holds the bodies of that sort alone): BK_PACK16 and BK_BITS, or BK_PACK,
+// BK_ITEMS and BK_ITEMS_HBM.
+enum BatchBodies : int { BATCH_ALL = 0, BATCH_SHORT = 1, BATCH_LONG = 2 };
+
 struct alignas(16) BatchUnit {
   const void* p0;      // pack: PackRow records of the class; items: the group's first item;
                        // bits: first item of the class's short rows
@@ -423,7 +428,7 @@ struct alignas(16) BatchUnit {
   uint32_t index;      // pack: pack number
   uint32_t slots;      // pack: table slots reserved for the pack; bits: hit counters (FULL)
   int32_t graph;       // entry of the plan's graph list (and of the output)
-  int32_t kind;        // BatchKind
+  int32_t kind;        // BatchKind; of BK_PACK16 also, from bit 8 on, which part of the pack, and from bit 16 on, log2 of how many
 };
 static_assert(sizeof(BatchUnit) == 32, "BatchUnit layout");
 
@@ -434,10 +439,10 @@ static_assert(sizeof(BatchUnit) == 32, "BatchUnit layout");
 // capture).
 void launch_batch(CountMode mode, const CountArgs* d_args, const BatchUnit* d_units, int64_t n_units,
                   uint32_t chunk, int64_t n_out, unsigned int* d_queue, int64_t* d_counts, unsigned grid,
-                  size_t lds, bool only16, hipStream_t st, bool timed);
+                  size_t lds, BatchBodies bodies, hipStream_t st, bool timed);
 // Allow the persistent kernel of `mode` `lds` bytes of dynamic LDS (call
-// outside any capture). only16: all units are BK_PACK16 or BK_BITS.
-void batch_kernel_lds(CountMode mode, size_t lds, bool only16);
+// outside any capture).
+void batch_kernel_lds(CountMode mode, size_t lds, BatchBodies bodies);
 // Batch plans (tc_batch.hip): one persistent launch over many graphs in one
 // mode; support modes write each entry's own support array (cleared by every
 // launch of the plan). tuning_json as tc_batch_create's. Synchronises st.

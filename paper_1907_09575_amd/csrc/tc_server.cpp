@@ -86,7 +86,7 @@ size_t lean_bytes(int64_t m_raw, int64_t n) { return (size_t)(56 * m_raw + 40 * 
 // arguments and unit sources, and its work units (the plan's units and, while
 // it is made, their first copy and sort keys).
 size_t plan_estimate(const Graph& g) {
-  int64_t units = g.w.n_packs[0] + g.w.n_packs[1];
+  int64_t units = (g.w.n_packs[0] + g.w.n_packs[1]) * (kPackWavesMax / kWaves);  // (a small plan cuts its packs)
   for (int c = CLS_WG_SMALL; c < NUM_CLASSES; ++c) units += g.w.n_items[c] / kWaves;
   return (size_t)512 + (size_t)units * (2 * sizeof(BatchUnit) + 4 * sizeof(uint32_t));
 }
