@@ -481,7 +481,7 @@ void tc_server_destroy(tc_server* s);
 #define TC_NUM_CLASSES 7
 
 typedef struct {
-  int64_t workgroups;   /* work-groups of the class's launch */
+  int64_t workgroups;   /* work-groups launched for the class's rows */
   int64_t rows;         /* hashed rows j in the class */
   int64_t table_keys;   /* sum of |U_j| over those rows (table build reads) */
   int64_t tasks;        /* nonzeros (i, j) whose probes the class performs */
