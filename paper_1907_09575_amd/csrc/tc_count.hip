@@ -1301,7 +1301,11 @@ void launch_bits(const WorkSet& w, const Args& A, hipStream_t st) {
 
 // The short rows' packs. With few of them (a small graph) more waves share
 // each pack: four would leave most of the GPU idle behind a few long chains
-// of windows.
+// of windows. Count of ER graphs with 4 / 8 / 16 waves: 418 packs 81 / 54 / 52 us,
+// 1029 packs 103 / 81 / 83, 1728 packs 150 / 116 / 137, 3167 packs 245 / 154 / 228;
+// where most probes are in items, which the packs run beside, more waves gain
+// little and then cost (RMAT n = 700001, 2806 packs: count 431 / 416 / 468 us,
+// oriented support 594 / 607 / 653 us).
 template <int MODE>
 void launch_packs16(const WorkSet& w, const Args& A, hipStream_t st) {
   uint32_t n[2], slots = 0;
@@ -1314,7 +1318,8 @@ void launch_packs16(const WorkSet& w, const Args& A, hipStream_t st) {
   const uint32_t packs = n[0] + n[1];
   if (packs == 0) return;
   constexpr int OCC = mode_keys(MODE) ? 4 : kOccPacks16;
-  const int waves = packs <= kPacks16Waves ? 16 : packs <= 2 * kPacks16Waves ? 8 : kWaves;
+  const bool most = 2 * (w.cls_probes[CLS_PACK_SMALL] + w.cls_probes[CLS_PACK_LARGE]) >= (uint64_t)w.probes;
+  const int waves = packs <= kPacks16Waves ? 16 : packs <= (most ? 4 : 2) * kPacks16Waves ? 8 : kWaves;
   const size_t lds = pack16_lds_bytes(slots, MODE, waves);
   auto* f = waves == 16 ? k_count_packs16<MODE, 4, 16> : waves == 8 ? k_count_packs16<MODE, 4, 8>
                                                                     : k_count_packs16<MODE, OCC, kWaves>;
