@@ -107,7 +107,7 @@ constexpr int kBucket = 4;              // slots per hash bucket (one 16-byte LD
 constexpr int64_t kMaxEdges = (1ll << 32) - 256;
 constexpr int64_t kMaxBufferEdges = (1ll << 30) - 64;  // below: probe reads by 32-bit byte offsets
 
-// Short columns. The last kShortSpan + 1 rows of U (ranks from n - kShortSpan
+// Short columns. The last kShortSpan rows of U (ranks from n - kShortSpan
 // up) have all their entries k in the same ranks, so the distance n - k of
 // any entry that a task of such a row looks up fits 16 bits, exactly. U's
 // columns are kept a second time in that form (Graph::col16), and the rows

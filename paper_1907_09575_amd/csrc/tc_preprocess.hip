@@ -464,7 +464,8 @@ __global__ void k_fill_i64(int64_t* p, int64_t n, int64_t v) {
 // bucket's entries, the lower endpoints from the distinct keys of S whose lo
 // lies in [v0, v1) (S is sorted by lo >> mc.low, and v0 is a multiple of
 // 2^mc.low; the range is found by binary search), with kDegBatch loads in
-// flight per thread before they are counted. It writes the rank keys deg(v) << s | v of its vertices.
+// flight per thread before they are counted. It writes the rank keys
+// deg(v) << s | v of its vertices.
 constexpr int kDegBinsLog2 = 15;
 constexpr int kDegBins = 1 << kDegBinsLog2;   // LDS counters of one work-group (128 KiB)
 constexpr int kDegThreads = 1024;
@@ -574,8 +575,8 @@ __global__ void k_perm(const uint64_t* __restrict__ rk, int64_t n, int s, int32_
 // top 8 bits of their upper endpoint (the last digit pass of the degree
 // count's partition, whose scanned digit starts it reuses); its source reads
 // S in order, so the lower endpoints' ranks are read interval by interval of
-// at most 32768 vertices (128 KiB of the map): element = rank(lo) << 32 | hi. (2) k_orient_hi reads the ranks of
-// the upper endpoints bucket by bucket (a bucket spans 2^(s-8) vertices: a
+// at most 32768 vertices (128 KiB of the map): element = rank(lo) << 32 | hi.
+// (2) k_orient_hi reads the ranks of the upper endpoints bucket by bucket (a bucket spans 2^(s-8) vertices: a
 // 256 KiB slice of the rank map at s = 24, 1 MiB at s = 26, which stays in
 // L2) and writes the oriented key in place.
 struct LoRankSrc {
@@ -1219,9 +1220,9 @@ constexpr size_t kSmallScanPool = (size_t)32 << 10;
 constexpr int64_t kArenaRaw = (int64_t)1 << 16;
 inline size_t arena_bytes_of(int64_t m_raw, int64_t n) { return (size_t)(48 * m_raw + 48 * n) + ((size_t)256 << 10); }
 
-// (32 keys per thread spill: 105 us for 32768 pairs, against 75 us in passes.)
-
-// LDS of a block sort: the keys, per wave and digit a count, scratch.
+// LDS of a block sort: the keys, per wave and digit a count, scratch. (At most
+// 16 keys per thread: with 32 they spill, 105 us for 32768 pairs against 75 us
+// in passes.)
 template <int IPT>
 struct BlockSort {
   uint32_t key[kSmallThreads * IPT];

@@ -1,8 +1,9 @@
 // tc_prims.h - device primitives for preprocessing: block/wave scans, an
-// exclusive scan over device arrays (reduce-then-scan, no inter-block waits)
-// and a stable LSD radix sort (8-bit digits) with wave-ballot ranking.
+// exclusive scan over device arrays (short ones in one kernel with decoupled
+// look-back, long ones reduce-then-scan), a stable compaction and a stable LSD
+// radix sort (8-bit digits) with wave-ballot ranking and decoupled look-back.
 //
-// All kernels use 256-thread work-groups (4 wave64 waves).
+// Work-groups are 256 threads (4 wave64 waves), those of a sort pass 512.
 #pragma once
 
 #include <algorithm>
@@ -695,9 +696,6 @@ __device__ __forceinline__ T digit_excl_scan(T v, T* s_wave, T& total) {
   return woff + inc - v;
 }
 
-// Two work-groups of a tile fit a CU (LDS), so the registers are held to two
-// waves a SIMD: a few more than 256 in the 12-byte pass with a source leave one
-// tile a CU (preprocessing and count at scale 24: 54.4 ms against 53.6 ms).
 // Two work-groups of a tile fit a CU (LDS). A tile's phases (loads, ranking,
 // look-back, scattered stores) leave the memory or the vector units idle in
 // turn, so a tile of 8192 8-byte keys is spread over 512 threads of 16 rather
