@@ -20,10 +20,12 @@ LDS-active cycles stalled by bank conflicts) and the L2 hit rate
 the launch classes that share one kernel instantiation.
 
 ``traffic`` turns one FETCH_SIZE run and one WRITE_SIZE run of
-``bench.py --copy-calibration`` into bytes per launch of the count class
-LABEL (e.g. count:wg_large): both counters are scaled by what they read for
-the 1 GiB calibration copy, and the launch is found by kernel name and grid
-size (the class's work-groups from the bench line, 64 threads per wave).
+``bench.py --copy-calibration`` into bytes per tc_count call (LABEL "count":
+all count-mode kernels of the run, divided by the calls, each of which launches
+every one of them once) or per launch of one class of 32-bit rows alone (LABEL
+count:wg_large, for instance: found by kernel name and grid size, the class's
+work-groups from the bench line, 64 threads per wave). Both counters are scaled
+by what they read for the 1 GiB calibration copy.
 FETCH_SIZE and WRITE_SIZE count the L2's requests to the fabric: L2 misses,
 served by the Infinity Cache (MALL) or by HBM, so the figure is reported as
 fabric traffic (an upper bound on HBM bytes, not a DRAM measurement).
@@ -42,6 +44,7 @@ from collections import defaultdict
 
 _CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
 CALIBRATION_BYTES = 1 << 30
+_COUNT_KERNELS = tuple("k_count_%s<0" % k for k in ("bits", "packs16", "items", "packs"))  # of MODE_COUNT
 
 
 def source_digest() -> str:
@@ -152,10 +155,12 @@ def _counter_rows(path, counter):
 
 def traffic(fetch_csv, write_csv, bench_json, label, out_json, commands=()):
     bench = json.loads(open(bench_json).read().strip().splitlines()[-1])
-    cls = label.split(":", 1)[1]
-    waves = 8 if cls in ("wg_huge", "wg_giant") else 4
-    grid = bench["classes"][cls]["workgroups"] * 64 * waves
-    kname = "k_count_packs" if cls.startswith("pack") else "k_count_items"
+    whole = label == "count"
+    if not whole:
+        cls = label.split(":", 1)[1]
+        waves = 8 if cls in ("wg_huge", "wg_giant") else 4
+        grid = bench["classes"][cls]["workgroups"] * 64 * waves
+        kname = "k_count_packs" if cls.startswith("pack") else "k_count_items"
     res = {"kernel": label, "workload": bench["config"]["workload"] + " seed %d" % bench["config"]["seed"],
            "source_digest": source_digest()}
     for key, path, counter in (("fetch", fetch_csv, "FETCH_SIZE"), ("write", write_csv, "WRITE_SIZE")):
@@ -164,9 +169,21 @@ def traffic(fetch_csv, write_csv, bench_json, label, out_json, commands=()):
         copies = [v for k, g, v in rows if "copy" in k.lower() and "count" not in k.lower()]
         assert copies, "no calibration copy in %s" % path
         cal = max(copies)
-        sel = [v for k, g, v in rows if short_name(k).startswith(kname) and "<0" in k and g == grid]
-        assert sel, "no launch of %s with grid %d in %s" % (kname, grid, path)
-        res[key + "_kib_per_launch"] = sum(sel) / len(sel)
+        if whole:
+            per = defaultdict(list)
+            for k, g, v in rows:
+                if short_name(k).startswith(_COUNT_KERNELS):
+                    per[(k, g)].append(v)
+            assert per, "no count kernel in %s" % path
+            calls = max(len(v) for v in per.values())
+            assert all(len(v) == calls for v in per.values()), "count kernels of several graphs in %s" % path
+            res[key + "_kib_per_launch"] = sum(sum(v) for v in per.values()) / calls
+            res["kernels"] = {"%s grid %d" % (short_name(k), g): round(sum(v) / calls, 1)
+                              for (k, g), v in per.items()} if key == "fetch" else res["kernels"]
+        else:
+            sel = [v for k, g, v in rows if short_name(k).startswith(kname) and "<0" in k and g == grid]
+            assert sel, "no launch of %s with grid %d in %s" % (kname, grid, path)
+            res[key + "_kib_per_launch"] = sum(sel) / len(sel)
         res.setdefault("calibration", {"copy_bytes": CALIBRATION_BYTES})
         res["calibration"][key + "_kib"] = cal
         res["calibration"][key + "_scale"] = CALIBRATION_BYTES / 1024.0 / cal
