@@ -203,7 +203,8 @@ struct Server {
         finish(q, TC_EINVAL, "tc_server: graph_key not resident and no edge list given");
         continue;
       }
-      if (reserved + need > (size_t)budget && !make_room(need, to_free)) {
+      // (cached graphs are not evicted for what cannot fit anyway)
+      if (reserved + need > (size_t)budget && (need > (size_t)budget || !make_room(need, to_free))) {
         if (active.empty() && need > (size_t)budget) {
           pending.pop_front();
           finish(q, TC_ENOMEM, "tc_server: request footprint exceeds the HBM budget");

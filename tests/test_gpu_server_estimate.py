@@ -77,3 +77,15 @@ def test_a_lone_graph_past_the_budget_is_built_lean(tc, n, m):
     with tc.Server(budget - 1, 4) as srv:
         r = srv.poll(srv.submit("count", s, d, n))
     assert r["status"] in (0, 2)
+
+
+def test_cached_graphs_stay_when_a_request_cannot_fit(tc):
+    s, d = graph("uniform", 4096, 32768)
+    with tc.Server(64 << 20, 4) as srv:
+        first = srv.poll(srv.submit("count", s, d, 4096, key=5))
+        big = srv.poll(srv.submit("count", s, d, 1 << 28))  # 40 bytes a vertex: far past the budget
+        again = srv.poll(srv.submit("count", None, None, 4096, key=5))
+        st = srv.stats()
+    assert first["status"] == 0 and big["status"] == 2
+    assert again["status"] == 0 and again["count"] == first["count"]
+    assert st["evicted"] == 0 and st["cache_hits"] == 1
