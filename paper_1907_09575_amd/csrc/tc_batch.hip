@@ -258,8 +258,10 @@ struct PlanHost {
   }
 };
 
+// fill: units that merging leaves and cutting goes up to (0: as few units as
+// there can be).
 void plan_host(PlanHost& H, const PlanEntry* entries, int64_t num, CountMode mode, const Tuning& t,
-               int device, int cus, std::vector<std::pair<int32_t*, int64_t>>* support) {
+               int device, int64_t fill, std::vector<std::pair<int32_t*, int64_t>>* support) {
   H.args.assign((size_t)std::max<int64_t>(num, 1), CountArgs{});
   H.srcs.assign((size_t)std::max<int64_t>(num, 1), BatchSrc{});
   size_t lds = 0;
@@ -268,8 +270,8 @@ void plan_host(PlanHost& H, const PlanEntry* entries, int64_t num, CountMode mod
   // how far to merge bundles and cut packs
   uint64_t probes = 0;
   for (int64_t i = 0; i < num; ++i) probes += entries[i].g ? (uint64_t)entries[i].g->w.probes : 0;
-  const int64_t fill = kFillUnits * cus;
-  const uint64_t unit_probes = std::min(kUnitProbes, std::max(kUnitProbesMin, probes / (uint64_t)fill));
+  const uint64_t unit_probes =
+      fill == 0 ? kUnitProbes : std::min(kUnitProbes, std::max(kUnitProbesMin, probes / (uint64_t)fill));
   auto merge_of = [&](const WorkSet& w) { return std::max<uint64_t>(1, unit_probes / w.bundle_w); };
   // (a pack of few probes is mostly the building of its tables)
   auto cut = [](const WorkSet& w) {
@@ -428,7 +430,7 @@ BatchPlan* make_plan(const PlanEntry* entries, int64_t num, CountMode mode, cons
     }
   }
   PlanHost H;
-  plan_host(H, ents.data(), num, mode, t, P->device, P->cus, &P->support);
+  plan_host(H, ents.data(), num, mode, t, P->device, kFillUnits * P->cus, &P->support);
   std::vector<CountArgs>& args = H.args;
   std::vector<BatchSrc>& srcs = H.srcs;
   const uint64_t off = H.units;
@@ -631,7 +633,11 @@ void count_batched_noalloc(const PlanEntry* entries, int64_t num, int64_t* d_cou
   Tuning t;  // the default schedule, graph order (no sort: sorting needs temporaries)
   t.lpt = false;
   PlanHost H;
-  plan_host(H, entries, num, MODE_COUNT, t, device, cus, nullptr);
+  plan_host(H, entries, num, MODE_COUNT, t, device, kFillUnits * cus, nullptr);
+  if (ScratchLayout(num, (int64_t)H.units).total > kScratchBytes) {
+    H = PlanHost();  // with the fewest units it may fit
+    plan_host(H, entries, num, MODE_COUNT, t, device, 0, nullptr);
+  }
   TC_REQUIRE(H.units < 0xFFFFFFF0ull, TC_EOVERFLOW, "tc_count_batched_noalloc: more than 2^32 work units");
   const ScratchLayout L(num, (int64_t)H.units);
   if (L.total > kScratchBytes)

@@ -3,6 +3,8 @@ bundles stay apart, up to as many as fill the GPU: counts and both supports (a
 part adds its own hits) against the oracle. Cliques (packs and rows with work-groups of
 their own), graphs of one pack, a graph without tasks, thresholds that make
 packs small, and plans in both orders."""
+import re
+
 import numpy as np
 import pytest
 
@@ -66,3 +68,43 @@ def test_counts_and_supports(tc, name):
                     r = srv.poll(t)
                     assert r["status"] == 0 and r["count"] == T and r["m"] == U.m
                     assert np.array_equal(np.asarray(r["support"])[:U.m], oracle.support(U, mode)[1][:U.m])
+
+
+def test_noalloc_takes_the_fewest_units_at_its_limit(tc):
+    """Near the end of the scratch array the units are as few as in a batch that
+    needs no filling: a small plan's finer units do not make it a refusal."""
+    med_raw = clique(300)
+    med, tiny = (tc.tc_preprocess(torch.from_numpy(s).cuda(), torch.from_numpy(d).cuda(), n)
+                 for s, d, n in (med_raw, clique(3)))
+    want = oracle.count(oracle.preprocess(*med_raw))
+    K = 2
+
+    def units(gs):
+        P = tc.tc_batch_create(gs)
+        u = tc.tc_batch_describe(P)["units"]
+        P.free()
+        return u
+
+    # 65536 probes a unit and no cuts from 33.5 M probes on: far less than 100 of these graphs
+    u_med, rest = divmod(units([med] * 100), 100)
+    assert rest == 0 and units([tiny]) == 1
+    assert units([med] * K) >= K * u_med + 64  # (finer where nothing else runs)
+
+    def refusal(n_tiny):
+        gs = [med] * K + [tiny] * n_tiny
+        with pytest.raises(tc.TCError, match="bytes of scratch") as e:
+            tc.tc_count_batched_noalloc(gs, torch.empty(len(gs), dtype=torch.int64, device="cuda"))
+        needs, n_units = re.search(r"needs (\d+) bytes of scratch \((\d+) work units\)", str(e.value)).groups()
+        return int(needs), int(n_units)
+
+    n0 = 200000
+    needs, n_units = refusal(n0)
+    assert n_units == K * u_med + n0
+    per = (refusal(2 * n0)[0] - needs) / n0
+    n1 = n0 - int(np.ceil((needs - (64 << 20) + 512) / per))  # the most that fit (the arrays' ends are rounded up to 256)
+    counts = torch.empty(K + n1, dtype=torch.int64, device="cuda")
+    tc.tc_count_batched_noalloc([med] * K + [tiny] * n1, counts)
+    assert counts.cpu().tolist() == [want] * K + [1] * n1
+    refusal(n1 + 16)
+    med.free()
+    tiny.free()
